@@ -261,7 +261,7 @@ os_status os_gemm_kept(const float* At, int64_t ldat, const float* Bt, int64_t l
     if (K == 0) return OS_ENOKEEP;
     if (!osk::plan_gemm_ok(m, l, bp, ldat, ldbt, 4)) return OS_EINVAL;
     return hip_status(osk::launch_gemm_kept(At, ldat, Bt, ldbt, m, l, bp, kept, K, 1.0f / (float)K, C,
-                                            ldc, (hipStream_t)stream));
+                                            ldc, nullptr, 0, (hipStream_t)stream));
 }
 
 os_status os_gemm_kept_cmask(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
@@ -342,7 +342,8 @@ os_status os_gemm_kept_prec(const void* At, int64_t ldat, const void* Bt, int64_
                                                     (hipStream_t)stream));
     return hip_status(osk::launch_gemm_kept_bf16(At, ldat, Bt, ldbt, m, l, bpq, kept, K,
                                                  is_split(precision), (int64_t)nst * bpq,
-                                                 1.0f / (float)K, C, ldc, (hipStream_t)stream));
+                                                 1.0f / (float)K, C, ldc, nullptr, 0,
+                                                 (hipStream_t)stream));
 }
 
 size_t os_matmul_ex_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, int64_t l,
@@ -506,7 +507,7 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     if ((st = sketch_lines(A, a_dtype, a_col_major != 0, m, lda, At, aq_p)) != OS_OK) return st;
     if ((st = sketch_lines(B, b_dtype, b_col_major == 0, l, ldb, Bt, bq_p)) != OS_OK) return st;
     if (precision == OS_PREC_FP32)
-        return hip_status(osk::launch_gemm_kept_split(
+        return hip_status(osk::launch_gemm_kept(
             At, zs, Bt, zs, m, l, bp, bs.kept_pos, bs.K, 1.0f / (float)bs.K, C, ldc,
             reinterpret_cast<float*>(part_p), part_bytes, s));
     const int split = is_split(precision);
@@ -524,7 +525,7 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
             bs.K, split, (int64_t)bs.nst * bpq, 1.0f / (float)bs.K, C, ldc,
             reinterpret_cast<float*>(part_p), part_bytes, s));
     }
-    return hip_status(osk::launch_gemm_kept_bf16_split(
+    return hip_status(osk::launch_gemm_kept_bf16(
         aq_p, wq, bq_p, wq, m, l, bpq, bs.kept_pos, bs.K, split, (int64_t)bs.nst * bpq,
         1.0f / (float)bs.K, C, ldc, reinterpret_cast<float*>(part_p), part_bytes, s));
 }

@@ -48,8 +48,8 @@ constexpr int kStepBytes = 128; // K step: 128 bytes of each tile row (32 FP32 /
 constexpr int kGroupM = 8;
 
 __device__ __forceinline__ int64_t xcd_task(int64_t L, int64_t tasks) {
-    if (tasks % 8 != 0) return L;
-    return (L % 8) * (tasks / 8) + L / 8;
+    const int64_t q = tasks / 8, r = tasks % 8, x = L % 8;
+    return x * q + min(x, r) + L / 8;
 }
 
 // Buffer resource of a matrix starting at p: no stride, no range limit
@@ -138,6 +138,8 @@ struct PrecF32 {
     static constexpr int kParts = 4;          // parts of a quad: the four K values kk
     static constexpr int kHead = 3;
     static constexpr int kTail = 1;
+    template <int kI>
+    static constexpr int parts = kParts;
     template <int kI, int kJ, int kLo = 0, int kHi = kParts>
     __device__ static __forceinline__ void mfma_quad(v16f (&acc)[kI][kJ], const float4 (&a)[kI],
                                                      const float4 (&b)[kJ]) {
@@ -154,9 +156,10 @@ struct PrecF32 {
 
 struct PrecBF16 {
     static constexpr int kElem = 2;
-    static constexpr int kParts = 4;          // parts of a quad: the row blocks i (kI = 4)
     static constexpr int kHead = 1;
     static constexpr int kTail = 0;
+    template <int kI>
+    static constexpr int parts = kI;          // parts of a quad: the row blocks i
     template <int kI, int kJ, int kLo = 0, int kHi = kI>
     __device__ static __forceinline__ void mfma_quad(v16f (&acc)[kI][kJ], const float4 (&a)[kI],
                                                      const float4 (&b)[kJ]) {
@@ -208,8 +211,30 @@ struct SplitK {
 // memory instruction).
 constexpr int kThreadsK = 512;
 
-template <typename P, bool kMask, bool kOdd, bool kSplit = false>
-__global__ __launch_bounds__(kThreadsK) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// Tile forms.  128 (four waves of 64 x 64, two workgroups per CU) and 64 (four
+// waves of 32 x 32, four workgroups per CU) run the same K loop; they read
+// more LDS and L2 per flop (0.96 and 0.92 of the 256 form's FP32 rate at 4096
+// x 4096 x 4096) but fill the CUs for products of few or ragged tiles: 2048 x
+// 1536 over K = 4096, 917 us as 48 tiles of 256, 219 us as 768 of 64.  Every
+// form sums an entry in the same order, bit for bit (pick_form chooses).
+template <int BT_, int WR_, int WC_, int kEu_>
+struct Tile {
+    static constexpr int BT = BT_;                   // tile side
+    static constexpr int WR = WR_;                   // waves along the rows
+    static constexpr int WC = WC_;                   //   and the columns
+    static constexpr int kWaves = WR * WC;
+    static constexpr int kThreads = 64 * kWaves;
+    static constexpr int kI = BT / (32 * WR);        // 32x32 blocks per wave: rows
+    static constexpr int kJ = BT / (32 * WC);        //   and columns
+    static constexpr int kU = BT / (8 * kWaves);     // direct loads per wave and operand
+    static constexpr int kEu = kEu_;                 // waves per SIMD
+};
+using Tile256 = Tile<256, 2, 4, 2>;
+using Tile128 = Tile<128, 2, 2, 2>;
+using Tile64 = Tile<64, 2, 2, 4>;
+
+template <typename P, typename S, bool kMask, bool kOdd, bool kSplit = false>
+__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kEu, S::kEu)))
 void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __restrict__ Bt,
                       int64_t ldbt, int64_t m, int64_t l, int32_t bp, BlockList kept,
                       int32_t nkept, int32_t nsub, int64_t lo_off, float scale,
@@ -218,17 +243,22 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     // two K-step buffers per operand, separate arrays so that the compiler
     // can tell the tile loads in flight (into one) from the fragment reads
     // (from the other)
-    __shared__ __align__(1024) float As0[BM * 32];
-    __shared__ __align__(1024) float As1[BM * 32];
-    __shared__ __align__(1024) float Bs0[BN * 32];
-    __shared__ __align__(1024) float Bs1[BN * 32];
+    constexpr int BT = S::BT;
+    constexpr int kI = S::kI;
+    constexpr int kJ = S::kJ;
+    constexpr int kU = S::kU;
+    constexpr int kParts = P::template parts<kI>;
+    __shared__ __align__(1024) float As0[BT * 32];
+    __shared__ __align__(1024) float As1[BT * 32];
+    __shared__ __align__(1024) float Bs0[BT * 32];
+    __shared__ __align__(1024) float Bs1[BT * 32];
     __shared__ int32_t klist[kMask ? OS_MAX_BLOCKS + 1 : 1];   // per-tile kept list, count last
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar M0 and selects
-    const int wm = wave >> 2;
-    const int wn = wave & 3;
+    const int wm = wave / S::WC;
+    const int wn = wave % S::WC;
 
     const int64_t ntiles = (int64_t)tilesM * tilesN;
     int32_t split = 0;
@@ -245,13 +275,13 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     const int64_t in_group = T - group * kGroupM * tilesN;
     const int64_t tm = first_m + in_group % gsz;
     const int64_t tn = in_group / gsz;
-    int64_t row0 = tm * BM;
-    int64_t col0 = tn * BN;
+    int64_t row0 = tm * BT;
+    int64_t col0 = tn * BT;
     if constexpr (kMask) {
         // tile (tm, tn) of the C-block grid: block (I, J), tile (ti, tj) in it
         const int64_t I = tm / cm.tb, J = tn / cm.tb;
-        row0 = I * cm.cblk + (tm % cm.tb) * BM;
-        col0 = J * cm.cblk + (tn % cm.tb) * BN;
+        row0 = I * cm.cblk + (tm % cm.tb) * BT;
+        col0 = J * cm.cblk + (tn % cm.tb) * BT;
         m = min(m, (I + 1) * cm.cblk);          // rows and columns of this block only
         l = min(l, (J + 1) * cm.cblk);
         if (row0 >= m || col0 >= l) return;     // past a partial block's end (uniform)
@@ -265,8 +295,8 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
         __syncthreads();
         nkept = __builtin_amdgcn_readfirstlane(klist[OS_MAX_BLOCKS]);
         if (nkept == 0) {
-            for (int64_t r = row0 + (tid >> 6); r < min(m, row0 + BM); r += kThreadsK / 64)
-                for (int64_t c = col0 + lane; c < min(l, col0 + BN); c += 64) C[r * ldc + c] = 0.f;
+            for (int64_t r = row0 + (tid >> 6); r < min(m, row0 + BT); r += S::kWaves)
+                for (int64_t c = col0 + lane; c < min(l, col0 + BT); c += 64) C[r * ldc + c] = 0.f;
             return;
         }
         scale = 1.0f / (float)nkept;
@@ -291,11 +321,11 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
         return j < 64 ? r0 : (j < 128 ? r1 : (j < 192 ? r2 : r3));
     };
 
-    v16f acc[4][2];
+    v16f acc[kI][kJ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < kJ; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
@@ -322,33 +352,32 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
         tile_rsrc(static_cast<const char*>(At) + row0 * ldat * P::kElem);
     const __amdgpu_buffer_rsrc_t rb_src =
         tile_rsrc(static_cast<const char*>(Bt) + col0 * ldbt * P::kElem);
-    // 256 tile rows per operand and step: 4 direct loads per wave
-    uint32_t va[4], vb[4];
-    direct_offsets<4>(va, ldat * P::kElem, (int)min((int64_t)BM - 1, m - 1 - row0), wave, lane);
-    direct_offsets<4>(vb, ldbt * P::kElem, (int)min((int64_t)BN - 1, l - 1 - col0), wave, lane);
+    uint32_t va[kU], vb[kU];
+    direct_offsets<kU>(va, ldat * P::kElem, (int)min((int64_t)BT - 1, m - 1 - row0), wave, lane);
+    direct_offsets<kU>(vb, ldbt * P::kElem, (int)min((int64_t)BT - 1, l - 1 - col0), wave, lane);
     int fa_off[4], fb_off[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        fa_off[q] = direct_frag_off(wm * 128 + (lane & 31), q, lane);
-        fb_off[q] = direct_frag_off(wn * 64 + (lane & 31), q, lane);
+        fa_off[q] = direct_frag_off(wm * 32 * kI + (lane & 31), q, lane);
+        fb_off[q] = direct_frag_off(wn * 32 * kJ + (lane & 31), q, lane);
     }
-    auto frag = [&](float4 (&a)[4], float4 (&b)[2], const float* as, const float* bs, int q) {
+    auto frag = [&](float4 (&a)[kI], float4 (&b)[kJ], const float* as, const float* bs, int q) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const float4*>(as + fa_off[q] + 1024 * i);
+        for (int i = 0; i < kI; ++i) a[i] = *reinterpret_cast<const float4*>(as + fa_off[q] + 1024 * i);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const float4*>(bs + fb_off[q] + 1024 * j);
+        for (int j = 0; j < kJ; ++j) b[j] = *reinterpret_cast<const float4*>(bs + fb_off[q] + 1024 * j);
     };
     auto issue = [&](float* as, float* bs, int step) {
         uint32_t ka, kb;
         step_ab(step, ka, kb);
-        direct_issue<4>(ra_src, as, va, ka, wave);
-        direct_issue<4>(rb_src, bs, vb, kb, wave);
+        direct_issue<kU>(ra_src, as, va, ka, wave);
+        direct_issue<kU>(rb_src, bs, vb, kb, wave);
     };
 
     issue(As0, Bs0, t_begin);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    float4 fa[4], fb[2], ga[4], gb[2];
+    float4 fa[kI], fb[kJ], ga[kI], gb[kJ];
     frag(fa, fb, As0, Bs0, 0);
     // One K step: the next step's tiles go straight into the other buffers
     // (last read before the previous step's barrier) while this step's four
@@ -364,31 +393,31 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     // address.  Steps run in pairs (one per buffer); when their count is odd
     // (kOdd kernels only) the last step runs alone after the pairs, from
     // the first buffer, where the last pair loaded it.
-    auto quad = [&](float4 (&a)[4], float4 (&b)[2], auto&& reads) {
-        P::template mfma_quad<4, 2, 0, P::kHead>(acc, a, b);
+    auto quad = [&](float4 (&a)[kI], float4 (&b)[kJ], auto&& reads) {
+        P::template mfma_quad<kI, kJ, 0, P::kHead>(acc, a, b);
         __builtin_amdgcn_sched_barrier(0);
         reads();
         __builtin_amdgcn_sched_barrier(0);
-        P::template mfma_quad<4, 2, P::kHead, P::kParts>(acc, a, b);
+        P::template mfma_quad<kI, kJ, P::kHead, kParts>(acc, a, b);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto kstep = [&](const float* as, const float* bs, float* na, float* nb, int t) {
         uint32_t ka, kb;
         step_ab(min(t + 1, t_end - 1), ka, kb);
-        direct_issue<4>(ra_src, na, va, ka, wave);
+        direct_issue<kU>(ra_src, na, va, ka, wave);
         __builtin_amdgcn_sched_barrier(0);
         quad(fa, fb, [&] { frag(ga, gb, as, bs, 1); });
-        direct_issue<4>(rb_src, nb, vb, kb, wave);
+        direct_issue<kU>(rb_src, nb, vb, kb, wave);
         __builtin_amdgcn_sched_barrier(0);
         quad(ga, gb, [&] { frag(fa, fb, as, bs, 2); });
         quad(fa, fb, [&] { frag(ga, gb, as, bs, 3); });
-        P::template mfma_quad<4, 2, 0, P::kParts - P::kTail>(acc, ga, gb);
+        P::template mfma_quad<kI, kJ, 0, kParts - P::kTail>(acc, ga, gb);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         frag(fa, fb, na, nb, 0);
         __builtin_amdgcn_sched_barrier(0);
-        P::template mfma_quad<4, 2, P::kParts - P::kTail, P::kParts>(acc, ga, gb);
+        P::template mfma_quad<kI, kJ, kParts - P::kTail, kParts>(acc, ga, gb);
         __builtin_amdgcn_sched_barrier(0);
     };
     int t = t_begin;
@@ -410,16 +439,114 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
         scale = 1.0f;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kI; ++i) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t col = col0 + wn * 64 + j * 32 + (lane & 31);
+        for (int j = 0; j < kJ; ++j) {
+            const int64_t col = col0 + wn * 32 * kJ + j * 32 + (lane & 31);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int64_t row = row0 + wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int64_t row = row0 + wm * 32 * kI + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (row < m && col < l) out[row * ldo + col] = acc[i][j][r] * scale;
             }
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Small products: one 32 x 32 tile of C per workgroup, the K steps dealt to
+// its kSmallWaves waves (wave w takes steps w, w + kSmallWaves, ...), each
+// wave's fragments loaded straight from the sketches into registers (a lane
+// reads the 64 bytes of its row that its half of a step uses), the waves'
+// partial tiles added in wave order through LDS.  Bound by latency: a product
+// of one or a few 256 tiles has too little work for tiles staged through LDS
+// and a second launch for the sum of split partials.  (96 x 128 over K =
+// 512: 26.4 us as one 256 tile split 8 ways and its sum, 7.1 us.)
+// ---------------------------------------------------------------------------
+constexpr int kSmallWaves = 8;
+constexpr int kSmallTile = 32;
+
+template <typename P>
+__global__ __launch_bounds__(64 * kSmallWaves)
+void gemm_small_kernel(const void* __restrict__ At, int64_t ldat, const void* __restrict__ Bt,
+                       int64_t ldbt, int64_t m, int64_t l, int32_t bp, BlockList kept,
+                       int32_t nkept, int32_t nsub, int64_t lo_off, float scale,
+                       float* __restrict__ C, int64_t ldc, int32_t tilesM, int32_t tilesN) {
+    __shared__ float red[kSmallWaves][kSmallTile * kSmallTile];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t T = xcd_task(blockIdx.x, (int64_t)tilesM * tilesN);
+    const int64_t row0 = T / tilesN * kSmallTile;
+    const int64_t col0 = T % tilesN * kSmallTile;
+
+    int32_t kv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) kv[q] = kept.idx[64 * q + lane];
+    auto kept_at = [&](int j) -> int32_t {
+        const int32_t r0 = __builtin_amdgcn_readlane(kv[0], j & 63);
+        const int32_t r1 = __builtin_amdgcn_readlane(kv[1], j & 63);
+        const int32_t r2 = __builtin_amdgcn_readlane(kv[2], j & 63);
+        const int32_t r3 = __builtin_amdgcn_readlane(kv[3], j & 63);
+        return j < 64 ? r0 : (j < 128 ? r1 : (j < 192 ? r2 : r3));
+    };
+    constexpr int kStep = kStepBytes / P::kElem;
+    const int tpb = bp / kStep;
+    const int total = nkept * nsub * tpb;
+    // rows past the matrix read its last row (their sums are not stored)
+    const int half = 64 * (lane >> 5);
+    const char* pa = static_cast<const char*>(At) +
+                     min(row0 + (lane & 31), m - 1) * ldat * P::kElem + half;
+    const char* pb = static_cast<const char*>(Bt) +
+                     min(col0 + (lane & 31), l - 1) * ldbt * P::kElem + half;
+    auto load = [&](float4 (&a)[4], float4 (&b)[4], int step) {
+        const int term = step / tpb;
+        const int j = term / nsub;
+        const int sub = term - j * nsub;
+        const int64_t c = (int64_t)kept_at(j) * bp + (int64_t)(step % tpb) * kStep;
+        const int64_t ka = (c + (sub == 2 ? lo_off : 0)) * P::kElem;
+        const int64_t kb = (c + (sub == 1 ? lo_off : 0)) * P::kElem;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            a[q] = *reinterpret_cast<const float4*>(pa + ka + 16 * q);
+            b[q] = *reinterpret_cast<const float4*>(pb + kb + 16 * q);
+        }
+    };
+    v16f acc[1][1];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+    auto sum = [&](const float4 (&a)[4], const float4 (&b)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 x[1] = {a[q]}, y[1] = {b[q]};
+            P::template mfma_quad<1, 1>(acc, x, y);
+        }
+    };
+    if (wave < total) {
+        float4 a0[4], b0[4], a1[4], b1[4];
+        load(a0, b0, wave);
+        int t = wave;
+        // two steps in flight; past the end the last step is loaded again
+        for (; t + kSmallWaves < total; t += 2 * kSmallWaves) {
+            load(a1, b1, t + kSmallWaves);
+            sum(a0, b0);
+            load(a0, b0, min(t + 2 * kSmallWaves, total - 1));
+            sum(a1, b1);
+        }
+        if (t < total) sum(a0, b0);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        red[wave][(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kSmallTile + (lane & 31)] =
+            acc[0][0][r];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSmallTile * kSmallTile / (64 * kSmallWaves); ++u) {
+        const int e = u * 64 * kSmallWaves + tid;
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) v += red[w][e];
+        const int64_t row = row0 + e / kSmallTile, col = col0 + e % kSmallTile;
+        if (row < m && col < l) C[row * ldc + col] = v * scale;
     }
 }
 
@@ -431,8 +558,15 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict_
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= m * l) return;
     const int64_t row = i / l;
+    // eight partials in flight (past the last one it is read again, not added)
     float v = 0.f;
-    for (int32_t s = 0; s < nsplit; ++s) v += part[(int64_t)s * m * l + i];
+    for (int32_t s = 0; s < nsplit; s += 8) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = part[(int64_t)min(s + u, nsplit - 1) * m * l + i];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v = s + u < nsplit ? v + x[u] : v;
+    }
     C[row * ldc + (i - row * l)] = v * scale;
 }
 
@@ -1106,20 +1240,7 @@ bool plan_gemm_ok(int64_t m, int64_t l, int32_t bp, int64_t ldat, int64_t ldbt, 
     return tilesM * tilesN <= 0x7fffffff;
 }
 
-hipError_t launch_gemm_kept(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
-                            int64_t m, int64_t l, int32_t bp, const BlockList& kept,
-                            int32_t nkept, float scale, float* C, int64_t ldc, hipStream_t s) {
-    if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 4) || nkept < 1) return hipErrorInvalidValue;
-    const int64_t tilesM = (m + BM - 1) / BM;
-    const int64_t tilesN = (l + BN - 1) / BN;
-    const bool odd = ((int64_t)nkept * (bp / 32)) % 2 != 0;
-    auto kern = odd ? gemm_kept_kernel<PrecF32, false, true> : gemm_kept_kernel<PrecF32, false, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tilesM * tilesN)), dim3(kThreadsK), 0, s, At, ldat,
-                       Bt, ldbt, m, l, bp, kept, nkept, 1, (int64_t)0, scale, C, ldc,
-                       (int32_t)tilesM, (int32_t)tilesN, CMask{nullptr, 0, 0, 0, 1},
-                       SplitK{nullptr, 0});
-    return hipGetLastError();
-}
+namespace {
 
 // Split K loop for products with few tiles: a single 256x256 tile runs on
 // one CU, so a small product (for example 256 x 256 over K = 1024) would leave
@@ -1129,31 +1250,22 @@ hipError_t launch_gemm_kept(const float* At, int64_t ldat, const float* Bt, int6
 constexpr int64_t kSplitSlots = 256;
 constexpr int64_t kSplitMinSteps = 2;
 
-namespace {
+int64_t tiles_of(int64_t m, int64_t l, int side) {
+    return ((m + side - 1) / side) * ((l + side - 1) / side);
+}
 
-int64_t tiles_of_product(int64_t m, int64_t l) { return ((m + BM - 1) / BM) * ((l + BN - 1) / BN); }
-
-// Most splits a product of `tiles` tiles over `steps` K steps takes (< 2: none).
-int64_t split_bound(int64_t tiles, int64_t steps) {
+// Most splits a product over `steps` K steps takes (< 2: none).
+int64_t split_bound(int64_t m, int64_t l, int64_t steps) {
+    const int64_t tiles = tiles_of(m, l, BM);
     if (tiles * 2 > kSplitSlots) return 1;
     return std::min(kSplitSlots / tiles, steps / kSplitMinSteps);
 }
-
-}  // namespace
-
-size_t gemm_split_bytes(int64_t m, int64_t l, int64_t max_steps) {
-    if (m < 1 || l < 1) return 0;
-    const int64_t S = split_bound(tiles_of_product(m, l), max_steps);
-    return S >= 2 ? (size_t)S * (size_t)m * (size_t)l * 4u : 0;
-}
-
-namespace {
 
 // Splits and steps per split for `total` K steps of an m x l product (false:
 // no split: enough tiles, too few steps, or too little partial space).
 bool split_plan(int64_t m, int64_t l, int64_t total, const float* part, size_t part_bytes,
                 int64_t& S, int64_t& chunk) {
-    S = split_bound(tiles_of_product(m, l), total);
+    S = split_bound(m, l, total);
     if (S < 2 || !part) return false;
     chunk = (total + S - 1) / S;
     chunk += chunk & 1;                            // whole step pairs, the last split may be odd
@@ -1161,6 +1273,77 @@ bool split_plan(int64_t m, int64_t l, int64_t total, const float* part, size_t p
     return S >= 2 && (size_t)S * (size_t)m * (size_t)l * 4u <= part_bytes;
 }
 
+// How a block product is run: tile side (256, 128 or 64; 32 = the small
+// kernel), and the split of its K loop (S = 1: none).
+struct Form {
+    int tile;
+    int64_t S;
+    int64_t chunk;
+};
+
+// Predicted microseconds per K step (128 bytes of every tile row) of
+// `tiles` tiles of a side, from timings on an MI355X (256 CUs; r = the
+// largest number of tiles on one CU).  A 256 tile has the least LDS and L2
+// traffic per flop, but a product of few tiles leaves CUs idle, and one of a
+// few more than a multiple of 256 tiles leaves most of them idle in its last
+// round; smaller tiles fill both (FP32, K = 4096, us at 256 / 128 / 64 / 32:
+// 512 x 512 906 / 250 / 80 / 37, 1024 x 1024 909 / 255 / 84 / 136,
+// 2048 x 2048 915 / 278 / 276 / -, 3333 x 2777 834 / 659 / 578 / -,
+// 4096 x 4096 922 / 959 / 1008 / -, 5120 x 5120 1830 / 1669 / 1576 / -;
+// BF16: 82 / 36 / 39 / 20, 84 / 50 / 41 / 72, 86 / 53 / 58 / -,
+// 87 / 108 / 124 / -, 113 / 126 / 207 / -, 196 / 229 / 323 / -).
+double step_us(bool f32, int tile, int64_t tiles) {
+    const double r = (double)((tiles + kSplitSlots - 1) / kSplitSlots);
+    if (f32) {
+        if (tile == 256) return 7.1 * r;
+        if (tile == 128) return 1.87 * r + 0.1;
+        if (tile == 64) return 0.49 * r + 0.15;
+        return 0.25 * r + 0.04;
+    }
+    if (tile == 256) return r > 1 || tiles > 192 ? 1.75 * r : 1.4;
+    if (tile == 128) return 0.5 * r + 0.3;
+    if (tile == 64) return std::max(0.62, 0.2 * r + 0.1);
+    return 0.25 * r + 0.04;
+}
+
+// The form predicted fastest.  Without partial space (part = nullptr) every
+// entry is summed in step order whatever the tile, bit for bit the same.  A
+// product the split K loop serves keeps its split (the number of partial
+// sums per entry) whatever the tile; the small kernel's waves split the K
+// loop eight ways themselves.
+Form pick_form(bool f32, int64_t m, int64_t l, int64_t total, const float* part,
+               size_t part_bytes) {
+    Form best{256, 1, total};
+    const bool split = split_plan(m, l, total, part, part_bytes, best.S, best.chunk);
+    if (!split) {
+        best.S = 1;
+        best.chunk = total;
+    }
+    const Form base = best;
+    double t = 0;
+    for (const int tile : {256, 128, 64, 32}) {
+        Form f = base;
+        f.tile = tile;
+        if (tile == 32) {
+            if (!part) continue;
+            f.S = 1;
+            f.chunk = total;
+        }
+        const int64_t tiles = tiles_of(m, l, tile) * f.S;
+        if (tiles > 0x7fffffff) continue;
+        double us = step_us(f32, tile, tiles) * (double)f.chunk;
+        // first loads and epilogue; a split's partials written and summed
+        if (tile == 256) us += 6;
+        if (f.S > 1) us += 4 + (double)f.S * (double)m * (double)l * 4 / 4e6;
+        if (tile == 256 || us < t) {
+            t = us;
+            best = f;
+        }
+    }
+    return best;
+}
+
+// C = scale * (the sum of the S partial products at part).
 hipError_t launch_split_sum(const float* part, int64_t S, int64_t m, int64_t l, float scale,
                             float* C, int64_t ldc, hipStream_t s) {
     hipError_t e = hipGetLastError();
@@ -1170,23 +1353,86 @@ hipError_t launch_split_sum(const float* part, int64_t S, int64_t m, int64_t l, 
     return hipGetLastError();
 }
 
+// Operands of a block product (any precision).
+struct Operands {
+    const void* At;
+    int64_t ldat;
+    const void* Bt;
+    int64_t ldbt;
+    int64_t m, l;
+    int32_t bp;
+    const BlockList* kept;
+    int32_t nkept, nsub;
+    int64_t lo_off;
+    float scale;
+    float* C;
+    int64_t ldc;
+};
+
+template <typename P, typename S>
+hipError_t launch_tile(const Operands& o, const Form& f, int64_t total, float* part,
+                       hipStream_t s) {
+    const int64_t tilesM = (o.m + S::BT - 1) / S::BT;
+    const int64_t tilesN = (o.l + S::BT - 1) / S::BT;
+    auto kern = f.S > 1      ? gemm_kept_kernel<P, S, false, true, true>
+                : total % 2 ? gemm_kept_kernel<P, S, false, true>
+                            : gemm_kept_kernel<P, S, false, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * tilesM * tilesN)), dim3(S::kThreads), 0, s,
+                       o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp, *o.kept, o.nkept, o.nsub,
+                       o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM, (int32_t)tilesN,
+                       CMask{nullptr, 0, 0, 0, 1}, SplitK{part, (int32_t)f.chunk});
+    if (f.S > 1) return launch_split_sum(part, f.S, o.m, o.l, o.scale, o.C, o.ldc, s);
+    return hipGetLastError();
+}
+
+template <typename P>
+hipError_t launch_form(const Operands& o, float* part, size_t part_bytes, hipStream_t s) {
+    const int64_t total = (int64_t)o.nkept * o.nsub * (o.bp / (kStepBytes / P::kElem));
+    const Form f = pick_form(P::kElem == 4, o.m, o.l, total, part, part_bytes);
+    if (f.tile == 256) return launch_tile<P, Tile256>(o, f, total, part, s);
+    if (f.tile == 128) return launch_tile<P, Tile128>(o, f, total, part, s);
+    if (f.tile == 64) return launch_tile<P, Tile64>(o, f, total, part, s);
+    const int64_t tilesM = (o.m + kSmallTile - 1) / kSmallTile;
+    const int64_t tilesN = (o.l + kSmallTile - 1) / kSmallTile;
+    hipLaunchKernelGGL(gemm_small_kernel<P>, dim3((unsigned)(tilesM * tilesN)),
+                       dim3(64 * kSmallWaves), 0, s, o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp,
+                       *o.kept, o.nkept, o.nsub, o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM,
+                       (int32_t)tilesN);
+    return hipGetLastError();
+}
+
+template <typename S>
+hipError_t launch_cmask_tile(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
+                             int64_t m, int64_t l, int32_t bp, const CMask& cm, int64_t tilesM,
+                             int64_t tilesN, float* C, int64_t ldc, hipStream_t s) {
+    BlockList none;
+    for (int j = 0; j < OS_MAX_BLOCKS; ++j) none.idx[j] = 0;
+    // a tile's step count is (its kept blocks) * bp / 32: always even when
+    // bp / 32 is, and then the unmasked pair loop serves every tile
+    auto kern = (bp / 32) % 2 == 0 ? gemm_kept_kernel<PrecF32, S, true, false>
+                                   : gemm_kept_kernel<PrecF32, S, true, true>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tilesM * tilesN)), dim3(S::kThreads), 0, s, At, ldat,
+                       Bt, ldbt, m, l, bp, none, 0, 1, (int64_t)0, 1.0f, C, ldc, (int32_t)tilesM,
+                       (int32_t)tilesN, cm, SplitK{nullptr, 0});
+    return hipGetLastError();
+}
+
 }  // namespace
 
-hipError_t launch_gemm_kept_split(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
-                                  int64_t m, int64_t l, int32_t bp, const BlockList& kept,
-                                  int32_t nkept, float scale, float* C, int64_t ldc, float* part,
-                                  size_t part_bytes, hipStream_t s) {
+size_t gemm_split_bytes(int64_t m, int64_t l, int64_t max_steps) {
+    if (m < 1 || l < 1) return 0;
+    const int64_t S = split_bound(m, l, max_steps);
+    return S >= 2 ? (size_t)S * (size_t)m * (size_t)l * 4u : 0;
+}
+
+hipError_t launch_gemm_kept(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
+                            int64_t m, int64_t l, int32_t bp, const BlockList& kept,
+                            int32_t nkept, float scale, float* C, int64_t ldc, float* part,
+                            size_t part_bytes, hipStream_t s) {
     if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 4) || nkept < 1) return hipErrorInvalidValue;
-    int64_t S = 0, chunk = 0;
-    if (!split_plan(m, l, (int64_t)nkept * (bp / 32), part, part_bytes, S, chunk))
-        return launch_gemm_kept(At, ldat, Bt, ldbt, m, l, bp, kept, nkept, scale, C, ldc, s);
-    const int64_t tilesM = (m + BM - 1) / BM;
-    const int64_t tilesN = (l + BN - 1) / BN;
-    hipLaunchKernelGGL((gemm_kept_kernel<PrecF32, false, true, true>),
-                       dim3((unsigned)(S * tilesM * tilesN)), dim3(kThreadsK), 0, s, At, ldat, Bt,
-                       ldbt, m, l, bp, kept, nkept, 1, (int64_t)0, scale, C, ldc, (int32_t)tilesM,
-                       (int32_t)tilesN, CMask{nullptr, 0, 0, 0, 1}, SplitK{part, (int32_t)chunk});
-    return launch_split_sum(part, S, m, l, scale, C, ldc, s);
+    return launch_form<PrecF32>(Operands{At, ldat, Bt, ldbt, m, l, bp, &kept, nkept, 1, 0, scale, C,
+                                         ldc},
+                                part, part_bytes, s);
 }
 
 hipError_t launch_gemm_cmask(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
@@ -1195,20 +1441,30 @@ hipError_t launch_gemm_cmask(const float* At, int64_t ldat, const float* Bt, int
     if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 4) || cblk < 1 || nst < 1 || nst > OS_MAX_BLOCKS)
         return hipErrorInvalidValue;
     const int64_t nbI = (m + cblk - 1) / cblk, nbJ = (l + cblk - 1) / cblk;
-    const int64_t tb = (cblk + BM - 1) / BM;
-    const int64_t tilesM = nbI * tb, tilesN = nbJ * tb;
-    if (tilesM * tilesN > 0x7fffffff || nbJ > 0x7fffffff) return hipErrorInvalidValue;
-    BlockList none;
-    for (int j = 0; j < OS_MAX_BLOCKS; ++j) none.idx[j] = 0;
-    // a tile's step count is (its kept blocks) * bp / 32: always even when
-    // bp / 32 is, and then the unmasked pair loop serves every tile
-    auto kern = (bp / 32) % 2 == 0 ? gemm_kept_kernel<PrecF32, true, false>
-                                   : gemm_kept_kernel<PrecF32, true, true>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tilesM * tilesN)), dim3(kThreadsK), 0, s, At, ldat,
-                       Bt, ldbt, m, l, bp, none, 0, 1, (int64_t)0, 1.0f, C, ldc, (int32_t)tilesM,
-                       (int32_t)tilesN, CMask{cmask, cblk, (int32_t)nbJ, nst, (int32_t)tb},
-                       SplitK{nullptr, 0});
-    return hipGetLastError();
+    // the tile side predicted fastest (every entry's sum is the same for all)
+    int side = 0;
+    double t = 0;
+    for (const int tile : {256, 128, 64}) {
+        const int64_t tb = (cblk + tile - 1) / tile;
+        const int64_t live = nbI * tb * nbJ * tb;
+        if (live > 0x7fffffff || nbJ > 0x7fffffff) continue;
+        const double us = step_us(true, tile, live);
+        if (!side || us < t) {
+            t = us;
+            side = tile;
+        }
+    }
+    if (!side) return hipErrorInvalidValue;
+    const int64_t tb = (cblk + side - 1) / side;
+    const CMask cm{cmask, cblk, (int32_t)nbJ, nst, (int32_t)tb};
+    if (side == 256)
+        return launch_cmask_tile<Tile256>(At, ldat, Bt, ldbt, m, l, bp, cm, nbI * tb, nbJ * tb, C,
+                                          ldc, s);
+    if (side == 128)
+        return launch_cmask_tile<Tile128>(At, ldat, Bt, ldbt, m, l, bp, cm, nbI * tb, nbJ * tb, C,
+                                          ldc, s);
+    return launch_cmask_tile<Tile64>(At, ldat, Bt, ldbt, m, l, bp, cm, nbI * tb, nbJ * tb, C, ldc,
+                                     s);
 }
 
 hipError_t launch_gemm_batch_sym(const BatchProblem* probs, const int4* tiles,
@@ -1292,38 +1548,11 @@ hipError_t launch_gemm_kept_fp8_split(const void* At, int64_t ldat, const void* 
 hipError_t launch_gemm_kept_bf16(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
                                  int64_t m, int64_t l, int32_t bp, const BlockList& kept,
                                  int32_t nkept, int split, int64_t lo_off, float scale, float* C,
-                                 int64_t ldc, hipStream_t s) {
+                                 int64_t ldc, float* part, size_t part_bytes, hipStream_t s) {
     if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 2) || nkept < 1) return hipErrorInvalidValue;
-    const int64_t tilesM = (m + BM - 1) / BM;
-    const int64_t tilesN = (l + BN - 1) / BN;
-    const bool odd = ((int64_t)nkept * (split ? 3 : 1) * (bp / 64)) % 2 != 0;
-    auto kern = odd ? gemm_kept_kernel<PrecBF16, false, true> : gemm_kept_kernel<PrecBF16, false, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tilesM * tilesN)), dim3(kThreadsK), 0, s, At, ldat,
-                       Bt, ldbt, m, l, bp, kept, nkept, split ? 3 : 1, lo_off, scale, C, ldc,
-                       (int32_t)tilesM, (int32_t)tilesN, CMask{nullptr, 0, 0, 0, 1},
-                       SplitK{nullptr, 0});
-    return hipGetLastError();
-}
-
-hipError_t launch_gemm_kept_bf16_split(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
-                                       int64_t m, int64_t l, int32_t bp, const BlockList& kept,
-                                       int32_t nkept, int split, int64_t lo_off, float scale,
-                                       float* C, int64_t ldc, float* part, size_t part_bytes,
-                                       hipStream_t s) {
-    if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 2) || nkept < 1) return hipErrorInvalidValue;
-    int64_t S = 0, chunk = 0;
-    const int64_t total = (int64_t)nkept * (split ? 3 : 1) * (bp / 64);
-    if (!split_plan(m, l, total, part, part_bytes, S, chunk))
-        return launch_gemm_kept_bf16(At, ldat, Bt, ldbt, m, l, bp, kept, nkept, split, lo_off,
-                                     scale, C, ldc, s);
-    const int64_t tilesM = (m + BM - 1) / BM;
-    const int64_t tilesN = (l + BN - 1) / BN;
-    hipLaunchKernelGGL((gemm_kept_kernel<PrecBF16, false, true, true>),
-                       dim3((unsigned)(S * tilesM * tilesN)), dim3(kThreadsK), 0, s, At, ldat, Bt,
-                       ldbt, m, l, bp, kept, nkept, split ? 3 : 1, lo_off, scale, C, ldc,
-                       (int32_t)tilesM, (int32_t)tilesN, CMask{nullptr, 0, 0, 0, 1},
-                       SplitK{part, (int32_t)chunk});
-    return launch_split_sum(part, S, m, l, scale, C, ldc, s);
+    return launch_form<PrecBF16>(Operands{At, ldat, Bt, ldbt, m, l, bp, &kept, nkept,
+                                          split ? 3 : 1, lo_off, scale, C, ldc},
+                                 part, part_bytes, s);
 }
 
 }  // namespace osk

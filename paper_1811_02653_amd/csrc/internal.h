@@ -178,30 +178,27 @@ bool plan_gemm_ok(int64_t m, int64_t l, int32_t bp, int64_t ldat, int64_t ldbt, 
 
 // C = scale * sum over the kept stored blocks (kept.idx[0 .. nkept)) of
 // At_j * Bt_j^T, with At (m x nst*bp) and Bt (l x nst*bp) line-major
-// sketches (column block j = columns j*bp .. j*bp + bp - 1).
+// sketches (column block j = columns j*bp .. j*bp + bp - 1).  With part (at
+// least gemm_split_bytes) a product of few tiles may split its K loop over
+// several workgroups per tile (partials in part, then summed in split order:
+// deterministic, but summed in a different order than unsplit); with part =
+// nullptr or too little space it never does.
 hipError_t launch_gemm_kept(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
                             int64_t m, int64_t l, int32_t bp, const BlockList& kept,
-                            int32_t nkept, float scale, float* C, int64_t ldc, hipStream_t s);
+                            int32_t nkept, float scale, float* C, int64_t ldc, float* part,
+                            size_t part_bytes, hipStream_t s);
 // Partial-product bytes the split launches may use for an m x l product of
 // at most max_steps K steps (128 bytes of every tile row each: 32 FP32, 64
 // BF16 or 128 FP8 values); 0 when it never splits (enough tiles to fill the
 // device).
 size_t gemm_split_bytes(int64_t m, int64_t l, int64_t max_steps);
-// launch_gemm_kept, with the K loop split over several workgroups per tile
-// when the product has few tiles (partials in part, then summed in split
-// order: deterministic, but summed in a different order than unsplit); the
-// plain launch when it would not split or part_bytes is too small.
-hipError_t launch_gemm_kept_split(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
-                                  int64_t m, int64_t l, int32_t bp, const BlockList& kept,
-                                  int32_t nkept, float scale, float* C, int64_t ldc, float* part,
-                                  size_t part_bytes, hipStream_t s);
 // The same with BF16 sketches (block stride bp, a multiple of 64; leading
 // dimensions in BF16 values).  split != 0 adds the terms A_j * lo(B_j)^T and
 // lo(A_j) * B_j^T, the low parts lo_off columns after the high parts.
 hipError_t launch_gemm_kept_bf16(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
                                  int64_t m, int64_t l, int32_t bp, const BlockList& kept,
                                  int32_t nkept, int split, int64_t lo_off, float scale, float* C,
-                                 int64_t ldc, hipStream_t s);
+                                 int64_t ldc, float* part, size_t part_bytes, hipStream_t s);
 // The same with FP8 copies (launch_quant_fp8 layout: ld in bytes, the scale
 // bytes of a row `scales` bytes after its start; block stride bp a multiple
 // of 128).
@@ -209,13 +206,8 @@ hipError_t launch_gemm_kept_fp8(const void* At, int64_t ldat, const void* Bt, in
                                 int64_t scales, int64_t m, int64_t l, int32_t bp,
                                 const BlockList& kept, int32_t nkept, int split, int64_t lo_off,
                                 float scale, float* C, int64_t ldc, hipStream_t s);
-// launch_gemm_kept_bf16 / launch_gemm_kept_fp8 with the split K loop of
-// launch_gemm_kept_split (partials in part, summed in split order).
-hipError_t launch_gemm_kept_bf16_split(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
-                                       int64_t m, int64_t l, int32_t bp, const BlockList& kept,
-                                       int32_t nkept, int split, int64_t lo_off, float scale,
-                                       float* C, int64_t ldc, float* part, size_t part_bytes,
-                                       hipStream_t s);
+// launch_gemm_kept_fp8 with the split K loop of launch_gemm_kept (partials
+// in part, summed in split order).
 hipError_t launch_gemm_kept_fp8_split(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
                                       int64_t scales, int64_t m, int64_t l, int32_t bp,
                                       const BlockList& kept, int32_t nkept, int split,

@@ -615,3 +615,53 @@ def test_grouped_order_follows_its_definition(n, b, N, e):
     h, _ = oracle.hash_tables(seed, N + e, n, b)
     for i in range(N + e):
         np.testing.assert_array_equal(order[i, :b], _grouped_order_reference(h[i], n, b))
+
+
+# ---------------------------------------------------------------------------
+# block product: tile forms (256, 128, 64 and the 32 x 32 small kernel)
+# ---------------------------------------------------------------------------
+
+@pytest.mark.parametrize("m,l", [(1, 1), (31, 33), (64, 65), (129, 127), (257, 300), (520, 513),
+                                 (1100, 900), (2100, 1030), (40, 5000)])
+@pytest.mark.parametrize("precision,b,nst", [("fp32", 96, 3), ("fp32", 256, 2), ("bf16", 64, 5),
+                                             ("bf16x3", 128, 1)])
+def test_block_product_tile_forms(m, l, precision, b, nst):
+    """Sizes around the tile sides, odd and even step counts: against the FP64
+    product of the operands as stored, and bit for bit against the same rows
+    of A in a product of another size (another tile form)."""
+    g = torch.Generator(device="cuda").manual_seed(m * 7919 + l)
+    w = nst * osk.block_stride(b)
+    At = torch.randn(m, w, generator=g, device="cuda")
+    Bt = torch.randn(l, w, generator=g, device="cuda")
+    if precision == "fp32":
+        Aq, Bq = At, Bt
+        want = At.double() @ Bt.double().t()
+    else:
+        Aq = osk.sketch_quantize(At, b, nst, precision)
+        Bq = osk.sketch_quantize(Bt, b, nst, precision)
+        parts = osk.quantized_row(b, nst, "bf16")
+        Ah, Bh = Aq[:, :parts].double(), Bq[:, :parts].double()
+        want = Ah @ Bh.t()
+        if precision == "bf16x3":
+            want += Ah @ Bq[:, parts:].double().t() + Aq[:, parts:].double() @ Bh.t()
+    C = osk.gemm_kept_prec(Aq, Bq, b, nst, precision)
+    assert rel(host(C), host(want / nst)) <= PRODUCT_TOL
+    k = (m + 1) // 2
+    np.testing.assert_array_equal(host(osk.gemm_kept_prec(Aq[:k], Bq, b, nst, precision)),
+                                  host(C[:k]))
+
+
+@pytest.mark.parametrize("m,n,l,b,N", [(33, 500, 31, 40, 3), (130, 1024, 200, 128, 4),
+                                       (700, 900, 400, 96, 3), (60, 2000, 4100, 256, 2)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_whole_path_tile_forms(m, n, l, b, N, precision):
+    """The whole path's forms (split K loop, small kernel) against the staged
+    steps on the same sketches, whose product is never split."""
+    A, B = synthetic.gaussian_pair(m, n, l, m + l)
+    Ad, Bd = dev(A), dev(B)
+    C = host(osk.matmul(Ad, Bd, b, N, 0, seed=5, precision=precision))
+    At, Bt = osk.sketch_cols(Ad, b, N, 0, seed=5), osk.sketch_rows(Bd, b, N, 0, seed=5)
+    if precision != "fp32":
+        At, Bt = (osk.sketch_quantize(S, b, N, precision) for S in (At, Bt))
+    Cs = host(osk.gemm_kept_prec(At, Bt, b, N, precision))
+    assert rel(C, Cs) <= 1e-6
