@@ -29,65 +29,11 @@
 // permutation of the offset, see win_slot) and the sign (bit 15); the
 // padding entry points at a zero row.
 #include <algorithm>
-#include <type_traits>
 
-#include "internal.h"
-#include "fp8.h"
+#include "sketch_launch.h"
 
 namespace osk {
 namespace {
-
-constexpr int kWin = kSketchWindow;    // sketched indices per window (8192)
-constexpr int kLines = 4;              // lines per workgroup
-constexpr int kThreads = 512;          // 8 waves
-constexpr int kWaves = kThreads / 64;
-constexpr int kPerThread = kWin / kThreads;   // window positions staged per thread (16)
-constexpr uint16_t kPad = (uint16_t)kWin;     // entry of the zero row, positive
-constexpr int kAhead = 3;              // list chunks of a slot fetched ahead
-constexpr int kDist = 1;               // slots ahead whose lists are fetched
-
-// LDS slot of window position p (p < kWin).  Thread t stages the quads of
-// positions 2048u + 4t + j (j < 4); they go to slots 2048u + 512j + t, so the
-// lanes of one staging write touch consecutive slots.  List entries hold the
-// slot of their position.
-__device__ __forceinline__ int win_slot(int p) {
-    return (p & ~2047) | ((p & 3) << 9) | ((p >> 2) & 511);
-}
-
-// f(integral_constant<int, I>) for I = B .. E - 1, unrolled by the compiler
-// whatever the size of f's body.
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
-// Spread consecutive task ids over the 8 XCDs in contiguous runs: task T is
-// run by the workgroup with linear id L where T = (L % 8) * (tasks / 8) + L / 8,
-// so neighbouring tasks share an XCD and its L2.
-__device__ __forceinline__ int64_t xcd_task(int64_t L, int64_t tasks) {
-    if (tasks % 8 != 0) return L;
-    return (L % 8) * (tasks / 8) + L / 8;
-}
-
-__device__ __forceinline__ uint64_t lanes_below() {
-    const int lane = threadIdx.x & 63;
-    return lane == 0 ? 0ull : (~0ull >> (64 - lane));
-}
-
-__device__ __forceinline__ float wave_maxf(float x) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x = fmaxf(x, __shfl_xor(x, d));
-    return x;
-}
-
-__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x = max(x, (uint32_t)__shfl_xor((int)x, d));
-    return x;
-}
 
 // ---------------------------------------------------------------------------
 // Prepared lists.  One wave per (window w, block i).
@@ -509,486 +455,6 @@ __global__ __launch_bounds__(256) void identity_inv_kernel(int32_t bp, int32_t* 
 }
 
 // ---------------------------------------------------------------------------
-// The sketch kernel.  Thread t stages window positions 2048u + 4t + j
-// (u, j < 4) into LDS slots win_slot(k) = 2048u + 512j + t; list entries
-// hold those slots.
-//   kRowLines = true : lines are rows of X (lines x n, ld ldx).  With vec
-//                      (X 16-byte aligned, ldx % 4 == 0, and the window whole
-//                      or n a multiple of 4) a line's 4 consecutive positions
-//                      come with one 16-byte load (1 KiB per wave,
-//                      coalesced): r[4*line + u] holds positions 4t + 2048u
-//                      .. +3 of that line.  Otherwise every value is loaded
-//                      on its own into the same layout.
-//   kRowLines = false: lines are columns of X (n x lines, ld ldx); r[4u + j]
-//                      holds X[k][line0 .. line0+3] for position k = 2048u +
-//                      4t + j, one 16-byte load when vec (X 16-byte aligned,
-//                      ldx % 4 == 0), else four.
-// kWeighted (row lines): every value at sketched index k is multiplied by
-// sqrt(wd[k]) (a diagonal weight, as in A D^{1/2} S for a Hessian A D A^T);
-// w[u] holds the weights of positions 4t + 2048u .. +3.  The weight is
-// applied when the window is written to LDS, not when it is loaded, so the
-// loads of the next window stay in flight while the current one is summed.
-// ---------------------------------------------------------------------------
-// Input values are held in registers as loaded (4 consecutive values of a
-// line: a float4 for FP32, their 4 bit patterns in a uint2 for BF16) and
-// converted to FP32 (exactly) when the window is written to LDS.
-// A window's FP32 values and weights are read once: non-temporal loads keep
-// them from displacing the bucket lists (which every line group reads) in
-// the caches (the FP32 sketch of A 2-5 % faster).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 load_stream(const float* __restrict__ p) {
-    const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
-    return make_float4(t[0], t[1], t[2], t[3]);
-}
-
-template <typename TI>
-struct RawQuad;
-template <>
-struct RawQuad<float> {
-    using type = float4;
-    static __device__ __forceinline__ type load(const float* __restrict__ p) {
-        return *reinterpret_cast<const float4*>(p);
-    }
-    static __device__ __forceinline__ type gather(const float* __restrict__ p,
-                                                  const int64_t (&k)[4]) {
-        return make_float4(p[k[0]], p[k[1]], p[k[2]], p[k[3]]);
-    }
-    static __device__ __forceinline__ float value(const type& v, int j) {
-        return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
-    }
-};
-template <>
-struct RawQuad<__bf16> {
-    using type = uint2;
-    static __device__ __forceinline__ uint32_t bits(const __bf16* __restrict__ p) {
-        return __builtin_bit_cast(uint16_t, *p);
-    }
-    static __device__ __forceinline__ type load(const __bf16* __restrict__ p) {
-        return *reinterpret_cast<const uint2*>(p);
-    }
-    static __device__ __forceinline__ type gather(const __bf16* __restrict__ p,
-                                                  const int64_t (&k)[4]) {
-        return make_uint2(bits(p + k[0]) | bits(p + k[1]) << 16,
-                          bits(p + k[2]) | bits(p + k[3]) << 16);
-    }
-    static __device__ __forceinline__ float value(const type& v, int j) {
-        const uint32_t w = j < 2 ? v.x : v.y;
-        return __uint_as_float((j & 1) ? (w & 0xFFFF0000u) : (w << 16));
-    }
-};
-
-// Loads pieces p0 .. p1 - 1 of a window (piece 4u + q: r[4q + u] of row
-// lines with w[u] at q = 0, r[4u + q] of column lines); all 16 pieces make
-// the window.  p0 and p1 are constants where the caller is unrolled.
-template <bool kRowLines, bool kWeighted, typename TI, bool kWhole = false>
-__device__ __forceinline__ void load_window(typename RawQuad<TI>::type (&r)[kPerThread],
-                                            float4 (&w)[4], const TI* __restrict__ X,
-                                            int64_t lines, int64_t ldx, int64_t line0, int64_t k0,
-                                            int kw, bool vec, const float* __restrict__ wd,
-                                            int p0 = 0, int p1 = kPerThread) {
-    using R = RawQuad<TI>;
-    static_assert(kRowLines || sizeof(TI) == 4, "column lines are read as FP32 only");
-    // Every load is unconditional (a branch around a load makes each use wait
-    // for all loads in flight): positions past the window's end are clamped to
-    // its last index (no entry refers to them) and lines past the matrix to
-    // its last line (their sums are never stored).
-    const int tid = threadIdx.x;
-    const int64_t l1 = min(line0 + 1, lines - 1) - line0;
-    const int64_t l2 = min(line0 + 2, lines - 1) - line0;
-    const int64_t l3 = min(line0 + 3, lines - 1) - line0;
-    if constexpr (kRowLines) {
-        const int64_t dl[4] = {0, l1, l2, l3};
-        if (vec) {
-            // kw is a multiple of 4 here: the last whole quad starts at kw - 4.
-            // Uniform line bases plus a 32-bit lane offset (scalar-base
-            // addressing: a piece issued late keeps one offset register live,
-            // not a 64-bit address).
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t off = (uint32_t)min(4 * tid + 2048 * u, kw - 4);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (4 * u + q < p0 || 4 * u + q >= p1) continue;
-                    const TI* base = X + (line0 + dl[q]) * ldx + k0;
-                    // (the FP32 load written here, not through R::load: through the
-                    // helper the FP32 kernels took 20 more registers and spilled)
-                    if constexpr (sizeof(TI) == 4)
-                        r[4 * q + u] = load_stream(base + off);
-                    else
-                        r[4 * q + u] = R::load(base + off);
-                    if constexpr (kWeighted)
-                        if (q == 0) w[u] = load_stream(wd + k0 + off);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                int64_t kk[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) kk[j] = k0 + min(4 * tid + 2048 * u + j, kw - 1);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (4 * u + q < p0 || 4 * u + q >= p1) continue;
-                    r[4 * q + u] = R::gather(X + (line0 + dl[q]) * ldx, kk);
-                    if constexpr (kWeighted)
-                        if (q == 0) w[u] = make_float4(wd[kk[0]], wd[kk[1]], wd[kk[2]], wd[kk[3]]);
-                }
-            }
-        }
-    } else {
-        // r[4u + j] = the 4 lines at position 2048u + 4t + j
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (4 * u + j < p0 || 4 * u + j >= p1) continue;
-                const int64_t kk = k0 + min(4 * tid + 2048 * u + j, kw - 1);
-                const TI* p = X + kk * ldx + line0;
-                if constexpr (kWhole)    // vec and every line group whole
-                    r[4 * u + j] = *reinterpret_cast<const float4*>(p);
-                else if (vec && l3 == 3)      // uniform
-                    r[4 * u + j] = *reinterpret_cast<const float4*>(p);
-                else
-                    r[4 * u + j] = make_float4(p[0], p[l1], p[l2], p[l3]);
-            }
-        }
-    }
-}
-
-__device__ __forceinline__ float comp4(const float4& v, int j) {
-    return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
-}
-
-// Writes a loaded window into LDS: win[win_slot(k)] = the 4 lines' values at
-// window position k (weighted when kWeighted).
-template <bool kRowLines, bool kWeighted, typename TI>
-__device__ __forceinline__ void stage_window(float4* __restrict__ win,
-                                             const typename RawQuad<TI>::type (&r)[kPerThread],
-                                             const float4 (&w)[4]) {
-    using R = RawQuad<TI>;
-    const int tid = threadIdx.x;
-    if constexpr (kRowLines) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float4 v = make_float4(R::value(r[u], j), R::value(r[4 + u], j),
-                                       R::value(r[8 + u], j), R::value(r[12 + u], j));
-                if constexpr (kWeighted) {
-                    const float sw = sqrtf(comp4(w[u], j));
-                    v.x *= sw;
-                    v.y *= sw;
-                    v.z *= sw;
-                    v.w *= sw;
-                }
-                win[2048 * u + 512 * j + tid] = v;      // slot of position 2048u + 4t + j
-            }
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                win[2048 * u + 512 * j + tid] =
-                    make_float4(R::value(r[4 * u + j], 0), R::value(r[4 * u + j], 1),
-                                R::value(r[4 * u + j], 2), R::value(r[4 * u + j], 3));
-    }
-}
-
-// Adds the 8 entries of one chunk (16-bit entries, two per word; sign bit 15
-// selects the sign of the FP32 +-1.0 factor).  All eight LDS reads are issued
-// before the first FMA so their latencies overlap.
-__device__ __forceinline__ void add_chunk(float4& acc, const float4* __restrict__ win, uint4 e) {
-    const uint32_t w[4] = {e.x, e.y, e.z, e.w};
-    float4 v[8];
-    float s[8];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        v[2 * u] = win[w[u] & 0x7FFFu];
-        v[2 * u + 1] = win[(w[u] >> 16) & 0x7FFFu];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        s[2 * u] = __uint_as_float(0x3F800000u | ((w[u] << 16) & 0x80000000u));
-        s[2 * u + 1] = __uint_as_float(0x3F800000u | (w[u] & 0x80000000u));
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        acc.x = fmaf(s[u], v[u].x, acc.x);
-        acc.y = fmaf(s[u], v[u].y, acc.y);
-        acc.z = fmaf(s[u], v[u].z, acc.z);
-        acc.w = fmaf(s[u], v[u].w, acc.w);
-    }
-}
-
-// One workgroup of 8 waves fills a CU's LDS, so each SIMD runs 2 waves: the
-// compiler may use up to 256 VGPRs per lane.
-template <int kSlots, bool kRowLines, bool kWeighted, typename TI, bool kFp8Out, bool kSpread>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void sketch_kernel(
-    const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int vec, int32_t bp,
-    int32_t qn, int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
-    const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell, void* __restrict__ out,
-    int64_t ldo, int32_t npass, const float* __restrict__ wd, int32_t obp, int32_t omode,
-    int64_t ozlo) {
-    __shared__ float4 win[kWin + 1];    // row kWin stays zero
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t groups = (lines + kLines - 1) / kLines;
-    const int64_t tasks = groups * npass;
-    const int gslots = nst * qn;         // groups of 64 buckets over the stored blocks
-    if (tid == 0) win[kWin] = make_float4(0.f, 0.f, 0.f, 0.f);
-
-    // vec for a row-lines window: whole windows always, the last one when n % 4 == 0
-    auto vec_at = [&](int64_t k0) {
-        return kRowLines ? (vec != 0 && (k0 + kWin <= n || (n & 3) == 0)) : vec != 0;
-    };
-    // Persistent: workgroup g takes tasks g, g + grid, ... (task = a group
-    // of 4 lines and a pass); the first window of its next task is fetched
-    // while the last window of the current one is summed, so only the first
-    // task of a workgroup waits for its first window.
-    //
-    // Slot bookkeeping stays out of the scalar path (a scalar load in the
-    // slot loop drains every LDS read in flight): lane s of each wave holds,
-    // for its slot s, the header index of the slot's bucket group in window
-    // 0 (hb, -1 for an unused slot), the region's chunk base in window 0
-    // (eb), the group's first output column (col) and how many of its 64
-    // buckets exist (lim, 0 for an unused slot).  A window's headers come in
-    // with one vector load, issued before the window's values are fetched.
-    auto line_of = [&](int64_t it) { return xcd_task(it, tasks) / npass * kLines; };
-    struct Meta {
-        int32_t hb, eb, col, lim;
-    };
-    auto meta_of = [&](int64_t it) -> Meta {
-        const int ps = (int)(xcd_task(it, tasks) % npass);
-        const int G = (ps * kSlots + lane) * kWaves + wave;
-        Meta m{-1, 0, 0, 0};
-        if (lane < kSlots && G < gslots) {
-            const int j = G / qn;
-            const int q = G - j * qn;
-            const int32_t i = bl.idx[j];
-            m.hb = (i * nwin) * qn + q;
-            m.eb = (int32_t)((int64_t)i * nwin * RC);
-            m.col = j * obp + q * 64;
-            m.lim = min(64, obp - q * 64);
-        }
-        return m;
-    };
-    auto headers = [&](int32_t hb, int w) -> uint32_t {
-        const uint32_t h = hdr[max(hb, 0) + w * qn];     // unconditional: index valid
-        return hb >= 0 ? h : 0u;
-    };
-    typename RawQuad<TI>::type pre[kPerThread];
-    float4 wpre[4];
-    uint32_t hnext = 0;
-    if ((int64_t)blockIdx.x < tasks) {
-        hnext = headers(meta_of(blockIdx.x).hb, 0);
-        load_window<kRowLines, kWeighted, TI>(pre, wpre, X, lines, ldx, line_of(blockIdx.x), 0,
-                                              (int)min((int64_t)kWin, n), vec_at(0), wd);
-    }
-    for (int64_t it = blockIdx.x; it < tasks; it += gridDim.x) {
-    const int64_t task = xcd_task(it, tasks);
-    const int64_t line0 = task / npass * kLines;
-    const Meta meta = meta_of(it);      // (its loads complete with the window's, before staging)
-
-    float4 acc[kSlots];
-#pragma unroll
-    for (int s = 0; s < kSlots; ++s) acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int w = 0; w < nwin; ++w) {
-        __syncthreads();                 // the previous window is no longer read
-        stage_window<kRowLines, kWeighted, TI>(win, pre, wpre);
-        __syncthreads();
-        const uint32_t hv = hnext;       // this window's headers (lane s: slot s)
-        // The list chunks of slot s + kDist (up to kAhead of them) are fetched
-        // while slot s is summed.  Fetches are unconditional: chunk indices
-        // past a slot's count repeat its last chunk, and an unused slot
-        // (header 0) reads chunk 0 of block 0's region (never summed).
-        const int64_t wrc = (int64_t)w * RC;
-        auto slot_list = [&](int s, uint32_t& nch) -> const uint4* {
-            const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)hv, s);
-            const int64_t eb = __builtin_amdgcn_readlane(meta.eb, s);
-            nch = h >> 16;
-            return ell + (eb + wrc + (h & 0xFFFFu)) * 64 + lane;
-        };
-        auto fetch = [&](uint4 (&d)[kAhead], const uint4* p, uint32_t nch) {
-            const uint32_t last = nch > 0 ? nch - 1 : 0;
-#pragma unroll
-            for (int c = 0; c < kAhead; ++c) d[c] = p[(int64_t)min((uint32_t)c, last) * 64];
-        };
-        // The next window (this task's, else the first of the next task) is
-        // loaded in kPerThread pieces spread over the slots, each issued
-        // after the list fetch of its slot: a wave's loads complete in
-        // order, so waiting for slot s's list waits only for pieces issued
-        // kDist or more slots earlier, not for the whole window.  When no
-        // window follows, the pieces read one quad of this window again
-        // (every lane the same address; loads stay unconditional).
-        int64_t l1 = line0, k1 = (int64_t)(w + 1) * kWin;
-        int32_t hb1 = meta.hb;
-        int kw1;
-        if (w + 1 < nwin) {
-            kw1 = (int)min((int64_t)kWin, n - k1);
-        } else if (it + gridDim.x < tasks) {
-            hb1 = meta_of(it + gridDim.x).hb;
-            l1 = line_of(it + gridDim.x);
-            k1 = 0;
-            kw1 = (int)min((int64_t)kWin, n);
-        } else {
-            k1 = (int64_t)w * kWin;
-            kw1 = (int)min((int64_t)4, n - k1);
-        }
-        const bool vec1 = vec_at(k1) && kw1 >= 4;
-        constexpr int kRing = kDist + 1;
-        uint4 lst[kRing][kAhead];
-        uint32_t nls[kRing];
-        const uint4* pls[kRing];
-#pragma unroll
-        for (int s = 0; s < kDist && s < kSlots; ++s) {
-            pls[s] = slot_list(s, nls[s]);
-            fetch(lst[s], pls[s], nls[s]);
-        }
-        hnext = headers(hb1, (int)(k1 / kWin));
-        constexpr int kSpreadSlots = kSlots < kPerThread ? kSlots : kPerThread;
-        constexpr int kPer = (kPerThread + kSpreadSlots - 1) / kSpreadSlots;
-        // (unrolled at compile time: acc[s] and the ring stay in registers
-        // however large the body)
-        static_for<0, kSlots>([&](auto sc) {
-            constexpr int s = decltype(sc)::value;
-            if constexpr (s + kDist < kSlots) {
-                constexpr int r = (s + kDist) % kRing;
-                pls[r] = slot_list(s + kDist, nls[r]);
-                fetch(lst[r], pls[r], nls[r]);
-            }
-            if constexpr (kSpread) {
-                if constexpr (s < kSpreadSlots)
-                    load_window<kRowLines, kWeighted, TI, true>(
-                        pre, wpre, X, lines, ldx, l1, k1, kw1, true, wd, s * kPer,
-                        (s + 1) * kPer < kPerThread ? (s + 1) * kPer : kPerThread);
-            } else if constexpr (s == 0) {
-                load_window<kRowLines, kWeighted, TI>(pre, wpre, X, lines, ldx, l1, k1, kw1, vec1,
-                                                      wd);
-            }
-            constexpr int r = s % kRing;
-#pragma unroll
-            for (int c = 0; c < kAhead; ++c)
-                if ((uint32_t)c < nls[r]) add_chunk(acc[s], win, lst[r][c]);
-            for (uint32_t c = kAhead; c < nls[r]; ++c) add_chunk(acc[s], win, pls[r][(int64_t)c * 64]);
-        });
-    }
-
-    // Output: FP32 (omode 0, blocks obp = bp apart), or the copy the block
-    // product reads, blocks obp = b rounded up to 64 apart:
-    //   omode 1: BF16, each sum rounded to nearest even; omode 2: also the
-    //            residual bf16(x - hi), ozlo values after the high part;
-    //   omode 3: FP8 E4M3 codes (bytes) with one E8M0 scale per 64 codes,
-    //            i.e. per slot group and line (its max over the wave's 64
-    //            lanes); the scale bytes follow the codes (ozlo bytes into
-    //            the row), in code order.
-#pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
-        // lanes below lim hold buckets of the block (the last group may be partial)
-        if (lane < __builtin_amdgcn_readlane(meta.lim, s)) {
-            const int64_t o0 = line0 * ldo + __builtin_amdgcn_readlane(meta.col, s) + lane;
-            const float v[4] = {acc[s].x, acc[s].y, acc[s].z, acc[s].w};
-            if (omode == 0) {
-                float* o = static_cast<float*>(out) + o0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (r == 0 || line0 + r < lines) o[r * ldo] = v[r];
-            } else if (!kFp8Out) {
-                __bf16* o = static_cast<__bf16*>(out) + o0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (r == 0 || line0 + r < lines) {
-                        const __bf16 hi = (__bf16)v[r];
-                        o[r * ldo] = hi;
-                        if (omode == 2) o[r * ldo + ozlo] = (__bf16)(v[r] - (float)hi);
-                    }
-                }
-            } else if constexpr (kFp8Out) {
-                // (a separate instantiation: this code would make the FP32
-                // and BF16 kernels with 20 or more slots spill.)  Every lane
-                // of the wave holds a bucket here (lim is 64), so a group's
-                // maximum is taken over all 64 lanes; the four lines' maxima
-                // run in one interleaved butterfly, so that each step's
-                // cross-lane reads overlap.
-                const int64_t col = __builtin_amdgcn_readlane(meta.col, s);
-                uint8_t* row = static_cast<uint8_t*>(out) + line0 * ldo;
-                float a[4];
-                int e[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) a[r] = fabsf(v[r]);
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) a[r] = fmaxf(a[r], __shfl_xor(a[r], d));
-#pragma unroll
-                for (int r = 0; r < 4; ++r) e[r] = e8m0_exponent(a[r]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (r == 0 || line0 + r < lines) {                // uniform
-                        row[r * ldo + col + lane] = (uint8_t)e4m3_rne(ldexpf(v[r], -e[r]));
-                        if (lane == 0) row[r * ldo + ozlo + col / 64] = (uint8_t)(e[r] + 127);
-                    }
-                }
-            }
-        }
-    }
-    }   // tasks
-}
-
-// Slot counts compiled: 1, 2, 4, 8, 12, 16, 20, 24 (4 registers per slot).
-constexpr int kMaxSlots = 24;
-
-// spread: every window is loaded with 16-byte loads -- row lines with vec
-// and n a multiple of 4, column lines with vec and every group of 4 lines
-// whole -- so the next window's loads can be spread over the slots
-// (kSpread).
-template <int S, bool R, bool W, typename TI, bool Q8>
-hipError_t launch_one(dim3 grid, hipStream_t st, bool spread, const TI* X, int64_t lines,
-                      int64_t n, int64_t ldx, int vec, int32_t bp, int32_t qn, int32_t nwin,
-                      int32_t nst, const BlockList& bl, int64_t RC, const uint32_t* hdr,
-                      const uint4* ell, void* out, int64_t ldo, int32_t npass, const float* wd,
-                      int32_t obp, int32_t omode, int64_t ozlo) {
-    if (spread) {
-        hipLaunchKernelGGL((sketch_kernel<S, R, W, TI, Q8, true>), grid, dim3(kThreads), 0, st, X,
-                           lines, n, ldx, vec, bp, qn, nwin, nst, bl, RC, hdr, ell, out, ldo,
-                           npass, wd, obp, omode, ozlo);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((sketch_kernel<S, R, W, TI, Q8, false>), grid, dim3(kThreads), 0, st, X,
-                       lines, n, ldx, vec, bp, qn, nwin, nst, bl, RC, hdr, ell, out, ldo, npass,
-                       wd, obp, omode, ozlo);
-    return hipGetLastError();
-}
-
-template <bool R, bool W, typename TI, bool Q8 = false>
-hipError_t launch_slots(int slots, dim3 grid, hipStream_t st, const TI* X, int64_t lines,
-                        int64_t n, int64_t ldx, int vec, int32_t bp, int32_t qn, int32_t nwin,
-                        int32_t nst, const BlockList& bl, int64_t RC, const uint32_t* hdr,
-                        const uint4* ell, void* out, int64_t ldo, int32_t npass,
-                        const float* wd, int32_t obp, int32_t omode, int64_t ozlo) {
-    const bool spread = vec && (R ? (n & 3) == 0 : (lines & 3) == 0);
-#define OSK_SLOT_CASE(S)                                                                        \
-    if (slots <= S)                                                                             \
-        return launch_one<S, R, W, TI, Q8>(grid, st, spread, X, lines, n, ldx, vec, bp, qn, nwin, \
-                                           nst, bl, RC, hdr, ell, out, ldo, npass, wd, obp, omode, \
-                                           ozlo);
-    OSK_SLOT_CASE(1)
-    OSK_SLOT_CASE(2)
-    OSK_SLOT_CASE(4)
-    OSK_SLOT_CASE(8)
-    OSK_SLOT_CASE(12)
-    OSK_SLOT_CASE(16)
-    OSK_SLOT_CASE(20)
-    if constexpr (!Q8) {        // (FP8 output: at most 20 slots, see sketch_fp8_fusable)
-        OSK_SLOT_CASE(24)
-    }
-#undef OSK_SLOT_CASE
-    return hipErrorInvalidValue;
-}
-
-// ---------------------------------------------------------------------------
 // Transpose: Y (cols x rows, ld ldy) = X^T for X rows x cols (ld ldx): FP32
 // to FP32, or BF16 to BF16 (values copied exactly; staged through LDS as
 // FP32, which holds every BF16 value).  A workgroup of 512 threads moves
@@ -1186,34 +652,14 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
     const uintptr_t quad = bf16 ? 7 : 15;
     const int vec = (reinterpret_cast<uintptr_t>(X) & quad) == 0 && (ldx & 3) == 0 &&
                     (reinterpret_cast<uintptr_t>(wd) & 15) == 0;
-    if (out_mode == 3) {          // FP8 copies: rows only, unweighted
-        if (!row_lines || wd) return hipErrorInvalidValue;
-        if (bf16)
-            return launch_slots<true, false, __bf16, true>(
-                slots, grid, s, static_cast<const __bf16*>(X), lines, n, ldx, vec, bp, p.qn,
-                p.nwin, nst, bl, p.RC, v.hdr, v.ell, out, ldo, npass, nullptr, obp, out_mode, ozlo);
-        return launch_slots<true, false, float, true>(
-            slots, grid, s, static_cast<const float*>(X), lines, n, ldx, vec, bp, p.qn, p.nwin,
-            nst, bl, p.RC, v.hdr, v.ell, out, ldo, npass, nullptr, obp, out_mode, ozlo);
-    }
-    if (bf16) {
-        if (!row_lines || wd) return hipErrorInvalidValue;
-        return launch_slots<true, false>(slots, grid, s, static_cast<const __bf16*>(X), lines, n,
-                                         ldx, vec, bp, p.qn, p.nwin, nst, bl, p.RC, v.hdr, v.ell,
-                                         out, ldo, npass, nullptr, obp, out_mode, ozlo);
-    }
-    const float* Xf = static_cast<const float*>(X);
-    if (wd && row_lines)   // weighted sketches are only taken along rows
-        return launch_slots<true, true>(slots, grid, s, Xf, lines, n, ldx, vec, bp, p.qn, p.nwin,
-                                        nst, bl, p.RC, v.hdr, v.ell, out, ldo, npass, wd, obp,
-                                        out_mode, ozlo);
-    if (row_lines)
-        return launch_slots<true, false>(slots, grid, s, Xf, lines, n, ldx, vec, bp, p.qn,
-                                         p.nwin, nst, bl, p.RC, v.hdr, v.ell, out, ldo, npass,
-                                         nullptr, obp, out_mode, ozlo);
-    return launch_slots<false, false>(slots, grid, s, Xf, lines, n, ldx, vec, bp, p.qn, p.nwin,
-                                      nst, bl, p.RC, v.hdr, v.ell, out, ldo, npass, nullptr, obp,
-                                      out_mode, ozlo);
+    const SketchArgs a{X,       lines, n,   ldx, vec,   bp, p.qn, p.nwin,  nst, &bl, p.RC,
+                       v.hdr,   v.ell, out, ldo, npass, wd, obp,  out_mode, ozlo};
+    if ((out_mode == 3 || bf16) && (!row_lines || wd)) return hipErrorInvalidValue;
+    if (out_mode == 3)
+        return bf16 ? sketch_rows_bf16_fp8(slots, grid, s, a) : sketch_rows_f32_fp8(slots, grid, s, a);
+    if (bf16) return sketch_rows_bf16(slots, grid, s, a);
+    if (!row_lines) return sketch_cols_f32(slots, grid, s, a);
+    return wd ? sketch_rows_weighted(slots, grid, s, a) : sketch_rows_f32(slots, grid, s, a);
 }
 
 }  // namespace

@@ -1,0 +1,57 @@
+// sketch_common.h -- constants and device helpers shared by the sketch kernel
+// (sketch_kernel.h) and the list builders (sketch.hip).
+#pragma once
+
+#include <type_traits>
+
+#include "internal.h"
+
+namespace osk {
+
+constexpr int kWin = kSketchWindow;    // sketched indices per window (8192)
+constexpr int kLines = 4;              // lines per workgroup
+constexpr int kThreads = 512;          // 8 waves
+constexpr int kWaves = kThreads / 64;
+constexpr int kPerThread = kWin / kThreads;   // window positions staged per thread (16)
+constexpr uint16_t kPad = (uint16_t)kWin;     // entry of the zero row, positive
+constexpr int kAhead = 3;              // list chunks of a slot fetched ahead
+constexpr int kDist = 1;               // slots ahead whose lists are fetched
+
+// LDS slot of window position p (p < kWin).  Thread t stages the quads of
+// positions 2048u + 4t + j (j < 4); they go to slots 2048u + 512j + t, so the
+// lanes of one staging write touch consecutive slots.  List entries hold the
+// slot of their position.
+__device__ __forceinline__ int win_slot(int p) {
+    return (p & ~2047) | ((p & 3) << 9) | ((p >> 2) & 511);
+}
+
+// f(integral_constant<int, I>) for I = B .. E - 1, unrolled by the compiler
+// whatever the size of f's body.
+template <int B, int E, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+
+// Spread consecutive task ids over the 8 XCDs in contiguous runs: task T is
+// run by the workgroup with linear id L where T = (L % 8) * (tasks / 8) + L / 8,
+// so neighbouring tasks share an XCD and its L2.
+__device__ __forceinline__ int64_t xcd_task(int64_t L, int64_t tasks) {
+    if (tasks % 8 != 0) return L;
+    return (L % 8) * (tasks / 8) + L / 8;
+}
+
+__device__ __forceinline__ uint64_t lanes_below() {
+    const int lane = threadIdx.x & 63;
+    return lane == 0 ? 0ull : (~0ull >> (64 - lane));
+}
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) x = max(x, (uint32_t)__shfl_xor((int)x, d));
+    return x;
+}
+
+}  // namespace osk

@@ -1,0 +1,39 @@
+// sketch_launch.h -- the sketch kernel's launchers, one per input form.
+#pragma once
+
+#include "sketch_common.h"
+
+namespace osk {
+
+// Slot counts compiled: 1, 2, 4, 8, 12, 16, 20, 24 (4 registers per slot).
+constexpr int kMaxSlots = 24;
+
+// Arguments of a sketch launch (see launch_sketch).
+struct SketchArgs {
+    const void* X;
+    int64_t lines, n, ldx;
+    int vec;
+    int32_t bp, qn, nwin, nst;
+    const BlockList* bl;
+    int64_t RC;
+    const uint32_t* hdr;
+    const uint4* ell;
+    void* out;
+    int64_t ldo;
+    int32_t npass;
+    const float* wd;
+    int32_t obp, omode;
+    int64_t ozlo;
+};
+
+// Launches the sketch kernel with at least `slots` slots per wave: rows of an
+// FP32 X, rows weighted by sqrt(wd), rows of a BF16 X, columns of an FP32 X,
+// and rows (FP32 or BF16) writing the FP8 copy.
+hipError_t sketch_rows_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_rows_weighted(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_rows_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_cols_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_rows_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_rows_bf16_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+
+}  // namespace osk
