@@ -387,8 +387,7 @@ size_t os_matmul_ex_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, i
  * values), in either layout.  A column-major A and a row-major B are first
  * transposed into the workspace in their own type (an FP32 one that is
  * 16-byte aligned with its ld and line count multiples of 4 is read in place
- * instead, unless the FP8 copy is written by the sketch); BF16 values are converted
- * exactly to FP32 as the sketch reads them, so the result equals that of the
+ * instead); BF16 values are converted exactly to FP32 as the sketch reads them, so the result equals that of the
  * FP32 path on the converted values, bit for bit.  With A = X^T for a
  * row-major X (n x m: A is
  * X read as column-major) and B = dY this is the sketched weight gradient of

@@ -451,7 +451,7 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     // except an FP32 row-major B whose columns the sketch can read with
     // 16-byte loads and its window spread over the slots
     // (sketch_rows_in_place_ok), which is faster read in place than
-    // transposed (no fused FP8 copy in that form; the sums are the same).
+    // transposed (the sums are the same).
     // BF16 values are converted exactly to FP32 as the sketch stages them.
     // With a BF16 block product the sketch writes its BF16 copy directly
     // (rounded in the sketch's epilogue, bit for bit what the quantization
@@ -468,13 +468,16 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
                             int64_t ldx, float* out, void* qout) -> os_status {
         const void* Xl = X;
         int64_t ldl = ldx;
-        if (transpose && dtype == OS_DTYPE_F32 && !fp8_fused &&
+        if (transpose && dtype == OS_DTYPE_F32 &&
             osk::sketch_rows_in_place_ok(static_cast<const float*>(X), lines, ldx)) {
             const float* Xf = static_cast<const float*>(X);
             if (bf16_product)
                 return hip_status(osk::launch_sketch_rows_q(Xf, n, lines, ldx, bs.stored, bs.nst,
                                                             nblocks(sk), bp, lists, qout, wq,
                                                             is_split(precision), s));
+            if (fp8_fused)
+                return hip_status(osk::launch_sketch_rows_fp8(Xf, n, lines, ldx, bs.stored, bs.nst,
+                                                              nblocks(sk), bp, lists, qout, wq, s));
             return hip_status(osk::launch_sketch_rows(Xf, n, lines, ldx, bs.stored, bs.nst,
                                                       nblocks(sk), bp, lists, out, zs, s));
         }

@@ -12,29 +12,29 @@
 
 namespace osk {
 
-__device__ __forceinline__ int e8m0_exponent(float amax) {
-    if (!(amax > 0.f)) return -127;
-    int E;
-    const float f = frexpf(amax, &E);          // amax = f * 2^E, f in [0.5, 1)
-    // 448 = 0.875 * 2^9: amax <= 448 * 2^s  <=>  s >= E - 9 + log2(f / 0.875)
-    int s = (f <= 0.875f) ? E - 9 : E - 8;
-    return max(-127, min(127, s));
+// s of a block whose largest |x| has these FP32 bits.  (amax = f * 2^E, f in
+// [0.5, 1): 448 = 0.875 * 2^9, so amax <= 448 * 2^s from s = E - 9 when f <=
+// 0.875, else E - 8.  A subnormal amax lands below the clamp either way.)  The
+// bits order like the values, with infinities and NaN above every finite one.
+__device__ __forceinline__ int e8m0_exponent(uint32_t amax) {
+    const int s = (int)(amax >> 23) - 126 - 9 + ((amax & 0x7FFFFFu) > 0x600000u ? 1 : 0);
+    return max(-127, s);
 }
 
-// E4M3 code (sign in bit 7) of v, |v| <= 448, round to nearest even.
-__device__ __forceinline__ uint32_t e4m3_rne(float v) {
-    const uint32_t bits = __float_as_uint(v);
-    const uint32_t sign = (bits >> 24) & 0x80u;
-    const float a = fabsf(v);
-    uint32_t code;
-    if (a < 0.015625f) {                        // below 2^-6: subnormal, step 2^-9
-        code = (uint32_t)rintf(a * 512.f);      // 0 .. 8 (8 = the smallest normal)
-    } else {
-        uint32_t u = __float_as_uint(a);        // keep 3 fraction bits, RNE on the 20 dropped
-        u += 0x7FFFFu + ((u >> 20) & 1u);
-        code = (u >> 20) - (120u << 3);         // exponent bias 127 -> 7
-    }
-    return sign | code;
+// E4M3 codes of four values |v| <= 448, v0 in the low byte (hardware
+// conversion, round to nearest even; an infinity or NaN becomes the E4M3 NaN).
+__device__ __forceinline__ uint32_t e4m3_pack4(float v0, float v1, float v2, float v3) {
+    const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(v0, v1, 0, false);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v2, v3, lo, true);
+}
+
+__device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
+
+// max(x, x of another lane picked by the DPP control), 0 where that lane is
+// outside the row
+template <int kCtrl, int kRows = 0xF>
+__device__ __forceinline__ uint32_t dpp_max(uint32_t x) {
+    return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRows, 0xF, true));
 }
 
 __device__ __forceinline__ float e4m3_value(uint32_t code) {

@@ -126,6 +126,10 @@ hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t
                                 const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                                 const void* lists, void* out, int64_t ldo, int split,
                                 hipStream_t s);
+// launch_sketch_rows writing the FP8 copy, as launch_sketch_cols_fp8.
+hipError_t launch_sketch_rows_fp8(const float* X, int64_t n, int64_t cols, int64_t ldx,
+                                  const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
+                                  const void* lists, void* out, int64_t ldo, hipStream_t s);
 // out (rows x nst*bp, ld ldo) = X S for X rows x n row-major (ld ldx);
 // with wd (DEVICE [n]) it is X diag(sqrt(wd)) S.
 hipError_t launch_sketch_cols(const float* X, int64_t rows, int64_t n, int64_t ldx,

@@ -83,59 +83,61 @@ hipError_t launch_quant_bf16(const float* S, int64_t lines, int64_t lds, int32_t
 // ---------------------------------------------------------------------------
 namespace {
 
-// One thread per (row, block of 64 values).
+// Sixteen lanes per (row, block of 64 values), four consecutive values each:
+// loads and code stores of a wave are whole cache lines, the block's maximum
+// is taken with DPP rotations within the 16 lanes.  Bound: HBM / L2 traffic
+// (one thread per block of 64 values, its lanes 256 bytes apart, took 30.8 us
+// for 2048 x 2560 values in the split form, this 9.0).
 __global__ __launch_bounds__(256) void quant_fp8_kernel(const float* __restrict__ S, int64_t lines,
                                                         int64_t lds, int32_t b, int32_t bp,
-                                                        int32_t bq, int32_t nst, int split,
+                                                        int32_t bq, int32_t nst, int split, int vec,
                                                         uint8_t* __restrict__ Q, int64_t ldq) {
     const int64_t zq = (int64_t)nst * bq;               // codes of the high part
     const int64_t width = zq * (split ? 2 : 1);
     const int64_t kb_per_row = zq / kFp8Block;
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= kb_per_row * lines) return;
+    const int64_t t = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    if (t >= kb_per_row * lines) return;                // (uniform over the 16 lanes)
+    const int sub = threadIdx.x & 15;
     const int64_t row = t / kb_per_row;
     const int64_t kb = t - row * kb_per_row;
     const int64_t oc = kb * kFp8Block;
     const int32_t j = (int32_t)(oc / bq);
-    const int32_t c0 = (int32_t)(oc - (int64_t)j * bq);
-    const float* src = S + row * lds + (int64_t)j * bp;
-    float x[kFp8Block];
-    float amax = 0.f;
+    const int32_t c0 = (int32_t)(oc - (int64_t)j * bq) + 4 * sub;
+    const float* src = S + row * lds + (int64_t)j * bp + c0;
+    float x[4];
+    if (vec && c0 + 3 < b) {
+        const float4 v = *reinterpret_cast<const float4*>(src);
+        x[0] = v.x;
+        x[1] = v.y;
+        x[2] = v.z;
+        x[3] = v.w;
+    } else {
 #pragma unroll
-    for (int u = 0; u < kFp8Block; ++u) {
-        x[u] = (c0 + u < b) ? src[c0 + u] : 0.f;
-        amax = fmaxf(amax, fabsf(x[u]));
+        for (int u = 0; u < 4; ++u) x[u] = c0 + u < b ? src[u] : 0.f;
     }
+    // codes of x and the block's exponent
+    auto encode = [&](const float (&y)[4], int& s) -> uint32_t {
+        uint32_t m = max(max(abs_bits(y[0]), abs_bits(y[1])), max(abs_bits(y[2]), abs_bits(y[3])));
+        m = dpp_max<0x128>(m);          // row_ror: 8, 4, 2, 1
+        m = dpp_max<0x124>(m);
+        m = dpp_max<0x122>(m);
+        m = dpp_max<0x121>(m);
+        s = e8m0_exponent(m);
+        return e4m3_pack4(ldexpf(y[0], -s), ldexpf(y[1], -s), ldexpf(y[2], -s), ldexpf(y[3], -s));
+    };
     uint8_t* qrow = Q + row * ldq;
     uint8_t* srow = qrow + width;                       // scale bytes after all codes
-    int s = e8m0_exponent(amax);
-    uint32_t w[kFp8Block / 4];
-    float r[kFp8Block];
-    float ramax = 0.f;
-#pragma unroll
-    for (int u = 0; u < kFp8Block; ++u) {
-        const uint32_t c = e4m3_rne(ldexpf(x[u], -s));
-        w[u / 4] = (u % 4 == 0 ? 0u : w[u / 4]) | (c << (8 * (u % 4)));
-        r[u] = x[u] - ldexpf(e4m3_value(c), s);
-        ramax = fmaxf(ramax, fabsf(r[u]));
-    }
-    uint4* dst = reinterpret_cast<uint4*>(qrow + oc);
-#pragma unroll
-    for (int v = 0; v < kFp8Block / 16; ++v)
-        dst[v] = make_uint4(w[4 * v], w[4 * v + 1], w[4 * v + 2], w[4 * v + 3]);
-    srow[kb] = (uint8_t)(s + 127);
+    int s;
+    const uint32_t hi = encode(x, s);
+    *reinterpret_cast<uint32_t*>(qrow + oc + 4 * sub) = hi;
+    if (sub == 0) srow[kb] = (uint8_t)(s + 127);
     if (split) {
-        const int s2 = e8m0_exponent(ramax);
+        float r[4];
 #pragma unroll
-        for (int u = 0; u < kFp8Block; ++u) {
-            const uint32_t c = e4m3_rne(ldexpf(r[u], -s2));
-            w[u / 4] = (u % 4 == 0 ? 0u : w[u / 4]) | (c << (8 * (u % 4)));
-        }
-        uint4* dlo = reinterpret_cast<uint4*>(qrow + zq + oc);
-#pragma unroll
-        for (int v = 0; v < kFp8Block / 16; ++v)
-            dlo[v] = make_uint4(w[4 * v], w[4 * v + 1], w[4 * v + 2], w[4 * v + 3]);
-        srow[kb_per_row + kb] = (uint8_t)(s2 + 127);
+        for (int u = 0; u < 4; ++u) r[u] = x[u] - ldexpf(e4m3_value((hi >> (8 * u)) & 0xFFu), s);
+        const uint32_t lo = encode(r, s);
+        *reinterpret_cast<uint32_t*>(qrow + zq + oc + 4 * sub) = lo;
+        if (sub == 0) srow[kb_per_row + kb] = (uint8_t)(s + 127);
     }
 }
 
@@ -153,10 +155,11 @@ hipError_t launch_quant_fp8(const float* S, int64_t lines, int64_t lds, int32_t 
     const int32_t bp = (int32_t)round_up(b, kBlockAlign);
     const int32_t bq = block_stride_fp8(b);
     const int64_t items = lines * ((int64_t)nst * bq / kFp8Block);
-    const int64_t grid = (items + 255) / 256;
+    const int64_t grid = (items + 15) / 16;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    const int vec = (reinterpret_cast<uintptr_t>(S) & 15) == 0 && (lds & 3) == 0;
     hipLaunchKernelGGL(quant_fp8_kernel, dim3((unsigned)grid), dim3(256), 0, s, S, lines, lds, b,
-                       bp, bq, nst, split, static_cast<uint8_t*>(Q), ldq);
+                       bp, bq, nst, split, vec, static_cast<uint8_t*>(Q), ldq);
     return hipGetLastError();
 }
 

@@ -654,9 +654,11 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
                     (reinterpret_cast<uintptr_t>(wd) & 15) == 0;
     const SketchArgs a{X,       lines, n,   ldx, vec,   bp, p.qn, p.nwin,  nst, &bl, p.RC,
                        v.hdr,   v.ell, out, ldo, npass, wd, obp,  out_mode, ozlo};
-    if ((out_mode == 3 || bf16) && (!row_lines || wd)) return hipErrorInvalidValue;
+    if ((bf16 && !row_lines) || ((out_mode == 3 || bf16) && wd)) return hipErrorInvalidValue;
     if (out_mode == 3)
-        return bf16 ? sketch_rows_bf16_fp8(slots, grid, s, a) : sketch_rows_f32_fp8(slots, grid, s, a);
+        return bf16        ? sketch_rows_bf16_fp8(slots, grid, s, a)
+               : row_lines ? sketch_rows_f32_fp8(slots, grid, s, a)
+                           : sketch_cols_f32_fp8(slots, grid, s, a);
     if (bf16) return sketch_rows_bf16(slots, grid, s, a);
     if (!row_lines) return sketch_cols_f32(slots, grid, s, a);
     return wd ? sketch_rows_weighted(slots, grid, s, a) : sketch_rows_f32(slots, grid, s, a);
@@ -776,6 +778,15 @@ hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t
     if (!plan_sketch_ok(cols, nst, bp, n)) return hipErrorInvalidValue;
     return launch_sketch(false, X, false, cols, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s,
                          nullptr, split ? 2 : 1);
+}
+
+hipError_t launch_sketch_rows_fp8(const float* X, int64_t n, int64_t cols, int64_t ldx,
+                                  const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
+                                  const void* lists, void* out, int64_t ldo, hipStream_t s) {
+    if (!plan_sketch_ok(cols, nst, bp, n) || !sketch_fp8_fusable(bp, nst))
+        return hipErrorInvalidValue;
+    return launch_sketch(false, X, false, cols, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s,
+                         nullptr, 3);
 }
 
 size_t transpose_bytes(int64_t rows, int64_t cols) {

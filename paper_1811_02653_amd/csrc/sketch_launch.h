@@ -28,12 +28,13 @@ struct SketchArgs {
 
 // Launches the sketch kernel with at least `slots` slots per wave: rows of an
 // FP32 X, rows weighted by sqrt(wd), rows of a BF16 X, columns of an FP32 X,
-// and rows (FP32 or BF16) writing the FP8 copy.
+// and rows (FP32 or BF16) and columns writing the FP8 copy.
 hipError_t sketch_rows_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_weighted(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_cols_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_cols_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 
 }  // namespace osk

@@ -380,3 +380,55 @@ def test_lognormal_split_forms_recover_accuracy(lognormal_case):
         err[prec] = oracle.rel_frob(C, d["ref"])
     assert err["bf16x3"] < err["bf16"] / 16
     assert err["fp8x3"] < err["fp8"] / 8
+
+
+@pytest.mark.parametrize("scale", [-140, -126, -20, 0, 30, 115])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_quantize_fp8_edges(scale, pad):
+    """Every E4M3 magnitude, every midpoint between neighbours and its two FP32
+    neighbours, in blocks whose maximum is at and one step past a scale
+    boundary (448 * 2^s), zeros and FP32 subnormals; rows 16-byte aligned or
+    not: bit-exact against the oracle."""
+    vals = oracle.e4m3_values()
+    mid = (vals[:-1] + vals[1:]) / 2
+    x = np.concatenate([vals, mid, np.nextafter(mid.astype(np.float32), np.float32(0)),
+                        np.nextafter(mid.astype(np.float32), np.float32(1e9))])
+    x = np.ldexp(np.concatenate([x, -x]), scale).astype(np.float32)
+    b, nst = 100, 2                                   # the second 64-block is partial
+    rows = -(-x.size // 63)
+    S = np.zeros((rows + 1, nst * osk.block_stride(b)), dtype=np.float32)
+    for r in range(rows):
+        part = x[63 * r:63 * (r + 1)]
+        S[r, :part.size] = part
+        top = np.float32(np.ldexp(448.0, scale))
+        S[r, 63] = top if r % 2 else np.nextafter(top, np.float32(np.inf))
+        S[r, 64:100] = part[:36] if part.size >= 36 else 0
+        S[r, 128:128 + min(100, part.size)] = part[:100]
+    buf = torch.zeros(S.shape[0], S.shape[1] + 4, device="cuda")[:, pad:pad + S.shape[1]]
+    buf.copy_(torch.from_numpy(S))
+    bq = osk.block_stride_prec(b, "fp8")
+    for split in (False, True):
+        Q = host_u8(osk.sketch_quantize(buf, b, nst, "fp8x3" if split else "fp8"))
+        val, s = decode_fp8(Q, b, nst, split)
+        X = np.zeros((S.shape[0], nst * bq))
+        for j in range(nst):
+            X[:, j * bq:j * bq + b] = S[:, j * 128:j * 128 + b]
+        hi, s_hi = oracle.fp8_block_quantize(X, FP8_BLOCK)
+        np.testing.assert_array_equal(val[:, :nst * bq], hi)
+        np.testing.assert_array_equal(s[:, :s_hi.shape[1]], s_hi)
+        if split:
+            lo, s_lo = oracle.fp8_block_quantize(X - hi, FP8_BLOCK)
+            np.testing.assert_array_equal(val[:, nst * bq:], lo)
+            np.testing.assert_array_equal(s[:, s_hi.shape[1]:], s_lo)
+
+
+@pytest.mark.parametrize("m,n,l,b,N", [(9, 9000, 132, 128, 2), (70, 700, 64, 256, 5),
+                                       (5, 8192, 260, 1024, 10)])
+def test_matmul_fp8_columns_in_place(m, n, l, b, N):
+    """An aligned row-major B sketched in place into its FP8 copy gives the
+    result of the same B stored column-major, bit for bit."""
+    A, B = synthetic.gaussian_pair(m, n, l, m + n)
+    Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    C = osk.matmul(Ad, Bd, b, N, 0, seed=3, precision="fp8")
+    Ct = osk.matmul(Ad, Bd.t().contiguous().t(), b, N, 0, seed=3, precision="fp8")
+    assert torch.equal(C, Ct)
