@@ -339,7 +339,7 @@ os_status os_gemm_kept_prec(const void* At, int64_t ldat, const void* Bt, int64_
                                                     quant_codes(b, nst, precision), m, l, bpq,
                                                     kept, K, is_split(precision),
                                                     (int64_t)nst * bpq, 1.0f / (float)K, C, ldc,
-                                                    (hipStream_t)stream));
+                                                    nullptr, 0, (hipStream_t)stream));
     return hip_status(osk::launch_gemm_kept_bf16(At, ldat, Bt, ldbt, m, l, bpq, kept, K,
                                                  is_split(precision), (int64_t)nst * bpq,
                                                  1.0f / (float)K, C, ldc, nullptr, 0,
@@ -523,7 +523,7 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
                                                        s))) != OS_OK)
                 return st;
         }
-        return hip_status(osk::launch_gemm_kept_fp8_split(
+        return hip_status(osk::launch_gemm_kept_fp8(
             aq_p, wq, bq_p, wq, quant_codes(sk->b, bs.nst, precision), m, l, bpq, bs.kept_pos,
             bs.K, split, (int64_t)bs.nst * bpq, 1.0f / (float)bs.K, C, ldc,
             reinterpret_cast<float*>(part_p), part_bytes, s));

@@ -94,6 +94,19 @@ __device__ __forceinline__ void direct_offsets(uint32_t (&vo)[kU], int64_t ld_by
     }
 }
 
+// The same for a split-precision step: chunks 0-3 of an LDS row hold 64 bytes
+// of the high part, chunks 4-7 the 64 bytes lo_bytes further in the row.
+template <int kU>
+__device__ __forceinline__ void direct_offsets_pair(uint32_t (&vo)[kU], int64_t ld_bytes, int last,
+                                                    int64_t lo_bytes, int wave, int lane) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        const int r = 8 * (kU * wave + u) + (lane >> 3);
+        const int c = (lane & 7) ^ chunk_key(r);
+        vo[u] = (uint32_t)((int64_t)min(r, last) * ld_bytes + 16 * (c & 3) + (c & 4 ? lo_bytes : 0));
+    }
+}
+
 // (The builtin exists only for the device target; the host pass of a
 // template kernel that names it would silently drop the kernel's launch
 // stubs, hence the guard.)
@@ -115,12 +128,21 @@ __device__ __forceinline__ int direct_frag_off(int rbase, int q, int lane) {
     return rbase * 32 + 4 * ((4 * (lane >> 5) + q) ^ chunk_key(rbase));
 }
 
+// The same in a pair step (high part in chunks 0-3, low part in chunks 4-7):
+// fragment q of lane half h is chunk 2h + (q & 1) of the high part (q < 2) or
+// of the low part.
+__device__ __forceinline__ int pair_frag_off(int rbase, int q, int lane) {
+    return rbase * 32 + 4 * ((4 * (q >> 1) + 2 * (lane >> 5) + (q & 1)) ^ chunk_key(rbase));
+}
+
 __device__ __forceinline__ float comp(const float4& v, int c) {
     return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+
+enum Kind { kF32, kBF16, kBF16X3, kFp8, kFp8X3 };   // operand precisions
 
 // Operand precisions of the block product.  A K step is 128 bytes of a tile
 // row in both: 32 FP32 values or 64 BF16 values.  A fragment is 16 bytes:
@@ -134,6 +156,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // 1, BF16 1 and 0 (BF16 3-4 % faster than the compiler's own placement,
 // which read each quad's fragments just before its MFMAs; FP32 unchanged).
 struct PrecF32 {
+    static constexpr Kind kKind = kF32;
+    static constexpr bool kPair = false;
     static constexpr int kElem = 4;
     static constexpr int kParts = 4;          // parts of a quad: the four K values kk
     static constexpr int kHead = 3;
@@ -155,6 +179,8 @@ struct PrecF32 {
 };
 
 struct PrecBF16 {
+    static constexpr Kind kKind = kBF16;
+    static constexpr bool kPair = false;
     static constexpr int kElem = 2;
     static constexpr int kHead = 1;
     static constexpr int kTail = 0;
@@ -173,10 +199,16 @@ struct PrecBF16 {
     }
 };
 
-// Terms of the K loop: kept block j contributes nsub terms.  Term 0 pairs
-// the A and B columns of the block; with nsub = 3 (split precision), term 1
-// pairs A's block with the low part of B's block (lo_off columns further)
-// and term 2 the low part of A's block with B's block.
+// Split BF16 operands: a step holds 32 K values of both parts of every tile
+// row (64 bytes high, 64 bytes low) and contributes hi*lo' + hi*hi' + lo*hi',
+// so the three terms share one load of the four tiles and each fragment read
+// (two thirds of the loads and LDS reads of three separate passes: 298 us
+// against 333-361 for 4096 x 4096, K = 4096).
+struct PrecBF16X3 : PrecBF16 {
+    static constexpr Kind kKind = kBF16X3;
+    static constexpr bool kPair = true;
+};
+
 // Per-C-block keep masks (cmask != nullptr, the paper's per-block
 // stragglers): C is divided into cblk x cblk blocks, block (I, J) keeps the
 // stored blocks j with cmask[(I * nbJ + J) * nstm + j] != 0 and is scaled by
@@ -209,8 +241,6 @@ struct SplitK {
 // wave's memory instructions issue while the other's MFMAs keep the pipe
 // busy (one wave per SIMD left the pipe idle for about one MFMA slot per
 // memory instruction).
-constexpr int kThreadsK = 512;
-
 // Tile forms.  128 (four waves of 64 x 64, two workgroups per CU) and 64 (four
 // waves of 32 x 32, four workgroups per CU) run the same K loop; they read
 // more LDS and L2 per flop (0.96 and 0.92 of the 256 form's FP32 rate at 4096
@@ -237,7 +267,7 @@ template <typename P, typename S, bool kMask, bool kOdd, bool kSplit = false>
 __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kEu, S::kEu)))
 void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __restrict__ Bt,
                       int64_t ldbt, int64_t m, int64_t l, int32_t bp, BlockList kept,
-                      int32_t nkept, int32_t nsub, int64_t lo_off, float scale,
+                      int32_t nkept, int64_t lo_off, float scale,
                       float* __restrict__ C, int64_t ldc, int32_t tilesM, int32_t tilesN,
                       CMask cm, SplitK sk) {
     // two K-step buffers per operand, separate arrays so that the compiler
@@ -329,23 +359,19 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    constexpr int kStep = kStepBytes / P::kElem;     // K values per step
-    const int tpb = bp / kStep;                       // K steps per term
+    // K values per step
+    constexpr int kStep = kStepBytes / P::kElem / (P::kPair ? 2 : 1);
+    const int tpb = bp / kStep;                       // K steps per block
     int t_begin = 0;
-    int t_end = nkept * nsub * tpb;                   // this workgroup's K steps
+    int t_end = nkept * tpb;                          // this workgroup's K steps
     if constexpr (kSplit) {
         t_begin = split * sk.chunk;
         t_end = min(t_end, t_begin + sk.chunk);
     }
-    // byte offsets of the first K column of step `step` in A and in B
-    // (terms in order, kStep columns per step)
-    auto step_ab = [&](int step, uint32_t& ka, uint32_t& kb) {
-        const int term = step / tpb;
-        const int j = term / nsub;
-        const int sub = term - j * nsub;
-        const int64_t c = (int64_t)kept_at(j) * bp + (int64_t)(step % tpb) * kStep;
-        ka = (uint32_t)((c + (sub == 2 ? lo_off : 0)) * P::kElem);
-        kb = (uint32_t)((c + (sub == 1 ? lo_off : 0)) * P::kElem);
+    // byte offset of the first K column of step `step` in A's and B's rows
+    auto step_k = [&](int step) -> uint32_t {
+        return (uint32_t)(((int64_t)kept_at(step / tpb) * bp + (int64_t)(step % tpb) * kStep) *
+                          P::kElem);
     };
 
     const __amdgpu_buffer_rsrc_t ra_src =
@@ -353,32 +379,53 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     const __amdgpu_buffer_rsrc_t rb_src =
         tile_rsrc(static_cast<const char*>(Bt) + col0 * ldbt * P::kElem);
     uint32_t va[kU], vb[kU];
-    direct_offsets<kU>(va, ldat * P::kElem, (int)min((int64_t)BT - 1, m - 1 - row0), wave, lane);
-    direct_offsets<kU>(vb, ldbt * P::kElem, (int)min((int64_t)BT - 1, l - 1 - col0), wave, lane);
+    const int alast = (int)min((int64_t)BT - 1, m - 1 - row0);
+    const int blast = (int)min((int64_t)BT - 1, l - 1 - col0);
+    if constexpr (P::kPair) {
+        direct_offsets_pair<kU>(va, ldat * P::kElem, alast, lo_off * P::kElem, wave, lane);
+        direct_offsets_pair<kU>(vb, ldbt * P::kElem, blast, lo_off * P::kElem, wave, lane);
+    } else {
+        direct_offsets<kU>(va, ldat * P::kElem, alast, wave, lane);
+        direct_offsets<kU>(vb, ldbt * P::kElem, blast, wave, lane);
+    }
+    // fragment q of a lane half: K bytes 64 h + 16 q of the step, or (pair
+    // steps) 32 h + 16 (q & 1) of the high (q < 2) or low part
     int fa_off[4], fb_off[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        fa_off[q] = direct_frag_off(wm * 32 * kI + (lane & 31), q, lane);
-        fb_off[q] = direct_frag_off(wn * 32 * kJ + (lane & 31), q, lane);
+        const int ra = wm * 32 * kI + (lane & 31), rb = wn * 32 * kJ + (lane & 31);
+        fa_off[q] = P::kPair ? pair_frag_off(ra, q, lane) : direct_frag_off(ra, q, lane);
+        fb_off[q] = P::kPair ? pair_frag_off(rb, q, lane) : direct_frag_off(rb, q, lane);
     }
-    auto frag = [&](float4 (&a)[kI], float4 (&b)[kJ], const float* as, const float* bs, int q) {
+    auto frag_a = [&](float4 (&a)[kI], const float* as, int q) {
 #pragma unroll
         for (int i = 0; i < kI; ++i) a[i] = *reinterpret_cast<const float4*>(as + fa_off[q] + 1024 * i);
+    };
+    auto frag_b = [&](float4 (&b)[kJ], const float* bs, int q) {
 #pragma unroll
         for (int j = 0; j < kJ; ++j) b[j] = *reinterpret_cast<const float4*>(bs + fb_off[q] + 1024 * j);
     };
+    auto frag = [&](float4 (&a)[kI], float4 (&b)[kJ], const float* as, const float* bs, int q) {
+        frag_a(a, as, q);
+        frag_b(b, bs, q);
+    };
     auto issue = [&](float* as, float* bs, int step) {
-        uint32_t ka, kb;
-        step_ab(step, ka, kb);
-        direct_issue<kU>(ra_src, as, va, ka, wave);
-        direct_issue<kU>(rb_src, bs, vb, kb, wave);
+        const uint32_t k = step_k(step);
+        direct_issue<kU>(ra_src, as, va, k, wave);
+        direct_issue<kU>(rb_src, bs, vb, k, wave);
     };
 
     issue(As0, Bs0, t_begin);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    // (pair steps: fa, fb the high parts' fragments, ga, gb the low parts')
     float4 fa[kI], fb[kJ], ga[kI], gb[kJ];
-    frag(fa, fb, As0, Bs0, 0);
+    if constexpr (P::kPair) {
+        frag_a(fa, As0, 0);
+        frag_b(gb, Bs0, 2);
+    } else {
+        frag(fa, fb, As0, Bs0, 0);
+    }
     // One K step: the next step's tiles go straight into the other buffers
     // (last read before the previous step's barrier) while this step's four
     // quads run; each quad's fragments are read during the previous quad's
@@ -401,24 +448,54 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
         P::template mfma_quad<kI, kJ, P::kHead, kParts>(acc, a, b);
         __builtin_amdgcn_sched_barrier(0);
     };
+    auto mfma = [&](const float4 (&a)[kI], const float4 (&b)[kJ]) {
+        P::template mfma_quad<kI, kJ>(acc, a, b);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     auto kstep = [&](const float* as, const float* bs, float* na, float* nb, int t) {
-        uint32_t ka, kb;
-        step_ab(min(t + 1, t_end - 1), ka, kb);
-        direct_issue<kU>(ra_src, na, va, ka, wave);
+        const uint32_t k = step_k(min(t + 1, t_end - 1));
+        direct_issue<kU>(ra_src, na, va, k, wave);
         __builtin_amdgcn_sched_barrier(0);
-        quad(fa, fb, [&] { frag(ga, gb, as, bs, 1); });
-        direct_issue<kU>(rb_src, nb, vb, kb, wave);
-        __builtin_amdgcn_sched_barrier(0);
-        quad(ga, gb, [&] { frag(fa, fb, as, bs, 2); });
-        quad(fa, fb, [&] { frag(ga, gb, as, bs, 3); });
-        P::template mfma_quad<kI, kJ, 0, kParts - P::kTail>(acc, ga, gb);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        frag(fa, fb, na, nb, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        P::template mfma_quad<kI, kJ, kParts - P::kTail, kParts>(acc, ga, gb);
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (P::kPair) {
+            // per 16 K values: hi*lo', hi*hi', lo*hi'; each fragment is read
+            // while the term before the one that needs it runs
+            frag_b(fb, bs, 0);
+            frag_a(ga, as, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma(fa, gb);
+            direct_issue<kU>(rb_src, nb, vb, k, wave);
+            frag_b(gb, bs, 3);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma(fa, fb);
+            frag_a(fa, as, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma(ga, fb);
+            frag_b(fb, bs, 1);
+            frag_a(ga, as, 3);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma(fa, gb);
+            mfma(fa, fb);
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            frag_a(fa, na, 0);
+            frag_b(gb, nb, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma(ga, fb);
+        } else {
+            quad(fa, fb, [&] { frag(ga, gb, as, bs, 1); });
+            direct_issue<kU>(rb_src, nb, vb, k, wave);
+            __builtin_amdgcn_sched_barrier(0);
+            quad(ga, gb, [&] { frag(fa, fb, as, bs, 2); });
+            quad(fa, fb, [&] { frag(ga, gb, as, bs, 3); });
+            P::template mfma_quad<kI, kJ, 0, kParts - P::kTail>(acc, ga, gb);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            frag(fa, fb, na, nb, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            P::template mfma_quad<kI, kJ, kParts - P::kTail, kParts>(acc, ga, gb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
     int t = t_begin;
     for (; t + 1 < t_end; t += 2) {
@@ -469,7 +546,7 @@ template <typename P>
 __global__ __launch_bounds__(64 * kSmallWaves)
 void gemm_small_kernel(const void* __restrict__ At, int64_t ldat, const void* __restrict__ Bt,
                        int64_t ldbt, int64_t m, int64_t l, int32_t bp, BlockList kept,
-                       int32_t nkept, int32_t nsub, int64_t lo_off, float scale,
+                       int32_t nkept, int64_t lo_off, float scale,
                        float* __restrict__ C, int64_t ldc, int32_t tilesM, int32_t tilesN) {
     __shared__ float red[kSmallWaves][kSmallTile * kSmallTile];
     const int tid = threadIdx.x;
@@ -489,36 +566,43 @@ void gemm_small_kernel(const void* __restrict__ At, int64_t ldat, const void* __
         const int32_t r3 = __builtin_amdgcn_readlane(kv[3], j & 63);
         return j < 64 ? r0 : (j < 128 ? r1 : (j < 192 ? r2 : r3));
     };
-    constexpr int kStep = kStepBytes / P::kElem;
+    constexpr int kStep = kStepBytes / P::kElem / (P::kPair ? 2 : 1);
     const int tpb = bp / kStep;
-    const int total = nkept * nsub * tpb;
+    const int total = nkept * tpb;
     // rows past the matrix read its last row (their sums are not stored)
-    const int half = 64 * (lane >> 5);
+    const int half = (P::kPair ? 32 : 64) * (lane >> 5);
     const char* pa = static_cast<const char*>(At) +
                      min(row0 + (lane & 31), m - 1) * ldat * P::kElem + half;
     const char* pb = static_cast<const char*>(Bt) +
                      min(col0 + (lane & 31), l - 1) * ldbt * P::kElem + half;
     auto load = [&](float4 (&a)[4], float4 (&b)[4], int step) {
-        const int term = step / tpb;
-        const int j = term / nsub;
-        const int sub = term - j * nsub;
-        const int64_t c = (int64_t)kept_at(j) * bp + (int64_t)(step % tpb) * kStep;
-        const int64_t ka = (c + (sub == 2 ? lo_off : 0)) * P::kElem;
-        const int64_t kb = (c + (sub == 1 ? lo_off : 0)) * P::kElem;
+        const int64_t k = ((int64_t)kept_at(step / tpb) * bp + (int64_t)(step % tpb) * kStep) *
+                          P::kElem;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            a[q] = *reinterpret_cast<const float4*>(pa + ka + 16 * q);
-            b[q] = *reinterpret_cast<const float4*>(pb + kb + 16 * q);
+            const int64_t at = k + (P::kPair ? 16 * (q & 1) + (q < 2 ? 0 : lo_off * P::kElem) : 16 * q);
+            a[q] = *reinterpret_cast<const float4*>(pa + at);
+            b[q] = *reinterpret_cast<const float4*>(pb + at);
         }
     };
     v16f acc[1][1];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
     auto sum = [&](const float4 (&a)[4], const float4 (&b)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 x[1] = {a[q]}, y[1] = {b[q]};
+        auto term = [&](int qa, int qb) {
+            const float4 x[1] = {a[qa]}, y[1] = {b[qb]};
             P::template mfma_quad<1, 1>(acc, x, y);
+        };
+        if constexpr (P::kPair) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                term(q, 2 + q);
+                term(q, q);
+                term(2 + q, q);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) term(q, q);
         }
     };
     if (wave < total) {
@@ -577,53 +661,81 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 // gfx950 scaled MFMA v_mfma_scale_f32_32x32x64_f8f6f4 (FP32 accumulation; the
 // hardware multiplies the products by the row scales of A and B).  A row of
 // an operand holds its codes, then one scale byte per 64 codes (`scales`
-// bytes after the row's start).  The pipeline is gemm_kept_kernel's: eight waves per
-// 256 x 256 tile (two per SIMD, 128 x 64 each), K steps of 128 codes (128
-// bytes of every tile row) loaded straight into LDS, two step buffers.  A
-// step is two substeps, one per 64-value scale block: substep s is one
-// scaled MFMA per 32x32 block, lane half h holding the 32 codes at byte
-// 64 s + 32 h of the step's row (two 16-byte LDS reads: logical chunks
-// 4 s + 2 h and 4 s + 2 h + 1), both halves passing the block's scale.
-// Scale bytes: the two of a step sit in one aligned 4-byte word of the row's
-// scale area (word at scales + (c / 64 & ~3) for code column c, the step's
-// pair in half hsel = (c / 128) & 1); every step each wave loads 64 such
-// words straight into LDS, A's rows by waves 0-3 and B's by waves 4-7, laid
-// out so that a fragment lane's four A rows (or two B rows) are consecutive
-// words: one 16-byte (8-byte) LDS read per lane per step.
+// bytes after the row's start).  The pipeline and the tile forms are
+// gemm_kept_kernel's (a 64 form was slower than the 128 form throughout), K
+// steps of 128 bytes of every tile row loaded straight into LDS, two step
+// buffers.  A step is two 64-byte parts, one scale block each; lane half h
+// holds the 32 codes at byte 64 p + 32 h of the step's row (two 16-byte LDS
+// reads: logical chunks 4 p + 2 h and 4 p + 2 h + 1), both halves passing the
+// block's scale.
+//   plain (kPair = false): the parts are 128 consecutive codes, one scaled
+//     MFMA per part and 32x32 block;
+//   split (kPair): part 0 is 64 codes of the high part, part 1 the 64 codes
+//     of the low part at the same columns (lo_off bytes on); hi*lo' + hi*hi'
+//     + lo*hi', three MFMAs per block from one load of the four tiles
+//     (4096 x 4096, K = 4096, blocks of 1024: 154 us, 2680 TFLOP/s, where
+//     three separate passes of the K loop reached 2210-2310).
+// Scale bytes: part p of a step has one byte per row, at column byte c / 64
+// of the scale area (c = the part's first code column).  Every step each
+// wave loads the aligned 4-byte word that holds it for 64 rows straight into
+// LDS (plain: both parts' bytes are in one word; split: a word per part),
+// laid out so that a fragment lane's kI A rows (or kJ B rows) are consecutive
+// words.  (No branch around these loads: a wave-uniform one made the kernel
+// spill 200-400 bytes per lane and run at less than half the speed.)
 // Scale chunks (kChunk, when the block stride is a multiple of 1024 codes
 // and rows and the scale area are 16-byte aligned): the scale loads above
 // read 64 rows per instruction, one 4-byte piece each, and cost about as
 // much as a whole step's tile loads; instead each wave loads 16 bytes of
-// its 64 rows (the scales of 8 steps) once per 8 steps, into one of two
-// chunk buffers, and each step reads its pair of scale bytes per row from
-// there (the chunk for steps 8c .. 8c + 7 is loaded during step 8c - 8).
+// its 64 rows (the scales of 8 steps, or of one part of 16 split steps) at
+// once, into one of two chunk buffers, and each step reads its scale bytes
+// from there (a chunk is loaded during the first step of the one before it).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int fp8_frag_off(int rbase, int s, int p, int lane) {
     return rbase * 32 + 4 * ((4 * s + 2 * (lane >> 5) + p) ^ chunk_key(rbase));
 }
 
-template <bool kOdd, bool kSplit = false, bool kChunk = false>
-__global__ __launch_bounds__(kThreadsK) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// kN (2 or 4) consecutive words of LDS, aligned to as many
+template <int kN>
+__device__ __forceinline__ void words(uint32_t (&d)[kN], const uint32_t* p) {
+    if constexpr (kN == 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(p);
+        d[0] = v.x;
+        d[1] = v.y;
+        d[2] = v.z;
+        d[3] = v.w;
+    } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(p);
+        d[0] = v.x;
+        d[1] = v.y;
+    }
+}
+
+template <typename S, bool kPair, bool kOdd, bool kSplit = false, bool kChunk = false>
+__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
                            const uint8_t* __restrict__ Bt, int64_t ldbt, int64_t scales,
                            int64_t m, int64_t l, int32_t bp, BlockList kept, int32_t nkept,
-                           int32_t nsub, int64_t lo_off, float scale, float* __restrict__ C,
-                           int64_t ldc, int32_t tilesM, int32_t tilesN, SplitK sk) {
-    __shared__ __align__(1024) float As0[BM * 32];
-    __shared__ __align__(1024) float As1[BM * 32];
-    __shared__ __align__(1024) float Bs0[BN * 32];
-    __shared__ __align__(1024) float Bs1[BN * 32];
-    // scale words of a step (A's rows, then B's), or two chunk buffers of
-    // 16 bytes per row
-    __shared__ __align__(16) uint32_t Sc0[kChunk ? 4 : BM + BN];
-    __shared__ __align__(16) uint32_t Sc1[kChunk ? 4 : BM + BN];
-    __shared__ __align__(16) uint32_t Sq[kChunk ? 2 * 4 * (BM + BN) : 4];
+                           int64_t lo_off, float scale, float* __restrict__ C, int64_t ldc,
+                           int32_t tilesM, int32_t tilesN, SplitK sk) {
+    constexpr int BT = S::BT;
+    constexpr int kI = S::kI;
+    constexpr int kJ = S::kJ;
+    constexpr int kU = S::kU;
+    __shared__ __align__(1024) float As0[BT * 32];
+    __shared__ __align__(1024) float As1[BT * 32];
+    __shared__ __align__(1024) float Bs0[BT * 32];
+    __shared__ __align__(1024) float Bs1[BT * 32];
+    // scale words, two buffers: per row (A's, then B's) a word per loaded
+    // part (kWords of them), or 16 bytes per row and loaded part
+    constexpr int kWords = kPair ? 2 : 1;
+    constexpr int kScaleBuf = kWords * 2 * BT * (kChunk ? 4 : 1);
+    __shared__ __align__(16) uint32_t Sc[2 * kScaleBuf];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar M0 and selects
-    const int wm = wave >> 2;
-    const int wn = wave & 3;
+    const int wm = wave / S::WC;
+    const int wn = wave % S::WC;
 
     const int64_t ntiles = (int64_t)tilesM * tilesN;
     int32_t split = 0;
@@ -640,8 +752,8 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     const int64_t in_group = T - group * kGroupM * tilesN;
     const int64_t tm = first_m + in_group % gsz;
     const int64_t tn = in_group / gsz;
-    const int64_t row0 = tm * BM;
-    const int64_t col0 = tn * BN;
+    const int64_t row0 = tm * BT;
+    const int64_t col0 = tn * BT;
 
     int32_t kv[4];
 #pragma unroll
@@ -654,109 +766,86 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
         return j < 64 ? r0 : (j < 128 ? r1 : (j < 192 ? r2 : r3));
     };
 
-    v16f acc[4][2];
+    v16f acc[kI][kJ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < kJ; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    constexpr int kStep = kStepBytes;                 // 128 codes per step
+    constexpr int kStep = kPair ? 64 : 128;           // code columns per step
+    constexpr int kPerChunk = kPair ? 16 : 8;         // steps per scale chunk
     const int tpb = bp / kStep;
     int t_begin = 0;
-    int t_end = nkept * nsub * tpb;                   // this workgroup's K steps
+    int t_end = nkept * tpb;                          // this workgroup's K steps
     if constexpr (kSplit) {
         t_begin = split * sk.chunk;
         t_end = min(t_end, t_begin + sk.chunk);
     }
-    // code byte offsets of step `step` in A and B (terms in order)
-    auto step_ab = [&](int step, uint32_t& ka, uint32_t& kb) {
-        const int term = step / tpb;
-        const int j = term / nsub;
-        const int sub = term - j * nsub;
-        const int64_t c = (int64_t)kept_at(j) * bp + (int64_t)(step % tpb) * kStep;
-        ka = (uint32_t)(c + (sub == 2 ? lo_off : 0));
-        kb = (uint32_t)(c + (sub == 1 ? lo_off : 0));
+    // first code column (= byte) of step `step`
+    auto step_k = [&](int step) -> uint32_t {
+        return (uint32_t)((int64_t)kept_at(step / tpb) * bp + (int64_t)(step % tpb) * kStep);
     };
 
-    const int alast = (int)min((int64_t)BM - 1, m - 1 - row0);
-    const int blast = (int)min((int64_t)BN - 1, l - 1 - col0);
+    const int alast = (int)min((int64_t)BT - 1, m - 1 - row0);
+    const int blast = (int)min((int64_t)BT - 1, l - 1 - col0);
     const __amdgpu_buffer_rsrc_t ra_src = tile_rsrc(At + row0 * ldat);
     const __amdgpu_buffer_rsrc_t rb_src = tile_rsrc(Bt + col0 * ldbt);
-    uint32_t va[4], vb[4];
-    direct_offsets<4>(va, ldat, alast, wave, lane);
-    direct_offsets<4>(vb, ldbt, blast, wave, lane);
-    // scale word of this lane's row: word p = 64 (wave % 4) + lane of A's
-    // (waves 0-3) or B's (waves 4-7) area holds row (4 consecutive words per
-    // A fragment lane: rows wm*128 + 32 i + r; 2 per B fragment lane: rows
-    // wn*64 + 32 j + r)
-    const int p = 64 * (wave & 3) + lane;
-    const bool a_side = wave < 4;
-    const int srow = a_side ? (p >> 7) * 128 + 32 * (p & 3) + ((p >> 2) & 31)
-                            : (p >> 6) * 64 + 32 * (p & 1) + ((p >> 1) & 31);
-    // scale chunks keep rows in their natural order (entry p: row p of A,
-    // or row p - 256 of B), so that the 32 lanes of a fragment half read
-    // 16-byte-spaced entries (two lanes per bank) instead of 64-byte-spaced
-    // ones (sixteen)
-    const int crow = kChunk ? 64 * (wave & 3) + lane : srow;
-    const uint32_t so = a_side ? (uint32_t)((int64_t)min(crow, alast) * ldat + scales)
-                               : (uint32_t)((int64_t)min(crow, blast) * ldbt + scales);
+    uint32_t va[kU], vb[kU];
+    if constexpr (kPair) {
+        direct_offsets_pair<kU>(va, ldat, alast, lo_off, wave, lane);
+        direct_offsets_pair<kU>(vb, ldbt, blast, lo_off, wave, lane);
+    } else {
+        direct_offsets<kU>(va, ldat, alast, wave, lane);
+        direct_offsets<kU>(vb, ldbt, blast, wave, lane);
+    }
+    // scale rows of this wave: word p = 64 (wave % (BT / 64)) + lane of A's
+    // (the first BT / 64 waves) or B's (the next) area holds row srow (kI
+    // consecutive words per A fragment lane: rows wm * 32 kI + 32 i + r; kJ per
+    // B fragment lane).  Chunks keep rows in their natural order, so that the
+    // 32 lanes of a fragment half read 16-byte-spaced entries (two lanes per
+    // bank) instead of 16 kI-byte-spaced ones.
+    constexpr int kSw = BT / 64;
+    static_assert(2 * kSw == S::kWaves, "every wave loads the scales of 64 rows");
+    const bool a_side = wave < kSw;
+    const int p = 64 * (wave % kSw) + lane;
+    constexpr int kIw = 32 * kI, kJw = 32 * kJ;
+    const int srow = kChunk ? p
+                     : a_side ? p / kIw * kIw + 32 * (p % kI) + ((p / kI) & 31)
+                              : p / kJw * kJw + 32 * (p % kJ) + ((p / kJ) & 31);
+    const uint32_t so = a_side ? (uint32_t)((int64_t)min(srow, alast) * ldat + scales)
+                               : (uint32_t)((int64_t)min(srow, blast) * ldbt + scales);
     const __amdgpu_buffer_rsrc_t rs_src = a_side ? ra_src : rb_src;
-    const int sbase = a_side ? 64 * (wave & 3) : BM + 64 * (wave & 3);
+    const int sbase = a_side ? 64 * (wave % kSw) : BT + 64 * (wave % kSw);
 
-    // the A tile and (per-step words) the scale words of a step; the B tile
-    // is issued on its own
-    auto issue_a = [&](float* as, uint32_t* sc, uint32_t ka, uint32_t kb) {
-        direct_issue<4>(ra_src, as, va, ka, wave);
+    // the scale words of a step (or the chunk it starts) into buffer `buf`
+    auto issue_scales = [&](int buf, uint32_t k) {
 #if defined(__HIP_DEVICE_COMPILE__)
-        if constexpr (!kChunk) {
-            const uint32_t kc = a_side ? ka : kb;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_src, (lds_void*)(sc + sbase), 4, so,
-                                                     (kc / kFp8Block) & ~3u, 0, 0);
+        if constexpr (kChunk) {
+            uint32_t* d = Sc + buf * kScaleBuf + 4 * sbase;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_src, (lds_void*)d, 16, so, k / kFp8Block,
+                                                     0, 0);
+            if constexpr (kPair)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rs_src, (lds_void*)(d + 8 * BT), 16, so,
+                    (uint32_t)((k + lo_off) / kFp8Block), 0, 0);
+        } else {
+            uint32_t* d = Sc + buf * kScaleBuf + sbase;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_src, (lds_void*)d, 4, so,
+                                                     (k / kFp8Block) & ~3u, 0, 0);
+            if constexpr (kPair)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rs_src, (lds_void*)(d + 2 * BT), 4, so,
+                    (uint32_t)((k + lo_off) / kFp8Block) & ~3u, 0, 0);
         }
 #else
-        (void)sc;
-        (void)kb;
-#endif
-    };
-    auto issue = [&](float* as, float* bs, uint32_t* sc, int step) {
-        uint32_t ka, kb;
-        step_ab(step, ka, kb);
-        direct_issue<4>(ra_src, as, va, ka, wave);
-        direct_issue<4>(rb_src, bs, vb, kb, wave);
-#if defined(__HIP_DEVICE_COMPILE__)
-        if constexpr (!kChunk) {
-            const uint32_t kc = a_side ? ka : kb;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_src, (lds_void*)(sc + sbase), 4, so,
-                                                     (kc / kFp8Block) & ~3u, 0, 0);
-        }
-#else
-        (void)sc;
+        (void)buf;
+        (void)k;
         (void)so;
         (void)rs_src;
         (void)sbase;
 #endif
-    };
-    // the scale chunk of steps step .. step + 7 (step a multiple of 8) into
-    // chunk buffer (step / 8) % 2: 16 bytes of each of the wave's 64 rows
-    auto issue_chunk = [&](int step) {
-#if defined(__HIP_DEVICE_COMPILE__)
-        uint32_t ka, kb;
-        step_ab(step, ka, kb);
-        const uint32_t kc = a_side ? ka : kb;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rs_src, (lds_void*)(Sq + ((step >> 3) & 1) * 4 * (BM + BN) + 4 * sbase), 16, so,
-            kc / kFp8Block, 0, 0);
-#else
-        (void)step;
-#endif
-    };
-    // the half of a step's scale word that holds its pair of scale bytes
-    auto hsel = [&](int step, bool a) -> uint32_t {
-        uint32_t ka, kb;
-        step_ab(step, ka, kb);
-        return (((a ? ka : kb) / kStep) & 1u) * 16u;
     };
 
     int fa_off[2][2], fb_off[2][2];
@@ -764,117 +853,175 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            fa_off[s2][q] = fp8_frag_off(wm * 128 + (lane & 31), s2, q, lane);
-            fb_off[s2][q] = fp8_frag_off(wn * 64 + (lane & 31), s2, q, lane);
+            fa_off[s2][q] = fp8_frag_off(wm * kIw + (lane & 31), s2, q, lane);
+            fb_off[s2][q] = fp8_frag_off(wn * kJw + (lane & 31), s2, q, lane);
         }
     auto as_i32x8 = [](const float4& lo, const float4& hi) -> i32x8 {
         return i32x8{__float_as_int(lo.x), __float_as_int(lo.y), __float_as_int(lo.z),
                      __float_as_int(lo.w), __float_as_int(hi.x), __float_as_int(hi.y),
                      __float_as_int(hi.z), __float_as_int(hi.w)};
     };
-    // A fragment of row block i of substep s2; B fragments of substep s2
+    // A fragment of row block i of part s2; B fragments of part s2
     auto frag_a = [&](const float* as, int s2, int i) -> i32x8 {
         return as_i32x8(*reinterpret_cast<const float4*>(as + fa_off[s2][0] + 1024 * i),
                         *reinterpret_cast<const float4*>(as + fa_off[s2][1] + 1024 * i));
     };
-    auto frag_b = [&](i32x8 (&b)[2], const float* bs, int s2) {
+    auto frag_b = [&](i32x8 (&b)[kJ], const float* bs, int s2) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < kJ; ++j)
             b[j] = as_i32x8(*reinterpret_cast<const float4*>(bs + fb_off[s2][0] + 1024 * j),
                             *reinterpret_cast<const float4*>(bs + fb_off[s2][1] + 1024 * j));
     };
-    const int sa_word = 4 * (wm * 32 + (lane & 31));
-    const int sb_word = BM + 2 * (wn * 32 + (lane & 31));
-    // the step's pair of scale bytes (substep 0 low, substep 1 high) of the
-    // lane's four A rows and two B rows
-    uint32_t sa[4], sb[2];
-    auto read_scales = [&](const uint32_t* sc, int step) {
+    // the step's scale bytes of the lane's A and B rows: part 0 in byte 0,
+    // part 1 in byte 1
+    uint32_t sa[kI], sb[kJ];
+    auto read_scales = [&](int step, int buf, uint32_t k) {
         if constexpr (kChunk) {
-            const uint16_t* q =
-                reinterpret_cast<const uint16_t*>(Sq + ((step >> 3) & 1) * 4 * (BM + BN));
-            const int h = step & 7;
+            const uint8_t* q = reinterpret_cast<const uint8_t*>(Sc + ((step / kPerChunk) & 1) * kScaleBuf);
+            const int ra = wm * kIw + (lane & 31), rb = BT + wn * kJw + (lane & 31);
+            auto at = [&](int row) -> uint32_t {
+                if constexpr (kPair) {
+                    const uint8_t* e = q + 16 * row + (step & 15);
+                    return e[0] | (uint32_t)e[32 * BT] << 8;
+                } else {
+                    return *reinterpret_cast<const uint16_t*>(q + 16 * row + 2 * (step & 7));
+                }
+            };
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sa[i] = q[8 * (wm * 128 + 32 * i + (lane & 31)) + h];
+            for (int i = 0; i < kI; ++i) sa[i] = at(ra + 32 * i);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) sb[j] = q[8 * (BM + wn * 64 + 32 * j + (lane & 31)) + h];
+            for (int j = 0; j < kJ; ++j) sb[j] = at(rb + 32 * j);
         } else {
-            const uint4 wa = *reinterpret_cast<const uint4*>(sc + sa_word);
-            const uint2 wb = *reinterpret_cast<const uint2*>(sc + sb_word);
-            const uint32_t ha = hsel(step, true);
-            const uint32_t hb = hsel(step, false);
-            sa[0] = wa.x >> ha;
-            sa[1] = wa.y >> ha;
-            sa[2] = wa.z >> ha;
-            sa[3] = wa.w >> ha;
-            sb[0] = wb.x >> hb;
-            sb[1] = wb.y >> hb;
+            const uint32_t* q = Sc + buf * kScaleBuf;
+            const int wa = kI * (wm * 32 + (lane & 31)), wb = BT + kJ * (wn * 32 + (lane & 31));
+            const uint32_t h0 = (k / kFp8Block & 3u) * 8u;
+            words<kI>(sa, q + wa);
+            words<kJ>(sb, q + wb);
+#pragma unroll
+            for (int i = 0; i < kI; ++i) sa[i] >>= h0;
+#pragma unroll
+            for (int j = 0; j < kJ; ++j) sb[j] >>= h0;
+            if constexpr (kPair) {
+                const uint32_t h1 = ((uint32_t)((k + lo_off) / kFp8Block) & 3u) * 8u;
+                uint32_t la[kI], lb[kJ];
+                words<kI>(la, q + 2 * BT + wa);
+                words<kJ>(lb, q + 2 * BT + wb);
+#pragma unroll
+                for (int i = 0; i < kI; ++i) sa[i] = (sa[i] & 0xFFu) | (la[i] >> h1 & 0xFFu) << 8;
+#pragma unroll
+                for (int j = 0; j < kJ; ++j) sb[j] = (sb[j] & 0xFFu) | (lb[j] >> h1 & 0xFFu) << 8;
+            }
         }
     };
+    auto mfma = [&](v16f& c, const i32x8& a, const i32x8& b, uint32_t s_a, uint32_t s_b, int pa,
+                    int pb) {
+        c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0,
+                                                            (int)((s_a >> (8 * pa)) & 0xFFu), 0,
+                                                            (int)((s_b >> (8 * pb)) & 0xFFu));
+    };
 
-    issue(As0, Bs0, Sc0, t_begin);
-    if constexpr (kChunk) issue_chunk(t_begin);
+    {
+        const uint32_t k = step_k(t_begin);
+        direct_issue<kU>(ra_src, As0, va, k, wave);
+        direct_issue<kU>(rb_src, Bs0, vb, k, wave);
+        issue_scales(0, k);        // (t_begin is even, and 0 with chunks)
+    }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    i32x8 fa, fb[2], fan, fbn[2];
+    // plain: fa / fan one part's A fragment and the next one's, fb / fbn the
+    // parts' B fragments; split: fa / ga one row block's high and low
+    // fragments, fan / gan the next one's, fb / fbn the B parts
+    i32x8 fa, fan, ga, gan, fb[kJ], fbn[kJ];
     fa = frag_a(As0, 0, 0);
     frag_b(fb, Bs0, 0);
-    read_scales(Sc0, t_begin);
+    if constexpr (kPair) {
+        ga = frag_a(As0, 1, 0);
+        frag_b(fbn, Bs0, 1);
+    }
+    read_scales(t_begin, 0, step_k(t_begin));
     // One step: the next step's tiles and scale words go straight into the
     // other buffers while this step runs (the A tile and scales at the step's
     // start, the B tile after a quarter of its MFMAs, as in gemm_kept_kernel:
-    // about 2 % faster); the A fragment of the next (substep, row block) is
-    // read during the current one's two MFMAs, and substep 1's B fragments
-    // during substep 0's last row block.  Steps run in pairs; an odd last
-    // step (kOdd) runs alone after them.
-    auto kstep = [&](const float* as, const float* bs, float* na, float* nb, uint32_t* nsc,
-                     int t) {
-        uint32_t ka, kb;
-        step_ab(min(t + 1, t_end - 1), ka, kb);
-        issue_a(na, nsc, ka, kb);
+    // about 2 % faster); the A fragment of the next (part, row block) is
+    // read during the current one's MFMAs, and part 1's B fragments during
+    // part 0's last row block.  Steps run in pairs; an odd last step (kOdd)
+    // runs alone after them.
+    auto kstep = [&](const float* as, const float* bs, float* na, float* nb, int nbuf, int t) {
+        const uint32_t k = step_k(min(t + 1, t_end - 1));
+        direct_issue<kU>(ra_src, na, va, k, wave);
         if constexpr (kChunk) {
-            if ((t & 7) == 0 && t + 8 < t_end) issue_chunk(t + 8);
+            if (t % kPerChunk == 0 && t + kPerChunk < t_end)
+                issue_scales((t / kPerChunk + 1) & 1, step_k(t + kPerChunk));
+        } else {
+            issue_scales(nbuf, k);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kPair) {
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (s2 == 0 && i == 2) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    direct_issue<4>(rb_src, nb, vb, kb, wave);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (i < 3) {
-                    fan = frag_a(as, s2, i + 1);
-                } else if (s2 == 0) {
-                    fan = frag_a(as, 1, 0);
-                    frag_b(fbn, bs, 1);
+            for (int i = 0; i < kI; ++i) {
+                if (i + 1 < kI) {
+                    fan = frag_a(as, 0, i + 1);
+                    gan = frag_a(as, 1, i + 1);
                 }
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        fa, fb[j], acc[i][j], 0, 0, 0, (int)((sa[i] >> (8 * s2)) & 0xFFu), 0,
-                        (int)((sb[j] >> (8 * s2)) & 0xFFu));
-                if (i < 3 || s2 == 0) fa = fan;
+                for (int j = 0; j < kJ; ++j) mfma(acc[i][j], fa, fbn[j], sa[i], sb[j], 0, 1);
+                if (i == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    direct_issue<kU>(rb_src, nb, vb, k, wave);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int j = 0; j < kJ; ++j) mfma(acc[i][j], fa, fb[j], sa[i], sb[j], 0, 0);
+#pragma unroll
+                for (int j = 0; j < kJ; ++j) mfma(acc[i][j], ga, fb[j], sa[i], sb[j], 1, 0);
+                if (i + 1 < kI) {
+                    fa = fan;
+                    ga = gan;
+                }
             }
-            if (s2 == 0) {
-                fb[0] = fbn[0];
-                fb[1] = fbn[1];
+        } else {
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2) {
+#pragma unroll
+                for (int i = 0; i < kI; ++i) {
+                    if (s2 == 0 && i == kI / 2) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        direct_issue<kU>(rb_src, nb, vb, k, wave);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (i + 1 < kI) {
+                        fan = frag_a(as, s2, i + 1);
+                    } else if (s2 == 0) {
+                        fan = frag_a(as, 1, 0);
+                        frag_b(fbn, bs, 1);
+                    }
+#pragma unroll
+                    for (int j = 0; j < kJ; ++j) mfma(acc[i][j], fa, fb[j], sa[i], sb[j], s2, s2);
+                    if (i + 1 < kI || s2 == 0) fa = fan;
+                }
+                if (s2 == 0) {
+#pragma unroll
+                    for (int j = 0; j < kJ; ++j) fb[j] = fbn[j];
+                }
             }
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         fa = frag_a(na, 0, 0);
         frag_b(fb, nb, 0);
-        read_scales(nsc, min(t + 1, t_end - 1));
+        if constexpr (kPair) {
+            ga = frag_a(na, 1, 0);
+            frag_b(fbn, nb, 1);
+        }
+        read_scales(min(t + 1, t_end - 1), nbuf, k);
     };
     int t = t_begin;
     for (; t + 1 < t_end; t += 2) {
-        kstep(As0, Bs0, As1, Bs1, Sc1, t);
-        kstep(As1, Bs1, As0, Bs0, Sc0, t + 1);
+        kstep(As0, Bs0, As1, Bs1, 1, t);
+        kstep(As1, Bs1, As0, Bs0, 0, t + 1);
     }
     if constexpr (kOdd) {
-        if (t < t_end) kstep(As0, Bs0, As1, Bs1, Sc1, t);
+        if (t < t_end) kstep(As0, Bs0, As1, Bs1, 1, t);
     }
 
     float* out = C;
@@ -886,13 +1033,13 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     }
 
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kI; ++i) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t col = col0 + wn * 64 + j * 32 + (lane & 31);
+        for (int j = 0; j < kJ; ++j) {
+            const int64_t col = col0 + wn * kJw + j * 32 + (lane & 31);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int64_t row = row0 + wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int64_t row = row0 + wm * kIw + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (row < m && col < l) out[row * ldo + col] = acc[i][j][r] * scale;
             }
         }
@@ -1286,60 +1433,66 @@ struct Form {
 // largest number of tiles on one CU).  A 256 tile has the least LDS and L2
 // traffic per flop, but a product of few tiles leaves CUs idle, and one of a
 // few more than a multiple of 256 tiles leaves most of them idle in its last
-// round; smaller tiles fill both (FP32, K = 4096, us at 256 / 128 / 64 / 32:
-// 512 x 512 906 / 250 / 80 / 37, 1024 x 1024 909 / 255 / 84 / 136,
-// 2048 x 2048 915 / 278 / 276 / -, 3333 x 2777 834 / 659 / 578 / -,
-// 4096 x 4096 922 / 959 / 1008 / -, 5120 x 5120 1830 / 1669 / 1576 / -;
-// BF16: 82 / 36 / 39 / 20, 84 / 50 / 41 / 72, 86 / 53 / 58 / -,
-// 87 / 108 / 124 / -, 113 / 126 / 207 / -, 196 / 229 / 323 / -).
-double step_us(bool f32, int tile, int64_t tiles) {
+// round; smaller tiles fill both.  Measured at K = 4096, us with sides 256 /
+// 128 / 64 / 32:
+//                 512 x 512         1024 x 1024        2048 x 2048     4096 x 4096      5120 x 5120
+//   FP32        906/250/80/37     909/255/84/136    915/278/276/-   922/959/1008/-  1830/1669/1576/-
+//   BF16         82/36/39/20       84/50/41/72       86/53/58/-     113/126/207/-    196/229/323/-
+//   split BF16  206/96/57/35      204/99/61/127     207/123/157/-   298/360/582/-    505/628/916/-
+//   FP8          44/22             45/31             51/34           65/83           112/142
+//   split FP8   111/52            111/64            114/73          153/202          267/330
+double step_us(Kind kind, int tile, int64_t tiles) {
     const double r = (double)((tiles + kSplitSlots - 1) / kSplitSlots);
-    if (f32) {
-        if (tile == 256) return 7.1 * r;
-        if (tile == 128) return 1.87 * r + 0.1;
-        if (tile == 64) return 0.49 * r + 0.15;
-        return 0.25 * r + 0.04;
+    const bool few = tiles <= 192;        // (256 tiles: less L2 contention, higher clock)
+    if (tile == 32) return 0.25 * r + 0.04;
+    switch (kind) {
+        case kF32:
+            return tile == 256 ? 7.1 * r : tile == 128 ? 1.87 * r + 0.1 : 0.49 * r + 0.15;
+        case kBF16:
+            return tile == 256   ? (few ? 1.4 : 1.75 * r)
+                   : tile == 128 ? 0.5 * r + 0.3
+                                 : std::max(0.62, 0.2 * r + 0.1);
+        case kBF16X3:
+            return tile == 256   ? (few ? 1.65 : 2.1 * r)
+                   : tile == 128 ? 0.67 * r + 0.25
+                                 : 0.28 * r + 0.17;
+        case kFp8: return tile == 256 ? (few ? 1.5 : 1.9 * r) : 0.6 * r + 0.35;
+        default: return tile == 256 ? (few ? 1.75 : 2.2 * r) : 0.7 * r + 0.35;
     }
-    if (tile == 256) return r > 1 || tiles > 192 ? 1.75 * r : 1.4;
-    if (tile == 128) return 0.5 * r + 0.3;
-    if (tile == 64) return std::max(0.62, 0.2 * r + 0.1);
-    return 0.25 * r + 0.04;
 }
 
 // The form predicted fastest.  Without partial space (part = nullptr) every
-// entry is summed in step order whatever the tile, bit for bit the same.  A
-// product the split K loop serves keeps its split (the number of partial
-// sums per entry) whatever the tile; the small kernel's waves split the K
-// loop eight ways themselves.
-Form pick_form(bool f32, int64_t m, int64_t l, int64_t total, const float* part,
+// entry is summed in step order whatever the tile, bit for bit the same.
+// Where the split K loop serves a product, FP32 and split BF16 keep its split
+// (the number of partial sums per entry, which their accuracy shows) whatever
+// the tile; the small kernel's waves split the K loop eight ways themselves.
+Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part,
                size_t part_bytes) {
-    Form best{256, 1, total};
-    const bool split = split_plan(m, l, total, part, part_bytes, best.S, best.chunk);
-    if (!split) {
-        best.S = 1;
-        best.chunk = total;
+    int64_t S = 1, chunk = total;
+    if (!split_plan(m, l, total, part, part_bytes, S, chunk)) {
+        S = 1;
+        chunk = total;
     }
-    const Form base = best;
+    const bool fp8 = kind == kFp8 || kind == kFp8X3;
+    Form best{256, S, chunk};
     double t = 0;
-    for (const int tile : {256, 128, 64, 32}) {
-        Form f = base;
-        f.tile = tile;
-        if (tile == 32) {
-            if (!part) continue;
-            f.S = 1;
-            f.chunk = total;
-        }
-        const int64_t tiles = tiles_of(m, l, tile) * f.S;
-        if (tiles > 0x7fffffff) continue;
-        double us = step_us(f32, tile, tiles) * (double)f.chunk;
+    auto consider = [&](const Form& f) {
+        const int64_t tiles = tiles_of(m, l, f.tile) * f.S;
+        if (tiles > 0x7fffffff) return;
         // first loads and epilogue; a split's partials written and summed
-        if (tile == 256) us += 6;
+        double us = step_us(kind, f.tile, tiles) * (double)f.chunk + (f.tile == 256 ? 6 : 0);
         if (f.S > 1) us += 4 + (double)f.S * (double)m * (double)l * 4 / 4e6;
-        if (tile == 256 || us < t) {
+        if (t == 0 || us < t) {
             t = us;
             best = f;
         }
+    };
+    for (const int tile : {256, 128, 64}) {
+        if (tile == 64 && fp8) continue;
+        consider(Form{tile, S, chunk});
+        if (S > 1 && (kind == kBF16 || fp8)) consider(Form{tile, 1, total});
     }
+    if (part && !fp8) consider(Form{32, 1, total});
     return best;
 }
 
@@ -1362,7 +1515,7 @@ struct Operands {
     int64_t m, l;
     int32_t bp;
     const BlockList* kept;
-    int32_t nkept, nsub;
+    int32_t nkept;
     int64_t lo_off;
     float scale;
     float* C;
@@ -1378,7 +1531,7 @@ hipError_t launch_tile(const Operands& o, const Form& f, int64_t total, float* p
                 : total % 2 ? gemm_kept_kernel<P, S, false, true>
                             : gemm_kept_kernel<P, S, false, false>;
     hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * tilesM * tilesN)), dim3(S::kThreads), 0, s,
-                       o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp, *o.kept, o.nkept, o.nsub,
+                       o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp, *o.kept, o.nkept,
                        o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM, (int32_t)tilesN,
                        CMask{nullptr, 0, 0, 0, 1}, SplitK{part, (int32_t)f.chunk});
     if (f.S > 1) return launch_split_sum(part, f.S, o.m, o.l, o.scale, o.C, o.ldc, s);
@@ -1387,8 +1540,8 @@ hipError_t launch_tile(const Operands& o, const Form& f, int64_t total, float* p
 
 template <typename P>
 hipError_t launch_form(const Operands& o, float* part, size_t part_bytes, hipStream_t s) {
-    const int64_t total = (int64_t)o.nkept * o.nsub * (o.bp / (kStepBytes / P::kElem));
-    const Form f = pick_form(P::kElem == 4, o.m, o.l, total, part, part_bytes);
+    const int64_t total = (int64_t)o.nkept * (o.bp / (kStepBytes / P::kElem / (P::kPair ? 2 : 1)));
+    const Form f = pick_form(P::kKind, o.m, o.l, total, part, part_bytes);
     if (f.tile == 256) return launch_tile<P, Tile256>(o, f, total, part, s);
     if (f.tile == 128) return launch_tile<P, Tile128>(o, f, total, part, s);
     if (f.tile == 64) return launch_tile<P, Tile64>(o, f, total, part, s);
@@ -1396,7 +1549,7 @@ hipError_t launch_form(const Operands& o, float* part, size_t part_bytes, hipStr
     const int64_t tilesN = (o.l + kSmallTile - 1) / kSmallTile;
     hipLaunchKernelGGL(gemm_small_kernel<P>, dim3((unsigned)(tilesM * tilesN)),
                        dim3(64 * kSmallWaves), 0, s, o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp,
-                       *o.kept, o.nkept, o.nsub, o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM,
+                       *o.kept, o.nkept, o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM,
                        (int32_t)tilesN);
     return hipGetLastError();
 }
@@ -1412,7 +1565,7 @@ hipError_t launch_cmask_tile(const float* At, int64_t ldat, const float* Bt, int
     auto kern = (bp / 32) % 2 == 0 ? gemm_kept_kernel<PrecF32, S, true, false>
                                    : gemm_kept_kernel<PrecF32, S, true, true>;
     hipLaunchKernelGGL(kern, dim3((unsigned)(tilesM * tilesN)), dim3(S::kThreads), 0, s, At, ldat,
-                       Bt, ldbt, m, l, bp, none, 0, 1, (int64_t)0, 1.0f, C, ldc, (int32_t)tilesM,
+                       Bt, ldbt, m, l, bp, none, 0, (int64_t)0, 1.0f, C, ldc, (int32_t)tilesM,
                        (int32_t)tilesN, cm, SplitK{nullptr, 0});
     return hipGetLastError();
 }
@@ -1430,8 +1583,7 @@ hipError_t launch_gemm_kept(const float* At, int64_t ldat, const float* Bt, int6
                             int32_t nkept, float scale, float* C, int64_t ldc, float* part,
                             size_t part_bytes, hipStream_t s) {
     if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 4) || nkept < 1) return hipErrorInvalidValue;
-    return launch_form<PrecF32>(Operands{At, ldat, Bt, ldbt, m, l, bp, &kept, nkept, 1, 0, scale, C,
-                                         ldc},
+    return launch_form<PrecF32>(Operands{At, ldat, Bt, ldbt, m, l, bp, &kept, nkept, 0, scale, C, ldc},
                                 part, part_bytes, s);
 }
 
@@ -1448,7 +1600,7 @@ hipError_t launch_gemm_cmask(const float* At, int64_t ldat, const float* Bt, int
         const int64_t tb = (cblk + tile - 1) / tile;
         const int64_t live = nbI * tb * nbJ * tb;
         if (live > 0x7fffffff || nbJ > 0x7fffffff) continue;
-        const double us = step_us(true, tile, live);
+        const double us = step_us(kF32, tile, live);
         if (!side || us < t) {
             t = us;
             side = tile;
@@ -1503,46 +1655,49 @@ int batch_sym_blocks_per_cu(int tile) {
     return e == hipSuccess ? n : 0;
 }
 
-hipError_t launch_gemm_kept_fp8(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
-                                int64_t scales, int64_t m, int64_t l, int32_t bp,
-                                const BlockList& kept, int32_t nkept, int split, int64_t lo_off,
-                                float scale, float* C, int64_t ldc, hipStream_t s) {
-    if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 1) || nkept < 1) return hipErrorInvalidValue;
-    const int64_t tilesM = (m + BM - 1) / BM;
-    const int64_t tilesN = (l + BN - 1) / BN;
-    const bool odd = ((int64_t)nkept * (split ? 3 : 1) * (bp / kStepBytes)) % 2 != 0;
-    // scale chunks of 8 steps: whole chunks per block, 16-byte aligned rows
-    // and scale area
-    const bool chunk = bp % 1024 == 0 && ldat % 16 == 0 && ldbt % 16 == 0 && scales % 16 == 0;
-    // (with chunks the step count is a multiple of 8: never odd)
-    auto kern = chunk ? gemm_kept_fp8d_kernel<false, false, true>
-                      : (odd ? gemm_kept_fp8d_kernel<true> : gemm_kept_fp8d_kernel<false>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tilesM * tilesN)), dim3(kThreadsK), 0, s,
-                       static_cast<const uint8_t*>(At), ldat, static_cast<const uint8_t*>(Bt),
-                       ldbt, scales, m, l, bp, kept, nkept, split ? 3 : 1, lo_off, scale, C, ldc,
-                       (int32_t)tilesM, (int32_t)tilesN, SplitK{nullptr, 0});
+namespace {
+
+template <typename S, bool kPair>
+hipError_t launch_fp8_tile(const Operands& o, int64_t scales, const Form& f, int64_t total,
+                           float* part, hipStream_t s) {
+    const int64_t tilesM = (o.m + S::BT - 1) / S::BT;
+    const int64_t tilesN = (o.l + S::BT - 1) / S::BT;
+    // scale chunks: whole chunks per block, 16-byte aligned rows and scale
+    // area (with them the step count is a multiple of 8, never odd)
+    const bool chunk = o.bp % 1024 == 0 && o.ldat % 16 == 0 && o.ldbt % 16 == 0 && scales % 16 == 0;
+    auto kern = f.S > 1     ? gemm_kept_fp8d_kernel<S, kPair, true, true>
+                : chunk     ? gemm_kept_fp8d_kernel<S, kPair, false, false, true>
+                : total % 2 ? gemm_kept_fp8d_kernel<S, kPair, true>
+                            : gemm_kept_fp8d_kernel<S, kPair, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * tilesM * tilesN)), dim3(S::kThreads), 0, s,
+                       static_cast<const uint8_t*>(o.At), o.ldat,
+                       static_cast<const uint8_t*>(o.Bt), o.ldbt, scales, o.m, o.l, o.bp, *o.kept,
+                       o.nkept, o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM, (int32_t)tilesN,
+                       SplitK{part, (int32_t)f.chunk});
+    if (f.S > 1) return launch_split_sum(part, f.S, o.m, o.l, o.scale, o.C, o.ldc, s);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_kept_fp8_split(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
-                                      int64_t scales, int64_t m, int64_t l, int32_t bp,
-                                      const BlockList& kept, int32_t nkept, int split,
-                                      int64_t lo_off, float scale, float* C, int64_t ldc,
-                                      float* part, size_t part_bytes, hipStream_t s) {
+template <bool kPair>
+hipError_t launch_fp8(const Operands& o, int64_t scales, float* part, size_t part_bytes,
+                      hipStream_t s) {
+    const int64_t total = (int64_t)o.nkept * (o.bp / (kPair ? 64 : 128));
+    const Form f = pick_form(kPair ? kFp8X3 : kFp8, o.m, o.l, total, part, part_bytes);
+    return f.tile == 256 ? launch_fp8_tile<Tile256, kPair>(o, scales, f, total, part, s)
+                         : launch_fp8_tile<Tile128, kPair>(o, scales, f, total, part, s);
+}
+
+}  // namespace
+
+hipError_t launch_gemm_kept_fp8(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
+                                int64_t scales, int64_t m, int64_t l, int32_t bp,
+                                const BlockList& kept, int32_t nkept, int split, int64_t lo_off,
+                                float scale, float* C, int64_t ldc, float* part,
+                                size_t part_bytes, hipStream_t s) {
     if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 1) || nkept < 1) return hipErrorInvalidValue;
-    int64_t S = 0, chunk = 0;
-    const int64_t total = (int64_t)nkept * (split ? 3 : 1) * (bp / kStepBytes);
-    if (!split_plan(m, l, total, part, part_bytes, S, chunk))
-        return launch_gemm_kept_fp8(At, ldat, Bt, ldbt, scales, m, l, bp, kept, nkept, split,
-                                    lo_off, scale, C, ldc, s);
-    const int64_t tilesM = (m + BM - 1) / BM;
-    const int64_t tilesN = (l + BN - 1) / BN;
-    hipLaunchKernelGGL((gemm_kept_fp8d_kernel<true, true>), dim3((unsigned)(S * tilesM * tilesN)),
-                       dim3(kThreadsK), 0, s, static_cast<const uint8_t*>(At), ldat,
-                       static_cast<const uint8_t*>(Bt), ldbt, scales, m, l, bp, kept, nkept,
-                       split ? 3 : 1, lo_off, scale, C, ldc, (int32_t)tilesM, (int32_t)tilesN,
-                       SplitK{part, (int32_t)chunk});
-    return launch_split_sum(part, S, m, l, scale, C, ldc, s);
+    const Operands o{At, ldat, Bt, ldbt, m, l, bp, &kept, nkept, lo_off, scale, C, ldc};
+    return split ? launch_fp8<true>(o, scales, part, part_bytes, s)
+                 : launch_fp8<false>(o, scales, part, part_bytes, s);
 }
 
 hipError_t launch_gemm_kept_bf16(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
@@ -1550,9 +1705,9 @@ hipError_t launch_gemm_kept_bf16(const void* At, int64_t ldat, const void* Bt, i
                                  int32_t nkept, int split, int64_t lo_off, float scale, float* C,
                                  int64_t ldc, float* part, size_t part_bytes, hipStream_t s) {
     if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 2) || nkept < 1) return hipErrorInvalidValue;
-    return launch_form<PrecBF16>(Operands{At, ldat, Bt, ldbt, m, l, bp, &kept, nkept,
-                                          split ? 3 : 1, lo_off, scale, C, ldc},
-                                 part, part_bytes, s);
+    const Operands o{At, ldat, Bt, ldbt, m, l, bp, &kept, nkept, lo_off, scale, C, ldc};
+    return split ? launch_form<PrecBF16X3>(o, part, part_bytes, s)
+                 : launch_form<PrecBF16>(o, part, part_bytes, s);
 }
 
 }  // namespace osk

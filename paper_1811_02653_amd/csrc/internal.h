@@ -209,14 +209,8 @@ hipError_t launch_gemm_kept_bf16(const void* At, int64_t ldat, const void* Bt, i
 hipError_t launch_gemm_kept_fp8(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
                                 int64_t scales, int64_t m, int64_t l, int32_t bp,
                                 const BlockList& kept, int32_t nkept, int split, int64_t lo_off,
-                                float scale, float* C, int64_t ldc, hipStream_t s);
-// launch_gemm_kept_fp8 with the split K loop of launch_gemm_kept (partials
-// in part, summed in split order).
-hipError_t launch_gemm_kept_fp8_split(const void* At, int64_t ldat, const void* Bt, int64_t ldbt,
-                                      int64_t scales, int64_t m, int64_t l, int32_t bp,
-                                      const BlockList& kept, int32_t nkept, int split,
-                                      int64_t lo_off, float scale, float* C, int64_t ldc,
-                                      float* part, size_t part_bytes, hipStream_t s);
+                                float scale, float* C, int64_t ldc, float* part,
+                                size_t part_bytes, hipStream_t s);
 // FP32 block product with a keep mask per C block: cmask DEVICE [ceil(m/cblk)]
 // [ceil(l/cblk)][nst]; block (I, J) of C (cblk x cblk) = (1/K_IJ) * sum of its
 // kept blocks' products (zero when it keeps none).
