@@ -82,8 +82,9 @@ inline size_t table_bytes(const os_sketch* sk, int64_t n) {
     return (size_t)nblocks(sk) * (size_t)table_stride(n) * 4u;
 }
 
-// Prepared buffer: the packed table, the bucket lists, then the position
-// map inv [N+e][bp] (bucket -> column of the sketch).
+// Prepared buffer: the packed table (used while preparing; not written where
+// the lists are built without it), the bucket lists, then the position map
+// inv [N+e][bp] (bucket -> column of the sketch).
 inline size_t prepare_bytes(const os_sketch* sk, int64_t n) {
     const int32_t bp = os_block_stride(sk->b);
     return align256(table_bytes(sk, n)) + align256(osk::list_bytes(nblocks(sk), n, bp)) +
@@ -109,15 +110,18 @@ inline os_status prepare(const os_sketch* sk, int64_t n, void* prep, hipStream_t
     const int64_t nt = table_stride(n);
     const int32_t bp = os_block_stride(sk->b);
     uint32_t* table = static_cast<uint32_t*>(prep);
+    int32_t* inv = const_cast<int32_t*>(prep_inv(prep, sk, n));
+    void* lists = static_cast<char*>(prep) + align256(table_bytes(sk, n));
+    if (!grouped && !osk::lists_need_table(bp))     // one launch instead of three
+        return hip_status(osk::launch_hash_lists(sk->seed, sk->h, sk->sigma, n, nblocks(sk), sk->b,
+                                                 bp, lists, inv, s));
     hipError_t e = sk->h ? osk::launch_table_explicit(sk->h, sk->sigma, nblocks(sk), n, nt, sk->b,
                                                       table, s)
                          : osk::launch_table_hash(sk->seed, nblocks(sk), n, nt, sk->b, table, s);
     if (e != hipSuccess) return hip_status(e);
-    int32_t* inv = const_cast<int32_t*>(prep_inv(prep, sk, n));
     e = grouped ? osk::launch_group_buckets(table, n, nt, nblocks(sk), sk->b, bp, inv, s)
                 : osk::launch_identity_inv(nblocks(sk), bp, inv, s);
     if (e != hipSuccess) return hip_status(e);
-    void* lists = static_cast<char*>(prep) + align256(table_bytes(sk, n));
     return hip_status(osk::launch_build_lists(table, n, nt, nblocks(sk), bp, lists, s,
                                               grouped && sk->b > 64 ? inv : nullptr));
 }

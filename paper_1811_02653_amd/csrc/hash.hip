@@ -10,32 +10,10 @@
 //   word  = SplitMix64 output mix of state
 //   bucket = high 32 bits of word scaled to [0, b) by multiply-shift
 //   sign   = -1 when the low bit of word is set
-#include "internal.h"
+#include "hash.h"
 
 namespace osk {
 namespace {
-
-constexpr uint64_t kGoldenGamma = 0x9E3779B97F4A7C15ull;
-
-__device__ __forceinline__ uint64_t splitmix64_output(uint64_t state) {
-    uint64_t w = state;
-    w = (w ^ (w >> 30)) * 0xBF58476D1CE4E5B9ull;
-    w = (w ^ (w >> 27)) * 0x94D049BB133111EBull;
-    return w ^ (w >> 31);
-}
-
-__device__ __forceinline__ uint64_t sketch_word(uint64_t seed, uint64_t blk, uint64_t k) {
-    const uint64_t ctr = (blk << 40) | k;
-    return splitmix64_output(seed + (ctr + 1ull) * kGoldenGamma);
-}
-
-__device__ __forceinline__ uint32_t word_bucket(uint64_t w, uint32_t b) {
-    return (uint32_t)(((w >> 32) * (uint64_t)b) >> 32);
-}
-
-__device__ __forceinline__ uint32_t clamp_bucket(int32_t h, int32_t b) {
-    return (uint32_t)(h < 0 ? 0 : (h >= b ? b - 1 : h));
-}
 
 // One packed entry per (block, index): bucket in bits 0..30, bit 31 = negative.
 __global__ __launch_bounds__(256) void table_hash_kernel(uint64_t seed, int64_t n, int64_t nt,
@@ -101,17 +79,8 @@ __global__ __launch_bounds__(256) void table_batch_kernel(const PrepDesc* __rest
         const int64_t blk = local / d.hash_chunks;
         const int64_t k = (local % d.hash_chunks) * 256 + threadIdx.x;
         if (k >= d.nt) continue;
-        uint32_t v = 0;
-        if (k < d.n) {
-            if (d.h) {
-                v = clamp_bucket(d.h[blk * d.n + k], d.b) |
-                    (d.sigma[blk * d.n + k] < 0 ? 0x80000000u : 0u);
-            } else {
-                const uint64_t w = sketch_word(d.seed, (uint64_t)blk, (uint64_t)k);
-                v = word_bucket(w, (uint32_t)d.b) | ((uint32_t)(w & 1ull) << 31);
-            }
-        }
-        d.table[blk * d.nt + k] = v;
+        d.table[blk * d.nt + k] =
+            k < d.n ? packed_entry(d.seed, d.h, d.sigma, blk, k, d.n, d.b) : 0u;
     }
 }
 

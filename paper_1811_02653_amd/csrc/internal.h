@@ -100,6 +100,14 @@ hipError_t launch_lists_batch(const PrepDesc* descs, int32_t count, int64_t task
 hipError_t launch_build_lists(const uint32_t* table, int64_t n, int64_t nt, int32_t nblk,
                               int32_t bp, void* lists, hipStream_t s,
                               const int32_t* inv = nullptr);
+// Lists in the natural bucket order straight from the hash (or, with h, the
+// explicit tables), without a packed table in memory: one launch for the
+// table, position map (inv, the identity) and lists.  Only when
+// !lists_need_table(bp).
+bool lists_need_table(int32_t bp);
+hipError_t launch_hash_lists(uint64_t seed, const int32_t* h, const int8_t* sigma, int64_t n,
+                             int32_t nblk, int32_t b, int32_t bp, void* lists, int32_t* inv,
+                             hipStream_t s);
 // inv for every block: buckets of similar list lengths grouped into the
 // same 64-bucket groups (the identity when b <= 64).
 hipError_t launch_group_buckets(const uint32_t* table, int64_t n, int64_t nt, int32_t nblk,

@@ -30,6 +30,7 @@
 // padding entry points at a zero row.
 #include <algorithm>
 
+#include "hash.h"
 #include "sketch_launch.h"
 
 namespace osk {
@@ -141,13 +142,19 @@ __device__ __forceinline__ void ell_build_region(const uint32_t* __restrict__ ta
     }
 }
 
-// The same region built by kBW waves (bp <= kBWMaxBp): wave v counts
-// and scatters its own contiguous part of the window; its cursors start at
-// the entries of the earlier parts (an exclusive scan over the waves' counts
-// per bucket), so every bucket's list stays in ascending k.  LDS: per-wave
+// The same region built by kBW waves (bp <= kBWMaxBp): wave v
+// scatters its own contiguous part of the window; its cursors start at
+// the entries of the earlier parts (an exclusive scan over the parts' counts
+// per bucket), so every bucket's list stays in ascending k.  With Z > 1, Z
+// workgroups build one region: each counts the whole window, scatters the
+// parts z * kBW .. z * kBW + kBW - 1 and pads every Z-th group (a prepare has
+// few regions, 5 to 40 in the usual sizes, and one region is a long serial
+// chain for its workgroup: counting takes about a third of it; n = 32768, 10
+// blocks of 1024: 20.4 us with one, 14.7; n = 8192, 5 blocks of 512: 15.9 and
+// 9.9).  LDS: per-wave
 // cursors [kBW][bp], totals [bp], group bases and lengths [qn] each.  The
 // single-sketch build takes 16 waves per region for bp <= 1024 and 8 up to
-// 2048 (full-size prepare 0.026 ms, against 0.030 with 8 and 0.041 with 4);
+// 2048 (full-size lists, Z = 1: 26 us against 30 with 8 and 41 with 4);
 // the batch build, which strides over many regions per workgroup, keeps 4
 // (8 were 20 % slower there).
 constexpr int kBWSingle = 8;
@@ -156,13 +163,13 @@ constexpr int kBWWideMaxBp = 1024;
 constexpr int kBWBatch = 4;
 constexpr int kBWMaxBp = 2048;
 
-template <int kBW>
-__device__ __forceinline__ void ell_build_region_waves(const uint32_t* __restrict__ table, int64_t n,
-                                                  int64_t nt, int32_t bp, int32_t qn,
-                                                  int32_t nwin, int64_t RC,
-                                                  uint32_t* __restrict__ hdr,
-                                                  uint16_t* __restrict__ ell, int w, int64_t i,
-                                                  uint32_t* sm, const int32_t* __restrict__ inv) {
+template <int kBW, typename F>
+__device__ __forceinline__ void ell_build_region_waves(F entry, int64_t n, int32_t bp, int32_t qn,
+                                                       int32_t nwin, int64_t RC,
+                                                       uint32_t* __restrict__ hdr,
+                                                       uint16_t* __restrict__ ell, int w, int64_t i,
+                                                       uint32_t* sm, const int32_t* __restrict__ inv,
+                                                       int z = 0, int Z = 1) {
     uint32_t* cur = sm;                 // [kBW][bp] counts, then cursors
     uint32_t* tot = sm + kBW * bp;      // [bp] entries per bucket
     uint32_t* qbase = tot + bp;         // [qn] chunk base of each group
@@ -172,12 +179,12 @@ __device__ __forceinline__ void ell_build_region_waves(const uint32_t* __restric
     const int wv = tid >> 6;
     const int64_t k0 = (int64_t)w * kWin;
     const int kw = (int)min((int64_t)kWin, n - k0);
-    const uint32_t* row = table + i * nt + k0;
     uint32_t* H = hdr + (i * nwin + w) * qn;
     uint16_t* region = ell + (i * nwin + w) * RC * 512;
     // this wave's part of the window: [t_beg, t_end)
-    const int part = ((kw + kBW - 1) / kBW + 63) / 64 * 64;
-    const int t_beg = min(kw, wv * part);
+    const int parts = kBW * Z;
+    const int part = ((kw + parts - 1) / parts + 63) / 64 * 64;
+    const int t_beg = min(kw, (z * kBW + wv) * part);
     const int t_end = min(kw, t_beg + part);
     uint32_t* mine = cur + wv * bp;
     uint32_t* pos = qlen + qn;          // [bp] the block's bucket -> position map
@@ -187,7 +194,10 @@ __device__ __forceinline__ void ell_build_region_waves(const uint32_t* __restric
         return inv ? pos[h] : h;
     };
 
-    for (int c = tid; c < kBW * bp; c += 64 * kBW) cur[c] = 0;
+    uint32_t* before = tab + kWin;      // [bp] (Z > 1) entries of the earlier workgroups' parts
+    for (int c = tid; c < (kBW + 1) * bp; c += 64 * kBW) cur[c] = 0;
+    if (Z > 1)
+        for (int c = tid; c < bp; c += 64 * kBW) before[c] = 0;
     if (inv)
         for (int c = tid; c < bp; c += 64 * kBW) pos[c] = (uint32_t)inv[i * bp + c];
     {
@@ -195,38 +205,53 @@ __device__ __forceinline__ void ell_build_region_waves(const uint32_t* __restric
         constexpr int kU = kWin / (64 * kBW);
         uint32_t e[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) e[u] = row[min(u * 64 * kBW + tid, kw - 1)];
+        for (int u = 0; u < kU; ++u)
+            if (u * 64 * kBW < kw) e[u] = entry(k0 + min(u * 64 * kBW + tid, kw - 1));
 #pragma unroll
-        for (int u = 0; u < kU; ++u) tab[u * 64 * kBW + tid] = e[u];
+        for (int u = 0; u < kU; ++u)
+            if (u * 64 * kBW < kw) tab[u * 64 * kBW + tid] = e[u];
     }
     __syncthreads();
-    for (int t = t_beg + lane; t < t_end; t += 64) atomicAdd(&mine[at(tab[t])], 1u);
+    for (int t0 = 64 * wv; t0 < kw; t0 += 64 * kBW) {
+        const int p = t0 / part - z * kBW;                  // (uniform: part is a multiple of 64)
+        uint32_t* to = p < 0 ? before : (p < kBW ? cur + p * bp : tot);
+        if (t0 + lane < kw) atomicAdd(&to[at(tab[t0 + lane])], 1u);
+    }
     __syncthreads();
     for (int c = tid; c < bp; c += 64 * kBW) {
-        uint32_t run = 0;
+        uint32_t run = Z > 1 ? before[c] : 0u;
 #pragma unroll
         for (int v = 0; v < kBW; ++v) {
             const uint32_t x = cur[v * bp + c];
             cur[v * bp + c] = run;
             run += x;
         }
-        tot[c] = run;
+        tot[c] += run;
     }
     __syncthreads();
 
-    if (wv == 0) {
-        uint32_t base = 0;
-        for (int q = 0; q < qn; ++q) {
-            const int c = 64 * q + lane;
-            const uint32_t x = c < bp ? tot[c] : 0u;
-            const uint32_t nch = (wave_max(x) + 7) / 8;
-            if (lane == 0) {
-                H[q] = base | (nch << 16);
-                qbase[q] = base;
-                qlen[q] = nch;
-            }
-            base += nch;
+    // chunk counts, a wave per group; then every wave adds up its bases
+    for (int q = wv; q < qn; q += kBW) {
+        const int c = 64 * q + lane;
+        const uint32_t nch = (wave_max(c < bp ? tot[c] : 0u) + 7) / 8;
+        if (lane == 0) qlen[q] = nch;
+    }
+    __syncthreads();
+    for (int q0 = 0, base = 0; q0 < qn; q0 += 64) {      // (qn <= 32 for the builds in use)
+        const int q = q0 + lane;
+        const uint32_t len = q < qn ? qlen[q] : 0u;
+        uint32_t sum = len;                               // inclusive scan over the lanes
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t up = (uint32_t)__shfl_up((int)sum, d);
+            sum += lane >= d ? up : 0u;
         }
+        if (q < qn) {
+            const uint32_t first = (uint32_t)base + sum - len;
+            if (wv == 0 && z == 0) H[q] = first | (len << 16);
+            qbase[q] = first;                             // (the same value from every wave)
+        }
+        base += __shfl((int)sum, 63);
     }
     __syncthreads();
 
@@ -255,10 +280,10 @@ __device__ __forceinline__ void ell_build_region_waves(const uint32_t* __restric
         if (valid && (peers >> lane) == 1ull) mine[h] += (uint32_t)__popcll(peers);
         __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
 
     // padding up to each group's chunk count, groups spread over the waves
-    for (int q = wv; q < qn; q += kBW) {
+    // (other entries than the scatter's: no barrier between them)
+    for (int q = wv * Z + z; q < qn; q += parts) {
         const int c = 64 * q + lane;
         const uint32_t have = c < bp ? tot[c] : 0u;
         const uint32_t len = qlen[q] * 8;
@@ -268,16 +293,28 @@ __device__ __forceinline__ void ell_build_region_waves(const uint32_t* __restric
     }
 }
 
+// table: the packed table, or nullptr to take every entry from the hash (or
+// explicit tables) as it is needed; inv_out: where the identity position map
+// goes (with table = nullptr; natural order only).
 template <int kW>
-__global__ __launch_bounds__(64 * kW) void ell_buildw_kernel(const uint32_t* __restrict__ table,
-                                                             int64_t n, int64_t nt, int32_t bp,
-                                                             int32_t qn, int32_t nwin, int64_t RC,
-                                                             uint32_t* __restrict__ hdr,
-                                                             uint16_t* __restrict__ ell,
-                                                             const int32_t* __restrict__ inv) {
+__global__ __launch_bounds__(64 * kW) void ell_buildw_kernel(
+    const uint32_t* __restrict__ table, uint64_t seed, const int32_t* __restrict__ h,
+    const int8_t* __restrict__ sigma, int64_t n, int64_t nt, int32_t b, int32_t bp, int32_t qn,
+    int32_t nwin, int64_t RC, uint32_t* __restrict__ hdr, uint16_t* __restrict__ ell,
+    const int32_t* __restrict__ inv, int32_t* __restrict__ inv_out) {
     extern __shared__ uint32_t sm[];
-    ell_build_region_waves<kW>(table, n, nt, bp, qn, nwin, RC, hdr, ell, (int)blockIdx.x,
-                               (int64_t)blockIdx.y, sm, inv);
+    const int64_t i = blockIdx.y;
+    const int z = (int)blockIdx.z, Z = (int)gridDim.z;
+    if (table) {
+        ell_build_region_waves<kW>([&](int64_t k) { return table[i * nt + k]; }, n, bp, qn, nwin,
+                                   RC, hdr, ell, (int)blockIdx.x, i, sm, inv, z, Z);
+    } else {
+        if (inv_out && blockIdx.x == 0 && z == 0)
+            for (int c = threadIdx.x; c < bp; c += 64 * kW) inv_out[i * bp + c] = c;
+        ell_build_region_waves<kW>([&](int64_t k) { return packed_entry(seed, h, sigma, i, k, n, b); },
+                                   n, bp, qn, nwin, RC, hdr, ell, (int)blockIdx.x, i, sm, nullptr, z,
+                                   Z);
+    }
 }
 
 __global__ __launch_bounds__(64) void ell_build_kernel(const uint32_t* __restrict__ table,
@@ -300,9 +337,10 @@ __global__ __launch_bounds__(64 * kBWBatch) void ell_build_batchw_kernel(
         });
         const PrepDesc& d = descs[p];
         const int64_t local = t - d.ell_task0;
-        ell_build_region_waves<kBWBatch>(d.table, d.n, d.nt, d.bp, d.qn, d.nwin, d.RC, d.hdr,
-                                         d.ell, (int)(local % d.nwin), local / d.nwin, sm,
-                                         d.inv);
+        const int64_t i = local / d.nwin;
+        const uint32_t* row = d.table + i * d.nt;
+        ell_build_region_waves<kBWBatch>([&](int64_t k) { return row[k]; }, d.n, d.bp, d.qn, d.nwin,
+                                         d.RC, d.hdr, d.ell, (int)(local % d.nwin), i, sm, d.inv);
         __syncthreads();
     }
 }
@@ -699,27 +737,56 @@ hipError_t launch_lists_batch(const PrepDesc* descs, int32_t count, int64_t task
     return hipGetLastError();
 }
 
-hipError_t launch_build_lists(const uint32_t* table, int64_t n, int64_t nt, int32_t nblk,
-                              int32_t bp, void* lists, hipStream_t s, const int32_t* inv) {
+namespace {
+
+// The wave-parallel builder (bp <= kBWMaxBp), from the packed table or (table
+// = nullptr) from the hash or explicit tables.
+hipError_t launch_lists_waves(const uint32_t* table, uint64_t seed, const int32_t* h,
+                              const int8_t* sigma, int64_t n, int64_t nt, int32_t nblk, int32_t b,
+                              int32_t bp, void* lists, const int32_t* inv, int32_t* inv_out,
+                              hipStream_t s) {
     const Plan p = plan_of(n, bp);
     const ListView v = carve_lists(lists, nblk, n, bp);
-    if (bp <= kBWWideMaxBp) {
-        const size_t lds = (size_t)((kBWWide + 2) * bp + 2 * p.qn + kWin) * 4;
-        hipLaunchKernelGGL(ell_buildw_kernel<kBWWide>, dim3((unsigned)p.nwin, (unsigned)nblk),
-                           dim3(64 * kBWWide), lds, s, table, n, nt, bp, p.qn, p.nwin, p.RC, v.hdr,
-                           reinterpret_cast<uint16_t*>(v.ell), inv);
-    } else if (bp <= kBWMaxBp) {
-        const size_t lds = (size_t)((kBWSingle + 2) * bp + 2 * p.qn + kWin) * 4;
-        hipLaunchKernelGGL(ell_buildw_kernel<kBWSingle>, dim3((unsigned)p.nwin, (unsigned)nblk),
-                           dim3(64 * kBWSingle), lds, s, table, n, nt, bp, p.qn, p.nwin, p.RC, v.hdr,
-                           reinterpret_cast<uint16_t*>(v.ell), inv);
-    } else {
-        const size_t lds = (size_t)(2 * bp + 2 * p.qn + kWin) * 4;
-        hipLaunchKernelGGL(ell_build_kernel, dim3((unsigned)p.nwin, (unsigned)nblk), dim3(64), lds,
-                           s, table, n, nt, bp, p.qn, p.nwin, p.RC, v.hdr,
-                           reinterpret_cast<uint16_t*>(v.ell), inv);
-    }
+    const bool wide = bp <= kBWWideMaxBp;
+    const int waves = wide ? kBWWide : kBWSingle;
+    // workgroups per region: up to 8 while the device has CUs for them, none
+    // with less than one 64-entry part per wave
+    int Z = 1;
+    while (Z < 8 && (int64_t)2 * Z * p.nwin * nblk <= 256 &&
+           2 * Z * waves * 64 <= std::min<int64_t>(n, kWin))
+        Z *= 2;
+    const size_t lds = (size_t)((waves + 2 + (Z > 1)) * bp + 2 * p.qn + kWin) * 4;
+    auto kern = wide ? ell_buildw_kernel<kBWWide> : ell_buildw_kernel<kBWSingle>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)p.nwin, (unsigned)nblk, (unsigned)Z), dim3(64 * waves),
+                       lds, s, table,
+                       seed, h, sigma, n, nt, b, bp, p.qn, p.nwin, p.RC, v.hdr,
+                       reinterpret_cast<uint16_t*>(v.ell), inv, inv_out);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_build_lists(const uint32_t* table, int64_t n, int64_t nt, int32_t nblk,
+                              int32_t bp, void* lists, hipStream_t s, const int32_t* inv) {
+    if (bp <= kBWMaxBp)
+        return launch_lists_waves(table, 0, nullptr, nullptr, n, nt, nblk, bp, bp, lists, inv,
+                                  nullptr, s);
+    const Plan p = plan_of(n, bp);
+    const ListView v = carve_lists(lists, nblk, n, bp);
+    const size_t lds = (size_t)(2 * bp + 2 * p.qn + kWin) * 4;
+    hipLaunchKernelGGL(ell_build_kernel, dim3((unsigned)p.nwin, (unsigned)nblk), dim3(64), lds, s,
+                       table, n, nt, bp, p.qn, p.nwin, p.RC, v.hdr,
+                       reinterpret_cast<uint16_t*>(v.ell), inv);
+    return hipGetLastError();
+}
+
+bool lists_need_table(int32_t bp) { return bp > kBWMaxBp; }
+
+hipError_t launch_hash_lists(uint64_t seed, const int32_t* h, const int8_t* sigma, int64_t n,
+                             int32_t nblk, int32_t b, int32_t bp, void* lists, int32_t* inv,
+                             hipStream_t s) {
+    if (lists_need_table(bp)) return hipErrorInvalidValue;
+    return launch_lists_waves(nullptr, seed, h, sigma, n, 0, nblk, b, bp, lists, nullptr, inv, s);
 }
 
 hipError_t launch_group_buckets(const uint32_t* table, int64_t n, int64_t nt, int32_t nblk,

@@ -665,3 +665,31 @@ def test_whole_path_tile_forms(m, n, l, b, N, precision):
         At, Bt = (osk.sketch_quantize(S, b, N, precision) for S in (At, Bt))
     Cs = host(osk.gemm_kept_prec(At, Bt, b, N, precision))
     assert rel(C, Cs) <= 1e-6
+
+
+@pytest.mark.parametrize("n", [1, 63, 1025, 2049, 8192, 8255, 20011])
+@pytest.mark.parametrize("b,N", [(1, 1), (33, 2), (1024, 3), (1500, 2)])
+@pytest.mark.parametrize("tables", ["hash", "one bucket", "ends"])
+def test_lists_split_over_workgroups(n, b, N, tables):
+    """Regions built by one and by several workgroups, from the hash and from
+    explicit tables (a bucket holding a whole window; all entries in the first
+    and last buckets): every bucket's FP32 sum in ascending k, bit for bit."""
+    if tables == "hash":
+        h, s = osk.hash_fill(n, b, N, 0, seed=n + b)
+        args = {"seed": n + b}
+    else:
+        rng = np.random.default_rng(n + b)
+        hh = np.zeros((N, n), np.int32) if tables == "one bucket" else \
+            rng.integers(0, 2, (N, n)).astype(np.int32) * (b - 1)
+        h = torch.from_numpy(hh).cuda()
+        s = torch.from_numpy(rng.choice([-1, 1], (N, n)).astype(np.int8)).cuda()
+        args = {"h": h, "sigma": s}
+    X = synthetic.gaussian_pair(3, n, 1, n)[0]
+    got = host(osk.sketch_cols(dev(X), b, N, 0, **args))
+    bp = osk.block_stride(b)
+    h, s = h.cpu().numpy(), s.cpu().numpy()
+    for i in range(N):
+        want = np.zeros((3, bp), np.float32)
+        for k in range(n):                            # FP32, ascending k
+            want[:, h[i, k]] += np.float32(s[i, k]) * X[:, k]
+        np.testing.assert_array_equal(got[:, i * bp:(i + 1) * bp], want)
