@@ -211,11 +211,11 @@ size_t os_sketch_rows_workspace_bytes(int64_t n, int64_t cols);
  * i.e. out = (S_{s_j}^T X)^T side by side over j.  Other arguments as in
  * os_sketch_cols; out: DEVICE cols x (nst*bp), ld ldo >= nst*bp.
  * workspace: optional DEVICE buffer (256-byte aligned, >=
- * os_sketch_rows_workspace_bytes, else OS_EWORKSPACE).  With it, X is first
- * transposed into the workspace and its rows sketched as by os_sketch_cols
- * (the faster path: every line is then read as whole cache lines); with
- * workspace = NULL the columns of X are sketched in place.  Both paths give
- * the same sums in the same order. */
+ * os_sketch_rows_workspace_bytes, else OS_EWORKSPACE).  With it, an X that is
+ * not 16-byte aligned with ldx and cols multiples of 4 is first transposed
+ * into the workspace and its rows sketched as by os_sketch_cols (faster: every
+ * line is then read as whole cache lines); otherwise the columns of X are
+ * sketched in place.  Both paths give the same sums in the same order. */
 os_status os_sketch_rows(const os_sketch* sk, const void* prep, size_t prep_bytes,
                          const float* X, int64_t n, int64_t cols, int64_t ldx,
                          const uint8_t* keep_host, int kept_only, float* out, int64_t ldo,

@@ -53,6 +53,15 @@ size_t split_part_bytes(const os_sketch* sk, int64_t m, int64_t l, int prec) {
     return align256(osk::gemm_split_bytes(m, l, steps));
 }
 
+// Whether the lines of A (rows in memory, or columns when at) and of B are the
+// same vectors: the product of a matrix with its own transpose (the paper's
+// B = A^T, a Gram matrix), whose one sketch serves both sides (the sketch of
+// B is the sketch of A; 5120 x 30720, 30 blocks of 512: 0.8 of 7.3 ms).
+bool same_lines(const void* A, int a_dtype, bool at, int64_t m, int64_t lda, const void* B,
+                int b_dtype, bool bt, int64_t l, int64_t ldb) {
+    return A == B && a_dtype == b_dtype && at == bt && m == l && lda == ldb;
+}
+
 }  // namespace
 
 extern "C" {
@@ -196,6 +205,10 @@ os_status os_sketch_rows(const os_sketch* sk, const void* prep, size_t prep_byte
     if (workspace) {
         if (!aligned(workspace, 256) || ws_bytes < osk::transpose_bytes(n, cols))
             return OS_EWORKSPACE;
+    }
+    // (in place also with a workspace where that is faster than the transpose:
+    // 16384 x 1536, 10 blocks of 512: 74 us against 33 + 67; the same sums)
+    if (workspace && !osk::sketch_rows_in_place_ok(X, cols, ldx)) {
         hipStream_t s = (hipStream_t)stream;
         float* Xt = static_cast<float*>(workspace);
         const int64_t ldt = osk::round_up(n, 4);
@@ -508,7 +521,12 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     };
     if ((st = prepare(sk, n, prep, s)) != OS_OK) return st;
     if ((st = sketch_lines(A, a_dtype, a_col_major != 0, m, lda, At, aq_p)) != OS_OK) return st;
-    if ((st = sketch_lines(B, b_dtype, b_col_major == 0, l, ldb, Bt, bq_p)) != OS_OK) return st;
+    if (same_lines(A, a_dtype, a_col_major != 0, m, lda, B, b_dtype, b_col_major == 0, l, ldb)) {
+        Bt = At;
+        bq_p = aq_p;
+    } else if ((st = sketch_lines(B, b_dtype, b_col_major == 0, l, ldb, Bt, bq_p)) != OS_OK) {
+        return st;
+    }
     if (precision == OS_PREC_FP32)
         return hip_status(osk::launch_gemm_kept(
             At, zs, Bt, zs, m, l, bp, bs.kept_pos, bs.K, 1.0f / (float)bs.K, C, ldc,
@@ -519,7 +537,8 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
             if ((st = hip_status(osk::launch_quant_fp8(At, m, zs, sk->b, bs.nst, split, aq_p, wq,
                                                        s))) != OS_OK)
                 return st;
-            if ((st = hip_status(osk::launch_quant_fp8(Bt, l, zs, sk->b, bs.nst, split, bq_p, wq,
+            if (bq_p != aq_p &&
+                (st = hip_status(osk::launch_quant_fp8(Bt, l, zs, sk->b, bs.nst, split, bq_p, wq,
                                                        s))) != OS_OK)
                 return st;
         }
@@ -580,7 +599,9 @@ os_status os_matmul_cmask(const os_sketch* sk, const float* A, int64_t lda, cons
     if ((st = hip_status(osk::launch_sketch_cols(A, m, n, lda, bs.stored, bs.nst, nblocks(sk), bp,
                                                  lists, At, zs, s))) != OS_OK)
         return st;
-    if (!b_col_major && osk::sketch_rows_in_place_ok(B, l, ldb)) {
+    if (same_lines(A, OS_DTYPE_F32, false, m, lda, B, OS_DTYPE_F32, !b_col_major, l, ldb)) {
+        Bt = At;
+    } else if (!b_col_major && osk::sketch_rows_in_place_ok(B, l, ldb)) {
         // B's columns read in place (faster than transposed, same sums)
         if ((st = hip_status(osk::launch_sketch_rows(B, n, l, ldb, bs.stored, bs.nst, nblocks(sk),
                                                      bp, lists, Bt, zs, s))) != OS_OK)

@@ -693,3 +693,28 @@ def test_lists_split_over_workgroups(n, b, N, tables):
         for k in range(n):                            # FP32, ascending k
             want[:, h[i, k]] += np.float32(s[i, k]) * X[:, k]
         np.testing.assert_array_equal(got[:, i * bp:(i + 1) * bp], want)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "fp8", "fp8x3"])
+@pytest.mark.parametrize("m,n,b,N,e", [(70, 1000, 64, 3, 1), (260, 9001, 300, 2, 1)])
+def test_product_with_own_transpose(m, n, b, N, e, precision):
+    """B = A^T as a view of A (one sketch serves both sides) and as a copy give
+    the same result, bit for bit, in every layout; a view of only part of A's
+    rows, or with another leading dimension, is sketched on its own."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn(m, n + 4, generator=g, device="cuda")[:, :n]
+    keep = synthetic.random_keep(N, e, n)
+    kw = dict(seed=4, keep=keep, precision=precision)
+    copy = torch.empty_like(A).copy_(A)
+    want = osk.matmul(A, copy.t(), b, N, e, **kw)
+    assert torch.equal(osk.matmul(A, A.t(), b, N, e, **kw), want)
+    assert torch.equal(osk.matmul(A, A[: m // 2].t(), b, N, e, **kw),
+                       osk.matmul(A, copy[: m // 2].t(), b, N, e, **kw))
+    X = A.t().contiguous()                            # columns as lines on both sides
+    assert torch.equal(osk.matmul_ex(X.t(), X, b, N, e, **kw),
+                       osk.matmul_ex(X.t(), X.clone(), b, N, e, **kw))
+    if precision == "fp32":
+        t = -(-m // b)
+        cmask = (np.random.default_rng(n).random((t, t, N + e)) < 0.7).astype(np.uint8)
+        assert torch.equal(osk.matmul_cmask(A, A.t(), b, N, e, cmask, seed=4),
+                           osk.matmul_cmask(A, copy.t(), b, N, e, cmask, seed=4))
