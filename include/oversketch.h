@@ -211,11 +211,10 @@ size_t os_sketch_rows_workspace_bytes(int64_t n, int64_t cols);
  * i.e. out = (S_{s_j}^T X)^T side by side over j.  Other arguments as in
  * os_sketch_cols; out: DEVICE cols x (nst*bp), ld ldo >= nst*bp.
  * workspace: optional DEVICE buffer (256-byte aligned, >=
- * os_sketch_rows_workspace_bytes, else OS_EWORKSPACE).  With it, an X that is
- * not 16-byte aligned with ldx and cols multiples of 4 is first transposed
- * into the workspace and its rows sketched as by os_sketch_cols (faster: every
- * line is then read as whole cache lines); otherwise the columns of X are
- * sketched in place.  Both paths give the same sums in the same order. */
+ * os_sketch_rows_workspace_bytes, else OS_EWORKSPACE).  An X of fewer than 4
+ * columns is transposed into it first and its rows sketched as by
+ * os_sketch_cols (faster); otherwise the columns of X are sketched in place.
+ * Both paths give the same sums in the same order. */
 os_status os_sketch_rows(const os_sketch* sk, const void* prep, size_t prep_bytes,
                          const float* X, int64_t n, int64_t cols, int64_t ldx,
                          const uint8_t* keep_host, int kept_only, float* out, int64_t ldo,
@@ -318,12 +317,13 @@ size_t os_matmul_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, int6
  * skips the dropped blocks already in the sketch step.  C: DEVICE m x l
  * (ldc).  workspace: DEVICE, 256-byte aligned, >= os_matmul_workspace_bytes
  * for the same b_col_major.  Enqueues: prepare, sketch of A, (transpose of
- * a row-major B,) sketch of B, block product.  A row-major B that is 16-byte
- * aligned with ldb and l multiples of 4 has its columns sketched in place
- * (no transpose; the same sums).  A product of at most 128 tiles splits
- * its block product's K loop over several workgroups per tile (partials in
- * the workspace, summed in a fixed order: repeatable bit for bit, summed in
- * another order than os_gemm_kept). */
+ * a row-major B,) sketch of B, block product.  A row-major B of at least 4
+ * columns has them sketched in place (no transpose; the same sums).  A product
+ * of at most 128 tiles of 256 x 256 may split its block product's K loop over
+ * several workgroups per tile (partials in the workspace) or over the waves
+ * of one, summed in a fixed order: repeatable bit for bit, summed in another
+ * order than os_gemm_kept.  When B is A^T in memory (the same pointer and
+ * leading dimension, b_col_major = 1, l = m) one sketch serves both sides. */
 os_status os_matmul(const os_sketch* sk, const float* A, int64_t lda, const float* B,
                     int64_t ldb, int b_col_major, int64_t m, int64_t n, int64_t l,
                     const uint8_t* keep_host, int kept_only, float* C, int64_t ldc,
@@ -348,7 +348,7 @@ size_t os_matmul_prec_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n,
  * row-major B,) sketch of B, quantization of both sketches as
  * os_sketch_quantize does it, block product.  The BF16 forms always, and
  * plain FP8 when b rounded up to 64 is a multiple of 128 and each wave of
- * the sketch holds at most 20 groups of 64 buckets per pass, quantize in
+ * the sketch holds at most 10 groups of 64 buckets per pass, quantize in
  * the sketch itself (same values, no FP32 sketch written).  Arguments as in os_matmul;
  * workspace >= os_matmul_prec_workspace_bytes for the same b_col_major and
  * precision. */
@@ -384,12 +384,11 @@ size_t os_matmul_ex_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, i
  * (a_col_major = 0, element (r, k) at A[r*lda + k]) or column-major
  * (a_col_major = 1, at A[k*lda + r], lda >= m); B n x l as in os_matmul.
  * a_dtype / b_dtype: OS_DTYPE_F32 or OS_DTYPE_BF16 (2-byte aligned, ld in
- * values), in either layout.  A column-major A and a row-major B are first
- * transposed into the workspace in their own type (an FP32 one that is
- * 16-byte aligned with its ld and line count multiples of 4 is read in place
- * instead); BF16 values are converted exactly to FP32 as the sketch reads them, so the result equals that of the
- * FP32 path on the converted values, bit for bit.  With A = X^T for a
- * row-major X (n x m: A is
+ * values), in either layout.  The columns of an FP32 column-major A or
+ * row-major B (at least 4 of them) are read in place; BF16 ones are first
+ * transposed into the workspace.  BF16 values are converted exactly to FP32 as
+ * the sketch reads them, so the result equals that of the FP32 path on the
+ * converted values, bit for bit.  With A = X^T for a row-major X (n x m: A is
  * X read as column-major) and B = dY this is the sketched weight gradient of
  * a linear layer, X^T S S^T dY, sketched over the n tokens (the product of
  * Section 4 with the tokens as the inner dimension).  Other arguments as in

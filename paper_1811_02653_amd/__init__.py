@@ -385,8 +385,8 @@ def sketch_rows(X, b, N, e, seed=0, keep=None, kept_only=False, h=None, sigma=No
 
     workspace: None (sketch X's columns in place), True (allocate one) or a
     uint8 CUDA tensor of at least sketch_rows_workspace_bytes(n, cols) bytes
-    (an X that is not aligned for 16-byte loads is transposed into it first:
-    the faster path then).  X may be float32 or
+    (an X of fewer than 4 columns is transposed into it first: the faster
+    path then).  X may be float32 or
     bfloat16; a bfloat16 X always takes the transposing path (converted
     exactly to FP32, FP32 sums)."""
     torch = _torch()

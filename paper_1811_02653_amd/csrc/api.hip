@@ -206,9 +206,9 @@ os_status os_sketch_rows(const os_sketch* sk, const void* prep, size_t prep_byte
         if (!aligned(workspace, 256) || ws_bytes < osk::transpose_bytes(n, cols))
             return OS_EWORKSPACE;
     }
-    // (in place also with a workspace where that is faster than the transpose:
-    // 16384 x 1536, 10 blocks of 512: 74 us against 33 + 67; the same sums)
-    if (workspace && !osk::sketch_rows_in_place_ok(X, cols, ldx)) {
+    // (in place also with a workspace: faster than the transpose and the same
+    // sums, see sketch_rows_in_place_ok)
+    if (workspace && !osk::sketch_rows_in_place_ok(cols)) {
         hipStream_t s = (hipStream_t)stream;
         float* Xt = static_cast<float*>(workspace);
         const int64_t ldt = osk::round_up(n, 4);
@@ -457,32 +457,30 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     hipStream_t s = (hipStream_t)stream;
     const void* lists = prep_lists(prep, sk, n);
 
-    // An operand's lines (rows of A, columns of B) are sketched as rows in
-    // memory: a column-major A and a row-major B are transposed first (in
-    // their own type), so that every sketch reads whole lines (16-byte
-    // requests along a column would each bring in a separate cache line) --
-    // except an FP32 row-major B whose columns the sketch can read with
-    // 16-byte loads and its window spread over the slots
-    // (sketch_rows_in_place_ok), which is faster read in place than
-    // transposed (the sums are the same).
+    // An operand's lines (rows of A, columns of B) that are rows in memory are
+    // sketched as they are; columns of an FP32 matrix (a row-major B, a
+    // column-major A) are read in place, which is faster than transposing them
+    // first (sketch_rows_in_place_ok); columns of a BF16 one are transposed as
+    // BF16 (a 16-byte request along a column brings in a whole cache line).
     // BF16 values are converted exactly to FP32 as the sketch stages them.
     // With a BF16 block product the sketch writes its BF16 copy directly
     // (rounded in the sketch's epilogue, bit for bit what the quantization
     // of the FP32 sketch gives); with an FP8 one its FP8 copy when every
     // code belongs to a sketch group (b rounded up to 64 is a multiple of
-    // 128) and the sketch takes at most 20 slots (FP8 without the split
+    // 128) and the sketch takes at most 10 slots (FP8 without the split
     // form); otherwise the FP32 sketch, quantized after.
     const bool bf16_product = precision != OS_PREC_FP32 && !is_fp8(precision);
     // (the split FP8 form stays staged: its second group maximum made the
     // fused sketch slower than the separate quantization)
     const bool fp8_fused =
-        is_fp8(precision) && !is_split(precision) && osk::sketch_fp8_fusable(sk->b, bs.nst);
+        is_fp8(precision) && !is_split(precision) && n >= 4 &&
+        osk::sketch_fp8_fusable(sk->b, bs.nst);
     auto sketch_lines = [&](const void* X, int dtype, bool transpose, int64_t lines,
                             int64_t ldx, float* out, void* qout) -> os_status {
         const void* Xl = X;
         int64_t ldl = ldx;
         if (transpose && dtype == OS_DTYPE_F32 &&
-            osk::sketch_rows_in_place_ok(static_cast<const float*>(X), lines, ldx)) {
+            osk::sketch_rows_in_place_ok(lines)) {
             const float* Xf = static_cast<const float*>(X);
             if (bf16_product)
                 return hip_status(osk::launch_sketch_rows_q(Xf, n, lines, ldx, bs.stored, bs.nst,
@@ -601,7 +599,7 @@ os_status os_matmul_cmask(const os_sketch* sk, const float* A, int64_t lda, cons
         return st;
     if (same_lines(A, OS_DTYPE_F32, false, m, lda, B, OS_DTYPE_F32, !b_col_major, l, ldb)) {
         Bt = At;
-    } else if (!b_col_major && osk::sketch_rows_in_place_ok(B, l, ldb)) {
+    } else if (!b_col_major && osk::sketch_rows_in_place_ok(l)) {
         // B's columns read in place (faster than transposed, same sums)
         if ((st = hip_status(osk::launch_sketch_rows(B, n, l, ldb, bs.stored, bs.nst, nblocks(sk),
                                                      bp, lists, Bt, zs, s))) != OS_OK)

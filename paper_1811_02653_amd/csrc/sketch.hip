@@ -13,7 +13,7 @@
 //
 // Scheme (read-once): a workgroup owns kLines = 4 lines and keeps ALL their
 // buckets -- every stored block -- in registers (a pass covers up to
-// 8 * kMaxSlots groups of 64 buckets; wider sketches take several passes).
+// 16 * kMaxSlots groups of 64 buckets; wider sketches take several passes).
 // It walks the sketched index in windows of kWin = 8192: the window of its
 // 4 lines is staged in LDS once as kWin float4 (the 4 lines' values at one
 // k side by side), and every lane then adds, for each bucket it owns, the
@@ -651,6 +651,49 @@ ListView carve_lists(void* lists, int32_t nblk, int64_t n, int32_t bp) {
     return v;
 }
 
+// Sketch of an operand too short for the sketch kernel's loads of 4 values
+// (rows of fewer than 4 values, fewer than 4 columns): a wave per line and
+// group of 64 buckets, each lane adding its bucket's entries one at a time,
+// the same sums in the same order.  Output modes 0 to 2 of sketch_kernel.
+template <typename TI>
+__global__ __launch_bounds__(64) void sketch_cell_kernel(
+    const TI* __restrict__ X, int row_lines, int64_t n, int64_t ldx, int32_t bp, int32_t qn,
+    int32_t nwin, BlockList bl, int64_t RC, const uint32_t* __restrict__ hdr,
+    const uint4* __restrict__ ell, void* __restrict__ out, int64_t ldo,
+    const float* __restrict__ wd, int32_t obp, int32_t omode, int64_t ozlo) {
+    const int lane = threadIdx.x;
+    const int64_t line = blockIdx.x;
+    const int q = blockIdx.y, j = blockIdx.z;
+    const int64_t i = bl.idx[j];
+    float acc = 0.f;
+    for (int w = 0; w < nwin; ++w) {
+        const uint32_t h = hdr[(i * nwin + w) * qn + q];
+        const uint4* list = ell + ((i * nwin + w) * RC + (h & 0xFFFFu)) * 64 + lane;
+        for (uint32_t c = 0; c < h >> 16; ++c) {
+            const uint4 e = list[(int64_t)c * 64];
+            const uint32_t words[4] = {e.x, e.y, e.z, e.w};
+            for (int t = 0; t < 8; ++t) {
+                const uint32_t v = words[t >> 1] >> (16 * (t & 1)) & 0xFFFFu;
+                const int slot = v & 0x7FFFu;
+                if (slot == kPad) continue;
+                const int64_t k = (int64_t)w * kWin + slot_pos(slot);
+                float x = (float)X[row_lines ? line * ldx + k : k * ldx + line];
+                if (wd) x *= sqrtf(wd[k]);
+                acc = fmaf(v & 0x8000u ? -1.f : 1.f, x, acc);
+            }
+        }
+    }
+    if (lane >= min(64, obp - 64 * q)) return;
+    const int64_t o = line * ldo + (int64_t)j * obp + 64 * q + lane;
+    if (omode == 0) {
+        static_cast<float*>(out)[o] = acc;
+    } else {
+        const __bf16 hi = (__bf16)acc;
+        static_cast<__bf16*>(out)[o] = hi;
+        if (omode == 2) static_cast<__bf16*>(out)[o + ozlo] = (__bf16)(acc - (float)hi);
+    }
+}
+
 // Passes and slots per pass for nst stored blocks.
 void pass_plan(int32_t nst, int32_t qn, int32_t* npass, int32_t* slots) {
     const int64_t gs = (int64_t)nst * qn;
@@ -686,13 +729,22 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
     if (out_mode < 0 || out_mode > 3) return hipErrorInvalidValue;
     const int32_t obp = out_mode ? p.qn * 64 : bp;
     const int64_t ozlo = out_mode >= 2 ? (int64_t)nst * obp : 0;
-    // vec: a quad of 4 values is one aligned load (16 bytes FP32, 8 BF16)
-    const uintptr_t quad = bf16 ? 7 : 15;
-    const int vec = (reinterpret_cast<uintptr_t>(X) & quad) == 0 && (ldx & 3) == 0 &&
-                    (reinterpret_cast<uintptr_t>(wd) & 15) == 0;
-    const SketchArgs a{X,       lines, n,   ldx, vec,   bp, p.qn, p.nwin,  nst, &bl, p.RC,
-                       v.hdr,   v.ell, out, ldo, npass, wd, obp,  out_mode, ozlo};
+    const SketchArgs a{X,     lines, n,   ldx, bp,    p.qn, p.nwin, nst,      &bl, p.RC,
+                       v.hdr, v.ell, out, ldo, npass, wd,   obp,    out_mode, ozlo};
     if ((bf16 && !row_lines) || ((out_mode == 3 || bf16) && wd)) return hipErrorInvalidValue;
+    if (row_lines ? n < 4 : lines < 4) {     // too short for loads of 4 values
+        if (out_mode == 3 || p.qn > 65535 || nst > 65535) return hipErrorInvalidValue;
+        const dim3 cells((unsigned)lines, (unsigned)p.qn, (unsigned)nst);
+        if (bf16)
+            hipLaunchKernelGGL(sketch_cell_kernel<__bf16>, cells, dim3(64), 0, s,
+                               static_cast<const __bf16*>(X), 1, n, ldx, bp, p.qn, p.nwin, bl, p.RC,
+                               v.hdr, v.ell, out, ldo, wd, obp, out_mode, ozlo);
+        else
+            hipLaunchKernelGGL(sketch_cell_kernel<float>, cells, dim3(64), 0, s,
+                               static_cast<const float*>(X), row_lines ? 1 : 0, n, ldx, bp, p.qn,
+                               p.nwin, bl, p.RC, v.hdr, v.ell, out, ldo, wd, obp, out_mode, ozlo);
+        return hipGetLastError();
+    }
     if (out_mode == 3)
         return bf16        ? sketch_rows_bf16_fp8(slots, grid, s, a)
                : row_lines ? sketch_rows_f32_fp8(slots, grid, s, a)
@@ -834,9 +886,7 @@ hipError_t launch_sketch_rows(const float* X, int64_t n, int64_t cols, int64_t l
     return launch_sketch(false, X, false, cols, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s);
 }
 
-bool sketch_rows_in_place_ok(const float* X, int64_t cols, int64_t ldx) {
-    return (reinterpret_cast<uintptr_t>(X) & 15) == 0 && (ldx & 3) == 0 && (cols & 3) == 0;
-}
+bool sketch_rows_in_place_ok(int64_t cols) { return cols >= 4; }
 
 hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t ldx,
                                 const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
@@ -916,10 +966,10 @@ hipError_t launch_sketch_cols_q(const void* X, bool x_bf16, int64_t rows, int64_
 
 bool sketch_fp8_fusable(int32_t b, int32_t nst) {
     if (round_up(b, 64) != block_stride_fp8(b)) return false;
-    // the 24-slot kernel with the FP8 epilogue spills (400 bytes per lane)
+    // (the 12-slot kernel with the FP8 epilogue would spill)
     int32_t npass, slots;
     pass_plan(nst, (int32_t)(round_up(b, kBlockAlign) + 63) / 64, &npass, &slots);
-    return slots <= 20;
+    return slots <= kMaxFp8Slots;
 }
 
 hipError_t launch_sketch_cols_fp8(const void* X, bool x_bf16, int64_t rows, int64_t n,

@@ -10,19 +10,24 @@ namespace osk {
 
 constexpr int kWin = kSketchWindow;    // sketched indices per window (8192)
 constexpr int kLines = 4;              // lines per workgroup
-constexpr int kThreads = 512;          // 8 waves
+constexpr int kThreads = 1024;         // 16 waves
 constexpr int kWaves = kThreads / 64;
-constexpr int kPerThread = kWin / kThreads;   // window positions staged per thread (16)
+constexpr int kPerThread = kWin / kThreads;   // window positions staged per thread (8)
 constexpr uint16_t kPad = (uint16_t)kWin;     // entry of the zero row, positive
-constexpr int kAhead = 3;              // list chunks of a slot fetched ahead
+constexpr int kAhead = 2;              // list chunks of a slot fetched ahead
 constexpr int kDist = 1;               // slots ahead whose lists are fetched
 
 // LDS slot of window position p (p < kWin).  Thread t stages the quads of
-// positions 2048u + 4t + j (j < 4); they go to slots 2048u + 512j + t, so the
+// positions 4096u + 4t + j (j < 4); they go to slots 4096u + 1024j + t, so the
 // lanes of one staging write touch consecutive slots.  List entries hold the
 // slot of their position.
 __device__ __forceinline__ int win_slot(int p) {
-    return (p & ~2047) | ((p & 3) << 9) | ((p >> 2) & 511);
+    return (p & ~4095) | ((p & 3) << 10) | ((p >> 2) & 1023);
+}
+
+// The position of a slot.
+__device__ __forceinline__ int slot_pos(int s) {
+    return (s & ~4095) | ((s & 1023) << 2) | ((s >> 10) & 3);
 }
 
 // f(integral_constant<int, I>) for I = B .. E - 1, unrolled by the compiler
@@ -35,12 +40,11 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-// Spread consecutive task ids over the 8 XCDs in contiguous runs: task T is
-// run by the workgroup with linear id L where T = (L % 8) * (tasks / 8) + L / 8,
-// so neighbouring tasks share an XCD and its L2.
+// Spread consecutive task ids over the 8 XCDs in contiguous runs (workgroup L
+// runs on XCD L % 8), so neighbouring tasks share an XCD and its L2.
 __device__ __forceinline__ int64_t xcd_task(int64_t L, int64_t tasks) {
-    if (tasks % 8 != 0) return L;
-    return (L % 8) * (tasks / 8) + L / 8;
+    const int64_t q = tasks / 8, r = tasks % 8, x = L % 8;
+    return x * q + min(x, r) + L / 8;
 }
 
 __device__ __forceinline__ uint64_t lanes_below() {

@@ -12,23 +12,24 @@ namespace osk {
 namespace {
 
 // ---------------------------------------------------------------------------
-// The sketch kernel.  Thread t stages window positions 2048u + 4t + j
-// (u, j < 4) into LDS slots win_slot(k) = 2048u + 512j + t; list entries
+// The sketch kernel.  Thread t stages window positions 4096u + 4t + j
+// (u < 2, j < 4) into LDS slots win_slot(k) = 4096u + 1024j + t; list entries
 // hold those slots.
-//   kRowLines = true : lines are rows of X (lines x n, ld ldx).  With vec
-//                      (X 16-byte aligned, ldx % 4 == 0, and the window whole
-//                      or n a multiple of 4) a line's 4 consecutive positions
-//                      come with one 16-byte load (1 KiB per wave,
-//                      coalesced): r[4*line + u] holds positions 4t + 2048u
-//                      .. +3 of that line.  Otherwise every value is loaded
-//                      on its own into the same layout.
-//   kRowLines = false: lines are columns of X (n x lines, ld ldx); r[4u + j]
-//                      holds X[k][line0 .. line0+3] for position k = 2048u +
-//                      4t + j, one 16-byte load when vec (X 16-byte aligned,
-//                      ldx % 4 == 0), else four.
+//   kRowLines = true : lines are rows of X (lines x n, ld ldx, n >= 4): a
+//                      line's 4 consecutive positions come with one load of 4
+//                      values (16 bytes FP32, 1 KiB per wave; any element
+//                      alignment): r[2*line + u] holds positions 4t + 4096u
+//                      .. +3 of that line.  The quad that straddles the end of
+//                      a window whose length is no multiple of 4 is loaded
+//                      from the last 4 positions and shifted when it is staged.
+//   kRowLines = false: lines are columns of X (n x lines, ld ldx, lines >= 4);
+//                      r[4u + j] holds X[k][line0 .. line0+3] for position k =
+//                      4096u + 4t + j, one 16-byte load.  The last group of
+//                      lines starts at lines - 4 (lines that two groups hold
+//                      are written twice with the same values).
 // kWeighted (row lines): every value at sketched index k is multiplied by
 // sqrt(wd[k]) (a diagonal weight, as in A D^{1/2} S for a Hessian A D A^T);
-// w[u] holds the weights of positions 4t + 2048u .. +3.  The weight is
+// w[u] holds the weights of positions 4t + 4096u .. +3.  The weight is
 // applied when the window is written to LDS, not when it is loaded, so the
 // loads of the next window stay in flight while the current one is summed.
 // ---------------------------------------------------------------------------
@@ -37,10 +38,12 @@ namespace {
 // converted to FP32 (exactly) when the window is written to LDS.
 // A window's FP32 values and weights are read once: non-temporal loads keep
 // them from displacing the bucket lists (which every line group reads) in
-// the caches (the FP32 sketch of A 2-5 % faster).
+// the caches (the FP32 sketch of A 2-5 % faster).  Loads need only the
+// alignment of an element (gfx950 loads 16 bytes at any dword).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 __device__ __forceinline__ float4 load_stream(const float* __restrict__ p) {
-    const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+    const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
     return make_float4(t[0], t[1], t[2], t[3]);
 }
 
@@ -49,110 +52,68 @@ struct RawQuad;
 template <>
 struct RawQuad<float> {
     using type = float4;
-    static __device__ __forceinline__ type load(const float* __restrict__ p) {
-        return *reinterpret_cast<const float4*>(p);
-    }
-    static __device__ __forceinline__ type gather(const float* __restrict__ p,
-                                                  const int64_t (&k)[4]) {
-        return make_float4(p[k[0]], p[k[1]], p[k[2]], p[k[3]]);
-    }
     static __device__ __forceinline__ float value(const type& v, int j) {
         return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
+    }
+    // the quad starting d values further (its last d values are not used)
+    static __device__ __forceinline__ type shift(const type& v, int d) {
+        return d == 1 ? make_float4(v.y, v.z, v.w, 0.f)
+                      : (d == 2 ? make_float4(v.z, v.w, 0.f, 0.f) : make_float4(v.w, 0.f, 0.f, 0.f));
     }
 };
 template <>
 struct RawQuad<__bf16> {
     using type = uint2;
-    static __device__ __forceinline__ uint32_t bits(const __bf16* __restrict__ p) {
-        return __builtin_bit_cast(uint16_t, *p);
-    }
+    typedef uint32_t pair2 __attribute__((ext_vector_type(2)));
+    typedef pair2 pair2_any __attribute__((aligned(2)));
     static __device__ __forceinline__ type load(const __bf16* __restrict__ p) {
-        return *reinterpret_cast<const uint2*>(p);
-    }
-    static __device__ __forceinline__ type gather(const __bf16* __restrict__ p,
-                                                  const int64_t (&k)[4]) {
-        return make_uint2(bits(p + k[0]) | bits(p + k[1]) << 16,
-                          bits(p + k[2]) | bits(p + k[3]) << 16);
+        const pair2 t = *reinterpret_cast<const pair2_any*>(p);
+        return make_uint2(t[0], t[1]);
     }
     static __device__ __forceinline__ float value(const type& v, int j) {
         const uint32_t w = j < 2 ? v.x : v.y;
         return __uint_as_float((j & 1) ? (w & 0xFFFF0000u) : (w << 16));
     }
+    static __device__ __forceinline__ type shift(const type& v, int d) {
+        const uint64_t x = ((uint64_t)v.y << 32 | v.x) >> (16 * d);
+        return make_uint2((uint32_t)x, (uint32_t)(x >> 32));
+    }
 };
 
-// Loads pieces p0 .. p1 - 1 of a window (piece 4u + q: r[4q + u] of row
-// lines with w[u] at q = 0, r[4u + q] of column lines); all 16 pieces make
-// the window.  p0 and p1 are constants where the caller is unrolled.
-template <bool kRowLines, bool kWeighted, typename TI, bool kWhole = false>
+// Loads pieces p0 .. p1 - 1 of a window (piece 4u + q: r[2q + u] of row
+// lines, r[4u + q] of column lines); all 8 pieces make the window.  p0 and p1 are constants (the callers are unrolled).  Every
+// load is unconditional (a branch around a load makes each use wait for all
+// loads in flight): positions past the window's end are clamped to its last
+// ones (no entry refers to them) and lines past the matrix to its last line
+// (their sums are never stored).
+template <bool kRowLines, typename TI>
 __device__ __forceinline__ void load_window(typename RawQuad<TI>::type (&r)[kPerThread],
-                                            float4 (&w)[4], const TI* __restrict__ X,
-                                            int64_t lines, int64_t ldx, int64_t line0, int64_t k0,
-                                            int kw, bool vec, const float* __restrict__ wd,
-                                            int p0 = 0, int p1 = kPerThread) {
-    using R = RawQuad<TI>;
+                                            const TI* __restrict__ X, int64_t lines, int64_t ldx,
+                                            int64_t line0, int64_t k0, int kw, int p0, int p1) {
     static_assert(kRowLines || sizeof(TI) == 4, "column lines are read as FP32 only");
-    // Every load is unconditional (a branch around a load makes each use wait
-    // for all loads in flight): positions past the window's end are clamped to
-    // its last index (no entry refers to them) and lines past the matrix to
-    // its last line (their sums are never stored).
     const int tid = threadIdx.x;
-    const int64_t l1 = min(line0 + 1, lines - 1) - line0;
-    const int64_t l2 = min(line0 + 2, lines - 1) - line0;
-    const int64_t l3 = min(line0 + 3, lines - 1) - line0;
-    if constexpr (kRowLines) {
-        const int64_t dl[4] = {0, l1, l2, l3};
-        if (vec) {
-            // kw is a multiple of 4 here: the last whole quad starts at kw - 4.
-            // Uniform line bases plus a 32-bit lane offset (scalar-base
-            // addressing: a piece issued late keeps one offset register live,
-            // not a 64-bit address).
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t off = (uint32_t)min(4 * tid + 2048 * u, kw - 4);
+    for (int u = 0; u < 2; ++u) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (4 * u + q < p0 || 4 * u + q >= p1) continue;
-                    const TI* base = X + (line0 + dl[q]) * ldx + k0;
-                    // (the FP32 load written here, not through R::load: through the
-                    // helper the FP32 kernels took 20 more registers and spilled)
-                    if constexpr (sizeof(TI) == 4)
-                        r[4 * q + u] = load_stream(base + off);
-                    else
-                        r[4 * q + u] = R::load(base + off);
-                    if constexpr (kWeighted)
-                        if (q == 0) w[u] = load_stream(wd + k0 + off);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                int64_t kk[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) kk[j] = k0 + min(4 * tid + 2048 * u + j, kw - 1);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (4 * u + q < p0 || 4 * u + q >= p1) continue;
-                    r[4 * q + u] = R::gather(X + (line0 + dl[q]) * ldx, kk);
-                    if constexpr (kWeighted)
-                        if (q == 0) w[u] = make_float4(wd[kk[0]], wd[kk[1]], wd[kk[2]], wd[kk[3]]);
-                }
-            }
-        }
-    } else {
-        // r[4u + j] = the 4 lines at position 2048u + 4t + j
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (4 * u + j < p0 || 4 * u + j >= p1) continue;
-                const int64_t kk = k0 + min(4 * tid + 2048 * u + j, kw - 1);
-                const TI* p = X + kk * ldx + line0;
-                if constexpr (kWhole)    // vec and every line group whole
-                    r[4 * u + j] = *reinterpret_cast<const float4*>(p);
-                else if (vec && l3 == 3)      // uniform
-                    r[4 * u + j] = *reinterpret_cast<const float4*>(p);
+        for (int q = 0; q < 4; ++q) {
+            if (4 * u + q < p0 || 4 * u + q >= p1) continue;
+            if constexpr (kRowLines) {
+                // Uniform line bases plus a 32-bit lane offset (scalar-base
+                // addressing: a piece issued late keeps one offset register
+                // live, not a 64-bit address); the offset may be negative when
+                // a last window has fewer than 4 positions
+                const int off = min(4 * tid + 4096 * u, kw - 4);
+                const TI* base = X + min(line0 + q, lines - 1) * ldx + k0;
+                // (the FP32 load written here, not through a RawQuad helper:
+                // through one the FP32 kernels took 20 more registers)
+                if constexpr (sizeof(TI) == 4)
+                    r[2 * q + u] = load_stream(base + off);
                 else
-                    r[4 * u + j] = make_float4(p[0], p[l1], p[l2], p[l3]);
+                    r[2 * q + u] = RawQuad<TI>::load(base + off);
+            } else {
+                const int64_t kk = k0 + min(4 * tid + 4096 * u + q, kw - 1);
+                const f32x4 t = *reinterpret_cast<const f32x4_any*>(X + kk * ldx + line0);
+                r[4 * u + q] = make_float4(t[0], t[1], t[2], t[3]);
             }
         }
     }
@@ -162,21 +123,40 @@ __device__ __forceinline__ float comp4(const float4& v, int j) {
     return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
 }
 
-// Writes a loaded window into LDS: win[win_slot(k)] = the 4 lines' values at
-// window position k (weighted when kWeighted).
+// The weights of this thread's positions of a window, as the loaded quads.
+__device__ __forceinline__ void load_weights(float4 (&w)[2], const float* __restrict__ wd,
+                                             int64_t k0, int kw) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        w[u] = load_stream(wd + k0 + min(4 * (int)threadIdx.x + 4096 * u, kw - 4));
+}
+
+// Writes a loaded window of kw positions into LDS: win[win_slot(k)] = the 4
+// lines' values at window position k (weighted when kWeighted).
 template <bool kRowLines, bool kWeighted, typename TI>
 __device__ __forceinline__ void stage_window(float4* __restrict__ win,
-                                             const typename RawQuad<TI>::type (&r)[kPerThread],
-                                             const float4 (&w)[4]) {
+                                             typename RawQuad<TI>::type (&r)[kPerThread],
+                                             float4 (&w)[2], int kw) {
     using R = RawQuad<TI>;
     const int tid = threadIdx.x;
     if constexpr (kRowLines) {
+        if (kw & 3) {       // uniform: a last window that ends inside a quad
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 2; ++u) {
+                const int d = 4 * tid + 4096 * u - (kw - 4);
+                if (d > 0 && d < 4) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) r[2 * q + u] = R::shift(r[2 * q + u], d);
+                    if constexpr (kWeighted) w[u] = RawQuad<float>::shift(w[u], d);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                float4 v = make_float4(R::value(r[u], j), R::value(r[4 + u], j),
-                                       R::value(r[8 + u], j), R::value(r[12 + u], j));
+                float4 v = make_float4(R::value(r[u], j), R::value(r[2 + u], j),
+                                       R::value(r[4 + u], j), R::value(r[6 + u], j));
                 if constexpr (kWeighted) {
                     const float sw = sqrtf(comp4(w[u], j));
                     v.x *= sw;
@@ -184,39 +164,40 @@ __device__ __forceinline__ void stage_window(float4* __restrict__ win,
                     v.z *= sw;
                     v.w *= sw;
                 }
-                win[2048 * u + 512 * j + tid] = v;      // slot of position 2048u + 4t + j
+                win[4096 * u + 1024 * j + tid] = v;      // slot of position 4096u + 4t + j
             }
         }
     } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                win[2048 * u + 512 * j + tid] =
+                win[4096 * u + 1024 * j + tid] =
                     make_float4(R::value(r[4 * u + j], 0), R::value(r[4 * u + j], 1),
                                 R::value(r[4 * u + j], 2), R::value(r[4 * u + j], 3));
     }
 }
 
-// Adds the 8 entries of one chunk (16-bit entries, two per word; sign bit 15
-// selects the sign of the FP32 +-1.0 factor).  All eight LDS reads are issued
-// before the first FMA so their latencies overlap.
-__device__ __forceinline__ void add_chunk(float4& acc, const float4* __restrict__ win, uint4 e) {
-    const uint32_t w[4] = {e.x, e.y, e.z, e.w};
-    float4 v[8];
-    float s[8];
+// Adds 4 entries (16 bits each, two per word; sign bit 15 selects the sign of
+// the FP32 +-1.0 factor).  All four LDS reads are issued before the first
+// FMA so their latencies overlap.
+__device__ __forceinline__ void add_half(float4& acc, const float4* __restrict__ win, uint32_t w0,
+                                         uint32_t w1) {
+    const uint32_t w[2] = {w0, w1};
+    float4 v[4];
+    float s[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 2; ++u) {
         v[2 * u] = win[w[u] & 0x7FFFu];
         v[2 * u + 1] = win[(w[u] >> 16) & 0x7FFFu];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 2; ++u) {
         s[2 * u] = __uint_as_float(0x3F800000u | ((w[u] << 16) & 0x80000000u));
         s[2 * u + 1] = __uint_as_float(0x3F800000u | (w[u] & 0x80000000u));
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < 4; ++u) {
         acc.x = fmaf(s[u], v[u].x, acc.x);
         acc.y = fmaf(s[u], v[u].y, acc.y);
         acc.z = fmaf(s[u], v[u].z, acc.z);
@@ -224,12 +205,23 @@ __device__ __forceinline__ void add_chunk(float4& acc, const float4* __restrict_
     }
 }
 
-// One workgroup of 8 waves fills a CU's LDS, so each SIMD runs 2 waves: the
-// compiler may use up to 256 VGPRs per lane.
-template <int kSlots, bool kRowLines, bool kWeighted, typename TI, bool kFp8Out, bool kSpread>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))
+// Adds the 8 entries of one chunk, four at a time (four waves per SIMD hide
+// the LDS latency; eight reads in flight would spill).
+__device__ __forceinline__ void add_chunk(float4& acc, const float4* __restrict__ win, uint4 e) {
+    add_half(acc, win, e.x, e.y);
+    __builtin_amdgcn_sched_barrier(0);
+    add_half(acc, win, e.z, e.w);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// One workgroup of 16 waves fills a CU's LDS, so each SIMD runs 4 waves of up
+// to 128 VGPRs.  (8 waves of 256 VGPRs with whole chunks in flight: the FP32
+// sketch of 8192 x 32768 into 10 blocks of 1024 took 506 us from rows and 785
+// from columns, this 486 and 736.)
+template <int kSlots, bool kRowLines, bool kWeighted, typename TI, bool kFp8Out>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sketch_kernel(
-    const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int vec, int32_t bp,
+    const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int32_t bp,
     int32_t qn, int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
     const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell, void* __restrict__ out,
     int64_t ldo, int32_t npass, const float* __restrict__ wd, int32_t obp, int32_t omode,
@@ -237,16 +229,13 @@ void sketch_kernel(
     __shared__ float4 win[kWin + 1];    // row kWin stays zero
     const int tid = threadIdx.x;
     const int lane = tid & 63;
+    const uint32_t lane16 = 16 * (uint32_t)lane;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t groups = (lines + kLines - 1) / kLines;
     const int64_t tasks = groups * npass;
     const int gslots = nst * qn;         // groups of 64 buckets over the stored blocks
     if (tid == 0) win[kWin] = make_float4(0.f, 0.f, 0.f, 0.f);
 
-    // vec for a row-lines window: whole windows always, the last one when n % 4 == 0
-    auto vec_at = [&](int64_t k0) {
-        return kRowLines ? (vec != 0 && (k0 + kWin <= n || (n & 3) == 0)) : vec != 0;
-    };
     // Persistent: workgroup g takes tasks g, g + grid, ... (task = a group
     // of 4 lines and a pass); the first window of its next task is fetched
     // while the last window of the current one is summed, so only the first
@@ -259,7 +248,10 @@ void sketch_kernel(
     // (eb), the group's first output column (col) and how many of its 64
     // buckets exist (lim, 0 for an unused slot).  A window's headers come in
     // with one vector load, issued before the window's values are fetched.
-    auto line_of = [&](int64_t it) { return xcd_task(it, tasks) / npass * kLines; };
+    auto line_of = [&](int64_t it) {
+        const int64_t l0 = xcd_task(it, tasks) / npass * kLines;
+        return kRowLines ? l0 : min(l0, lines - 4);
+    };
     struct Meta {
         int32_t hb, eb, col, lim;
     };
@@ -283,16 +275,16 @@ void sketch_kernel(
         return hb >= 0 ? h : 0u;
     };
     typename RawQuad<TI>::type pre[kPerThread];
-    float4 wpre[4];
+    float4 wpre[2];
     uint32_t hnext = 0;
     if ((int64_t)blockIdx.x < tasks) {
         hnext = headers(meta_of(blockIdx.x).hb, 0);
-        load_window<kRowLines, kWeighted, TI>(pre, wpre, X, lines, ldx, line_of(blockIdx.x), 0,
-                                              (int)min((int64_t)kWin, n), vec_at(0), wd);
+        const int kw = (int)min((int64_t)kWin, n);
+        load_window<kRowLines, TI>(pre, X, lines, ldx, line_of(blockIdx.x), 0, kw, 0, kPerThread);
+        if constexpr (kWeighted) load_weights(wpre, wd, 0, kw);
     }
     for (int64_t it = blockIdx.x; it < tasks; it += gridDim.x) {
-    const int64_t task = xcd_task(it, tasks);
-    const int64_t line0 = task / npass * kLines;
+    const int64_t line0 = line_of(it);
     const Meta meta = meta_of(it);      // (its loads complete with the window's, before staging)
 
     float4 acc[kSlots];
@@ -300,7 +292,8 @@ void sketch_kernel(
     for (int s = 0; s < kSlots; ++s) acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int w = 0; w < nwin; ++w) {
         __syncthreads();                 // the previous window is no longer read
-        stage_window<kRowLines, kWeighted, TI>(win, pre, wpre);
+        stage_window<kRowLines, kWeighted, TI>(
+            win, pre, wpre, (int)min((int64_t)kWin, n - (int64_t)w * kWin));
         __syncthreads();
         const uint32_t hv = hnext;       // this window's headers (lane s: slot s)
         // The list chunks of slot s + kDist (up to kAhead of them) are fetched
@@ -308,16 +301,20 @@ void sketch_kernel(
         // past a slot's count repeat its last chunk, and an unused slot
         // (header 0) reads chunk 0 of block 0's region (never summed).
         const int64_t wrc = (int64_t)w * RC;
-        auto slot_list = [&](int s, uint32_t& nch) -> const uint4* {
+        // (List addresses stay scalar: uniform base plus the lane's 16 bytes.)
+        auto slot_list = [&](int s, uint32_t& nch) -> const char* {
             const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)hv, s);
             const int64_t eb = __builtin_amdgcn_readlane(meta.eb, s);
             nch = h >> 16;
-            return ell + (eb + wrc + (h & 0xFFFFu)) * 64 + lane;
+            return reinterpret_cast<const char*>(ell) + ((eb + wrc + (h & 0xFFFFu)) << 10);
         };
-        auto fetch = [&](uint4 (&d)[kAhead], const uint4* p, uint32_t nch) {
+        auto chunk_at = [&](const char* p, uint32_t c) -> uint4 {
+            return *reinterpret_cast<const uint4*>(p + (c << 10) + lane16);
+        };
+        auto fetch = [&](uint4 (&d)[kAhead], const char* p, uint32_t nch) {
             const uint32_t last = nch > 0 ? nch - 1 : 0;
 #pragma unroll
-            for (int c = 0; c < kAhead; ++c) d[c] = p[(int64_t)min((uint32_t)c, last) * 64];
+            for (int c = 0; c < kAhead; ++c) d[c] = chunk_at(p, min((uint32_t)c, last));
         };
         // The next window (this task's, else the first of the next task) is
         // loaded in kPerThread pieces spread over the slots, each issued
@@ -337,14 +334,13 @@ void sketch_kernel(
             k1 = 0;
             kw1 = (int)min((int64_t)kWin, n);
         } else {
-            k1 = (int64_t)w * kWin;
-            kw1 = (int)min((int64_t)4, n - k1);
+            k1 = 0;
+            kw1 = (int)min((int64_t)4, n);
         }
-        const bool vec1 = vec_at(k1) && kw1 >= 4;
         constexpr int kRing = kDist + 1;
         uint4 lst[kRing][kAhead];
         uint32_t nls[kRing];
-        const uint4* pls[kRing];
+        const char* pls[kRing];
 #pragma unroll
         for (int s = 0; s < kDist && s < kSlots; ++s) {
             pls[s] = slot_list(s, nls[s]);
@@ -362,21 +358,19 @@ void sketch_kernel(
                 pls[r] = slot_list(s + kDist, nls[r]);
                 fetch(lst[r], pls[r], nls[r]);
             }
-            if constexpr (kSpread) {
-                if constexpr (s < kSpreadSlots)
-                    load_window<kRowLines, kWeighted, TI, true>(
-                        pre, wpre, X, lines, ldx, l1, k1, kw1, true, wd, s * kPer,
-                        (s + 1) * kPer < kPerThread ? (s + 1) * kPer : kPerThread);
-            } else if constexpr (s == 0) {
-                load_window<kRowLines, kWeighted, TI>(pre, wpre, X, lines, ldx, l1, k1, kw1, vec1,
-                                                      wd);
-            }
+            if constexpr (s < kSpreadSlots)
+                load_window<kRowLines, TI>(
+                    pre, X, lines, ldx, l1, k1, kw1, s * kPer,
+                    (s + 1) * kPer < kPerThread ? (s + 1) * kPer : kPerThread);
             constexpr int r = s % kRing;
 #pragma unroll
             for (int c = 0; c < kAhead; ++c)
                 if ((uint32_t)c < nls[r]) add_chunk(acc[s], win, lst[r][c]);
-            for (uint32_t c = kAhead; c < nls[r]; ++c) add_chunk(acc[s], win, pls[r][(int64_t)c * 64]);
+            for (uint32_t c = kAhead; c < nls[r]; ++c) add_chunk(acc[s], win, chunk_at(pls[r], c));
         });
+        // (the next window's weights last: eight registers fewer during the
+        // slots; every line group reads them, so they come from L2)
+        if constexpr (kWeighted) load_weights(wpre, wd, k1, kw1);
     }
 
     // Output: FP32 (omode 0, blocks obp = bp apart), or the copy the block
@@ -466,35 +460,28 @@ void sketch_kernel(
     }   // tasks
 }
 
-template <int S, bool R, bool W, typename TI, bool Q8, bool kSpread>
+template <int S, bool R, bool W, typename TI, bool Q8>
 hipError_t launch_one(dim3 grid, hipStream_t st, const SketchArgs& a) {
-    hipLaunchKernelGGL((sketch_kernel<S, R, W, TI, Q8, kSpread>), grid, dim3(kThreads), 0, st,
-                       static_cast<const TI*>(a.X), a.lines, a.n, a.ldx, a.vec, a.bp, a.qn, a.nwin,
-                       a.nst, *a.bl, a.RC, a.hdr, a.ell, a.out, a.ldo, a.npass, a.wd, a.obp,
-                       a.omode, a.ozlo);
+    hipLaunchKernelGGL((sketch_kernel<S, R, W, TI, Q8>), grid, dim3(kThreads), 0, st,
+                       static_cast<const TI*>(a.X), a.lines, a.n, a.ldx, a.bp, a.qn, a.nwin, a.nst,
+                       *a.bl, a.RC, a.hdr, a.ell, a.out, a.ldo, a.npass, a.wd, a.obp, a.omode,
+                       a.ozlo);
     return hipGetLastError();
 }
 
-// spread: every window is loaded with 16-byte loads -- row lines with vec
-// and n a multiple of 4, column lines with vec and every group of 4 lines
-// whole -- so the next window's loads can be spread over the slots
-// (kSpread).
 template <bool R, bool W, typename TI, bool Q8 = false>
 hipError_t launch_slots(int slots, dim3 grid, hipStream_t st, const SketchArgs& a) {
-    const bool spread = a.vec && (R ? (a.n & 3) == 0 : (a.lines & 3) == 0);
-#define OSK_SLOT_CASE(S)                                                             \
-    if (slots <= S)                                                                  \
-        return spread ? launch_one<S, R, W, TI, Q8, true>(grid, st, a)               \
-                      : launch_one<S, R, W, TI, Q8, false>(grid, st, a);
+#define OSK_SLOT_CASE(S) \
+    if (slots <= S) return launch_one<S, R, W, TI, Q8>(grid, st, a);
     OSK_SLOT_CASE(1)
     OSK_SLOT_CASE(2)
+    OSK_SLOT_CASE(3)
     OSK_SLOT_CASE(4)
+    OSK_SLOT_CASE(6)
     OSK_SLOT_CASE(8)
-    OSK_SLOT_CASE(12)
-    OSK_SLOT_CASE(16)
-    OSK_SLOT_CASE(20)
-    if constexpr (!Q8) {        // (FP8 output: at most 20 slots, see sketch_fp8_fusable)
-        OSK_SLOT_CASE(24)
+    OSK_SLOT_CASE(10)
+    if constexpr (!Q8) {        // (FP8 output: see sketch_fp8_fusable)
+        OSK_SLOT_CASE(12)
     }
 #undef OSK_SLOT_CASE
     return hipErrorInvalidValue;

@@ -5,14 +5,14 @@
 
 namespace osk {
 
-// Slot counts compiled: 1, 2, 4, 8, 12, 16, 20, 24 (4 registers per slot).
-constexpr int kMaxSlots = 24;
+// Slot counts compiled: 1, 2, 3, 4, 6, 8, 10, 12 (4 registers per slot).
+constexpr int kMaxSlots = 12;
+constexpr int kMaxFp8Slots = 10;       // with the FP8 epilogue
 
 // Arguments of a sketch launch (see launch_sketch).
 struct SketchArgs {
     const void* X;
     int64_t lines, n, ldx;
-    int vec;
     int32_t bp, qn, nwin, nst;
     const BlockList* bl;
     int64_t RC;

@@ -718,3 +718,40 @@ def test_product_with_own_transpose(m, n, b, N, e, precision):
         cmask = (np.random.default_rng(n).random((t, t, N + e)) < 0.7).astype(np.uint8)
         assert torch.equal(osk.matmul_cmask(A, A.t(), b, N, e, cmask, seed=4),
                            osk.matmul_cmask(A, copy.t(), b, N, e, cmask, seed=4))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8191, 8193, 8194, 8195, 16390])
+@pytest.mark.parametrize("lines", [1, 3, 4, 6, 9])
+def test_sketch_window_ends_and_alignment(n, lines):
+    """Windows that end inside a quad of positions (or hold fewer than 4), line
+    groups that are not whole, and operands at any element alignment: rows
+    (FP32 and BF16, and weighted through a batch) and columns in place give the
+    ascending-k FP32 sums, bit for bit."""
+    b, N = 70, 2
+    h, s = oracle.hash_tables(9, N, n, b)
+    X = synthetic.gaussian_pair(lines, n, 1, n + lines)[0]
+    ref = _fp32_ascending_sums(X, h, s, b)            # [block, bucket, line]
+    want = np.concatenate([ref[i].T for i in range(N)], axis=1)
+    buf = torch.zeros(lines * (n + 3) + n * (lines + 3) + 8, device="cuda")
+    rows = buf[1:1 + lines * (n + 3)].view(lines, n + 3)[:, :n]
+    rows.copy_(torch.from_numpy(X))
+    got = unpad(host(osk.sketch_cols(rows, b, N, 0, seed=9)), N, b)
+    np.testing.assert_array_equal(got, want)
+    cols = buf[lines * (n + 3) + 2:][:n * (lines + 3)].view(n, lines + 3)[:, :lines]
+    cols.copy_(torch.from_numpy(X).t())
+    for ws in (None, True):
+        got = unpad(host(osk.sketch_rows(cols, b, N, 0, seed=9, workspace=ws)), N, b)
+        np.testing.assert_array_equal(got, want)
+    # BF16 rows at an odd address: the FP32 path on the converted values
+    Xb = torch.from_numpy(X).bfloat16()
+    hb = torch.zeros(lines * (n + 3) + 1, dtype=torch.bfloat16, device="cuda")[1:]
+    hb = hb.view(lines, n + 3)[:, :n]
+    hb.copy_(Xb)
+    D = torch.eye(4, device="cuda")[:, :1].expand(4, n).t().contiguous()
+    f = lambda A: osk.matmul_ex(A, D, b, N, 0, seed=9)  # noqa: E731
+    assert torch.equal(f(hb), f(Xb.float().cuda()))
+    # weights 4 = sqrt 2 exactly: twice the sketch, so four times the Gram matrix
+    d = torch.full((n + 1,), 4.0, device="cuda")[1:]
+    H1 = osk.GramBatch([rows], None, b=b, N=N, e=0, seeds=[9]).run()[0]
+    H4 = osk.GramBatch([rows], [d], b=b, N=N, e=0, seeds=[9]).run()[0]
+    assert torch.equal(H4, 4 * H1)
