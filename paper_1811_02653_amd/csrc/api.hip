@@ -518,12 +518,27 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
                                           bs.stored, bs.nst, nblocks(sk), bp, lists, out, zs, s));
     };
     if ((st = prepare(sk, n, prep, s)) != OS_OK) return st;
-    if ((st = sketch_lines(A, a_dtype, a_col_major != 0, m, lda, At, aq_p)) != OS_OK) return st;
-    if (same_lines(A, a_dtype, a_col_major != 0, m, lda, B, b_dtype, b_col_major == 0, l, ldb)) {
+    const bool same =
+        same_lines(A, a_dtype, a_col_major != 0, m, lda, B, b_dtype, b_col_major == 0, l, ldb);
+    const bool f32 = a_dtype == OS_DTYPE_F32 && b_dtype == OS_DTYPE_F32;
+    hipError_t e = hipSuccess;
+    if (!same && f32 && !fp8_fused &&
+        osk::launch_sketch_pair(static_cast<const float*>(A), a_col_major == 0, m, lda,
+                                bf16_product ? static_cast<void*>(aq_p) : At,
+                                static_cast<const float*>(B), b_col_major != 0, l, ldb,
+                                bf16_product ? static_cast<void*>(bq_p) : Bt, n, bs.stored, bs.nst,
+                                nblocks(sk), bp, lists, bf16_product ? wq : zs,
+                                bf16_product ? (is_split(precision) ? 2 : 1) : 0, s, &e)) {
+        if (e != hipSuccess) return hip_status(e);
+    } else {
+        if ((st = sketch_lines(A, a_dtype, a_col_major != 0, m, lda, At, aq_p)) != OS_OK) return st;
+        if (!same &&
+            (st = sketch_lines(B, b_dtype, b_col_major == 0, l, ldb, Bt, bq_p)) != OS_OK)
+            return st;
+    }
+    if (same) {
         Bt = At;
         bq_p = aq_p;
-    } else if ((st = sketch_lines(B, b_dtype, b_col_major == 0, l, ldb, Bt, bq_p)) != OS_OK) {
-        return st;
     }
     if (precision == OS_PREC_FP32)
         return hip_status(osk::launch_gemm_kept(

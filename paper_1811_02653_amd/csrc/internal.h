@@ -130,6 +130,16 @@ hipError_t launch_sketch_rows(const float* X, int64_t n, int64_t cols, int64_t l
 // against 0.39 + 0.49 ms; 20011 x 2777 at ld 2777, 5 blocks of 900: 133
 // against 115 + 92 us; the sums are the same, bit for bit).
 bool sketch_rows_in_place_ok(int64_t cols);
+// The sketches of both FP32 operands of a product (each given by its lines:
+// rows, or columns of a row-major matrix; ld ldo both) in one launch, when
+// their tasks fit on the device at once; out_mode 0: FP32, 1 / 2: the BF16
+// copy without / with residuals.  False when the pair is to be launched one
+// by one; else *err is the launch's error.
+bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, void* outA,
+                        const float* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,
+                        const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
+                        const void* lists, int64_t ldo, int out_mode, hipStream_t s,
+                        hipError_t* err);
 // launch_sketch_rows writing the BF16 copy, as launch_sketch_cols_q.
 hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t ldx,
                                 const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,

@@ -694,11 +694,24 @@ __global__ __launch_bounds__(64) void sketch_cell_kernel(
     }
 }
 
-// Passes and slots per pass for nst stored blocks.
-void pass_plan(int32_t nst, int32_t qn, int32_t* npass, int32_t* slots) {
+// Compute units of the current device (0 if unknown).
+int device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return cus;
+}
+
+// Passes and slots per pass for nst stored blocks: as few passes as the slots
+// allow, and more (each a workgroup's own task) while the line groups leave
+// CUs idle and the passes' waves hold more than one slot.
+void pass_plan(int32_t nst, int32_t qn, int32_t* npass, int32_t* slots, int64_t groups = 0,
+               int cus = 0) {
     const int64_t gs = (int64_t)nst * qn;
     const int64_t per = (int64_t)kWaves * kMaxSlots;
-    const int64_t P = (gs + per - 1) / per;
+    int64_t P = (gs + per - 1) / per;
+    while (groups > 0 && groups * (P + 1) <= cus && gs > P * kWaves) ++P;
     const int64_t need = (gs + P - 1) / P;               // groups per pass
     *npass = (int32_t)P;
     *slots = (int32_t)((need + kWaves - 1) / kWaves);
@@ -715,16 +728,13 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
                          const float* wd = nullptr, int out_mode = 0) {
     const Plan p = plan_of(n, bp);
     const ListView v = carve_lists(const_cast<void*>(lists), nblk, n, bp);
-    int32_t npass, slots;
-    pass_plan(nst, p.qn, &npass, &slots);
     const int64_t groups = (lines + kLines - 1) / kLines;
+    const int cus = device_cus();
+    int32_t npass, slots;
+    pass_plan(nst, p.qn, &npass, &slots, groups, cus);
     // persistent workgroups: one per CU (a window fills a CU's LDS)
-    int dev = 0, cus = 0;
     int64_t nwg = groups * npass;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        cus > 0)
-        nwg = std::min<int64_t>(nwg, cus);
+    if (cus > 0) nwg = std::min<int64_t>(nwg, cus);
     const dim3 grid((unsigned)nwg);
     if (out_mode < 0 || out_mode > 3) return hipErrorInvalidValue;
     const int32_t obp = out_mode ? p.qn * 64 : bp;
@@ -887,6 +897,31 @@ hipError_t launch_sketch_rows(const float* X, int64_t n, int64_t cols, int64_t l
 }
 
 bool sketch_rows_in_place_ok(int64_t cols) { return cols >= 4; }
+
+bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, void* outA,
+                        const float* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,
+                        const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
+                        const void* lists, int64_t ldo, int out_mode, hipStream_t s,
+                        hipError_t* err) {
+    const Plan p = plan_of(n, bp);
+    const int64_t ga = (m + kLines - 1) / kLines, gb = (l + kLines - 1) / kLines;
+    const int cus = device_cus();
+    int32_t npass, slots;
+    pass_plan(nst, p.qn, &npass, &slots, ga + gb, cus);
+    if ((ga + gb) * npass > cus || slots > kMaxPairSlots || out_mode < 0 || out_mode > 2 ||
+        (a_rows ? n : m) < 4 || (b_rows ? n : l) < 4 || !plan_sketch_ok(m, nst, bp, n) ||
+        !plan_sketch_ok(l, nst, bp, n))
+        return false;
+    const ListView v = carve_lists(const_cast<void*>(lists), nblk, n, bp);
+    const int32_t obp = out_mode ? p.qn * 64 : bp;
+    const SketchArgs a{nullptr, 0,       n,   0,   bp,    p.qn,    p.nwin, nst,      &bl,
+                       p.RC,    v.hdr,   v.ell, nullptr, ldo, npass, nullptr, obp, out_mode,
+                       out_mode >= 2 ? (int64_t)nst * obp : 0};
+    const SketchSide x{A, m, lda, outA, (int32_t)(ga * npass), a_rows ? 1 : 0};
+    const SketchSide y{B, l, ldb, outB, (int32_t)(gb * npass), b_rows ? 1 : 0};
+    *err = sketch_pair(slots, s, a, x, y);
+    return true;
+}
 
 hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t ldx,
                                 const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,

@@ -218,15 +218,15 @@ __device__ __forceinline__ void add_chunk(float4& acc, const float4* __restrict_
 // to 128 VGPRs.  (8 waves of 256 VGPRs with whole chunks in flight: the FP32
 // sketch of 8192 x 32768 into 10 blocks of 1024 took 506 us from rows and 785
 // from columns, this 486 and 736.)
+// sketch_tasks: the tasks of workgroup wg of nwg (win: its kWin + 1 rows of LDS).
 template <int kSlots, bool kRowLines, bool kWeighted, typename TI, bool kFp8Out>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void sketch_kernel(
-    const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int32_t bp,
-    int32_t qn, int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
-    const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell, void* __restrict__ out,
-    int64_t ldo, int32_t npass, const float* __restrict__ wd, int32_t obp, int32_t omode,
-    int64_t ozlo) {
-    __shared__ float4 win[kWin + 1];    // row kWin stays zero
+__device__ __forceinline__ void sketch_tasks(
+    float4* __restrict__ win, int64_t wg, int64_t nwg, const TI* __restrict__ X, int64_t lines,
+    int64_t n, int64_t ldx, int32_t bp, int32_t qn, int32_t nwin, int32_t nst, const BlockList& bl,
+    int64_t RC, const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell,
+    void* __restrict__ out, int64_t ldo, int32_t npass, const float* __restrict__ wd, int32_t obp,
+    int32_t omode, int64_t ozlo) {
+    // (row kWin of win stays zero)
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const uint32_t lane16 = 16 * (uint32_t)lane;
@@ -277,13 +277,13 @@ void sketch_kernel(
     typename RawQuad<TI>::type pre[kPerThread];
     float4 wpre[2];
     uint32_t hnext = 0;
-    if ((int64_t)blockIdx.x < tasks) {
-        hnext = headers(meta_of(blockIdx.x).hb, 0);
+    if (wg < tasks) {
+        hnext = headers(meta_of(wg).hb, 0);
         const int kw = (int)min((int64_t)kWin, n);
-        load_window<kRowLines, TI>(pre, X, lines, ldx, line_of(blockIdx.x), 0, kw, 0, kPerThread);
+        load_window<kRowLines, TI>(pre, X, lines, ldx, line_of(wg), 0, kw, 0, kPerThread);
         if constexpr (kWeighted) load_weights(wpre, wd, 0, kw);
     }
-    for (int64_t it = blockIdx.x; it < tasks; it += gridDim.x) {
+    for (int64_t it = wg; it < tasks; it += nwg) {
     const int64_t line0 = line_of(it);
     const Meta meta = meta_of(it);      // (its loads complete with the window's, before staging)
 
@@ -328,9 +328,9 @@ void sketch_kernel(
         int kw1;
         if (w + 1 < nwin) {
             kw1 = (int)min((int64_t)kWin, n - k1);
-        } else if (it + gridDim.x < tasks) {
-            hb1 = meta_of(it + gridDim.x).hb;
-            l1 = line_of(it + gridDim.x);
+        } else if (it + nwg < tasks) {
+            hb1 = meta_of(it + nwg).hb;
+            l1 = line_of(it + nwg);
             k1 = 0;
             kw1 = (int)min((int64_t)kWin, n);
         } else {
@@ -458,6 +458,19 @@ void sketch_kernel(
         }
     }
     }   // tasks
+}
+
+template <int kSlots, bool kRowLines, bool kWeighted, typename TI, bool kFp8Out>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void sketch_kernel(const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int32_t bp,
+                   int32_t qn, int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
+                   const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell,
+                   void* __restrict__ out, int64_t ldo, int32_t npass,
+                   const float* __restrict__ wd, int32_t obp, int32_t omode, int64_t ozlo) {
+    __shared__ float4 win[kWin + 1];
+    sketch_tasks<kSlots, kRowLines, kWeighted, TI, kFp8Out>(
+        win, blockIdx.x, gridDim.x, X, lines, n, ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, out, ldo,
+        npass, wd, obp, omode, ozlo);
 }
 
 template <int S, bool R, bool W, typename TI, bool Q8>

@@ -667,6 +667,35 @@ def test_whole_path_tile_forms(m, n, l, b, N, precision):
     assert rel(C, Cs) <= 1e-6
 
 
+@pytest.mark.parametrize("m,n,l,b,N", [(4, 4, 5, 3, 1), (3, 700, 9, 64, 2), (257, 9001, 130, 300, 4),
+                                       (509, 2050, 515, 1000, 3), (513, 2050, 515, 1000, 3),
+                                       (100, 3000, 60, 700, 7)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "bf16x3"])
+def test_both_sketches_in_one_launch(m, n, l, b, N, precision):
+    """Products whose sketches run in one launch, in every layout, with one to
+    three slots per wave and more passes than the slots need, and the first
+    sizes past that (lines < 4, more than 1024 lines): the same result in every
+    layout, and the product of the separate sketches."""
+    A, B = synthetic.gaussian_pair(m, n, l, m + l)
+    Ad, Bd = dev(A), dev(B)
+    kw = dict(seed=5, precision=precision)
+    C = osk.matmul(Ad, Bd, b, N, 0, **kw)
+    At, Bt = osk.sketch_cols(Ad, b, N, 0, seed=5), osk.sketch_rows(Bd, b, N, 0, seed=5)
+    if precision != "fp32":
+        At, Bt = (osk.sketch_quantize(S, b, N, precision) for S in (At, Bt))
+    At, Bt = (S.double().cpu().numpy() for S in (At, Bt))
+    w = At.shape[1] // (2 if precision == "bf16x3" else 1)        # then the residuals
+    want = At[:, :w] @ Bt[:, :w].T
+    if precision == "bf16x3":
+        want += At[:, :w] @ Bt[:, w:].T + At[:, w:] @ Bt[:, :w].T
+    assert rel(host(C), want / N) <= 1e-6
+    for a_cm in (False, True):
+        for b_cm in (False, True):
+            got = osk.matmul_ex(_in_layout(A, a_cm, torch.float32),
+                                _in_layout(B, b_cm, torch.float32), b, N, 0, **kw)
+            assert torch.equal(got, C), (a_cm, b_cm)
+
+
 @pytest.mark.parametrize("n", [1, 63, 1025, 2049, 8192, 8255, 20011])
 @pytest.mark.parametrize("b,N", [(1, 1), (33, 2), (1024, 3), (1500, 2)])
 @pytest.mark.parametrize("tables", ["hash", "one bucket", "ends"])
