@@ -682,13 +682,16 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 // laid out so that a fragment lane's kI A rows (or kJ B rows) are consecutive
 // words.  (No branch around these loads: a wave-uniform one made the kernel
 // spill 200-400 bytes per lane and run at less than half the speed.)
-// Scale chunks (kChunk, when the block stride is a multiple of 1024 codes
-// and rows and the scale area are 16-byte aligned): the scale loads above
-// read 64 rows per instruction, one 4-byte piece each, and cost about as
-// much as a whole step's tile loads; instead each wave loads 16 bytes of
-// its 64 rows (the scales of 8 steps, or of one part of 16 split steps) at
-// once, into one of two chunk buffers, and each step reads its scale bytes
-// from there (a chunk is loaded during the first step of the one before it).
+// Scale chunks: the scale loads above read 64 rows per instruction, one
+// 4-byte piece each, and cost about as much as a whole step's tile loads;
+// instead each wave loads kChunk bytes of its 64 rows at once (16: the
+// scales of 8 steps, or of one part of 16 split steps, when the block stride
+// is a multiple of 1024 codes and rows and the scale area are 16-byte
+// aligned; 4: of 2 or 4 steps, when it is a multiple of 256), into one of two
+// chunk buffers, and each step reads its scale bytes from there (a chunk is
+// loaded during the first step of the one before it).
+// (Split, 2048 x 2048, K = 2048, blocks of 512: 57 us loading every step, 48
+// with 4-byte chunks; blocks of 1024 with 16-byte chunks: 46.)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int fp8_frag_off(int rbase, int s, int p, int lane) {
     return rbase * 32 + 4 * ((4 * s + 2 * (lane >> 5) + p) ^ chunk_key(rbase));
@@ -710,7 +713,7 @@ __device__ __forceinline__ void words(uint32_t (&d)[kN], const uint32_t* p) {
     }
 }
 
-template <typename S, bool kPair, bool kOdd, bool kSplit = false, bool kChunk = false>
+template <typename S, bool kPair, bool kOdd, bool kSplit = false, int kChunk = 0>
 __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
                            const uint8_t* __restrict__ Bt, int64_t ldbt, int64_t scales,
@@ -728,7 +731,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     // scale words, two buffers: per row (A's, then B's) a word per loaded
     // part (kWords of them), or 16 bytes per row and loaded part
     constexpr int kWords = kPair ? 2 : 1;
-    constexpr int kScaleBuf = kWords * 2 * BT * (kChunk ? 4 : 1);
+    constexpr int kScaleBuf = kWords * 2 * BT * (kChunk == 16 ? 4 : 1);
     __shared__ __align__(16) uint32_t Sc[2 * kScaleBuf];
 
     const int tid = threadIdx.x;
@@ -775,7 +778,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     constexpr int kStep = kPair ? 64 : 128;           // code columns per step
-    constexpr int kPerChunk = kPair ? 16 : 8;         // steps per scale chunk
+    constexpr int kPerChunk = kPair ? kChunk : kChunk / 2;   // steps per scale chunk
     const int tpb = bp / kStep;
     int t_begin = 0;
     int t_end = nkept * tpb;                          // this workgroup's K steps
@@ -811,7 +814,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     const bool a_side = wave < kSw;
     const int p = 64 * (wave % kSw) + lane;
     constexpr int kIw = 32 * kI, kJw = 32 * kJ;
-    const int srow = kChunk ? p
+    const int srow = kChunk == 16 ? p
                      : a_side ? p / kIw * kIw + 32 * (p % kI) + ((p / kI) & 31)
                               : p / kJw * kJw + 32 * (p % kJ) + ((p / kJ) & 31);
     const uint32_t so = a_side ? (uint32_t)((int64_t)min(srow, alast) * ldat + scales)
@@ -822,7 +825,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     // the scale words of a step (or the chunk it starts) into buffer `buf`
     auto issue_scales = [&](int buf, uint32_t k) {
 #if defined(__HIP_DEVICE_COMPILE__)
-        if constexpr (kChunk) {
+        if constexpr (kChunk == 16) {
             uint32_t* d = Sc + buf * kScaleBuf + 4 * sbase;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_src, (lds_void*)d, 16, so, k / kFp8Block,
                                                      0, 0);
@@ -876,7 +879,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     // part 1 in byte 1
     uint32_t sa[kI], sb[kJ];
     auto read_scales = [&](int step, int buf, uint32_t k) {
-        if constexpr (kChunk) {
+        if constexpr (kChunk == 16) {
             const uint8_t* q = reinterpret_cast<const uint8_t*>(Sc + ((step / kPerChunk) & 1) * kScaleBuf);
             const int ra = wm * kIw + (lane & 31), rb = BT + wn * kJw + (lane & 31);
             auto at = [&](int row) -> uint32_t {
@@ -892,7 +895,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
 #pragma unroll
             for (int j = 0; j < kJ; ++j) sb[j] = at(rb + 32 * j);
         } else {
-            const uint32_t* q = Sc + buf * kScaleBuf;
+            const uint32_t* q = Sc + (kChunk ? (step / kPerChunk) & 1 : buf) * kScaleBuf;
             const int wa = kI * (wm * 32 + (lane & 31)), wb = BT + kJ * (wn * 32 + (lane & 31));
             const uint32_t h0 = (k / kFp8Block & 3u) * 8u;
             words<kI>(sa, q + wa);
@@ -949,7 +952,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     auto kstep = [&](const float* as, const float* bs, float* na, float* nb, int nbuf, int t) {
         const uint32_t k = step_k(min(t + 1, t_end - 1));
         direct_issue<kU>(ra_src, na, va, k, wave);
-        if constexpr (kChunk) {
+        if constexpr (kChunk != 0) {
             if (t % kPerChunk == 0 && t + kPerChunk < t_end)
                 issue_scales((t / kPerChunk + 1) & 1, step_k(t + kPerChunk));
         } else {
@@ -1662,11 +1665,13 @@ hipError_t launch_fp8_tile(const Operands& o, int64_t scales, const Form& f, int
                            float* part, hipStream_t s) {
     const int64_t tilesM = (o.m + S::BT - 1) / S::BT;
     const int64_t tilesN = (o.l + S::BT - 1) / S::BT;
-    // scale chunks: whole chunks per block, 16-byte aligned rows and scale
-    // area (with them the step count is a multiple of 8, never odd)
-    const bool chunk = o.bp % 1024 == 0 && o.ldat % 16 == 0 && o.ldbt % 16 == 0 && scales % 16 == 0;
+    // scale chunks: whole chunks per block; 16-byte ones also need 16-byte
+    // aligned rows and scale area (with either the step count is even)
+    const bool c16 = o.bp % 1024 == 0 && o.ldat % 16 == 0 && o.ldbt % 16 == 0 && scales % 16 == 0;
+    const bool c4 = o.bp % 256 == 0 && o.lo_off % 256 == 0;
     auto kern = f.S > 1     ? gemm_kept_fp8d_kernel<S, kPair, true, true>
-                : chunk     ? gemm_kept_fp8d_kernel<S, kPair, false, false, true>
+                : c16       ? gemm_kept_fp8d_kernel<S, kPair, false, false, 16>
+                : c4        ? gemm_kept_fp8d_kernel<S, kPair, false, false, 4>
                 : total % 2 ? gemm_kept_fp8d_kernel<S, kPair, true>
                             : gemm_kept_fp8d_kernel<S, kPair, false>;
     hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * tilesM * tilesN)), dim3(S::kThreads), 0, s,

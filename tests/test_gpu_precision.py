@@ -460,3 +460,12 @@ def test_fp8_block_product_tile_forms(m, l, b, nst, precision):
     assert np.all(np.abs(C - ref) <= mag * (2.0 ** -14 + z * 2.0 ** -24))
     k = (m + 1) // 2
     np.testing.assert_array_equal(host(osk.gemm_kept_prec(Qa[:k], Qb, b, nst, precision)), C[:k])
+
+
+@pytest.mark.parametrize("m,l", [(65, 130), (257, 200), (2100, 1800)])
+@pytest.mark.parametrize("b,nst", [(256, 1), (500, 3), (768, 2)])
+@pytest.mark.parametrize("precision", ["fp8", "fp8x3"])
+def test_fp8_block_product_scale_words(m, l, b, nst, precision):
+    """Block strides that are multiples of 256 but not of 1024 (scales loaded
+    a word of 2 or 4 steps at a time): the bounds of the other forms."""
+    test_fp8_block_product_tile_forms(m, l, b, nst, precision)
