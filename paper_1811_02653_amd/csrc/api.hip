@@ -467,14 +467,10 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     // (rounded in the sketch's epilogue, bit for bit what the quantization
     // of the FP32 sketch gives); with an FP8 one its FP8 copy when every
     // code belongs to a sketch group (b rounded up to 64 is a multiple of
-    // 128) and the sketch takes at most 10 slots (FP8 without the split
-    // form); otherwise the FP32 sketch, quantized after.
+    // 128) and the sketch takes at most 10 slots; otherwise the FP32 sketch, quantized after.
     const bool bf16_product = precision != OS_PREC_FP32 && !is_fp8(precision);
-    // (the split FP8 form stays staged: its second group maximum made the
-    // fused sketch slower than the separate quantization)
     const bool fp8_fused =
-        is_fp8(precision) && !is_split(precision) && n >= 4 &&
-        osk::sketch_fp8_fusable(sk->b, bs.nst);
+        is_fp8(precision) && n >= 4 && osk::sketch_fp8_fusable(sk->b, bs.nst);
     auto sketch_lines = [&](const void* X, int dtype, bool transpose, int64_t lines,
                             int64_t ldx, float* out, void* qout) -> os_status {
         const void* Xl = X;
@@ -488,7 +484,8 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
                                                             is_split(precision), s));
             if (fp8_fused)
                 return hip_status(osk::launch_sketch_rows_fp8(Xf, n, lines, ldx, bs.stored, bs.nst,
-                                                              nblocks(sk), bp, lists, qout, wq, s));
+                                                              nblocks(sk), bp, lists, qout, wq,
+                                                              is_split(precision), s));
             return hip_status(osk::launch_sketch_rows(Xf, n, lines, ldx, bs.stored, bs.nst,
                                                       nblocks(sk), bp, lists, out, zs, s));
         }
@@ -509,7 +506,8 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
         if (fp8_fused)
             return hip_status(osk::launch_sketch_cols_fp8(Xl, dtype == OS_DTYPE_BF16, lines, n,
                                                           ldl, bs.stored, bs.nst, nblocks(sk), bp,
-                                                          lists, qout, wq, s));
+                                                          lists, qout, wq,
+                                                          is_split(precision), s));
         return hip_status(
             dtype == OS_DTYPE_BF16
                 ? osk::launch_sketch_cols_bf16(Xl, lines, n, ldl, bs.stored, bs.nst, nblocks(sk),
@@ -522,13 +520,14 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
         same_lines(A, a_dtype, a_col_major != 0, m, lda, B, b_dtype, b_col_major == 0, l, ldb);
     const bool f32 = a_dtype == OS_DTYPE_F32 && b_dtype == OS_DTYPE_F32;
     hipError_t e = hipSuccess;
-    if (!same && f32 && !fp8_fused &&
+    const bool copy = bf16_product || fp8_fused;      // the sketch writes the product's operand
+    const int mode = copy ? (bf16_product ? 1 : 3) + (is_split(precision) ? 1 : 0) : 0;
+    if (!same && f32 &&
         osk::launch_sketch_pair(static_cast<const float*>(A), a_col_major == 0, m, lda,
-                                bf16_product ? static_cast<void*>(aq_p) : At,
+                                copy ? static_cast<void*>(aq_p) : At,
                                 static_cast<const float*>(B), b_col_major != 0, l, ldb,
-                                bf16_product ? static_cast<void*>(bq_p) : Bt, n, bs.stored, bs.nst,
-                                nblocks(sk), bp, lists, bf16_product ? wq : zs,
-                                bf16_product ? (is_split(precision) ? 2 : 1) : 0, s, &e)) {
+                                copy ? static_cast<void*>(bq_p) : Bt, n, bs.stored, bs.nst,
+                                nblocks(sk), bp, lists, copy ? wq : zs, mode, s, &e)) {
         if (e != hipSuccess) return hip_status(e);
     } else {
         if ((st = sketch_lines(A, a_dtype, a_col_major != 0, m, lda, At, aq_p)) != OS_OK) return st;

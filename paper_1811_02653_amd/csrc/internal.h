@@ -133,7 +133,7 @@ bool sketch_rows_in_place_ok(int64_t cols);
 // The sketches of both FP32 operands of a product (each given by its lines:
 // rows, or columns of a row-major matrix; ld ldo both) in one launch, when
 // their tasks fit on the device at once; out_mode 0: FP32, 1 / 2: the BF16
-// copy without / with residuals.  False when the pair is to be launched one
+// copy without / with residuals, 3 / 4: the FP8 one.  False when the pair is to be launched one
 // by one; else *err is the launch's error.
 bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, void* outA,
                         const float* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,
@@ -148,7 +148,8 @@ hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t
 // launch_sketch_rows writing the FP8 copy, as launch_sketch_cols_fp8.
 hipError_t launch_sketch_rows_fp8(const float* X, int64_t n, int64_t cols, int64_t ldx,
                                   const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
-                                  const void* lists, void* out, int64_t ldo, hipStream_t s);
+                                  const void* lists, void* out, int64_t ldo, int split,
+                                  hipStream_t s);
 // out (rows x nst*bp, ld ldo) = X S for X rows x n row-major (ld ldx);
 // with wd (DEVICE [n]) it is X diag(sqrt(wd)) S.
 hipError_t launch_sketch_cols(const float* X, int64_t rows, int64_t n, int64_t ldx,
@@ -183,8 +184,8 @@ hipError_t launch_sketch_cols_q(const void* X, bool x_bf16, int64_t rows, int64_
                                 const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                                 const void* lists, void* out, int64_t ldo, int split,
                                 hipStream_t s);
-// The same for the FP8 copy launch_quant_fp8 would make without the split
-// form (codes and E8M0 scales, ldo in bytes), bit for bit.  Only when
+// The same for the FP8 copy launch_quant_fp8 would make (codes and E8M0
+// scales, ldo in bytes), bit for bit.  Only when
 // sketch_fp8_fusable(b, nst):
 // the FP8 block stride (b rounded up to 128) equals the sketch's 64-bucket
 // groups (b rounded up to 64), so every code of the copy belongs to a group,
@@ -192,7 +193,7 @@ hipError_t launch_sketch_cols_q(const void* X, bool x_bf16, int64_t rows, int64_
 bool sketch_fp8_fusable(int32_t b, int32_t nst);
 hipError_t launch_sketch_cols_fp8(const void* X, bool x_bf16, int64_t rows, int64_t n,
                                   int64_t ldx, const BlockList& bl, int32_t nst, int32_t nblk,
-                                  int32_t bp, const void* lists, void* out, int64_t ldo,
+                                  int32_t bp, const void* lists, void* out, int64_t ldo, int split,
                                   hipStream_t s);
 
 // Shapes the block product supports for operands of elem bytes per value

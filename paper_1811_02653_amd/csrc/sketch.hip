@@ -717,11 +717,10 @@ void pass_plan(int32_t nst, int32_t qn, int32_t* npass, int32_t* slots, int64_t 
     *slots = (int32_t)((need + kWaves - 1) / kWaves);
 }
 
-// X: FP32, or BF16 when bf16 (rows only, unweighted).
 // X: FP32, or BF16 when bf16 (rows only, unweighted).  out_mode: 0 = FP32
 // sketch (blocks bp apart); 1 = its BF16 rounding, 2 = BF16 and residual
-// (nst blocks after), 3 = FP8 codes, then their scales (blocks
-// round_up(bp, 64) apart).
+// (nst blocks after), 3 = FP8 codes, then their scales, 4 = FP8 codes, the
+// residuals' codes, then the scales of both (blocks round_up(bp, 64) apart).
 hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines, int64_t n,
                          int64_t ldx, const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                          const void* lists, void* out, int64_t ldo, hipStream_t s,
@@ -736,14 +735,14 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
     int64_t nwg = groups * npass;
     if (cus > 0) nwg = std::min<int64_t>(nwg, cus);
     const dim3 grid((unsigned)nwg);
-    if (out_mode < 0 || out_mode > 3) return hipErrorInvalidValue;
+    if (out_mode < 0 || out_mode > 4) return hipErrorInvalidValue;
     const int32_t obp = out_mode ? p.qn * 64 : bp;
     const int64_t ozlo = out_mode >= 2 ? (int64_t)nst * obp : 0;
     const SketchArgs a{X,     lines, n,   ldx, bp,    p.qn, p.nwin, nst,      &bl, p.RC,
                        v.hdr, v.ell, out, ldo, npass, wd,   obp,    out_mode, ozlo};
-    if ((bf16 && !row_lines) || ((out_mode == 3 || bf16) && wd)) return hipErrorInvalidValue;
+    if ((bf16 && !row_lines) || ((out_mode >= 3 || bf16) && wd)) return hipErrorInvalidValue;
     if (row_lines ? n < 4 : lines < 4) {     // too short for loads of 4 values
-        if (out_mode == 3 || p.qn > 65535 || nst > 65535) return hipErrorInvalidValue;
+        if (out_mode >= 3 || p.qn > 65535 || nst > 65535) return hipErrorInvalidValue;
         const dim3 cells((unsigned)lines, (unsigned)p.qn, (unsigned)nst);
         if (bf16)
             hipLaunchKernelGGL(sketch_cell_kernel<__bf16>, cells, dim3(64), 0, s,
@@ -759,6 +758,10 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
         return bf16        ? sketch_rows_bf16_fp8(slots, grid, s, a)
                : row_lines ? sketch_rows_f32_fp8(slots, grid, s, a)
                            : sketch_cols_f32_fp8(slots, grid, s, a);
+    if (out_mode == 4)
+        return bf16        ? sketch_rows_bf16_fp8x3(slots, grid, s, a)
+               : row_lines ? sketch_rows_f32_fp8x3(slots, grid, s, a)
+                           : sketch_cols_f32_fp8x3(slots, grid, s, a);
     if (bf16) return sketch_rows_bf16(slots, grid, s, a);
     if (!row_lines) return sketch_cols_f32(slots, grid, s, a);
     return wd ? sketch_rows_weighted(slots, grid, s, a) : sketch_rows_f32(slots, grid, s, a);
@@ -908,7 +911,8 @@ bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, voi
     const int cus = device_cus();
     int32_t npass, slots;
     pass_plan(nst, p.qn, &npass, &slots, ga + gb, cus);
-    if ((ga + gb) * npass > cus || slots > kMaxPairSlots || out_mode < 0 || out_mode > 2 ||
+    if ((ga + gb) * npass > cus || slots > kMaxPairSlots || out_mode < 0 || out_mode > 4 ||
+        (out_mode >= 3 && !sketch_fp8_fusable(bp, nst)) ||
         (a_rows ? n : m) < 4 || (b_rows ? n : l) < 4 || !plan_sketch_ok(m, nst, bp, n) ||
         !plan_sketch_ok(l, nst, bp, n))
         return false;
@@ -934,11 +938,12 @@ hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t
 
 hipError_t launch_sketch_rows_fp8(const float* X, int64_t n, int64_t cols, int64_t ldx,
                                   const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
-                                  const void* lists, void* out, int64_t ldo, hipStream_t s) {
+                                  const void* lists, void* out, int64_t ldo, int split,
+                                  hipStream_t s) {
     if (!plan_sketch_ok(cols, nst, bp, n) || !sketch_fp8_fusable(bp, nst))
         return hipErrorInvalidValue;
     return launch_sketch(false, X, false, cols, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s,
-                         nullptr, 3);
+                         nullptr, split ? 4 : 3);
 }
 
 size_t transpose_bytes(int64_t rows, int64_t cols) {
@@ -1010,11 +1015,12 @@ bool sketch_fp8_fusable(int32_t b, int32_t nst) {
 hipError_t launch_sketch_cols_fp8(const void* X, bool x_bf16, int64_t rows, int64_t n,
                                   int64_t ldx, const BlockList& bl, int32_t nst, int32_t nblk,
                                   int32_t bp, const void* lists, void* out, int64_t ldo,
+                                  int split,
                                   hipStream_t s) {
     if (!plan_sketch_ok(rows, nst, bp, n) || !sketch_fp8_fusable(bp, nst))
         return hipErrorInvalidValue;
     return launch_sketch(true, X, x_bf16, rows, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s,
-                         nullptr, 3);
+                         nullptr, split ? 4 : 3);
 }
 
 }  // namespace osk

@@ -4,15 +4,15 @@
 namespace osk {
 
 hipError_t sketch_rows_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a) {
-    return launch_slots<true, false, float, true>(slots, grid, st, a);
+    return launch_slots<true, false, float, 1>(slots, grid, st, a);
 }
 
 hipError_t sketch_rows_bf16_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a) {
-    return launch_slots<true, false, __bf16, true>(slots, grid, st, a);
+    return launch_slots<true, false, __bf16, 1>(slots, grid, st, a);
 }
 
 hipError_t sketch_cols_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a) {
-    return launch_slots<false, false, float, true>(slots, grid, st, a);
+    return launch_slots<false, false, float, 1>(slots, grid, st, a);
 }
 
 }  // namespace osk

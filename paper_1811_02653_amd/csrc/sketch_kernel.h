@@ -219,7 +219,7 @@ __device__ __forceinline__ void add_chunk(float4& acc, const float4* __restrict_
 // sketch of 8192 x 32768 into 10 blocks of 1024 took 506 us from rows and 785
 // from columns, this 486 and 736.)
 // sketch_tasks: the tasks of workgroup wg of nwg (win: its kWin + 1 rows of LDS).
-template <int kSlots, bool kRowLines, bool kWeighted, typename TI, bool kFp8Out>
+template <int kSlots, bool kRowLines, bool kWeighted, typename TI, int kFp8Out>
 __device__ __forceinline__ void sketch_tasks(
     float4* __restrict__ win, int64_t wg, int64_t nwg, const TI* __restrict__ X, int64_t lines,
     int64_t n, int64_t ldx, int32_t bp, int32_t qn, int32_t nwin, int32_t nst, const BlockList& bl,
@@ -380,7 +380,8 @@ __device__ __forceinline__ void sketch_tasks(
     //   omode 3: FP8 E4M3 codes (bytes) with one E8M0 scale per 64 codes,
     //            i.e. per slot group and line (its max over the wave's 64
     //            lanes); the scale bytes follow the codes (ozlo bytes into
-    //            the row), in code order.
+    //            the row), in code order; omode 4: then the same for the
+    //            residuals (codes, ozlo bytes after the first ones, and scales).
     // FP8 (a separate instantiation: this code would make the FP32 and BF16
     // kernels with 20 or more slots spill).  Every lane of the wave holds a
     // bucket (lim is 64).  The maxima of a group's four lines are taken with
@@ -391,21 +392,19 @@ __device__ __forceinline__ void sketch_tasks(
     // until the end.  Bound: VALU issue (no other work overlaps it); with a
     // ds_bpermute butterfly, a software conversion and byte stores the sketch of
     // a 8192 x 32768 matrix into 10 blocks of 1024 took 690 us, now 555-570
-    // (510 with FP32 output).
-    if constexpr (kFp8Out) {
+    // (510 with FP32 output).  Split: 31.6 us for 2048 x 8192 into 5 blocks of
+    // 512, where the FP32 sketch and its quantization took 29.9 + 8.8.
+    if constexpr (kFp8Out != 0) {
         const int r4 = lane & 3;
         const uint32_t sel1 = (lane & 1) ? 0x03070105u : 0x06020400u;
         const uint32_t sel2 = (lane & 2) ? 0x03020706u : 0x05040100u;
         uint8_t* const rows = static_cast<uint8_t*>(out) + line0 * ldo;
         uint8_t* const mine = rows + r4 * ldo + 4 * (lane >> 2);
         const bool live = line0 + r4 < lines;
-        uint32_t scales = 0;
-#pragma unroll
-        for (int s = 0; s < kSlots; ++s) {
-            if (__builtin_amdgcn_readlane(meta.lim, s) == 0) continue;      // uniform
-            const float v[4] = {acc[s].x, acc[s].y, acc[s].z, acc[s].w};
+        constexpr bool kSplit = kFp8Out == 2;
+        // the four lines' codes of v (one byte each), scale exponents e
+        auto encode = [&](const float (&v)[4], int (&e)[4]) -> uint32_t {
             float y[4];
-            uint32_t sc = 0;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 uint32_t m = abs_bits(v[r]);
@@ -415,22 +414,48 @@ __device__ __forceinline__ void sketch_tasks(
                 m = dpp_max<0x118>(m);
                 m = dpp_max<0x142, 0xA>(m);     // row_bcast: 15, 31
                 m = dpp_max<0x143, 0xC>(m);
-                const int e = e8m0_exponent((uint32_t)__builtin_amdgcn_readlane((int)m, 63));
-                y[r] = ldexpf(v[r], -e);
-                sc |= (uint32_t)(e + 127) << (8 * r);
+                e[r] = e8m0_exponent((uint32_t)__builtin_amdgcn_readlane((int)m, 63));
+                y[r] = ldexpf(v[r], -e[r]);
             }
-            uint32_t d = e4m3_pack4(y[0], y[1], y[2], y[3]);
+            return e4m3_pack4(y[0], y[1], y[2], y[3]);
+        };
+        auto store = [&](uint32_t d, int64_t col) {
             d = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0xB1, 0xF, 0xF, true), d, sel1);
             d = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0x4E, 0xF, 0xF, true), d, sel2);
-            if (live)
-                *reinterpret_cast<uint32_t*>(mine + __builtin_amdgcn_readlane(meta.col, s)) = d;
-            scales = lane == s ? sc : scales;
+            if (live) *reinterpret_cast<uint32_t*>(mine + col) = d;
+        };
+        auto scale_bytes = [](const int (&e)[4]) -> uint32_t {
+            return (uint32_t)(e[0] + 127) | (uint32_t)(e[1] + 127) << 8 |
+                   (uint32_t)(e[2] + 127) << 16 | (uint32_t)(e[3] + 127) << 24;
+        };
+        uint32_t scales = 0, scales_lo = 0;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            if (__builtin_amdgcn_readlane(meta.lim, s) == 0) continue;      // uniform
+            float v[4] = {acc[s].x, acc[s].y, acc[s].z, acc[s].w};
+            const int64_t col = __builtin_amdgcn_readlane(meta.col, s);
+            int e[4];
+            const uint32_t d = encode(v, e);
+            store(d, col);
+            scales = lane == s ? scale_bytes(e) : scales;
+            if constexpr (kSplit) {
+                // the residuals, exact in FP32
+                v[0] -= ldexpf(__builtin_amdgcn_cvt_f32_fp8((int)d, 0), e[0]);
+                v[1] -= ldexpf(__builtin_amdgcn_cvt_f32_fp8((int)d, 1), e[1]);
+                v[2] -= ldexpf(__builtin_amdgcn_cvt_f32_fp8((int)d, 2), e[2]);
+                v[3] -= ldexpf(__builtin_amdgcn_cvt_f32_fp8((int)d, 3), e[3]);
+                store(encode(v, e), ozlo + col);
+                scales_lo = lane == s ? scale_bytes(e) : scales_lo;
+            }
         }
         if (lane < kSlots && meta.lim > 0) {
+            uint8_t* const sc = rows + ozlo * (kSplit ? 2 : 1) + meta.col / 64;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (line0 + r < lines)
-                    rows[r * ldo + ozlo + meta.col / 64] = (uint8_t)(scales >> (8 * r));
+                if (line0 + r < lines) {
+                    sc[r * ldo] = (uint8_t)(scales >> (8 * r));
+                    if constexpr (kSplit) sc[r * ldo + ozlo / 64] = (uint8_t)(scales_lo >> (8 * r));
+                }
         }
     } else
 #pragma unroll
@@ -460,7 +485,7 @@ __device__ __forceinline__ void sketch_tasks(
     }   // tasks
 }
 
-template <int kSlots, bool kRowLines, bool kWeighted, typename TI, bool kFp8Out>
+template <int kSlots, bool kRowLines, bool kWeighted, typename TI, int kFp8Out>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sketch_kernel(const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int32_t bp,
                    int32_t qn, int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
@@ -473,7 +498,7 @@ void sketch_kernel(const TI* __restrict__ X, int64_t lines, int64_t n, int64_t l
         npass, wd, obp, omode, ozlo);
 }
 
-template <int S, bool R, bool W, typename TI, bool Q8>
+template <int S, bool R, bool W, typename TI, int Q8>
 hipError_t launch_one(dim3 grid, hipStream_t st, const SketchArgs& a) {
     hipLaunchKernelGGL((sketch_kernel<S, R, W, TI, Q8>), grid, dim3(kThreads), 0, st,
                        static_cast<const TI*>(a.X), a.lines, a.n, a.ldx, a.bp, a.qn, a.nwin, a.nst,
@@ -482,7 +507,7 @@ hipError_t launch_one(dim3 grid, hipStream_t st, const SketchArgs& a) {
     return hipGetLastError();
 }
 
-template <bool R, bool W, typename TI, bool Q8 = false>
+template <bool R, bool W, typename TI, int Q8 = 0>
 hipError_t launch_slots(int slots, dim3 grid, hipStream_t st, const SketchArgs& a) {
 #define OSK_SLOT_CASE(S) \
     if (slots <= S) return launch_one<S, R, W, TI, Q8>(grid, st, a);
@@ -493,7 +518,7 @@ hipError_t launch_slots(int slots, dim3 grid, hipStream_t st, const SketchArgs& 
     OSK_SLOT_CASE(6)
     OSK_SLOT_CASE(8)
     OSK_SLOT_CASE(10)
-    if constexpr (!Q8) {        // (FP8 output: see sketch_fp8_fusable)
+    if constexpr (Q8 == 0) {        // (FP8 output: see sketch_fp8_fusable)
         OSK_SLOT_CASE(12)
     }
 #undef OSK_SLOT_CASE

@@ -37,13 +37,13 @@ struct SketchSide {
 // Slot counts of the pair kernel: 1 to kMaxPairSlots.
 constexpr int kMaxPairSlots = 3;
 // Both sides of a product in one launch, a workgroup per task (a's fields X,
-// lines, ldx, out, wd unused; FP32 operands, output modes 0 to 2).
+// lines, ldx, out, wd unused; FP32 operands).
 hipError_t sketch_pair(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                        const SketchSide& y);
 
 // Launches the sketch kernel with at least `slots` slots per wave: rows of an
 // FP32 X, rows weighted by sqrt(wd), rows of a BF16 X, columns of an FP32 X,
-// and rows (FP32 or BF16) and columns writing the FP8 copy.
+// and rows (FP32 or BF16) and columns writing the FP8 copy, plain or split.
 hipError_t sketch_rows_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_weighted(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
@@ -51,5 +51,8 @@ hipError_t sketch_cols_f32(int slots, dim3 grid, hipStream_t st, const SketchArg
 hipError_t sketch_rows_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_cols_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_rows_f32_fp8x3(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_rows_bf16_fp8x3(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_cols_f32_fp8x3(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 
 }  // namespace osk

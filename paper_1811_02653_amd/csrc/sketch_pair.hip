@@ -12,7 +12,7 @@
 namespace osk {
 namespace {
 
-template <int kSlots>
+template <int kSlots, int kFp8Out>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t bp, int32_t qn,
                         int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
@@ -23,13 +23,25 @@ void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t bp, int32
     const int64_t wg = second ? blockIdx.x - x.wgs : blockIdx.x;
     const SketchSide& s = second ? y : x;
     if (s.rows)
-        sketch_tasks<kSlots, true, false, float, false>(win, wg, s.wgs, s.X, s.lines, n, s.ldx, bp,
+        sketch_tasks<kSlots, true, false, float, kFp8Out>(win, wg, s.wgs, s.X, s.lines, n, s.ldx, bp,
                                                         qn, nwin, nst, bl, RC, hdr, ell, s.out,
                                                         ldo, npass, nullptr, obp, omode, ozlo);
     else
-        sketch_tasks<kSlots, false, false, float, false>(win, wg, s.wgs, s.X, s.lines, n, s.ldx, bp,
+        sketch_tasks<kSlots, false, false, float, kFp8Out>(win, wg, s.wgs, s.X, s.lines, n, s.ldx, bp,
                                                          qn, nwin, nst, bl, RC, hdr, ell, s.out,
                                                          ldo, npass, nullptr, obp, omode, ozlo);
+}
+
+template <int kFp8Out>
+hipError_t launch_pair(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
+                       const SketchSide& y) {
+    auto kern = slots == 1 ? sketch_pair_kernel<1, kFp8Out>
+                           : (slots == 2 ? sketch_pair_kernel<2, kFp8Out>
+                                         : sketch_pair_kernel<3, kFp8Out>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(x.wgs + y.wgs)), dim3(kThreads), 0, st, x, y, a.n, a.bp,
+                       a.qn, a.nwin, a.nst, *a.bl, a.RC, a.hdr, a.ell, a.ldo, a.npass, a.obp,
+                       a.omode, a.ozlo);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -37,12 +49,8 @@ void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t bp, int32
 hipError_t sketch_pair(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                        const SketchSide& y) {
     if (slots < 1 || slots > kMaxPairSlots) return hipErrorInvalidValue;
-    auto kern = slots == 1 ? sketch_pair_kernel<1>
-                           : (slots == 2 ? sketch_pair_kernel<2> : sketch_pair_kernel<3>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(x.wgs + y.wgs)), dim3(kThreads), 0, st, x, y, a.n, a.bp,
-                       a.qn, a.nwin, a.nst, *a.bl, a.RC, a.hdr, a.ell, a.ldo, a.npass, a.obp,
-                       a.omode, a.ozlo);
-    return hipGetLastError();
+    if (a.omode == 4) return launch_pair<2>(slots, st, a, x, y);
+    return a.omode == 3 ? launch_pair<1>(slots, st, a, x, y) : launch_pair<0>(slots, st, a, x, y);
 }
 
 }  // namespace osk

@@ -469,3 +469,32 @@ def test_fp8_block_product_scale_words(m, l, b, nst, precision):
     """Block strides that are multiples of 256 but not of 1024 (scales loaded
     a word of 2 or 4 steps at a time): the bounds of the other forms."""
     test_fp8_block_product_tile_forms(m, l, b, nst, precision)
+
+
+@pytest.mark.parametrize("m,n,l", [(520, 700, 517), (37, 9001, 6)])
+@pytest.mark.parametrize("b,N", [(128, 2), (500, 5), (1024, 6), (1024, 10), (1000, 11), (300, 2)])
+@pytest.mark.parametrize("precision", ["fp8", "fp8x3"])
+def test_fp8_copies_written_by_the_sketch(m, n, l, b, N, precision):
+    """The FP8 copies written by the sketch (1 to 10 slots per wave, several
+    passes) and, where it does not write them, by the quantization: the codes
+    and scales of the staged steps, so the same product up to the order of its
+    sums, with a row of huge, a row of tiny and a row of no values."""
+    A, B = synthetic.gaussian_pair(m, n, l, m + n)
+    A[0] *= 1e30
+    A[1] *= 1e-42
+    A[2] = 0
+    Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    C = osk.matmul_ex(Ad, Bd, b, N, 0, seed=3, precision=precision)
+    Qa = osk.sketch_quantize(osk.sketch_cols(Ad, b, N, 0, seed=3), b, N, precision)
+    Qb = osk.sketch_quantize(osk.sketch_rows(Bd, b, N, 0, seed=3), b, N, precision)
+    want = host(osk.gemm_kept_prec(Qa, Qb, b, N, precision))
+    # the whole path may split the K loop: both are within the scaled MFMA's
+    # inner-sum precision (2^-14 of the products' magnitude) and an FP32 ulp per
+    # accumulation of the product of the same codes
+    split = precision == "fp8x3"
+    va, vb = (decode_fp8(host_u8(Q), b, N, split)[0] for Q in (Qa, Qb))
+    z = N * osk.block_stride_prec(b, precision)
+    mag = np.abs(va[:, :z]) @ np.abs(vb[:, :z]).T / N
+    if split:
+        mag += (np.abs(va[:, :z]) @ np.abs(vb[:, z:]).T + np.abs(va[:, z:]) @ np.abs(vb[:, :z]).T) / N
+    assert np.all(np.abs(host(C) - want) <= 2 * mag * (2.0 ** -14 + z * 2.0 ** -24))
