@@ -460,8 +460,9 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     // An operand's lines (rows of A, columns of B) that are rows in memory are
     // sketched as they are; columns of an FP32 matrix (a row-major B, a
     // column-major A) are read in place, which is faster than transposing them
-    // first (sketch_rows_in_place_ok); columns of a BF16 one are transposed as
-    // BF16 (a 16-byte request along a column brings in a whole cache line).
+    // first (sketch_rows_in_place_ok); columns of a BF16 one are read
+    // in place 8 at a time (sketch_rows_bf16_in_place_ok), else transposed as
+    // BF16.
     // BF16 values are converted exactly to FP32 as the sketch stages them.
     // With a BF16 block product the sketch writes its BF16 copy directly
     // (rounded in the sketch's epilogue, bit for bit what the quantization
@@ -489,6 +490,12 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
             return hip_status(osk::launch_sketch_rows(Xf, n, lines, ldx, bs.stored, bs.nst,
                                                       nblocks(sk), bp, lists, out, zs, s));
         }
+        if (transpose && dtype == OS_DTYPE_BF16 && !fp8_fused &&
+            osk::sketch_rows_bf16_in_place_ok(n, lines, bs.nst, bp))
+            return hip_status(osk::launch_sketch_rows_bf16(
+                X, n, lines, ldx, bs.stored, bs.nst, nblocks(sk), bp, lists,
+                bf16_product ? qout : out, bf16_product ? wq : zs,
+                bf16_product ? (is_split(precision) ? 2 : 1) : 0, s));
         if (transpose) {
             ldl = osk::round_up(n, 4);
             const hipError_t e =

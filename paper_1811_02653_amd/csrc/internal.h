@@ -130,6 +130,22 @@ hipError_t launch_sketch_rows(const float* X, int64_t n, int64_t cols, int64_t l
 // against 0.39 + 0.49 ms; 20011 x 2777 at ld 2777, 5 blocks of 900: 133
 // against 115 + 92 us; the sums are the same, bit for bit).
 bool sketch_rows_in_place_ok(int64_t cols);
+// True when the columns of a BF16 matrix are read in place, 8 per workgroup
+// (at least 8 of them, at most 6 slots per wave: a slot takes 8 registers),
+// and that is faster than transposing it first: every 16-byte request brings
+// its own cache line into a CU, so the line groups have to keep half the CUs
+// busy unless one window (8192 positions) is all there is.  Both operands and
+// the product, transposed / in place, us: 16384 x 4096, 4 blocks of 512,
+// 298 / 253, 6 of 1024 452 / 394 (8 slots, 8 of 1024: 543 / 530 with 46
+// registers spilled), 4 of 512 at 1501 (odd rows) 135 / 115, at 401 71 / 95,
+// at 256 62 / 76; 4096 x 128, 3 blocks of 256 42 / 36.
+bool sketch_rows_bf16_in_place_ok(int64_t n, int64_t cols, int32_t nst, int32_t bp);
+// launch_sketch_rows for a BF16 X (out_mode 0: the FP32 sketch, 1 / 2: its
+// BF16 copy as launch_sketch_cols_q writes it).
+hipError_t launch_sketch_rows_bf16(const void* X, int64_t n, int64_t cols, int64_t ldx,
+                                   const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
+                                   const void* lists, void* out, int64_t ldo, int out_mode,
+                                   hipStream_t s);
 // The sketches of both FP32 operands of a product (each given by its lines:
 // rows, or columns of a row-major matrix; ld ldo both) in one launch, when
 // their tasks fit on the device at once; out_mode 0: FP32, 1 / 2: the BF16

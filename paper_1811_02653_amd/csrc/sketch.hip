@@ -717,7 +717,8 @@ void pass_plan(int32_t nst, int32_t qn, int32_t* npass, int32_t* slots, int64_t 
     *slots = (int32_t)((need + kWaves - 1) / kWaves);
 }
 
-// X: FP32, or BF16 when bf16 (rows only, unweighted).  out_mode: 0 = FP32
+// X: FP32, or BF16 when bf16 (unweighted; its columns: out_mode 0 to 2 and
+// sketch_rows_bf16_in_place_ok).  out_mode: 0 = FP32
 // sketch (blocks bp apart); 1 = its BF16 rounding, 2 = BF16 and residual
 // (nst blocks after), 3 = FP8 codes, then their scales, 4 = FP8 codes, the
 // residuals' codes, then the scales of both (blocks round_up(bp, 64) apart).
@@ -727,7 +728,9 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
                          const float* wd = nullptr, int out_mode = 0) {
     const Plan p = plan_of(n, bp);
     const ListView v = carve_lists(const_cast<void*>(lists), nblk, n, bp);
-    const int64_t groups = (lines + kLines - 1) / kLines;
+    const bool wide = bf16 && !row_lines;
+    const int L = wide ? 2 * kLines : kLines;
+    const int64_t groups = (lines + L - 1) / L;
     const int cus = device_cus();
     int32_t npass, slots;
     pass_plan(nst, p.qn, &npass, &slots, groups, cus);
@@ -740,7 +743,7 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
     const int64_t ozlo = out_mode >= 2 ? (int64_t)nst * obp : 0;
     const SketchArgs a{X,     lines, n,   ldx, bp,    p.qn, p.nwin, nst,      &bl, p.RC,
                        v.hdr, v.ell, out, ldo, npass, wd,   obp,    out_mode, ozlo};
-    if ((bf16 && !row_lines) || ((out_mode >= 3 || bf16) && wd)) return hipErrorInvalidValue;
+    if ((wide && (out_mode > 2 || lines < L || slots > kMaxWideSlots)) || ((out_mode >= 3 || bf16) && wd)) return hipErrorInvalidValue;
     if (row_lines ? n < 4 : lines < 4) {     // too short for loads of 4 values
         if (out_mode >= 3 || p.qn > 65535 || nst > 65535) return hipErrorInvalidValue;
         const dim3 cells((unsigned)lines, (unsigned)p.qn, (unsigned)nst);
@@ -762,6 +765,7 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
         return bf16        ? sketch_rows_bf16_fp8x3(slots, grid, s, a)
                : row_lines ? sketch_rows_f32_fp8x3(slots, grid, s, a)
                            : sketch_cols_f32_fp8x3(slots, grid, s, a);
+    if (wide) return sketch_cols_bf16(slots, grid, s, a);
     if (bf16) return sketch_rows_bf16(slots, grid, s, a);
     if (!row_lines) return sketch_cols_f32(slots, grid, s, a);
     return wd ? sketch_rows_weighted(slots, grid, s, a) : sketch_rows_f32(slots, grid, s, a);
@@ -900,6 +904,23 @@ hipError_t launch_sketch_rows(const float* X, int64_t n, int64_t cols, int64_t l
 }
 
 bool sketch_rows_in_place_ok(int64_t cols) { return cols >= 4; }
+
+bool sketch_rows_bf16_in_place_ok(int64_t n, int64_t cols, int32_t nst, int32_t bp) {
+    const Plan p = plan_of(n, bp);
+    int32_t npass, slots;
+    pass_plan(nst, p.qn, &npass, &slots);
+    if (cols < 2 * kLines || slots > kMaxWideSlots) return false;
+    return p.nwin == 1 || cols / kLines >= device_cus();
+}
+
+hipError_t launch_sketch_rows_bf16(const void* X, int64_t n, int64_t cols, int64_t ldx,
+                                   const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
+                                   const void* lists, void* out, int64_t ldo, int out_mode,
+                                   hipStream_t s) {
+    if (!plan_sketch_ok(cols, nst, bp, n)) return hipErrorInvalidValue;
+    return launch_sketch(false, X, true, cols, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s,
+                         nullptr, out_mode);
+}
 
 bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, void* outA,
                         const float* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,

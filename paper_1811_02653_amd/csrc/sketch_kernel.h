@@ -4,6 +4,8 @@
 // parallel.
 #pragma once
 
+#include <type_traits>
+
 #include "sketch_launch.h"
 #include "fp8.h"
 
@@ -27,6 +29,12 @@ namespace {
 //                      4096u + 4t + j, one 16-byte load.  The last group of
 //                      lines starts at lines - 4 (lines that two groups hold
 //                      are written twice with the same values).
+//     BF16 columns   : the same with 8 lines (16 bytes) per workgroup; LDS
+//                      keeps the 8 BF16 values of a position, converted as
+//                      they are added.  Bound by those requests, a cache
+//                      line each (16384 x 4096 into 4 blocks of 512: 85-90
+//                      us, where the transpose and the sketch of its rows
+//                      took 49 + 67).
 // kWeighted (row lines): every value at sketched index k is multiplied by
 // sqrt(wd[k]) (a diagonal weight, as in A D^{1/2} S for a Hessian A D A^T);
 // w[u] holds the weights of positions 4t + 4096u .. +3.  The weight is
@@ -42,6 +50,7 @@ namespace {
 // alignment of an element (gfx950 loads 16 bytes at any dword).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef f32x4 f32x4_any2 __attribute__((aligned(2)));
 __device__ __forceinline__ float4 load_stream(const float* __restrict__ p) {
     const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
     return make_float4(t[0], t[1], t[2], t[3]);
@@ -80,17 +89,23 @@ struct RawQuad<__bf16> {
     }
 };
 
+// Lines per workgroup, and a piece of a window as loaded.
+template <bool kRowLines, typename TI>
+constexpr int kLinesOf = !kRowLines && sizeof(TI) == 2 ? 8 : kLines;
+template <bool kRowLines, typename TI>
+using Piece = std::conditional_t<kRowLines, typename RawQuad<TI>::type, float4>;
+
 // Loads pieces p0 .. p1 - 1 of a window (piece 4u + q: r[2q + u] of row
-// lines, r[4u + q] of column lines); all 8 pieces make the window.  p0 and p1 are constants (the callers are unrolled).  Every
+// lines, r[4u + q] of column lines); all 8 pieces make the window.  p0 and p1
+// are constants (the callers are unrolled).  Every
 // load is unconditional (a branch around a load makes each use wait for all
 // loads in flight): positions past the window's end are clamped to its last
 // ones (no entry refers to them) and lines past the matrix to its last line
 // (their sums are never stored).
 template <bool kRowLines, typename TI>
-__device__ __forceinline__ void load_window(typename RawQuad<TI>::type (&r)[kPerThread],
+__device__ __forceinline__ void load_window(Piece<kRowLines, TI> (&r)[kPerThread],
                                             const TI* __restrict__ X, int64_t lines, int64_t ldx,
                                             int64_t line0, int64_t k0, int kw, int p0, int p1) {
-    static_assert(kRowLines || sizeof(TI) == 4, "column lines are read as FP32 only");
     const int tid = threadIdx.x;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -112,7 +127,11 @@ __device__ __forceinline__ void load_window(typename RawQuad<TI>::type (&r)[kPer
                     r[2 * q + u] = RawQuad<TI>::load(base + off);
             } else {
                 const int64_t kk = k0 + min(4 * tid + 4096 * u + q, kw - 1);
-                const f32x4 t = *reinterpret_cast<const f32x4_any*>(X + kk * ldx + line0);
+                f32x4 t;
+                if constexpr (sizeof(TI) == 4)
+                    t = *reinterpret_cast<const f32x4_any*>(X + kk * ldx + line0);
+                else
+                    t = *reinterpret_cast<const f32x4_any2*>(X + kk * ldx + line0);
                 r[4 * u + q] = make_float4(t[0], t[1], t[2], t[3]);
             }
         }
@@ -135,7 +154,7 @@ __device__ __forceinline__ void load_weights(float4 (&w)[2], const float* __rest
 // lines' values at window position k (weighted when kWeighted).
 template <bool kRowLines, bool kWeighted, typename TI>
 __device__ __forceinline__ void stage_window(float4* __restrict__ win,
-                                             typename RawQuad<TI>::type (&r)[kPerThread],
+                                             Piece<kRowLines, TI> (&r)[kPerThread],
                                              float4 (&w)[2], int kw) {
     using R = RawQuad<TI>;
     const int tid = threadIdx.x;
@@ -172,16 +191,15 @@ __device__ __forceinline__ void stage_window(float4* __restrict__ win,
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                win[4096 * u + 1024 * j + tid] =
-                    make_float4(R::value(r[4 * u + j], 0), R::value(r[4 * u + j], 1),
-                                R::value(r[4 * u + j], 2), R::value(r[4 * u + j], 3));
+                win[4096 * u + 1024 * j + tid] = r[4 * u + j];
     }
 }
 
 // Adds 4 entries (16 bits each, two per word; sign bit 15 selects the sign of
 // the FP32 +-1.0 factor).  All four LDS reads are issued before the first
-// FMA so their latencies overlap.
-__device__ __forceinline__ void add_half(float4& acc, const float4* __restrict__ win, uint32_t w0,
+// FMA so their latencies overlap.  kQ = 2: 8 BF16 lines per position.
+template <int kQ>
+__device__ __forceinline__ void add_half(float4 (&acc)[kQ], const float4* __restrict__ win, uint32_t w0,
                                          uint32_t w1) {
     const uint32_t w[2] = {w0, w1};
     float4 v[4];
@@ -198,16 +216,29 @@ __device__ __forceinline__ void add_half(float4& acc, const float4* __restrict__
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        acc.x = fmaf(s[u], v[u].x, acc.x);
-        acc.y = fmaf(s[u], v[u].y, acc.y);
-        acc.z = fmaf(s[u], v[u].z, acc.z);
-        acc.w = fmaf(s[u], v[u].w, acc.w);
+        float4 x[kQ];
+        if constexpr (kQ == 1) {
+            x[0] = v[u];
+        } else {
+            auto lo = [](float w) { return __uint_as_float(__float_as_uint(w) << 16); };
+            auto hi = [](float w) { return __uint_as_float(__float_as_uint(w) & 0xFFFF0000u); };
+            x[0] = make_float4(lo(v[u].x), hi(v[u].x), lo(v[u].y), hi(v[u].y));
+            x[1] = make_float4(lo(v[u].z), hi(v[u].z), lo(v[u].w), hi(v[u].w));
+        }
+#pragma unroll
+        for (int h = 0; h < kQ; ++h) {
+            acc[h].x = fmaf(s[u], x[h].x, acc[h].x);
+            acc[h].y = fmaf(s[u], x[h].y, acc[h].y);
+            acc[h].z = fmaf(s[u], x[h].z, acc[h].z);
+            acc[h].w = fmaf(s[u], x[h].w, acc[h].w);
+        }
     }
 }
 
 // Adds the 8 entries of one chunk, four at a time (four waves per SIMD hide
 // the LDS latency; eight reads in flight would spill).
-__device__ __forceinline__ void add_chunk(float4& acc, const float4* __restrict__ win, uint4 e) {
+template <int kQ>
+__device__ __forceinline__ void add_chunk(float4 (&acc)[kQ], const float4* __restrict__ win, uint4 e) {
     add_half(acc, win, e.x, e.y);
     __builtin_amdgcn_sched_barrier(0);
     add_half(acc, win, e.z, e.w);
@@ -231,7 +262,10 @@ __device__ __forceinline__ void sketch_tasks(
     const int lane = tid & 63;
     const uint32_t lane16 = 16 * (uint32_t)lane;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t groups = (lines + kLines - 1) / kLines;
+    constexpr int kL = kLinesOf<kRowLines, TI>;
+    constexpr int kQ = kL / 4;
+    static_assert(kQ == 1 || (kFp8Out == 0 && !kWeighted));
+    const int64_t groups = (lines + kL - 1) / kL;
     const int64_t tasks = groups * npass;
     const int gslots = nst * qn;         // groups of 64 buckets over the stored blocks
     if (tid == 0) win[kWin] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -249,8 +283,8 @@ __device__ __forceinline__ void sketch_tasks(
     // buckets exist (lim, 0 for an unused slot).  A window's headers come in
     // with one vector load, issued before the window's values are fetched.
     auto line_of = [&](int64_t it) {
-        const int64_t l0 = xcd_task(it, tasks) / npass * kLines;
-        return kRowLines ? l0 : min(l0, lines - 4);
+        const int64_t l0 = xcd_task(it, tasks) / npass * kL;
+        return kRowLines ? l0 : min(l0, lines - kL);
     };
     struct Meta {
         int32_t hb, eb, col, lim;
@@ -274,7 +308,7 @@ __device__ __forceinline__ void sketch_tasks(
         const uint32_t h = hdr[max(hb, 0) + w * qn];     // unconditional: index valid
         return hb >= 0 ? h : 0u;
     };
-    typename RawQuad<TI>::type pre[kPerThread];
+    Piece<kRowLines, TI> pre[kPerThread];
     float4 wpre[2];
     uint32_t hnext = 0;
     if (wg < tasks) {
@@ -287,9 +321,11 @@ __device__ __forceinline__ void sketch_tasks(
     const int64_t line0 = line_of(it);
     const Meta meta = meta_of(it);      // (its loads complete with the window's, before staging)
 
-    float4 acc[kSlots];
+    float4 acc[kSlots][kQ];
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s = 0; s < kSlots; ++s)
+#pragma unroll
+        for (int h = 0; h < kQ; ++h) acc[s][h] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int w = 0; w < nwin; ++w) {
         __syncthreads();                 // the previous window is no longer read
         stage_window<kRowLines, kWeighted, TI>(
@@ -432,7 +468,7 @@ __device__ __forceinline__ void sketch_tasks(
 #pragma unroll
         for (int s = 0; s < kSlots; ++s) {
             if (__builtin_amdgcn_readlane(meta.lim, s) == 0) continue;      // uniform
-            float v[4] = {acc[s].x, acc[s].y, acc[s].z, acc[s].w};
+            float v[4] = {acc[s][0].x, acc[s][0].y, acc[s][0].z, acc[s][0].w};
             const int64_t col = __builtin_amdgcn_readlane(meta.col, s);
             int e[4];
             const uint32_t d = encode(v, e);
@@ -462,21 +498,25 @@ __device__ __forceinline__ void sketch_tasks(
     for (int s = 0; s < kSlots; ++s) {
         // lanes below lim hold buckets of the block (the last group may be partial)
         if (lane < __builtin_amdgcn_readlane(meta.lim, s)) {
-            const int64_t o0 = line0 * ldo + __builtin_amdgcn_readlane(meta.col, s) + lane;
-            const float v[4] = {acc[s].x, acc[s].y, acc[s].z, acc[s].w};
-            if (omode == 0) {
-                float* o = static_cast<float*>(out) + o0;
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (r == 0 || line0 + r < lines) o[r * ldo] = v[r];
-            } else {
-                __bf16* o = static_cast<__bf16*>(out) + o0;
+            for (int h = 0; h < kQ; ++h) {
+                const int64_t l4 = line0 + 4 * h;
+                const int64_t o0 = l4 * ldo + __builtin_amdgcn_readlane(meta.col, s) + lane;
+                const float v[4] = {acc[s][h].x, acc[s][h].y, acc[s][h].z, acc[s][h].w};
+                if (omode == 0) {
+                    float* o = static_cast<float*>(out) + o0;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (r == 0 || line0 + r < lines) {
-                        const __bf16 hi = (__bf16)v[r];
-                        o[r * ldo] = hi;
-                        if (omode == 2) o[r * ldo + ozlo] = (__bf16)(v[r] - (float)hi);
+                    for (int r = 0; r < 4; ++r)
+                        if (r == 0 || l4 + r < lines) o[r * ldo] = v[r];
+                } else {
+                    __bf16* o = static_cast<__bf16*>(out) + o0;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (r == 0 || l4 + r < lines) {
+                            const __bf16 hi = (__bf16)v[r];
+                            o[r * ldo] = hi;
+                            if (omode == 2) o[r * ldo + ozlo] = (__bf16)(v[r] - (float)hi);
+                        }
                     }
                 }
             }
@@ -507,10 +547,11 @@ hipError_t launch_one(dim3 grid, hipStream_t st, const SketchArgs& a) {
     return hipGetLastError();
 }
 
-template <bool R, bool W, typename TI, int Q8 = 0>
+template <bool R, bool W, typename TI, int Q8 = 0, int kMost = Q8 ? kMaxFp8Slots : kMaxSlots>
 hipError_t launch_slots(int slots, dim3 grid, hipStream_t st, const SketchArgs& a) {
 #define OSK_SLOT_CASE(S) \
-    if (slots <= S) return launch_one<S, R, W, TI, Q8>(grid, st, a);
+    if constexpr (S <= kMost) \
+        if (slots <= S) return launch_one<S, R, W, TI, Q8>(grid, st, a);
     OSK_SLOT_CASE(1)
     OSK_SLOT_CASE(2)
     OSK_SLOT_CASE(3)
@@ -518,9 +559,7 @@ hipError_t launch_slots(int slots, dim3 grid, hipStream_t st, const SketchArgs& 
     OSK_SLOT_CASE(6)
     OSK_SLOT_CASE(8)
     OSK_SLOT_CASE(10)
-    if constexpr (Q8 == 0) {        // (FP8 output: see sketch_fp8_fusable)
-        OSK_SLOT_CASE(12)
-    }
+    OSK_SLOT_CASE(12)
 #undef OSK_SLOT_CASE
     return hipErrorInvalidValue;
 }

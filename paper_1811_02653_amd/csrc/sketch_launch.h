@@ -8,6 +8,7 @@ namespace osk {
 // Slot counts compiled: 1, 2, 3, 4, 6, 8, 10, 12 (4 registers per slot).
 constexpr int kMaxSlots = 12;
 constexpr int kMaxFp8Slots = 10;       // with the FP8 epilogue
+constexpr int kMaxWideSlots = 6;       // 8 BF16 column lines (8 registers per slot)
 
 // Arguments of a sketch launch (see launch_sketch).
 struct SketchArgs {
@@ -42,12 +43,14 @@ hipError_t sketch_pair(int slots, hipStream_t st, const SketchArgs& a, const Ske
                        const SketchSide& y);
 
 // Launches the sketch kernel with at least `slots` slots per wave: rows of an
-// FP32 X, rows weighted by sqrt(wd), rows of a BF16 X, columns of an FP32 X,
+// FP32 X, rows weighted by sqrt(wd), rows of a BF16 X, columns of an FP32 X
+// and of a BF16 one (8 lines per workgroup),
 // and rows (FP32 or BF16) and columns writing the FP8 copy, plain or split.
 hipError_t sketch_rows_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_weighted(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_cols_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_cols_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_cols_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);

@@ -696,6 +696,26 @@ def test_both_sketches_in_one_launch(m, n, l, b, N, precision):
             assert torch.equal(got, C), (a_cm, b_cm)
 
 
+@pytest.mark.parametrize("n,lines", [(1, 8), (700, 7), (700, 8), (2049, 9), (8192, 41), (8193, 41),
+                                     (8194, 1024), (16390, 1030), (20011, 1027)])
+@pytest.mark.parametrize("b,N", [(64, 1), (500, 4), (1024, 4), (1024, 6), (1000, 7)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "bf16x3"])
+def test_bf16_columns_in_place(n, lines, b, N, precision):
+    """Columns of a BF16 matrix, read in place 8 at a time or transposed (fewer
+    than 8, more slots than compiled, more than one window and few lines),
+    aligned and not: the product of the same values as rows in memory, bit for
+    bit."""
+    g = torch.Generator(device="cuda").manual_seed(n + lines)
+    A = torch.randn(33, n, generator=g, device="cuda").bfloat16()
+    B = torch.randn(n, lines + 5, generator=g, device="cuda").bfloat16()
+    kw = dict(seed=6, precision=precision)
+    for Bv in (B[:, :lines], B[:, 3:3 + lines], B[:, 4:4 + lines]):
+        want = osk.matmul_ex(A, Bv.t().contiguous().t(), b, N, 0, **kw)
+        assert torch.equal(osk.matmul_ex(A, Bv, b, N, 0, **kw), want)
+        assert torch.equal(osk.matmul_ex(Bv.t(), A.t().contiguous(), b, N, 0, **kw),
+                           osk.matmul_ex(Bv.t().contiguous(), A.t(), b, N, 0, **kw))
+
+
 @pytest.mark.parametrize("n", [1, 63, 1025, 2049, 8192, 8255, 20011])
 @pytest.mark.parametrize("b,N", [(1, 1), (33, 2), (1024, 3), (1500, 2)])
 @pytest.mark.parametrize("tables", ["hash", "one bucket", "ends"])
