@@ -148,7 +148,8 @@ hipError_t launch_sketch_rows_bf16(const void* X, int64_t n, int64_t cols, int64
                                    hipStream_t s);
 // The sketches of both FP32 operands of a product (each given by its lines:
 // rows, or columns of a row-major matrix; ld ldo both) in one launch, when
-// their tasks fit on the device at once; out_mode 0: FP32, 1 / 2: the BF16
+// that is predicted to end sooner (always when their tasks fit on the device
+// together); out_mode 0: FP32, 1 / 2: the BF16
 // copy without / with residuals, 3 / 4: the FP8 one.  False when the pair is to be launched one
 // by one; else *err is the launch's error.
 bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, void* outA,

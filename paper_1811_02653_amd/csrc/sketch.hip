@@ -932,19 +932,52 @@ bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, voi
     const int cus = device_cus();
     int32_t npass, slots;
     pass_plan(nst, p.qn, &npass, &slots, ga + gb, cus);
-    if ((ga + gb) * npass > cus || slots > kMaxPairSlots || out_mode < 0 || out_mode > 4 ||
+    if (cus < 16 || slots > (out_mode >= 3 ? kMaxPairFp8Slots : kMaxPairSlots) || out_mode < 0 || out_mode > 4 ||
         (out_mode >= 3 && !sketch_fp8_fusable(bp, nst)) ||
         (a_rows ? n : m) < 4 || (b_rows ? n : l) < 4 || !plan_sketch_ok(m, nst, bp, n) ||
         !plan_sketch_ok(l, nst, bp, n))
         return false;
+    // Workgroups of each side: one per task when they fit, else the split of
+    // the CUs that ends first, in multiples of the 8 XCDs (a workgroup's tasks
+    // then stay on one XCD); a task of columns lasts 1.5 times one of rows.
+    // The two launches one by one leave CUs idle in two last rounds; apart /
+    // together, whole product, us: 1100 x 10000 x 1100 FP8, 5 blocks of 500,
+    // 111 / 80; 1500 x 8000 x 1300 BF16, 5 of 700, 98 / 86; 512 x 8192 x 300,
+    // 9 of 512, 76 / 68; where less than a fifteenth is predicted (3333 x
+    // 20011 x 2777, 5 of 900, 840 / 849) they stay apart.
+    const int64_t ta = ga * npass, tb = gb * npass;
+    const double ca = a_rows ? 1 : 1.5, cb = b_rows ? 1 : 1.5;
+    int64_t wa = ta, wb = tb;
+    if (ta + tb > cus) {
+        auto rounds = [](int64_t t, int64_t w) { return (double)((t + w - 1) / w); };
+        auto alone = [&](int64_t g) {                    // (a pass is its share of a task)
+            int32_t P, ns;
+            pass_plan(nst, p.qn, &P, &ns, g, cus);
+            return rounds(g * P, cus) * npass / P;
+        };
+        const double apart = ca * alone(ga) + cb * alone(gb);
+        double best = 0;
+        for (int64_t w = 8; w < cus; w += 8) {
+            const double t = std::max(ca * rounds(ta, w), cb * rounds(tb, cus - w));
+            if (best == 0 || t < best) {
+                best = t;
+                wa = w;
+            }
+        }
+        if (best >= 0.93 * apart) return false;
+        wb = std::min(cus - wa, tb);
+        wa = std::min(wa, ta);
+    }
     const ListView v = carve_lists(const_cast<void*>(lists), nblk, n, bp);
     const int32_t obp = out_mode ? p.qn * 64 : bp;
     const SketchArgs a{nullptr, 0,       n,   0,   bp,    p.qn,    p.nwin, nst,      &bl,
                        p.RC,    v.hdr,   v.ell, nullptr, ldo, npass, nullptr, obp, out_mode,
                        out_mode >= 2 ? (int64_t)nst * obp : 0};
-    const SketchSide x{A, m, lda, outA, (int32_t)(ga * npass), a_rows ? 1 : 0};
-    const SketchSide y{B, l, ldb, outB, (int32_t)(gb * npass), b_rows ? 1 : 0};
-    *err = sketch_pair(slots, s, a, x, y);
+    const SketchSide x{A, m, lda, outA, (int32_t)wa, a_rows ? 1 : 0};
+    const SketchSide y{B, l, ldb, outB, (int32_t)wb, b_rows ? 1 : 0};
+    *err = out_mode == 4   ? sketch_pair_fp8x3(slots, s, a, x, y)
+           : out_mode == 3 ? sketch_pair_fp8(slots, s, a, x, y)
+                           : sketch_pair(slots, s, a, x, y);
     return true;
 }
 

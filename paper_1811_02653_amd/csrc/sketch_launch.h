@@ -27,20 +27,25 @@ struct SketchArgs {
     int64_t ozlo;
 };
 
+constexpr int kMaxPairSlots = 10;      // both operands in one launch
+constexpr int kMaxPairFp8Slots = 8;
+
 // One operand of a pair launch.
 struct SketchSide {
     const float* X;
     int64_t lines, ldx;
     void* out;
-    int32_t wgs;       // its workgroups (= its tasks)
+    int32_t wgs;       // its workgroups
     int32_t rows;      // lines are rows (else columns)
 };
-// Slot counts of the pair kernel: 1 to kMaxPairSlots.
-constexpr int kMaxPairSlots = 3;
-// Both sides of a product in one launch, a workgroup per task (a's fields X,
-// lines, ldx, out, wd unused; FP32 operands).
+// Both sides of a product in one launch (a's fields X, lines, ldx, out, wd
+// unused; FP32 operands): FP32 or BF16, FP8 and split FP8 output.
 hipError_t sketch_pair(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                        const SketchSide& y);
+hipError_t sketch_pair_fp8(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
+                           const SketchSide& y);
+hipError_t sketch_pair_fp8x3(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
+                             const SketchSide& y);
 
 // Launches the sketch kernel with at least `slots` slots per wave: rows of an
 // FP32 X, rows weighted by sqrt(wd), rows of a BF16 X, columns of an FP32 X

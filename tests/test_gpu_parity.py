@@ -696,6 +696,37 @@ def test_both_sketches_in_one_launch(m, n, l, b, N, precision):
             assert torch.equal(got, C), (a_cm, b_cm)
 
 
+@pytest.mark.parametrize("m,n,l,b,N", [(1100, 700, 1100, 500, 5), (2500, 300, 300, 1000, 9),
+                                       (300, 9001, 1030, 600, 16), (520, 700, 517, 1000, 12),
+                                       (1030, 2050, 5, 300, 4), (4100, 300, 4090, 64, 1)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
+def test_both_sketches_share_the_device(m, n, l, b, N, precision):
+    """Products whose line groups exceed the device, in one launch (1 to 10
+    slots per wave, one or both sides in several rounds) or two: the same in
+    every layout, bit for bit, and within an FP32 ulp per accumulation of the
+    64-bit product of the separate sketches."""
+    A, B = synthetic.gaussian_pair(m, n, l, m + l)
+    kw = dict(seed=5, precision=precision)
+    Ad, Bd = _in_layout(A, False, torch.float32), _in_layout(B, False, torch.float32)
+    C = osk.matmul_ex(Ad, Bd, b, N, 0, **kw)
+    for a_cm in (False, True):
+        for b_cm in (False, True):
+            got = osk.matmul_ex(_in_layout(A, a_cm, torch.float32),
+                                _in_layout(B, b_cm, torch.float32), b, N, 0, **kw)
+            assert torch.equal(got, C), (a_cm, b_cm)
+    At, Bt = osk.sketch_cols(Ad, b, N, 0, seed=5), osk.sketch_rows(Bd, b, N, 0, seed=5)
+    if precision == "fp32":
+        pairs = [(At.double(), Bt.double())]
+    else:
+        At, Bt = (osk.sketch_quantize(S, b, N, precision).double() for S in (At, Bt))
+        w = At.shape[1] // 2
+        pairs = [(At[:, :w], Bt[:, :w]), (At[:, :w], Bt[:, w:]), (At[:, w:], Bt[:, :w])]
+    want = sum(x @ y.t() for x, y in pairs) / N
+    mag = sum(x.abs() @ y.abs().t() for x, y in pairs) / N
+    terms = len(pairs) * pairs[0][0].shape[1]
+    assert bool(((C.double() - want).abs() <= mag * terms * 2.0 ** -24).all())
+
+
 @pytest.mark.parametrize("n,lines", [(1, 8), (700, 7), (700, 8), (2049, 9), (8192, 41), (8193, 41),
                                      (8194, 1024), (16390, 1030), (20011, 1027)])
 @pytest.mark.parametrize("b,N", [(64, 1), (500, 4), (1024, 4), (1024, 6), (1000, 7)])
