@@ -525,14 +525,13 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     if ((st = prepare(sk, n, prep, s)) != OS_OK) return st;
     const bool same =
         same_lines(A, a_dtype, a_col_major != 0, m, lda, B, b_dtype, b_col_major == 0, l, ldb);
-    const bool f32 = a_dtype == OS_DTYPE_F32 && b_dtype == OS_DTYPE_F32;
     hipError_t e = hipSuccess;
     const bool copy = bf16_product || fp8_fused;      // the sketch writes the product's operand
     const int mode = copy ? (bf16_product ? 1 : 3) + (is_split(precision) ? 1 : 0) : 0;
-    if (!same && f32 &&
-        osk::launch_sketch_pair(static_cast<const float*>(A), a_col_major == 0, m, lda,
+    if (!same && a_dtype == b_dtype &&
+        osk::launch_sketch_pair(a_dtype == OS_DTYPE_BF16, A, a_col_major == 0, m, lda,
                                 copy ? static_cast<void*>(aq_p) : At,
-                                static_cast<const float*>(B), b_col_major != 0, l, ldb,
+                                B, b_col_major != 0, l, ldb,
                                 copy ? static_cast<void*>(bq_p) : Bt, n, bs.stored, bs.nst,
                                 nblocks(sk), bp, lists, copy ? wq : zs, mode, s, &e)) {
         if (e != hipSuccess) return hip_status(e);

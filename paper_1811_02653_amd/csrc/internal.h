@@ -146,14 +146,14 @@ hipError_t launch_sketch_rows_bf16(const void* X, int64_t n, int64_t cols, int64
                                    const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                                    const void* lists, void* out, int64_t ldo, int out_mode,
                                    hipStream_t s);
-// The sketches of both FP32 operands of a product (each given by its lines:
+// The sketches of both operands of a product, FP32 or (columns only) BF16 (each given by its lines:
 // rows, or columns of a row-major matrix; ld ldo both) in one launch, when
 // that is predicted to end sooner (always when their tasks fit on the device
 // together); out_mode 0: FP32, 1 / 2: the BF16
 // copy without / with residuals, 3 / 4: the FP8 one.  False when the pair is to be launched one
 // by one; else *err is the launch's error.
-bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, void* outA,
-                        const float* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,
+bool launch_sketch_pair(bool bf16, const void* A, bool a_rows, int64_t m, int64_t lda, void* outA,
+                        const void* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,
                         const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                         const void* lists, int64_t ldo, int out_mode, hipStream_t s,
                         hipError_t* err);

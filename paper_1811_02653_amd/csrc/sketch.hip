@@ -922,19 +922,25 @@ hipError_t launch_sketch_rows_bf16(const void* X, int64_t n, int64_t cols, int64
                          nullptr, out_mode);
 }
 
-bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, void* outA,
-                        const float* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,
+bool launch_sketch_pair(bool bf16, const void* A, bool a_rows, int64_t m, int64_t lda, void* outA,
+                        const void* B, bool b_rows, int64_t l, int64_t ldb, void* outB, int64_t n,
                         const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                         const void* lists, int64_t ldo, int out_mode, hipStream_t s,
                         hipError_t* err) {
     const Plan p = plan_of(n, bp);
-    const int64_t ga = (m + kLines - 1) / kLines, gb = (l + kLines - 1) / kLines;
+    const int L = bf16 ? 2 * kLines : kLines;
+    const int64_t ga = (m + L - 1) / L, gb = (l + L - 1) / L;
     const int cus = device_cus();
     int32_t npass, slots;
     pass_plan(nst, p.qn, &npass, &slots, ga + gb, cus);
-    if (cus < 16 || slots > (out_mode >= 3 ? kMaxPairFp8Slots : kMaxPairSlots) || out_mode < 0 || out_mode > 4 ||
-        (out_mode >= 3 && !sketch_fp8_fusable(bp, nst)) ||
-        (a_rows ? n : m) < 4 || (b_rows ? n : l) < 4 || !plan_sketch_ok(m, nst, bp, n) ||
+    const int most = bf16 ? kMaxWideSlots : (out_mode >= 3 ? kMaxPairFp8Slots : kMaxPairSlots);
+    if (cus < 16 || slots > most || out_mode < 0 || out_mode > (bf16 ? 2 : 4) ||
+        (out_mode >= 3 && !sketch_fp8_fusable(bp, nst)))
+        return false;
+    // (BF16: columns only, both in place by the rule for one, on their sum)
+    if (bf16 && (a_rows || b_rows || !sketch_rows_bf16_in_place_ok(n, m + l, nst, bp)))
+        return false;
+    if ((a_rows ? n : m) < L || (b_rows ? n : l) < L || !plan_sketch_ok(m, nst, bp, n) ||
         !plan_sketch_ok(l, nst, bp, n))
         return false;
     // Workgroups of each side: one per task when they fit, else the split of
@@ -943,7 +949,8 @@ bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, voi
     // The two launches one by one leave CUs idle in two last rounds; apart /
     // together, whole product, us: 1100 x 10000 x 1100 FP8, 5 blocks of 500,
     // 111 / 80; 1500 x 8000 x 1300 BF16, 5 of 700, 98 / 86; 512 x 8192 x 300,
-    // 9 of 512, 76 / 68; where less than a fifteenth is predicted (3333 x
+    // 9 of 512, 76 / 68; BF16 columns, 9000 x 1001 (both), 4 of 400, 84 / 61,
+    // 4096 x 1024 and 300, 3 of 256, 40 / 32; where less than a fifteenth is predicted (3333 x
     // 20011 x 2777, 5 of 900, 840 / 849) they stay apart.
     const int64_t ta = ga * npass, tb = gb * npass;
     const double ca = a_rows ? 1 : 1.5, cb = b_rows ? 1 : 1.5;
@@ -975,7 +982,8 @@ bool launch_sketch_pair(const float* A, bool a_rows, int64_t m, int64_t lda, voi
                        out_mode >= 2 ? (int64_t)nst * obp : 0};
     const SketchSide x{A, m, lda, outA, (int32_t)wa, a_rows ? 1 : 0};
     const SketchSide y{B, l, ldb, outB, (int32_t)wb, b_rows ? 1 : 0};
-    *err = out_mode == 4   ? sketch_pair_fp8x3(slots, s, a, x, y)
+    *err = bf16            ? sketch_pair_bf16(slots, s, a, x, y)
+           : out_mode == 4   ? sketch_pair_fp8x3(slots, s, a, x, y)
            : out_mode == 3 ? sketch_pair_fp8(slots, s, a, x, y)
                            : sketch_pair(slots, s, a, x, y);
     return true;

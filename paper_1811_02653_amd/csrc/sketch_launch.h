@@ -32,16 +32,19 @@ constexpr int kMaxPairFp8Slots = 8;
 
 // One operand of a pair launch.
 struct SketchSide {
-    const float* X;
+    const void* X;
     int64_t lines, ldx;
     void* out;
     int32_t wgs;       // its workgroups
     int32_t rows;      // lines are rows (else columns)
 };
 // Both sides of a product in one launch (a's fields X, lines, ldx, out, wd
-// unused; FP32 operands): FP32 or BF16, FP8 and split FP8 output.
+// unused): FP32 operands with FP32 or BF16, FP8 and split FP8 output, and
+// columns of BF16 operands with FP32 or BF16 output.
 hipError_t sketch_pair(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                        const SketchSide& y);
+hipError_t sketch_pair_bf16(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
+                            const SketchSide& y);
 hipError_t sketch_pair_fp8(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                            const SketchSide& y);
 hipError_t sketch_pair_fp8x3(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,

@@ -5,7 +5,7 @@ namespace osk {
 
 hipError_t sketch_pair(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                        const SketchSide& y) {
-    return launch_pair<0>(slots, st, a, x, y);
+    return launch_pair<float, 0, kMaxPairSlots>(slots, st, a, x, y);
 }
 
 }  // namespace osk

@@ -5,7 +5,7 @@ namespace osk {
 
 hipError_t sketch_pair_fp8(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                            const SketchSide& y) {
-    return launch_pair<1>(slots, st, a, x, y);
+    return launch_pair<float, 1, kMaxPairFp8Slots>(slots, st, a, x, y);
 }
 
 }  // namespace osk

@@ -5,7 +5,7 @@ namespace osk {
 
 hipError_t sketch_pair_fp8x3(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                              const SketchSide& y) {
-    return launch_pair<2>(slots, st, a, x, y);
+    return launch_pair<float, 2, kMaxPairFp8Slots>(slots, st, a, x, y);
 }
 
 }  // namespace osk

@@ -14,7 +14,7 @@ namespace osk {
 namespace {
 
 // The first x.wgs workgroups take x's tasks, the rest y's.
-template <int kSlots, int kFp8Out>
+template <int kSlots, typename TI, int kFp8Out>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t bp, int32_t qn,
                         int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
@@ -24,26 +24,31 @@ void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t bp, int32
     const bool second = (int32_t)blockIdx.x >= x.wgs;
     const int64_t wg = second ? blockIdx.x - x.wgs : blockIdx.x;
     const SketchSide& s = second ? y : x;
-    if (s.rows)
-        sketch_tasks<kSlots, true, false, float, kFp8Out>(
-            win, wg, s.wgs, s.X, s.lines, n, s.ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, s.out, ldo,
-            npass, nullptr, obp, omode, ozlo);
-    else
-        sketch_tasks<kSlots, false, false, float, kFp8Out>(
-            win, wg, s.wgs, s.X, s.lines, n, s.ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, s.out, ldo,
-            npass, nullptr, obp, omode, ozlo);
+    const TI* const X = static_cast<const TI*>(s.X);
+    if constexpr (sizeof(TI) == 4) {
+        if (s.rows) {
+            sketch_tasks<kSlots, true, false, TI, kFp8Out>(
+                win, wg, s.wgs, X, s.lines, n, s.ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, s.out,
+                ldo, npass, nullptr, obp, omode, ozlo);
+            return;
+        }
+    }
+    sketch_tasks<kSlots, false, false, TI, kFp8Out>(
+        win, wg, s.wgs, X, s.lines, n, s.ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, s.out, ldo,
+        npass, nullptr, obp, omode, ozlo);
 }
 
-template <int kFp8Out>
+template <typename TI, int kFp8Out, int kMost>
 hipError_t launch_pair(int slots, hipStream_t st, const SketchArgs& a, const SketchSide& x,
                        const SketchSide& y) {
-#define OSK_SLOT_CASE(S)                                                                         \
-    if constexpr (S <= (kFp8Out ? kMaxPairFp8Slots : kMaxPairSlots))                             \
-        if (slots <= S) {                                                                        \
-            hipLaunchKernelGGL((sketch_pair_kernel<S, kFp8Out>), dim3((unsigned)(x.wgs + y.wgs)), \
-                               dim3(kThreads), 0, st, x, y, a.n, a.bp, a.qn, a.nwin, a.nst, *a.bl, \
-                               a.RC, a.hdr, a.ell, a.ldo, a.npass, a.obp, a.omode, a.ozlo);      \
-            return hipGetLastError();                                                            \
+#define OSK_SLOT_CASE(S)                                                                          \
+    if constexpr (S <= kMost)                                                                     \
+        if (slots <= S) {                                                                         \
+            hipLaunchKernelGGL((sketch_pair_kernel<S, TI, kFp8Out>),                              \
+                               dim3((unsigned)(x.wgs + y.wgs)), dim3(kThreads), 0, st, x, y, a.n,  \
+                               a.bp, a.qn, a.nwin, a.nst, *a.bl, a.RC, a.hdr, a.ell, a.ldo,       \
+                               a.npass, a.obp, a.omode, a.ozlo);                                  \
+            return hipGetLastError();                                                             \
         }
     OSK_SLOT_CASE(1)
     OSK_SLOT_CASE(2)

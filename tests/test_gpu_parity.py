@@ -696,6 +696,23 @@ def test_both_sketches_in_one_launch(m, n, l, b, N, precision):
             assert torch.equal(got, C), (a_cm, b_cm)
 
 
+@pytest.mark.parametrize("m,n,l,b,N", [(8, 1, 8, 64, 1), (9, 700, 2000, 500, 4), (7, 700, 600, 500, 4),
+                                       (300, 9001, 300, 256, 3), (530, 9001, 515, 256, 3),
+                                       (2100, 2050, 2100, 1000, 6), (3000, 300, 400, 1024, 8)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "bf16x3"])
+def test_bf16_columns_of_both_operands(m, n, l, b, N, precision):
+    """Both operands' lines columns of BF16 matrices (one launch when they are
+    read in place and fit together, else two, or transposed): the product of
+    the same values as rows in memory, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    X = torch.randn(n, m + 3, generator=g, device="cuda").bfloat16()
+    Y = torch.randn(n, l + 8, generator=g, device="cuda").bfloat16()
+    kw = dict(seed=6, precision=precision)
+    for Xv, Yv in ((X[:, :m], Y[:, :l]), (X[:, 3:], Y[:, 8:])):
+        want = osk.matmul_ex(Xv.t().contiguous(), Yv.t().contiguous().t(), b, N, 0, **kw)
+        assert torch.equal(osk.matmul_ex(Xv.t(), Yv, b, N, 0, **kw), want)
+
+
 @pytest.mark.parametrize("m,n,l,b,N", [(1100, 700, 1100, 500, 5), (2500, 300, 300, 1000, 9),
                                        (300, 9001, 1030, 600, 16), (520, 700, 517, 1000, 12),
                                        (1030, 2050, 5, 300, 4), (4100, 300, 4090, 64, 1)])
