@@ -232,6 +232,14 @@ struct SplitK {
     int32_t chunk;
 };
 
+// The part of a product that a launch computes: its tiles are the sub x sub
+// parts of the tiles first, first + 1, ... (in raster order) of the tilesM x
+// tilesN grid of sides sub * BT.  {0, 1}: all of it.
+struct Part {
+    int32_t first;
+    int32_t sub;
+};
+
 // kOdd: the K step count may be odd (per-C-block masks, whose count varies
 // per tile, with an odd bp / 32; split K loops): an odd last step runs
 // alone after the step pairs.
@@ -269,7 +277,7 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
                       int64_t ldbt, int64_t m, int64_t l, int32_t bp, BlockList kept,
                       int32_t nkept, int64_t lo_off, float scale,
                       float* __restrict__ C, int64_t ldc, int32_t tilesM, int32_t tilesN,
-                      CMask cm, SplitK sk) {
+                      CMask cm, SplitK sk, Part pt) {
     // two K-step buffers per operand, separate arrays so that the compiler
     // can tell the tile loads in flight (into one) from the fragment reads
     // (from the other)
@@ -293,11 +301,16 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     const int64_t ntiles = (int64_t)tilesM * tilesN;
     int32_t split = 0;
     int64_t T;
+    int32_t sr = 0, sc = 0;              // part of the tile (sub > 1)
     if constexpr (kSplit) {
         split = (int32_t)(blockIdx.x / ntiles);
         T = (int64_t)blockIdx.x - (int64_t)split * ntiles;
     } else {
-        T = xcd_task(blockIdx.x, ntiles);
+        T = xcd_task(blockIdx.x, gridDim.x);
+        const int32_t c = (int32_t)(T % (pt.sub * pt.sub));
+        T = pt.first + T / (pt.sub * pt.sub);
+        sr = c / pt.sub;
+        sc = c - sr * pt.sub;
     }
     const int64_t group = T / ((int64_t)kGroupM * tilesN);
     const int64_t first_m = group * kGroupM;
@@ -305,13 +318,15 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     const int64_t in_group = T - group * kGroupM * tilesN;
     const int64_t tm = first_m + in_group % gsz;
     const int64_t tn = in_group / gsz;
-    int64_t row0 = tm * BT;
-    int64_t col0 = tn * BT;
-    if constexpr (kMask) {
+    int64_t row0 = (tm * pt.sub + sr) * BT;
+    int64_t col0 = (tn * pt.sub + sc) * BT;
+    if constexpr (!kMask) {
+        if (row0 >= m || col0 >= l) return;     // a part past the matrix (uniform)
+    } else {
         // tile (tm, tn) of the C-block grid: block (I, J), tile (ti, tj) in it
         const int64_t I = tm / cm.tb, J = tn / cm.tb;
-        row0 = I * cm.cblk + (tm % cm.tb) * BT;
-        col0 = J * cm.cblk + (tn % cm.tb) * BT;
+        row0 = I * cm.cblk + (tm % cm.tb * pt.sub + sr) * BT;
+        col0 = J * cm.cblk + (tn % cm.tb * pt.sub + sc) * BT;
         m = min(m, (I + 1) * cm.cblk);          // rows and columns of this block only
         l = min(l, (J + 1) * cm.cblk);
         if (row0 >= m || col0 >= l) return;     // past a partial block's end (uniform)
@@ -719,7 +734,7 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
                            const uint8_t* __restrict__ Bt, int64_t ldbt, int64_t scales,
                            int64_t m, int64_t l, int32_t bp, BlockList kept, int32_t nkept,
                            int64_t lo_off, float scale, float* __restrict__ C, int64_t ldc,
-                           int32_t tilesM, int32_t tilesN, SplitK sk) {
+                           int32_t tilesM, int32_t tilesN, SplitK sk, Part pt) {
     constexpr int BT = S::BT;
     constexpr int kI = S::kI;
     constexpr int kJ = S::kJ;
@@ -743,11 +758,16 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     const int64_t ntiles = (int64_t)tilesM * tilesN;
     int32_t split = 0;
     int64_t T;
+    int32_t sr = 0, sc = 0;              // part of the tile (sub > 1)
     if constexpr (kSplit) {
         split = (int32_t)(blockIdx.x / ntiles);
         T = (int64_t)blockIdx.x - (int64_t)split * ntiles;
     } else {
-        T = xcd_task(blockIdx.x, ntiles);
+        T = xcd_task(blockIdx.x, gridDim.x);
+        const int32_t c = (int32_t)(T % (pt.sub * pt.sub));
+        T = pt.first + T / (pt.sub * pt.sub);
+        sr = c / pt.sub;
+        sc = c - sr * pt.sub;
     }
     const int64_t group = T / ((int64_t)kGroupM * tilesN);
     const int64_t first_m = group * kGroupM;
@@ -755,8 +775,9 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     const int64_t in_group = T - group * kGroupM * tilesN;
     const int64_t tm = first_m + in_group % gsz;
     const int64_t tn = in_group / gsz;
-    const int64_t row0 = tm * BT;
-    const int64_t col0 = tn * BT;
+    const int64_t row0 = (tm * pt.sub + sr) * BT;
+    const int64_t col0 = (tn * pt.sub + sc) * BT;
+    if (row0 >= m || col0 >= l) return;         // a part past the matrix (uniform)
 
     int32_t kv[4];
 #pragma unroll
@@ -1424,12 +1445,44 @@ bool split_plan(int64_t m, int64_t l, int64_t total, const float* part, size_t p
 }
 
 // How a block product is run: tile side (256, 128 or 64; 32 = the small
-// kernel), and the split of its K loop (S = 1: none).
+// kernel), the split of its K loop (S = 1: none), and the side of the tiles of
+// its last, partial round (0: as the others).
 struct Form {
     int tile;
     int64_t S;
     int64_t chunk;
+    int rest = 0;
 };
+
+// Tiles in whole rounds of the device, of `tiles`.
+int64_t whole_rounds(int64_t tiles) { return tiles / kSplitSlots * kSplitSlots; }
+
+// Predicted us per K step of `tiles` tiles of side f.tile, those past the
+// whole rounds as tiles of side f.rest in a launch of their own.  (A product
+// of a few more than a multiple of 256 tiles leaves most CUs idle in its last
+// round, and smaller tiles throughout cost 8 % (FP32) to 80 % (BF16) more LDS
+// and L2 traffic.  K = 4096, us without / with: 5120 x 5120 FP32 1523 / 1473;
+// 4500 x 4200 BF16 168 / 162, split BF16 475 / 410, FP8 120 / 109, split FP8
+// 259 / 226; 7000 x 8000 split BF16 1080 / 1054, FP8 246 / 238.)
+double step_us(Kind kind, int tile, int64_t tiles);
+
+double rest_us(Kind kind, int tile, int rest, int64_t tiles) {
+    const int64_t n1 = whole_rounds(tiles);
+    const int64_t sub = tile / rest;
+    return step_us(kind, tile, n1) + step_us(kind, rest, (tiles - n1) * sub * sub);
+}
+
+// f(tile, rest) for every remainder form of a product with tiles(side) tiles.
+template <typename F, typename G>
+void remainder_forms(bool fp8, G tiles, F f) {
+    for (const int tile : {256, 128})
+        for (const int rest : {128, 64}) {
+            if (rest >= tile || (fp8 && rest == 64)) continue;
+            const int64_t n = tiles(tile);
+            const int64_t n1 = whole_rounds(n);
+            if (n1 > 0 && n1 < n && n <= 0x7fffffff / 16) f(tile, rest, n);
+        }
+}
 
 // Predicted microseconds per K step (128 bytes of every tile row) of
 // `tiles` tiles of a side, from timings on an MI355X (256 CUs; r = the
@@ -1496,6 +1549,15 @@ Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part
         if (S > 1 && (kind == kBF16 || fp8)) consider(Form{tile, 1, total});
     }
     if (part && !fp8) consider(Form{32, 1, total});
+    if (best.S == 1)
+        remainder_forms(fp8, [&](int side) { return tiles_of(m, l, side); },
+                        [&](int tile, int rest, int64_t n) {
+                            const double us = rest_us(kind, tile, rest, n) * (double)total + 12;
+                            if (us < t) {
+                                t = us;
+                                best = Form{tile, 1, total, rest};
+                            }
+                        });
     return best;
 }
 
@@ -1525,20 +1587,43 @@ struct Operands {
     int64_t ldc;
 };
 
+// Launches `count` tiles of side sub * S::BT, from tile `first` on, in parts of
+// side S::BT (all of them: 0, tiles, 1).
 template <typename P, typename S>
-hipError_t launch_tile(const Operands& o, const Form& f, int64_t total, float* part,
-                       hipStream_t s) {
-    const int64_t tilesM = (o.m + S::BT - 1) / S::BT;
-    const int64_t tilesN = (o.l + S::BT - 1) / S::BT;
+hipError_t launch_part(const Operands& o, const Form& f, int64_t total, float* part, int64_t first,
+                       int64_t count, int sub, hipStream_t s) {
+    const int64_t side = (int64_t)sub * S::BT;
+    const int64_t tilesM = (o.m + side - 1) / side;
+    const int64_t tilesN = (o.l + side - 1) / side;
     auto kern = f.S > 1      ? gemm_kept_kernel<P, S, false, true, true>
                 : total % 2 ? gemm_kept_kernel<P, S, false, true>
                             : gemm_kept_kernel<P, S, false, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * tilesM * tilesN)), dim3(S::kThreads), 0, s,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * count * sub * sub)), dim3(S::kThreads), 0, s,
                        o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp, *o.kept, o.nkept,
                        o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM, (int32_t)tilesN,
-                       CMask{nullptr, 0, 0, 0, 1}, SplitK{part, (int32_t)f.chunk});
-    if (f.S > 1) return launch_split_sum(part, f.S, o.m, o.l, o.scale, o.C, o.ldc, s);
+                       CMask{nullptr, 0, 0, 0, 1}, SplitK{part, (int32_t)f.chunk},
+                       Part{(int32_t)first, sub});
     return hipGetLastError();
+}
+
+template <typename P, typename S>
+hipError_t launch_tile(const Operands& o, const Form& f, int64_t total, float* part,
+                       hipStream_t s) {
+    const int64_t tiles = tiles_of(o.m, o.l, S::BT);
+    if constexpr (S::BT > 64) {
+        if (f.rest) {
+            const int64_t n1 = whole_rounds(tiles);
+            const hipError_t e = launch_part<P, S>(o, f, total, part, 0, n1, 1, s);
+            if (e != hipSuccess) return e;
+            if constexpr (S::BT == 256)
+                if (f.rest == 128)
+                    return launch_part<P, Tile128>(o, f, total, part, n1, tiles - n1, 2, s);
+            return launch_part<P, Tile64>(o, f, total, part, n1, tiles - n1, S::BT / 64, s);
+        }
+    }
+    const hipError_t e = launch_part<P, S>(o, f, total, part, 0, tiles, 1, s);
+    if (e != hipSuccess || f.S == 1) return e;
+    return launch_split_sum(part, f.S, o.m, o.l, o.scale, o.C, o.ldc, s);
 }
 
 template <typename P>
@@ -1557,19 +1642,22 @@ hipError_t launch_form(const Operands& o, float* part, size_t part_bytes, hipStr
     return hipGetLastError();
 }
 
+// As launch_part, tb = tiles of side sub * S::BT per C block side.
 template <typename S>
-hipError_t launch_cmask_tile(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
-                             int64_t m, int64_t l, int32_t bp, const CMask& cm, int64_t tilesM,
-                             int64_t tilesN, float* C, int64_t ldc, hipStream_t s) {
+hipError_t launch_cmask_part(const float* At, int64_t ldat, const float* Bt, int64_t ldbt,
+                             int64_t m, int64_t l, int32_t bp, const CMask& cm, int64_t nbI,
+                             int64_t first, int64_t count, int sub, float* C, int64_t ldc,
+                             hipStream_t s) {
     BlockList none;
     for (int j = 0; j < OS_MAX_BLOCKS; ++j) none.idx[j] = 0;
     // a tile's step count is (its kept blocks) * bp / 32: always even when
     // bp / 32 is, and then the unmasked pair loop serves every tile
     auto kern = (bp / 32) % 2 == 0 ? gemm_kept_kernel<PrecF32, S, true, false>
                                    : gemm_kept_kernel<PrecF32, S, true, true>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tilesM * tilesN)), dim3(S::kThreads), 0, s, At, ldat,
-                       Bt, ldbt, m, l, bp, none, 0, (int64_t)0, 1.0f, C, ldc, (int32_t)tilesM,
-                       (int32_t)tilesN, cm, SplitK{nullptr, 0});
+    hipLaunchKernelGGL(kern, dim3((unsigned)(count * sub * sub)), dim3(S::kThreads), 0, s, At, ldat,
+                       Bt, ldbt, m, l, bp, none, 0, (int64_t)0, 1.0f, C, ldc,
+                       (int32_t)(nbI * cm.tb), (int32_t)(cm.nbJ * cm.tb), cm, SplitK{nullptr, 0},
+                       Part{(int32_t)first, sub});
     return hipGetLastError();
 }
 
@@ -1596,12 +1684,15 @@ hipError_t launch_gemm_cmask(const float* At, int64_t ldat, const float* Bt, int
     if (!plan_gemm_ok(m, l, bp, ldat, ldbt, 4) || cblk < 1 || nst < 1 || nst > OS_MAX_BLOCKS)
         return hipErrorInvalidValue;
     const int64_t nbI = (m + cblk - 1) / cblk, nbJ = (l + cblk - 1) / cblk;
-    // the tile side predicted fastest (every entry's sum is the same for all)
-    int side = 0;
+    // the form predicted fastest (every entry's sum is the same for all)
+    auto tiles = [&](int side) -> int64_t {
+        const int64_t tb = (cblk + side - 1) / side;
+        return nbI * tb * nbJ * tb;
+    };
+    int side = 0, rest = 0;
     double t = 0;
     for (const int tile : {256, 128, 64}) {
-        const int64_t tb = (cblk + tile - 1) / tile;
-        const int64_t live = nbI * tb * nbJ * tb;
+        const int64_t live = tiles(tile);
         if (live > 0x7fffffff || nbJ > 0x7fffffff) continue;
         const double us = step_us(kF32, tile, live);
         if (!side || us < t) {
@@ -1610,16 +1701,26 @@ hipError_t launch_gemm_cmask(const float* At, int64_t ldat, const float* Bt, int
         }
     }
     if (!side) return hipErrorInvalidValue;
-    const int64_t tb = (cblk + side - 1) / side;
-    const CMask cm{cmask, cblk, (int32_t)nbJ, nst, (int32_t)tb};
-    if (side == 256)
-        return launch_cmask_tile<Tile256>(At, ldat, Bt, ldbt, m, l, bp, cm, nbI * tb, nbJ * tb, C,
-                                          ldc, s);
-    if (side == 128)
-        return launch_cmask_tile<Tile128>(At, ldat, Bt, ldbt, m, l, bp, cm, nbI * tb, nbJ * tb, C,
-                                          ldc, s);
-    return launch_cmask_tile<Tile64>(At, ldat, Bt, ldbt, m, l, bp, cm, nbI * tb, nbJ * tb, C, ldc,
-                                     s);
+    remainder_forms(false, tiles, [&](int tile, int part, int64_t n) {
+        const double us = rest_us(kF32, tile, part, n);
+        if (us < t) {
+            t = us;
+            side = tile;
+            rest = part;
+        }
+    });
+    const int64_t n = tiles(side);
+    const CMask cm{cmask, cblk, (int32_t)nbJ, nst, (int32_t)((cblk + side - 1) / side)};
+    auto run = [&](int bt, int64_t first, int64_t count, int sub) {
+        auto launch = bt == 256   ? launch_cmask_part<Tile256>
+                      : bt == 128 ? launch_cmask_part<Tile128>
+                                  : launch_cmask_part<Tile64>;
+        return launch(At, ldat, Bt, ldbt, m, l, bp, cm, nbI, first, count, sub, C, ldc, s);
+    };
+    if (!rest) return run(side, 0, n, 1);
+    const int64_t n1 = whole_rounds(n);
+    const hipError_t e = run(side, 0, n1, 1);
+    return e != hipSuccess ? e : run(rest, n1, n - n1, side / rest);
 }
 
 hipError_t launch_gemm_batch_sym(const BatchProblem* probs, const int4* tiles,
@@ -1660,11 +1761,13 @@ int batch_sym_blocks_per_cu(int tile) {
 
 namespace {
 
+// (As launch_part and launch_tile.)
 template <typename S, bool kPair>
-hipError_t launch_fp8_tile(const Operands& o, int64_t scales, const Form& f, int64_t total,
-                           float* part, hipStream_t s) {
-    const int64_t tilesM = (o.m + S::BT - 1) / S::BT;
-    const int64_t tilesN = (o.l + S::BT - 1) / S::BT;
+hipError_t launch_fp8_part(const Operands& o, int64_t scales, const Form& f, int64_t total,
+                           float* part, int64_t first, int64_t count, int sub, hipStream_t s) {
+    const int64_t side = (int64_t)sub * S::BT;
+    const int64_t tilesM = (o.m + side - 1) / side;
+    const int64_t tilesN = (o.l + side - 1) / side;
     // scale chunks: whole chunks per block; 16-byte ones also need 16-byte
     // aligned rows and scale area (with either the step count is even)
     const bool c16 = o.bp % 1024 == 0 && o.ldat % 16 == 0 && o.ldbt % 16 == 0 && scales % 16 == 0;
@@ -1674,13 +1777,28 @@ hipError_t launch_fp8_tile(const Operands& o, int64_t scales, const Form& f, int
                 : c4        ? gemm_kept_fp8d_kernel<S, kPair, false, false, 4>
                 : total % 2 ? gemm_kept_fp8d_kernel<S, kPair, true>
                             : gemm_kept_fp8d_kernel<S, kPair, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * tilesM * tilesN)), dim3(S::kThreads), 0, s,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * count * sub * sub)), dim3(S::kThreads), 0, s,
                        static_cast<const uint8_t*>(o.At), o.ldat,
                        static_cast<const uint8_t*>(o.Bt), o.ldbt, scales, o.m, o.l, o.bp, *o.kept,
                        o.nkept, o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM, (int32_t)tilesN,
-                       SplitK{part, (int32_t)f.chunk});
-    if (f.S > 1) return launch_split_sum(part, f.S, o.m, o.l, o.scale, o.C, o.ldc, s);
+                       SplitK{part, (int32_t)f.chunk}, Part{(int32_t)first, sub});
     return hipGetLastError();
+}
+
+template <typename S, bool kPair>
+hipError_t launch_fp8_tile(const Operands& o, int64_t scales, const Form& f, int64_t total,
+                           float* part, hipStream_t s) {
+    const int64_t tiles = tiles_of(o.m, o.l, S::BT);
+    if (f.rest) {                                     // (256 and 128 tiles only)
+        const int64_t n1 = whole_rounds(tiles);
+        const hipError_t e = launch_fp8_part<S, kPair>(o, scales, f, total, part, 0, n1, 1, s);
+        if (e != hipSuccess) return e;
+        return launch_fp8_part<Tile128, kPair>(o, scales, f, total, part, n1, tiles - n1,
+                                               S::BT / 128, s);
+    }
+    const hipError_t e = launch_fp8_part<S, kPair>(o, scales, f, total, part, 0, tiles, 1, s);
+    if (e != hipSuccess || f.S == 1) return e;
+    return launch_split_sum(part, f.S, o.m, o.l, o.scale, o.C, o.ldc, s);
 }
 
 template <bool kPair>

@@ -651,6 +651,45 @@ def test_block_product_tile_forms(m, l, precision, b, nst):
                                   host(C[:k]))
 
 
+@pytest.mark.parametrize("m,l", [(4500, 4200), (5120, 5000), (16385, 1023), (2200, 2300)])
+@pytest.mark.parametrize("precision,b,nst", [("fp32", 64, 5), ("bf16", 64, 9), ("bf16x3", 128, 4),
+                                             ("fp8", 128, 12), ("fp8x3", 256, 4)])
+def test_block_product_last_round(m, l, precision, b, nst):
+    """Products of some whole rounds of tiles and a part of one, run as smaller
+    tiles: bit for bit the rows and columns of smaller products; the masked
+    form's the product's of the blocks it keeps."""
+    g = torch.Generator(device="cuda").manual_seed(m + l)
+    w = nst * osk.block_stride(b)
+    At, Bt = (torch.randn(r, w, generator=g, device="cuda") for r in (m, l))
+    if precision != "fp32":
+        At, Bt = (osk.sketch_quantize(S, b, nst, precision) for S in (At, Bt))
+    C = osk.gemm_kept_prec(At, Bt, b, nst, precision)
+    for r0, r1, c0, c1 in ((0, 700, 0, l), (m - 300, m, 0, l), (0, m, l - 130, l), (0, m, 0, 257)):
+        part = osk.gemm_kept_prec(At[r0:r1], Bt[c0:c1], b, nst, precision)
+        assert torch.equal(C[r0:r1, c0:c1], part), (r0, r1, c0, c1)
+
+
+@pytest.mark.parametrize("t,u,b", [(10, 10, 512), (9, 7, 600), (20, 3, 300)])
+def test_masked_product_last_round(t, u, b):
+    """The per-block masked product over part of a last round: each C block is
+    that of a product over the blocks it keeps, bit for bit."""
+    N, n = 4, 1000
+    m, l = t * b - 40, u * b - 7
+    A, B = synthetic.gaussian_pair(m, n, l, m)
+    Ad, Bd = dev(A), dev(B)
+    rng = np.random.default_rng(t)
+    cmask = (rng.random((t, u, N)) < 0.6).astype(np.uint8)
+    C = osk.matmul_cmask(Ad, Bd, b, N, 0, cmask, seed=2)
+    At, Bt = osk.sketch_cols(Ad, b, N, 0, seed=2), osk.sketch_rows(Bd, b, N, 0, seed=2)
+    for I, J in [(0, 0), (t - 1, u - 1), (t // 2, 0), (t - 1, 0), (t - 2, u - 1)]:
+        rows, cols = slice(I * b, min(m, (I + 1) * b)), slice(J * b, min(l, (J + 1) * b))
+        if cmask[I, J].any():
+            want = osk.gemm_kept_prec(At[rows], Bt[cols], b, N, "fp32", keep=cmask[I, J])
+        else:
+            want = torch.zeros_like(C[rows, cols])
+        assert torch.equal(C[rows, cols], want), (I, J)
+
+
 @pytest.mark.parametrize("m,n,l,b,N", [(33, 500, 31, 40, 3), (130, 1024, 200, 128, 4),
                                        (700, 900, 400, 96, 3), (60, 2000, 4100, 256, 2)])
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
