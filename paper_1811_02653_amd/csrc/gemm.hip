@@ -135,6 +135,25 @@ __device__ __forceinline__ int pair_frag_off(int rbase, int q, int lane) {
     return rbase * 32 + 4 * ((4 * (q >> 1) + 2 * (lane >> 5) + (q & 1)) ^ chunk_key(rbase));
 }
 
+// Waits until at most kLoads of this wave's loads (the youngest) and none of
+// its LDS accesses are outstanding, then for the workgroup's other waves.
+// (__syncthreads() would wait for every load in flight, also those into LDS
+// meant for later steps; the fence keeps later LDS reads below the barrier.)
+template <int kLoads>
+__device__ __forceinline__ void wait_step() {
+    static_assert(kLoads >= 0 && kLoads < 64);
+    if constexpr (kLoads == 0) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    } else {
+#if defined(__HIP_DEVICE_COMPILE__)
+        __builtin_amdgcn_s_waitcnt((kLoads & 15) | ((kLoads >> 4) << 14) | 0x70);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+#endif
+    }
+}
+
 __device__ __forceinline__ float comp(const float4& v, int c) {
     return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
 }
@@ -271,8 +290,15 @@ using Tile256 = Tile<256, 2, 4, 2>;
 using Tile128 = Tile<128, 2, 2, 2>;
 using Tile64 = Tile<64, 2, 2, 4>;
 
-template <typename P, typename S, bool kMask, bool kOdd, bool kSplit = false>
-__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kEu, S::kEu)))
+//
+// Deep kernels (kDeep): a ring of four step buffers instead of two, loads
+// issued three steps ahead, each step waiting for its own loads only.  For
+// products with at most one workgroup per CU, whose short steps otherwise
+// wait for the latency of a load each.  Steps run in fours, the last ones
+// (any count) singly; the sums are the same.
+template <typename P, typename S, bool kMask, bool kOdd, bool kSplit = false, bool kDeep = false>
+__global__ __launch_bounds__(S::kThreads)
+__attribute__((amdgpu_waves_per_eu(kDeep ? S::kEu / 2 : S::kEu, kDeep ? S::kEu / 2 : S::kEu)))
 void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __restrict__ Bt,
                       int64_t ldbt, int64_t m, int64_t l, int32_t bp, BlockList kept,
                       int32_t nkept, int64_t lo_off, float scale,
@@ -290,6 +316,13 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     __shared__ __align__(1024) float As1[BT * 32];
     __shared__ __align__(1024) float Bs0[BT * 32];
     __shared__ __align__(1024) float Bs1[BT * 32];
+    constexpr int kRing = kDeep ? BT * 32 : 1;
+    __shared__ __align__(1024) float As2[kRing];
+    __shared__ __align__(1024) float As3[kRing];
+    __shared__ __align__(1024) float Bs2[kRing];
+    __shared__ __align__(1024) float Bs3[kRing];
+    constexpr int kLead = kDeep ? 3 : 1;         // steps ahead that loads are issued
+    constexpr int kLoads = (kLead - 1) * 2 * kU; // loads of the steps after the next one
     __shared__ int32_t klist[kMask ? OS_MAX_BLOCKS + 1 : 1];   // per-tile kept list, count last
 
     const int tid = threadIdx.x;
@@ -431,8 +464,11 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
     };
 
     issue(As0, Bs0, t_begin);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+    if constexpr (kDeep) {
+        issue(As1, Bs1, min(t_begin + 1, t_end - 1));
+        issue(As2, Bs2, min(t_begin + 2, t_end - 1));
+    }
+    wait_step<kLoads>();
     // (pair steps: fa, fb the high parts' fragments, ga, gb the low parts')
     float4 fa[kI], fb[kJ], ga[kI], gb[kJ];
     if constexpr (P::kPair) {
@@ -467,8 +503,11 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
         P::template mfma_quad<kI, kJ>(acc, a, b);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto kstep = [&](const float* as, const float* bs, float* na, float* nb, int t) {
-        const uint32_t k = step_k(min(t + 1, t_end - 1));
+    // (as, bs: this step's buffers; xa, xb: the next step's; na, nb: those that
+    // are loaded, the next step's unless kDeep)
+    auto kstep = [&](const float* as, const float* bs, const float* xa, const float* xb, float* na,
+                     float* nb, int t) {
+        const uint32_t k = step_k(min(t + kLead, t_end - 1));
         direct_issue<kU>(ra_src, na, va, k, wave);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (P::kPair) {
@@ -490,10 +529,9 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
             __builtin_amdgcn_sched_barrier(0);
             mfma(fa, gb);
             mfma(fa, fb);
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            frag_a(fa, na, 0);
-            frag_b(gb, nb, 2);
+            wait_step<kLoads>();
+            frag_a(fa, xa, 0);
+            frag_b(gb, xb, 2);
             __builtin_amdgcn_sched_barrier(0);
             mfma(ga, fb);
         } else {
@@ -504,21 +542,33 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
             quad(fa, fb, [&] { frag(ga, gb, as, bs, 3); });
             P::template mfma_quad<kI, kJ, 0, kParts - P::kTail>(acc, ga, gb);
             __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            frag(fa, fb, na, nb, 0);
+            wait_step<kLoads>();
+            frag(fa, fb, xa, xb, 0);
             __builtin_amdgcn_sched_barrier(0);
             P::template mfma_quad<kI, kJ, kParts - P::kTail, kParts>(acc, ga, gb);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     int t = t_begin;
-    for (; t + 1 < t_end; t += 2) {
-        kstep(As0, Bs0, As1, Bs1, t);
-        kstep(As1, Bs1, As0, Bs0, t + 1);
-    }
-    if constexpr (kOdd) {
-        if (t < t_end) kstep(As0, Bs0, As1, Bs1, t);
+    if constexpr (kDeep) {
+        for (; t + 3 < t_end; t += 4) {
+            kstep(As0, Bs0, As1, Bs1, As3, Bs3, t);
+            kstep(As1, Bs1, As2, Bs2, As0, Bs0, t + 1);
+            kstep(As2, Bs2, As3, Bs3, As1, Bs1, t + 2);
+            kstep(As3, Bs3, As0, Bs0, As2, Bs2, t + 3);
+        }
+        if (t < t_end) kstep(As0, Bs0, As1, Bs1, As3, Bs3, t);
+        if (t + 1 < t_end) kstep(As1, Bs1, As2, Bs2, As0, Bs0, t + 1);
+        if (t + 2 < t_end) kstep(As2, Bs2, As3, Bs3, As1, Bs1, t + 2);
+        __builtin_amdgcn_s_waitcnt(0);       // no load into LDS outlives the workgroup
+    } else {
+        for (; t + 1 < t_end; t += 2) {
+            kstep(As0, Bs0, As1, Bs1, As1, Bs1, t);
+            kstep(As1, Bs1, As0, Bs0, As0, Bs0, t + 1);
+        }
+        if constexpr (kOdd) {
+            if (t < t_end) kstep(As0, Bs0, As1, Bs1, As1, Bs1, t);
+        }
     }
 
     // 32x32 accumulator layout: register r of lane L holds row
@@ -728,8 +778,10 @@ __device__ __forceinline__ void words(uint32_t (&d)[kN], const uint32_t* p) {
     }
 }
 
-template <typename S, bool kPair, bool kOdd, bool kSplit = false, int kChunk = 0>
-__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <typename S, bool kPair, bool kOdd, bool kSplit = false, int kChunk = 0,
+          bool kDeep = false>
+__global__ __launch_bounds__(S::kThreads)
+__attribute__((amdgpu_waves_per_eu(kDeep ? 1 : 2, kDeep ? 1 : 2)))
 void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
                            const uint8_t* __restrict__ Bt, int64_t ldbt, int64_t scales,
                            int64_t m, int64_t l, int32_t bp, BlockList kept, int32_t nkept,
@@ -743,6 +795,13 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     __shared__ __align__(1024) float As1[BT * 32];
     __shared__ __align__(1024) float Bs0[BT * 32];
     __shared__ __align__(1024) float Bs1[BT * 32];
+    constexpr int kRing = kDeep ? BT * 32 : 1;
+    __shared__ __align__(1024) float As2[kRing];
+    __shared__ __align__(1024) float As3[kRing];
+    __shared__ __align__(1024) float Bs2[kRing];
+    __shared__ __align__(1024) float Bs3[kRing];
+    constexpr int kLead = kDeep ? 3 : 1;         // steps ahead that loads are issued
+    constexpr int kLoads = (kLead - 1) * 2 * kU; // loads of the steps after the next one
     // scale words, two buffers: per row (A's, then B's) a word per loaded
     // part (kWords of them), or 16 bytes per row and loaded part
     constexpr int kWords = kPair ? 2 : 1;
@@ -800,6 +859,10 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
 
     constexpr int kStep = kPair ? 64 : 128;           // code columns per step
     constexpr int kPerChunk = kPair ? kChunk : kChunk / 2;   // steps per scale chunk
+    // kDeep: as in gemm_kept_kernel, scales in chunks of at least four steps: a
+    // chunk is loaded during the first step of the one before it, so that more
+    // than kLoads later loads follow it by the end of that one.
+    static_assert(!kDeep || (!kSplit && kPerChunk >= 4));
     const int tpb = bp / kStep;
     int t_begin = 0;
     int t_end = nkept * tpb;                          // this workgroup's K steps
@@ -950,8 +1013,15 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
         direct_issue<kU>(rb_src, Bs0, vb, k, wave);
         issue_scales(0, k);        // (t_begin is even, and 0 with chunks)
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+    if constexpr (kDeep) {
+        const uint32_t k1 = step_k(min(t_begin + 1, t_end - 1));
+        direct_issue<kU>(ra_src, As1, va, k1, wave);
+        direct_issue<kU>(rb_src, Bs1, vb, k1, wave);
+        const uint32_t k2 = step_k(min(t_begin + 2, t_end - 1));
+        direct_issue<kU>(ra_src, As2, va, k2, wave);
+        direct_issue<kU>(rb_src, Bs2, vb, k2, wave);
+    }
+    wait_step<kLoads>();
     // plain: fa / fan one part's A fragment and the next one's, fb / fbn the
     // parts' B fragments; split: fa / ga one row block's high and low
     // fragments, fan / gan the next one's, fb / fbn the B parts
@@ -970,11 +1040,14 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
     // read during the current one's MFMAs, and part 1's B fragments during
     // part 0's last row block.  Steps run in pairs; an odd last step (kOdd)
     // runs alone after them.
-    auto kstep = [&](const float* as, const float* bs, float* na, float* nb, int nbuf, int t) {
-        const uint32_t k = step_k(min(t + 1, t_end - 1));
+    auto kstep = [&](const float* as, const float* bs, const float* xa, const float* xb, float* na,
+                     float* nb, int nbuf, int t) {
+        const uint32_t k = step_k(min(t + kLead, t_end - 1));
         direct_issue<kU>(ra_src, na, va, k, wave);
         if constexpr (kChunk != 0) {
-            if (t % kPerChunk == 0 && t + kPerChunk < t_end)
+            // (nbuf, kDeep: the step's place in its four; t_begin is 0)
+            if ((!kDeep || nbuf == 0) && t % kPerChunk == 0 &&
+                t + kPerChunk < t_end)
                 issue_scales((t / kPerChunk + 1) & 1, step_k(t + kPerChunk));
         } else {
             issue_scales(nbuf, k);
@@ -1029,23 +1102,36 @@ void gemm_kept_fp8d_kernel(const uint8_t* __restrict__ At, int64_t ldat,
                 }
             }
         }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        fa = frag_a(na, 0, 0);
-        frag_b(fb, nb, 0);
+        wait_step<kLoads>();
+        fa = frag_a(xa, 0, 0);
+        frag_b(fb, xb, 0);
         if constexpr (kPair) {
-            ga = frag_a(na, 1, 0);
-            frag_b(fbn, nb, 1);
+            ga = frag_a(xa, 1, 0);
+            frag_b(fbn, xb, 1);
         }
-        read_scales(min(t + 1, t_end - 1), nbuf, k);
+        const int tn = min(t + 1, t_end - 1);
+        read_scales(tn, nbuf, kDeep ? step_k(tn) : k);
     };
     int t = t_begin;
-    for (; t + 1 < t_end; t += 2) {
-        kstep(As0, Bs0, As1, Bs1, 1, t);
-        kstep(As1, Bs1, As0, Bs0, 0, t + 1);
-    }
-    if constexpr (kOdd) {
-        if (t < t_end) kstep(As0, Bs0, As1, Bs1, 1, t);
+    if constexpr (kDeep) {
+        for (; t + 3 < t_end; t += 4) {
+            kstep(As0, Bs0, As1, Bs1, As3, Bs3, 0, t);
+            kstep(As1, Bs1, As2, Bs2, As0, Bs0, 1, t + 1);
+            kstep(As2, Bs2, As3, Bs3, As1, Bs1, 2, t + 2);
+            kstep(As3, Bs3, As0, Bs0, As2, Bs2, 3, t + 3);
+        }
+        if (t < t_end) kstep(As0, Bs0, As1, Bs1, As3, Bs3, 0, t);
+        if (t + 1 < t_end) kstep(As1, Bs1, As2, Bs2, As0, Bs0, 1, t + 1);
+        if (t + 2 < t_end) kstep(As2, Bs2, As3, Bs3, As1, Bs1, 2, t + 2);
+        __builtin_amdgcn_s_waitcnt(0);       // no load into LDS outlives the workgroup
+    } else {
+        for (; t + 1 < t_end; t += 2) {
+            kstep(As0, Bs0, As1, Bs1, As1, Bs1, 1, t);
+            kstep(As1, Bs1, As0, Bs0, As0, Bs0, 0, t + 1);
+        }
+        if constexpr (kOdd) {
+            if (t < t_end) kstep(As0, Bs0, As1, Bs1, As1, Bs1, 1, t);
+        }
     }
 
     float* out = C;
@@ -1452,6 +1538,7 @@ struct Form {
     int64_t S;
     int64_t chunk;
     int rest = 0;
+    bool deep = false;
 };
 
 // Tiles in whole rounds of the device, of `tiles`.
@@ -1517,13 +1604,39 @@ double step_us(Kind kind, int tile, int64_t tiles) {
     }
 }
 
+// The same for the deep kernels, 0 where there is none or it does not pay:
+// at most one workgroup of 128 tiles, or two of 64, per CU (chunk: bytes per
+// FP8 scale chunk).  Measured us, two step buffers / four, K = 4096 (2048 *):
+//                 512 x 512   1024 x 1024   1500 x 1500   2048 x 2048 *   300 x 6000 *
+//   BF16   128       34/34         49/36         50/37          31/26          28/23
+//           64       38/20         39/22         41/43          31/33          24/18
+//   split  128       97/77        100/80        107/83          66/55          53/44
+//           64       59/34         61/39         92/99          83/79          42/39
+//   FP8    128       25/28         34/31         36/32          24/23          18/20
+//     (blocks of 1024)             32/27                  K = 4096 36/30
+//   split  128       56/51         65/53         70/56          47/38          43/33
+//     (blocks of 1024)             64/49                  K = 4096 77/57
+double deep_us(Kind kind, int tile, int64_t tiles, int chunk) {
+    const bool few = tiles <= 160;
+    if (tiles > (tile == 64 ? 512 : 256) || tile == 256) return 0;
+    switch (kind) {
+        case kBF16:
+            return tile == 64 ? (tiles <= 256 ? 0.28 : 0.45) : (few ? 0.52 : 0.68);
+        case kBF16X3:
+            return tile == 64 ? (tiles <= 256 ? 0.27 : 0.58) : (few ? 0.62 : 0.8);
+        case kFp8: return tile == 128 && chunk == 16 ? (few ? 0.7 : 0.8) : 0;
+        case kFp8X3: return tile == 128 && chunk ? (few ? 0.75 : (chunk == 16 ? 0.83 : 1.0)) : 0;
+        default: return 0;
+    }
+}
+
 // The form predicted fastest.  Without partial space (part = nullptr) every
 // entry is summed in step order whatever the tile, bit for bit the same.
 // Where the split K loop serves a product, FP32 and split BF16 keep its split
 // (the number of partial sums per entry, which their accuracy shows) whatever
 // the tile; the small kernel's waves split the K loop eight ways themselves.
 Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part,
-               size_t part_bytes) {
+               size_t part_bytes, int chunk_bytes = 0) {
     int64_t S = 1, chunk = total;
     if (!split_plan(m, l, total, part, part_bytes, S, chunk)) {
         S = 1;
@@ -1536,7 +1649,9 @@ Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part
         const int64_t tiles = tiles_of(m, l, f.tile) * f.S;
         if (tiles > 0x7fffffff) return;
         // first loads and epilogue; a split's partials written and summed
-        double us = step_us(kind, f.tile, tiles) * (double)f.chunk + (f.tile == 256 ? 6 : 0);
+        double us = (f.deep ? deep_us(kind, f.tile, tiles, chunk_bytes)
+                            : step_us(kind, f.tile, tiles)) * (double)f.chunk +
+                    (f.tile == 256 ? 6 : 0);
         if (f.S > 1) us += 4 + (double)f.S * (double)m * (double)l * 4 / 4e6;
         if (t == 0 || us < t) {
             t = us;
@@ -1546,7 +1661,10 @@ Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part
     for (const int tile : {256, 128, 64}) {
         if (tile == 64 && fp8) continue;
         consider(Form{tile, S, chunk});
-        if (S > 1 && (kind == kBF16 || fp8)) consider(Form{tile, 1, total});
+        const bool whole = S == 1 || kind == kBF16 || fp8;     // (may run unsplit)
+        if (S > 1 && whole) consider(Form{tile, 1, total});
+        if (whole && deep_us(kind, tile, tiles_of(m, l, tile), chunk_bytes) > 0)
+            consider(Form{tile, 1, total, 0, true});
     }
     if (part && !fp8) consider(Form{32, 1, total});
     if (best.S == 1)
@@ -1598,6 +1716,8 @@ hipError_t launch_part(const Operands& o, const Form& f, int64_t total, float* p
     auto kern = f.S > 1      ? gemm_kept_kernel<P, S, false, true, true>
                 : total % 2 ? gemm_kept_kernel<P, S, false, true>
                             : gemm_kept_kernel<P, S, false, false>;
+    if constexpr (S::BT < 256 && P::kKind != kF32)
+        if (f.deep) kern = gemm_kept_kernel<P, S, false, true, false, true>;
     hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * count * sub * sub)), dim3(S::kThreads), 0, s,
                        o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp, *o.kept, o.nkept,
                        o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM, (int32_t)tilesN,
@@ -1761,6 +1881,13 @@ int batch_sym_blocks_per_cu(int tile) {
 
 namespace {
 
+// Bytes per scale chunk: whole chunks per block; 16-byte ones also need
+// 16-byte aligned rows and scale area (with either the step count is even).
+int scale_chunk(const Operands& o, int64_t scales) {
+    if (o.bp % 1024 == 0 && o.ldat % 16 == 0 && o.ldbt % 16 == 0 && scales % 16 == 0) return 16;
+    return o.bp % 256 == 0 && o.lo_off % 256 == 0 ? 4 : 0;
+}
+
 // (As launch_part and launch_tile.)
 template <typename S, bool kPair>
 hipError_t launch_fp8_part(const Operands& o, int64_t scales, const Form& f, int64_t total,
@@ -1768,15 +1895,19 @@ hipError_t launch_fp8_part(const Operands& o, int64_t scales, const Form& f, int
     const int64_t side = (int64_t)sub * S::BT;
     const int64_t tilesM = (o.m + side - 1) / side;
     const int64_t tilesN = (o.l + side - 1) / side;
-    // scale chunks: whole chunks per block; 16-byte ones also need 16-byte
-    // aligned rows and scale area (with either the step count is even)
-    const bool c16 = o.bp % 1024 == 0 && o.ldat % 16 == 0 && o.ldbt % 16 == 0 && scales % 16 == 0;
-    const bool c4 = o.bp % 256 == 0 && o.lo_off % 256 == 0;
-    auto kern = f.S > 1     ? gemm_kept_fp8d_kernel<S, kPair, true, true>
-                : c16       ? gemm_kept_fp8d_kernel<S, kPair, false, false, 16>
-                : c4        ? gemm_kept_fp8d_kernel<S, kPair, false, false, 4>
-                : total % 2 ? gemm_kept_fp8d_kernel<S, kPair, true>
-                            : gemm_kept_fp8d_kernel<S, kPair, false>;
+    const int chunk = scale_chunk(o, scales);
+    auto kern = f.S > 1       ? gemm_kept_fp8d_kernel<S, kPair, true, true>
+                : chunk == 16 ? gemm_kept_fp8d_kernel<S, kPair, false, false, 16>
+                : chunk == 4  ? gemm_kept_fp8d_kernel<S, kPair, false, false, 4>
+                : total % 2  ? gemm_kept_fp8d_kernel<S, kPair, true>
+                             : gemm_kept_fp8d_kernel<S, kPair, false>;
+    if constexpr (S::BT == 128) {
+        if (f.deep) {
+            kern = gemm_kept_fp8d_kernel<S, kPair, false, false, 16, true>;
+            if constexpr (kPair)
+                if (chunk == 4) kern = gemm_kept_fp8d_kernel<S, kPair, false, false, 4, true>;
+        }
+    }
     hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * count * sub * sub)), dim3(S::kThreads), 0, s,
                        static_cast<const uint8_t*>(o.At), o.ldat,
                        static_cast<const uint8_t*>(o.Bt), o.ldbt, scales, o.m, o.l, o.bp, *o.kept,
@@ -1805,7 +1936,8 @@ template <bool kPair>
 hipError_t launch_fp8(const Operands& o, int64_t scales, float* part, size_t part_bytes,
                       hipStream_t s) {
     const int64_t total = (int64_t)o.nkept * (o.bp / (kPair ? 64 : 128));
-    const Form f = pick_form(kPair ? kFp8X3 : kFp8, o.m, o.l, total, part, part_bytes);
+    const Form f = pick_form(kPair ? kFp8X3 : kFp8, o.m, o.l, total, part, part_bytes,
+                             scale_chunk(o, scales));
     return f.tile == 256 ? launch_fp8_tile<Tile256, kPair>(o, scales, f, total, part, s)
                          : launch_fp8_tile<Tile128, kPair>(o, scales, f, total, part, s);
 }

@@ -669,6 +669,29 @@ def test_block_product_last_round(m, l, precision, b, nst):
         assert torch.equal(C[r0:r1, c0:c1], part), (r0, r1, c0, c1)
 
 
+@pytest.mark.parametrize("precision,b,nst", [("bf16", 64, k) for k in range(1, 10)] +
+                         [("bf16x3", 64, k) for k in (1, 2, 3, 4, 5)] +
+                         [("fp8", 1024, 1), ("fp8", 1000, 3), ("fp8", 300, 3), ("fp8", 512, 3),
+                          ("fp8x3", 256, 1), ("fp8x3", 250, 2), ("fp8x3", 256, 3),
+                          ("fp8x3", 1024, 1), ("fp8x3", 1000, 2), ("fp8x3", 320, 2)])
+def test_block_product_deep_pipeline(precision, b, nst):
+    """Products of few tiles, with loads three steps ahead, at every remainder
+    of their step count: bit for bit the entries of a product of many tiles."""
+    m, l = 2250, 2200
+    g = torch.Generator(device="cuda").manual_seed(b + nst)
+    w = nst * osk.block_stride(b)
+    At, Bt = (torch.randn(r, w, generator=g, device="cuda") for r in (m, l))
+    At, Bt = (osk.sketch_quantize(S, b, nst, precision) for S in (At, Bt))
+    keeps = [None]
+    if nst > 1:
+        keeps.append([j != 1 for j in range(nst)])
+    for keep in keeps:
+        C = osk.gemm_kept_prec(At, Bt, b, nst, precision, keep=keep)
+        for r, c in ((1, 1), (65, 64), (700, 129), (1000, 2000), (129, l), (2048, 2048)):
+            part = osk.gemm_kept_prec(At[:r], Bt[:c], b, nst, precision, keep=keep)
+            assert torch.equal(C[:r, :c], part), (r, c, keep)
+
+
 @pytest.mark.parametrize("t,u,b", [(10, 10, 512), (9, 7, 600), (20, 3, 300)])
 def test_masked_product_last_round(t, u, b):
     """The per-block masked product over part of a last round: each C block is
