@@ -366,7 +366,7 @@ size_t os_matmul_ex_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, i
         return 0;
     // Sized for all N+e blocks whatever the mask, so one workspace serves
     // every call; an operand whose lines are not rows in memory (a
-    // column-major A, a row-major B) is transposed first, one after the
+    // column-major A, a row-major B) may be transposed first, one after the
     // other, into one buffer; a low-precision product adds the quantized
     // copies of both sketches.
     const int64_t zp = (int64_t)nblocks(sk) * os_block_stride(sk->b);

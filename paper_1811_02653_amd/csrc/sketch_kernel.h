@@ -418,8 +418,8 @@ __device__ __forceinline__ void sketch_tasks(
     //            lanes); the scale bytes follow the codes (ozlo bytes into
     //            the row), in code order; omode 4: then the same for the
     //            residuals (codes, ozlo bytes after the first ones, and scales).
-    // FP8 (a separate instantiation: this code would make the FP32 and BF16
-    // kernels with 20 or more slots spill).  Every lane of the wave holds a
+    // FP8 (separate instantiations: this code would make the FP32 and BF16
+    // kernels with many slots spill).  Every lane of the wave holds a
     // bucket (lim is 64).  The maxima of a group's four lines are taken with
     // DPP moves and read into scalar registers; a lane's four codes (one per
     // line) are packed by the hardware conversion, transposed within each
