@@ -498,3 +498,19 @@ def test_fp8_copies_written_by_the_sketch(m, n, l, b, N, precision):
     if split:
         mag += (np.abs(va[:, :z]) @ np.abs(vb[:, z:]).T + np.abs(va[:, z:]) @ np.abs(vb[:, :z]).T) / N
     assert np.all(np.abs(host(C) - want) <= 2 * mag * (2.0 ** -14 + z * 2.0 ** -24))
+
+
+@pytest.mark.parametrize("b,N", [(128, 2), (1024, 6), (1024, 11), (300, 2)])
+@pytest.mark.parametrize("precision", ["fp8", "fp8x3"])
+@pytest.mark.parametrize("a_cm,b_cm", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_fp8_copies_of_bf16_operands(b, N, precision, a_cm, b_cm):
+    """BF16 operands in every layout, FP8 copies written by the sketch or by
+    the quantization: the product of the same values in FP32, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(b + N)
+    A = torch.randn(260, 3001, generator=g, device="cuda").bfloat16()
+    B = torch.randn(3001, 130, generator=g, device="cuda").bfloat16()
+    Av = A.t().contiguous().t() if a_cm else A
+    Bv = B.t().contiguous().t() if b_cm else B
+    got = osk.matmul_ex(Av, Bv, b, N, 0, seed=2, precision=precision)
+    want = osk.matmul_ex(A.float(), B.float(), b, N, 0, seed=2, precision=precision)
+    assert torch.equal(got, want)
