@@ -1538,25 +1538,31 @@ struct Form {
     int64_t S;
     int64_t chunk;
     int rest = 0;
-    bool deep = false;
+    bool deep = false;         // the deep kernel (rest: for those tiles only)
 };
 
 // Tiles in whole rounds of the device, of `tiles`.
 int64_t whole_rounds(int64_t tiles) { return tiles / kSplitSlots * kSplitSlots; }
 
 // Predicted us per K step of `tiles` tiles of side f.tile, those past the
-// whole rounds as tiles of side f.rest in a launch of their own.  (A product
+// whole rounds as tiles of side f.rest in a launch of their own (f.deep: by the
+// deep kernel).  (A product
 // of a few more than a multiple of 256 tiles leaves most CUs idle in its last
 // round, and smaller tiles throughout cost 8 % (FP32) to 80 % (BF16) more LDS
 // and L2 traffic.  K = 4096, us without / with: 5120 x 5120 FP32 1523 / 1473;
 // 4500 x 4200 BF16 168 / 162, split BF16 475 / 410, FP8 120 / 109, split FP8
-// 259 / 226; 7000 x 8000 split BF16 1080 / 1054, FP8 246 / 238.)
+// 259 / 226; 7000 x 8000 split BF16 1080 / 1054, FP8 246 / 238; with deep
+// kernels for the rest 4500 x 4200 BF16 156, split BF16 394, split FP8 221.)
 double step_us(Kind kind, int tile, int64_t tiles);
+double deep_us(Kind kind, int tile, int64_t tiles, int chunk);
 
-double rest_us(Kind kind, int tile, int rest, int64_t tiles) {
+double rest_us(Kind kind, int tile, int rest, int64_t tiles, int chunk, bool* deep) {
     const int64_t n1 = whole_rounds(tiles);
     const int64_t sub = tile / rest;
-    return step_us(kind, tile, n1) + step_us(kind, rest, (tiles - n1) * sub * sub);
+    const int64_t n2 = (tiles - n1) * sub * sub;
+    const double us = step_us(kind, rest, n2), d = deep_us(kind, rest, n2, chunk);
+    *deep = d > 0 && d < us;
+    return step_us(kind, tile, n1) + (*deep ? d : us);
 }
 
 // f(tile, rest) for every remainder form of a product with tiles(side) tiles.
@@ -1670,10 +1676,13 @@ Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part
     if (best.S == 1)
         remainder_forms(fp8, [&](int side) { return tiles_of(m, l, side); },
                         [&](int tile, int rest, int64_t n) {
-                            const double us = rest_us(kind, tile, rest, n) * (double)total + 12;
+                            bool deep;
+                            const double us =
+                                rest_us(kind, tile, rest, n, chunk_bytes, &deep) * (double)total +
+                                12;
                             if (us < t) {
                                 t = us;
-                                best = Form{tile, 1, total, rest};
+                                best = Form{tile, 1, total, rest, deep};
                             }
                         });
     return best;
@@ -1717,7 +1726,8 @@ hipError_t launch_part(const Operands& o, const Form& f, int64_t total, float* p
                 : total % 2 ? gemm_kept_kernel<P, S, false, true>
                             : gemm_kept_kernel<P, S, false, false>;
     if constexpr (S::BT < 256 && P::kKind != kF32)
-        if (f.deep) kern = gemm_kept_kernel<P, S, false, true, false, true>;
+        if (f.deep && (!f.rest || sub > 1))
+            kern = gemm_kept_kernel<P, S, false, true, false, true>;
     hipLaunchKernelGGL(kern, dim3((unsigned)(f.S * count * sub * sub)), dim3(S::kThreads), 0, s,
                        o.At, o.ldat, o.Bt, o.ldbt, o.m, o.l, o.bp, *o.kept, o.nkept,
                        o.lo_off, o.scale, o.C, o.ldc, (int32_t)tilesM, (int32_t)tilesN,
@@ -1822,7 +1832,8 @@ hipError_t launch_gemm_cmask(const float* At, int64_t ldat, const float* Bt, int
     }
     if (!side) return hipErrorInvalidValue;
     remainder_forms(false, tiles, [&](int tile, int part, int64_t n) {
-        const double us = rest_us(kF32, tile, part, n);
+        bool deep;
+        const double us = rest_us(kF32, tile, part, n, 0, &deep);
         if (us < t) {
             t = us;
             side = tile;
@@ -1902,7 +1913,7 @@ hipError_t launch_fp8_part(const Operands& o, int64_t scales, const Form& f, int
                 : total % 2  ? gemm_kept_fp8d_kernel<S, kPair, true>
                              : gemm_kept_fp8d_kernel<S, kPair, false>;
     if constexpr (S::BT == 128) {
-        if (f.deep) {
+        if (f.deep && (!f.rest || sub > 1)) {
             kern = gemm_kept_fp8d_kernel<S, kPair, false, false, 16, true>;
             if constexpr (kPair)
                 if (chunk == 4) kern = gemm_kept_fp8d_kernel<S, kPair, false, false, 4, true>;
