@@ -42,7 +42,7 @@ METRIC = "sketched AB eff. TFLOP/s (2mnl/t) at fixed rel-Frob err vs exact GEMM,
 # kernel source it was measured on (SHA-256 of that source, see
 # gemm_kept_source_sha); None otherwise.
 GEMM_TRAFFIC = {
-    "source_sha256": "e2ed55fd7fa4ba4e5144bf06b5765ef246328f49fdb4244231ba31f80eedfa37",
+    "source_sha256": "cb24e04eb6b4f29028dcfbb6b9c15d37c31bec74bbcdc56f5d20c001e7c5a97e",
     "workload": (8192, 32768, 8192, 1024, 8, 2),
     "fetch_kib": 1573064.0, "fetch_scale": 2.000,
     "write_kib": 262144.0, "write_scale": 1.000,

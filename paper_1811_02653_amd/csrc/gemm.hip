@@ -599,12 +599,16 @@ void gemm_kept_kernel(const void* __restrict__ At, int64_t ldat, const void* __r
 // its kSmallWaves waves (wave w takes steps w, w + kSmallWaves, ...), each
 // wave's fragments loaded straight from the sketches into registers (a lane
 // reads the 64 bytes of its row that its half of a step uses), the waves'
-// partial tiles added in wave order through LDS.  Bound by latency: a product
+// partial tiles added in wave order through LDS; a wave sums even and odd
+// quads apart (16 partial sums per entry: 600 x 300 over K = 832 FP32, relative
+// error 1.84e-7 with 8, 1.39e-7, where the split K loop has 1.53e-7; the same
+// time).  Bound by latency: a product
 // of one or a few 256 tiles has too little work for tiles staged through LDS
 // and a second launch for the sum of split partials.  (96 x 128 over K =
 // 512: 26.4 us as one 256 tile split 8 ways and its sum, 7.1 us.)
 // ---------------------------------------------------------------------------
 constexpr int kSmallWaves = 8;
+constexpr int kSmallSums = 2 * kSmallWaves;     // partial sums per entry
 constexpr int kSmallTile = 32;
 
 template <typename P>
@@ -650,13 +654,15 @@ void gemm_small_kernel(const void* __restrict__ At, int64_t ldat, const void* __
             b[q] = *reinterpret_cast<const float4*>(pb + at);
         }
     };
-    v16f acc[1][1];
+    v16f acc[2][1][1];            // even and odd quads
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[h][0][0][r] = 0.f;
     auto sum = [&](const float4 (&a)[4], const float4 (&b)[4]) {
         auto term = [&](int qa, int qb) {
             const float4 x[1] = {a[qa]}, y[1] = {b[qb]};
-            P::template mfma_quad<1, 1>(acc, x, y);
+            P::template mfma_quad<1, 1>(acc[qa & 1], x, y);
         };
         if constexpr (P::kPair) {
 #pragma unroll
@@ -686,7 +692,7 @@ void gemm_small_kernel(const void* __restrict__ At, int64_t ldat, const void* __
 #pragma unroll
     for (int r = 0; r < 16; ++r)
         red[wave][(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kSmallTile + (lane & 31)] =
-            acc[0][0][r];
+            acc[0][0][0][r] + acc[1][0][0][r];
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kSmallTile * kSmallTile / (64 * kSmallWaves); ++u) {
@@ -1640,7 +1646,7 @@ double deep_us(Kind kind, int tile, int64_t tiles, int chunk) {
 // entry is summed in step order whatever the tile, bit for bit the same.
 // Where the split K loop serves a product, FP32 and split BF16 keep its split
 // (the number of partial sums per entry, which their accuracy shows) whatever
-// the tile; the small kernel's waves split the K loop eight ways themselves.
+// the tile, and take the small kernel only if that has as many.
 Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part,
                size_t part_bytes, int chunk_bytes = 0) {
     int64_t S = 1, chunk = total;
@@ -1672,7 +1678,7 @@ Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part
         if (whole && deep_us(kind, tile, tiles_of(m, l, tile), chunk_bytes) > 0)
             consider(Form{tile, 1, total, 0, true});
     }
-    if (part && !fp8) consider(Form{32, 1, total});
+    if (part && !fp8 && (kind == kBF16 || S <= kSmallSums)) consider(Form{32, 1, total});
     if (best.S == 1)
         remainder_forms(fp8, [&](int side) { return tiles_of(m, l, side); },
                         [&](int tile, int rest, int64_t n) {
