@@ -317,7 +317,8 @@ size_t os_matmul_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, int6
  * skips the dropped blocks already in the sketch step.  C: DEVICE m x l
  * (ldc).  workspace: DEVICE, 256-byte aligned, >= os_matmul_workspace_bytes
  * for the same b_col_major.  Enqueues: prepare, sketch of A, (transpose of
- * a row-major B,) sketch of B, block product.  A row-major B of at least 4
+ * a row-major B,) sketch of B (with A's in one launch where that is faster),
+ * block product.  A row-major B of at least 4
  * columns has them sketched in place (no transpose; the same sums).  A product
  * of at most 128 tiles of 256 x 256 may split its block product's K loop over
  * several workgroups per tile (partials in the workspace) or over the waves
@@ -347,7 +348,7 @@ size_t os_matmul_prec_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n,
  * is precision OS_PREC_FP32): prepare, sketch of A, (transpose of a
  * row-major B,) sketch of B, quantization of both sketches as
  * os_sketch_quantize does it, block product.  The BF16 forms always, and
- * plain FP8 when b rounded up to 64 is a multiple of 128 and each wave of
+ * FP8 (plain and split) when b rounded up to 64 is a multiple of 128 and each wave of
  * the sketch holds at most 10 groups of 64 buckets per pass, quantize in
  * the sketch itself (same values, no FP32 sketch written).  Arguments as in os_matmul;
  * workspace >= os_matmul_prec_workspace_bytes for the same b_col_major and
@@ -385,8 +386,8 @@ size_t os_matmul_ex_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, i
  * (a_col_major = 1, at A[k*lda + r], lda >= m); B n x l as in os_matmul.
  * a_dtype / b_dtype: OS_DTYPE_F32 or OS_DTYPE_BF16 (2-byte aligned, ld in
  * values), in either layout.  The columns of an FP32 column-major A or
- * row-major B (at least 4 of them) are read in place; BF16 ones are first
- * transposed into the workspace.  BF16 values are converted exactly to FP32 as
+ * row-major B (at least 4 of them) are read in place; BF16 ones are, 8 at a
+ * time, where that is faster, else first transposed into the workspace.  BF16 values are converted exactly to FP32 as
  * the sketch reads them, so the result equals that of the FP32 path on the
  * converted values, bit for bit.  With A = X^T for a row-major X (n x m: A is
  * X read as column-major) and B = dY this is the sketched weight gradient of
