@@ -95,7 +95,8 @@ __global__ __launch_bounds__(256) void quant_fp8_kernel(const float* __restrict_
     const int64_t zq = (int64_t)nst * bq;               // codes of the high part
     const int64_t width = zq * (split ? 2 : 1);
     const int64_t kb_per_row = zq / kFp8Block;
-    const int64_t t = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int64_t t =
+        ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (threadIdx.x >> 4);
     if (t >= kb_per_row * lines) return;                // (uniform over the 16 lanes)
     const int sub = threadIdx.x & 15;
     const int64_t row = t / kb_per_row;
@@ -155,11 +156,14 @@ hipError_t launch_quant_fp8(const float* S, int64_t lines, int64_t lds, int32_t 
     const int32_t bp = (int32_t)round_up(b, kBlockAlign);
     const int32_t bq = block_stride_fp8(b);
     const int64_t items = lines * ((int64_t)nst * bq / kFp8Block);
-    const int64_t grid = (items + 15) / 16;
-    if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    // (a launch holds fewer than 2^32 threads along x: 2^34 values, 64 GiB of sketch)
+    const int64_t groups = (items + 15) / 16;
+    const int64_t gx = groups < (1 << 23) ? groups : 1 << 23;
+    const int64_t gy = (groups + gx - 1) / gx;
+    if (gy > 65535) return hipErrorInvalidValue;
     const int vec = (reinterpret_cast<uintptr_t>(S) & 15) == 0 && (lds & 3) == 0;
-    hipLaunchKernelGGL(quant_fp8_kernel, dim3((unsigned)grid), dim3(256), 0, s, S, lines, lds, b,
-                       bp, bq, nst, split, vec, static_cast<uint8_t*>(Q), ldq);
+    hipLaunchKernelGGL(quant_fp8_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, S,
+                       lines, lds, b, bp, bq, nst, split, vec, static_cast<uint8_t*>(Q), ldq);
     return hipGetLastError();
 }
 

@@ -514,3 +514,20 @@ def test_fp8_copies_of_bf16_operands(b, N, precision, a_cm, b_cm):
     got = osk.matmul_ex(Av, Bv, b, N, 0, seed=2, precision=precision)
     want = osk.matmul_ex(A.float(), B.float(), b, N, 0, seed=2, precision=precision)
     assert torch.equal(got, want)
+
+
+def test_quantize_fp8_of_a_huge_sketch():
+    """A sketch of 2^34 values (64 GiB): at a thread per 4 values one more than
+    a one-dimensional launch holds."""
+    lines, b = (1 << 24), 1024
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GiB of free device memory")
+    torch.cuda.empty_cache()
+    S = torch.zeros(lines, b, device="cuda")
+    rows = [0, lines // 2 - 1, lines // 2, lines - 1]
+    S[rows] = torch.randn(4, b, generator=torch.Generator().manual_seed(3)).cuda()
+    Q = osk.sketch_quantize(S, b, 1, "fp8")
+    assert torch.equal(Q[rows], osk.sketch_quantize(S[rows], b, 1, "fp8"))
+    assert int((Q[::4099, :b] != 0).sum()) == int((Q[0, :b] != 0).sum())     # row 0 is one of them
+    del S, Q
+    torch.cuda.empty_cache()
