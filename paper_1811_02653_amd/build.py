@@ -21,7 +21,8 @@ CEIL_OUT = os.path.join(HERE, "libosk_ceilings.so")
 BUILD = os.path.join(os.path.dirname(HERE), "_build")
 SOURCES = ["sketch_rows.hip", "sketch_columns.hip", "sketch_weighted.hip", "sketch_bf16.hip",
            "sketch_fp8.hip", "sketch_fp8x3.hip", "sketch_pair.hip", "sketch_pair_bf16.hip",
-           "sketch_pair_fp8.hip", "sketch_pair_fp8x3.hip", "sketch.hip", "gemm.hip", "hash.hip",
+           "sketch_pair_fp8.hip", "sketch_pair_fp8x3.hip", "sketch_short.hip", "sketch.hip",
+           "gemm.hip", "hash.hip",
            "quant.hip", "api.hip", "gram.hip", "noalloc.hip"]
 CEIL_SOURCES = ["ceilings.hip"]
 ARCH = "gfx950"

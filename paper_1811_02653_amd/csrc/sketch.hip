@@ -651,49 +651,6 @@ ListView carve_lists(void* lists, int32_t nblk, int64_t n, int32_t bp) {
     return v;
 }
 
-// Sketch of an operand too short for the sketch kernel's loads of 4 values
-// (rows of fewer than 4 values, fewer than 4 columns): a wave per line and
-// group of 64 buckets, each lane adding its bucket's entries one at a time,
-// the same sums in the same order.  Output modes 0 to 2 of sketch_kernel.
-template <typename TI>
-__global__ __launch_bounds__(64) void sketch_cell_kernel(
-    const TI* __restrict__ X, int row_lines, int64_t n, int64_t ldx, int32_t bp, int32_t qn,
-    int32_t nwin, BlockList bl, int64_t RC, const uint32_t* __restrict__ hdr,
-    const uint4* __restrict__ ell, void* __restrict__ out, int64_t ldo,
-    const float* __restrict__ wd, int32_t obp, int32_t omode, int64_t ozlo) {
-    const int lane = threadIdx.x;
-    const int64_t line = blockIdx.x;
-    const int q = blockIdx.y, j = blockIdx.z;
-    const int64_t i = bl.idx[j];
-    float acc = 0.f;
-    for (int w = 0; w < nwin; ++w) {
-        const uint32_t h = hdr[(i * nwin + w) * qn + q];
-        const uint4* list = ell + ((i * nwin + w) * RC + (h & 0xFFFFu)) * 64 + lane;
-        for (uint32_t c = 0; c < h >> 16; ++c) {
-            const uint4 e = list[(int64_t)c * 64];
-            const uint32_t words[4] = {e.x, e.y, e.z, e.w};
-            for (int t = 0; t < 8; ++t) {
-                const uint32_t v = words[t >> 1] >> (16 * (t & 1)) & 0xFFFFu;
-                const int slot = v & 0x7FFFu;
-                if (slot == kPad) continue;
-                const int64_t k = (int64_t)w * kWin + slot_pos(slot);
-                float x = (float)X[row_lines ? line * ldx + k : k * ldx + line];
-                if (wd) x *= sqrtf(wd[k]);
-                acc = fmaf(v & 0x8000u ? -1.f : 1.f, x, acc);
-            }
-        }
-    }
-    if (lane >= min(64, obp - 64 * q)) return;
-    const int64_t o = line * ldo + (int64_t)j * obp + 64 * q + lane;
-    if (omode == 0) {
-        static_cast<float*>(out)[o] = acc;
-    } else {
-        const __bf16 hi = (__bf16)acc;
-        static_cast<__bf16*>(out)[o] = hi;
-        if (omode == 2) static_cast<__bf16*>(out)[o + ozlo] = (__bf16)(acc - (float)hi);
-    }
-}
-
 // Compute units of the current device (0 if unknown).
 int device_cus() {
     int dev = 0, cus = 0;
@@ -741,21 +698,19 @@ hipError_t launch_sketch(bool row_lines, const void* X, bool bf16, int64_t lines
     if (out_mode < 0 || out_mode > 4) return hipErrorInvalidValue;
     const int32_t obp = out_mode ? p.qn * 64 : bp;
     const int64_t ozlo = out_mode >= 2 ? (int64_t)nst * obp : 0;
-    const SketchArgs a{X,     lines, n,   ldx, bp,    p.qn, p.nwin, nst,      &bl, p.RC,
-                       v.hdr, v.ell, out, ldo, npass, wd,   obp,    out_mode, ozlo};
-    if ((wide && (out_mode > 2 || lines < L || slots > kMaxWideSlots)) || ((out_mode >= 3 || bf16) && wd)) return hipErrorInvalidValue;
-    if (row_lines ? n < 4 : lines < 4) {     // too short for loads of 4 values
-        if (out_mode >= 3 || p.qn > 65535 || nst > 65535) return hipErrorInvalidValue;
-        const dim3 cells((unsigned)lines, (unsigned)p.qn, (unsigned)nst);
-        if (bf16)
-            hipLaunchKernelGGL(sketch_cell_kernel<__bf16>, cells, dim3(64), 0, s,
-                               static_cast<const __bf16*>(X), 1, n, ldx, bp, p.qn, p.nwin, bl, p.RC,
-                               v.hdr, v.ell, out, ldo, wd, obp, out_mode, ozlo);
-        else
-            hipLaunchKernelGGL(sketch_cell_kernel<float>, cells, dim3(64), 0, s,
-                               static_cast<const float*>(X), row_lines ? 1 : 0, n, ldx, bp, p.qn,
-                               p.nwin, bl, p.RC, v.hdr, v.ell, out, ldo, wd, obp, out_mode, ozlo);
-        return hipGetLastError();
+    SketchArgs a{X,     lines, n,   ldx,   0,  p.qn, p.nwin,   nst, &bl, p.RC, v.hdr,
+                 v.ell, out,   ldo, npass, wd, obp,  out_mode, ozlo};
+    if ((wide && (out_mode > 2 || lines < L || slots > kMaxWideSlots)) ||
+        ((out_mode >= 3 || bf16) && wd))
+        return hipErrorInvalidValue;
+    if (row_lines ? n < 4 : lines < 4) {     // loads of 4 values would leave the matrix
+        if (out_mode >= 3) return hipErrorInvalidValue;
+        if (!row_lines && n >= 4) return sketch_narrow(slots, grid, s, a);
+        a.ldx = row_lines ? ldx : 1;
+        a.ldk = row_lines ? 1 : ldx;
+        return wd     ? sketch_short_weighted(slots, grid, s, a)
+               : bf16 ? sketch_short_bf16(slots, grid, s, a)
+                      : sketch_short(slots, grid, s, a);
     }
     if (out_mode == 3)
         return bf16        ? sketch_rows_bf16_fp8(slots, grid, s, a)
@@ -977,8 +932,8 @@ bool launch_sketch_pair(bool bf16, const void* A, bool a_rows, int64_t m, int64_
     }
     const ListView v = carve_lists(const_cast<void*>(lists), nblk, n, bp);
     const int32_t obp = out_mode ? p.qn * 64 : bp;
-    const SketchArgs a{nullptr, 0,       n,   0,   bp,    p.qn,    p.nwin, nst,      &bl,
-                       p.RC,    v.hdr,   v.ell, nullptr, ldo, npass, nullptr, obp, out_mode,
+    const SketchArgs a{nullptr, 0,     n,     0,       0,   p.qn,  p.nwin,  nst, &bl,
+                       p.RC,    v.hdr, v.ell, nullptr, ldo, npass, nullptr, obp, out_mode,
                        out_mode >= 2 ? (int64_t)nst * obp : 0};
     const SketchSide x{A, m, lda, outA, (int32_t)wa, a_rows ? 1 : 0};
     const SketchSide y{B, l, ldb, outB, (int32_t)wb, b_rows ? 1 : 0};

@@ -25,11 +25,6 @@ __device__ __forceinline__ int win_slot(int p) {
     return (p & ~4095) | ((p & 3) << 10) | ((p >> 2) & 1023);
 }
 
-// The position of a slot.
-__device__ __forceinline__ int slot_pos(int s) {
-    return (s & ~4095) | ((s & 1023) << 2) | ((s >> 10) & 3);
-}
-
 // f(integral_constant<int, I>) for I = B .. E - 1, unrolled by the compiler
 // whatever the size of f's body.
 template <int B, int E, typename F>

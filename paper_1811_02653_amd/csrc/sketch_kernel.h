@@ -35,6 +35,16 @@ namespace {
 //                      line each (16384 x 4096 into 4 blocks of 512: 85-90
 //                      us, where the transpose and the sketch of its rows
 //                      took 49 + 67).
+// kForm (kRowLines = false), where loads of 4 values would leave the matrix:
+//   kNarrow          : fewer than 4 columns (n >= 4), 16-byte loads as for
+//                      columns, reading on into the next row; those that would
+//                      end past the matrix are repeated by value.
+//                      1000000 x 3 into 2 blocks of 64: 1250 us (a wave per line
+//                      and 64 buckets, gathering from global memory, 6150).
+//   kShort           : rows of fewer than 4 values, and anything as small: every
+//                      value loaded by itself, as FP32, from X[line * ldx + k *
+//                      ldk].  Bound by the writes of the sums (100000 rows of 3
+//                      into 8 blocks of 1024: 700 us, 2700 gathering).
 // kWeighted (row lines): every value at sketched index k is multiplied by
 // sqrt(wd[k]) (a diagonal weight, as in A D^{1/2} S for a Hessian A D A^T);
 // w[u] holds the weights of positions 4t + 4096u .. +3.  The weight is
@@ -138,16 +148,73 @@ __device__ __forceinline__ void load_window(Piece<kRowLines, TI> (&r)[kPerThread
     }
 }
 
+enum Form { kWhole, kNarrow, kShort };
+
+// load_window of a kNarrow kernel (n positions of `lines` columns in all).
+__device__ __forceinline__ void load_narrow(float4 (&r)[kPerThread], const float* __restrict__ X,
+                                            int64_t lines, int64_t n, int64_t ldx, int64_t k0,
+                                            int kw, int p0, int p1) {
+#pragma unroll
+    for (int p = 0; p < kPerThread; ++p) {
+        if (p < p0 || p >= p1) continue;
+        const int64_t k = k0 + min(4 * (int)threadIdx.x + 4096 * (p / 4) + p % 4, kw - 1);
+        const f32x4 t = *reinterpret_cast<const f32x4_any*>(
+            X + min(k * ldx, (n - 1) * ldx + lines - 4));
+        r[p] = make_float4(t[0], t[1], t[2], t[3]);
+    }
+}
+
+// The positions whose loads by load_narrow were moved down, loaded again one
+// value at a time (window from k0 on, the last one).
+__device__ __forceinline__ void reload_narrow(float4 (&r)[kPerThread], const float* __restrict__ X,
+                                              int64_t lines, int64_t n, int64_t ldx, int64_t k0) {
+#pragma unroll
+    for (int p = 0; p < kPerThread; ++p) {
+        const int64_t k = k0 + 4 * (int)threadIdx.x + 4096 * (p / 4) + p % 4;
+        if (k < n && k * ldx > (n - 1) * ldx + lines - 4) {
+            const float* x = X + k * ldx;
+            r[p] = make_float4(x[0], x[min((int64_t)1, lines - 1)], x[lines - 1], 0.f);
+        }
+    }
+}
+
+// load_window of a kShort kernel.
+template <typename TI>
+__device__ __forceinline__ void load_short(float4 (&r)[kPerThread], const TI* __restrict__ X,
+                                           int64_t lines, int64_t ldx, int64_t ldk, int64_t line0,
+                                           int64_t k0, int kw, int p0, int p1) {
+#pragma unroll
+    for (int p = 0; p < kPerThread; ++p) {
+        if (p < p0 || p >= p1) continue;
+        const int64_t k = k0 + min(4 * (int)threadIdx.x + 4096 * (p / 4) + p % 4, kw - 1);
+        auto at = [&](int q) { return (float)X[min(line0 + q, lines - 1) * ldx + k * ldk]; };
+        r[p] = make_float4(at(0), at(1), at(2), at(3));
+    }
+}
+
 __device__ __forceinline__ float comp4(const float4& v, int j) {
     return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
 }
 
 // The weights of this thread's positions of a window, as the loaded quads.
+template <Form kForm>
 __device__ __forceinline__ void load_weights(float4 (&w)[2], const float* __restrict__ wd,
                                              int64_t k0, int kw) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-        w[u] = load_stream(wd + k0 + min(4 * (int)threadIdx.x + 4096 * u, kw - 4));
+    for (int u = 0; u < 2; ++u) {
+        const int t = 4 * (int)threadIdx.x + 4096 * u;
+        if constexpr (kForm == kShort) {
+            auto at = [&](int j) { return wd[k0 + min(t + j, kw - 1)]; };
+            w[u] = make_float4(at(0), at(1), at(2), at(3));
+        } else {
+            w[u] = load_stream(wd + k0 + min(t, kw - 4));
+        }
+    }
+}
+
+__device__ __forceinline__ float4 weigh(float4 v, float w) {
+    const float sw = sqrtf(w);
+    return make_float4(v.x * sw, v.y * sw, v.z * sw, v.w * sw);
 }
 
 // Writes a loaded window of kw positions into LDS: win[win_slot(k)] = the 4
@@ -176,13 +243,7 @@ __device__ __forceinline__ void stage_window(float4* __restrict__ win,
             for (int j = 0; j < 4; ++j) {
                 float4 v = make_float4(R::value(r[u], j), R::value(r[2 + u], j),
                                        R::value(r[4 + u], j), R::value(r[6 + u], j));
-                if constexpr (kWeighted) {
-                    const float sw = sqrtf(comp4(w[u], j));
-                    v.x *= sw;
-                    v.y *= sw;
-                    v.z *= sw;
-                    v.w *= sw;
-                }
+                if constexpr (kWeighted) v = weigh(v, comp4(w[u], j));
                 win[4096 * u + 1024 * j + tid] = v;      // slot of position 4096u + 4t + j
             }
         }
@@ -190,8 +251,11 @@ __device__ __forceinline__ void stage_window(float4* __restrict__ win,
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                win[4096 * u + 1024 * j + tid] = r[4 * u + j];
+            for (int j = 0; j < 4; ++j) {
+                float4 v = r[4 * u + j];
+                if constexpr (kWeighted) v = weigh(v, comp4(w[u], j));
+                win[4096 * u + 1024 * j + tid] = v;
+            }
     }
 }
 
@@ -250,10 +314,10 @@ __device__ __forceinline__ void add_chunk(float4 (&acc)[kQ], const float4* __res
 // sketch of 8192 x 32768 into 10 blocks of 1024 took 506 us from rows and 785
 // from columns, this 486 and 736.)
 // sketch_tasks: the tasks of workgroup wg of nwg (win: its kWin + 1 rows of LDS).
-template <int kSlots, bool kRowLines, bool kWeighted, typename TI, int kFp8Out>
+template <int kSlots, bool kRowLines, bool kWeighted, typename TI, int kFp8Out, Form kForm = kWhole>
 __device__ __forceinline__ void sketch_tasks(
     float4* __restrict__ win, int64_t wg, int64_t nwg, const TI* __restrict__ X, int64_t lines,
-    int64_t n, int64_t ldx, int32_t bp, int32_t qn, int32_t nwin, int32_t nst, const BlockList& bl,
+    int64_t n, int64_t ldx, int64_t ldk, int32_t qn, int32_t nwin, int32_t nst, const BlockList& bl,
     int64_t RC, const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell,
     void* __restrict__ out, int64_t ldo, int32_t npass, const float* __restrict__ wd, int32_t obp,
     int32_t omode, int64_t ozlo) {
@@ -262,9 +326,20 @@ __device__ __forceinline__ void sketch_tasks(
     const int lane = tid & 63;
     const uint32_t lane16 = 16 * (uint32_t)lane;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int kL = kLinesOf<kRowLines, TI>;
+    constexpr int kL = kForm == kShort ? kLines : kLinesOf<kRowLines, TI>;
     constexpr int kQ = kL / 4;
     static_assert(kQ == 1 || (kFp8Out == 0 && !kWeighted));
+    static_assert(kForm == kWhole || !kRowLines);
+    static_assert(!kWeighted || kRowLines || kForm == kShort);
+    auto load = [&](Piece<kRowLines, TI> (&r)[kPerThread], int64_t l0, int64_t k0, int kw, int p0,
+                    int p1) {
+        if constexpr (kForm == kNarrow)
+            load_narrow(r, X, lines, n, ldx, k0, kw, p0, p1);
+        else if constexpr (kForm == kShort)
+            load_short(r, X, lines, ldx, ldk, l0, k0, kw, p0, p1);
+        else
+            load_window<kRowLines, TI>(r, X, lines, ldx, l0, k0, kw, p0, p1);
+    };
     const int64_t groups = (lines + kL - 1) / kL;
     const int64_t tasks = groups * npass;
     const int gslots = nst * qn;         // groups of 64 buckets over the stored blocks
@@ -284,7 +359,7 @@ __device__ __forceinline__ void sketch_tasks(
     // with one vector load, issued before the window's values are fetched.
     auto line_of = [&](int64_t it) {
         const int64_t l0 = xcd_task(it, tasks) / npass * kL;
-        return kRowLines ? l0 : min(l0, lines - kL);
+        return kRowLines || kForm != kWhole ? l0 : min(l0, lines - kL);
     };
     struct Meta {
         int32_t hb, eb, col, lim;
@@ -314,8 +389,8 @@ __device__ __forceinline__ void sketch_tasks(
     if (wg < tasks) {
         hnext = headers(meta_of(wg).hb, 0);
         const int kw = (int)min((int64_t)kWin, n);
-        load_window<kRowLines, TI>(pre, X, lines, ldx, line_of(wg), 0, kw, 0, kPerThread);
-        if constexpr (kWeighted) load_weights(wpre, wd, 0, kw);
+        load(pre, line_of(wg), 0, kw, 0, kPerThread);
+        if constexpr (kWeighted) load_weights<kForm>(wpre, wd, 0, kw);
     }
     for (int64_t it = wg; it < tasks; it += nwg) {
     const int64_t line0 = line_of(it);
@@ -328,6 +403,9 @@ __device__ __forceinline__ void sketch_tasks(
         for (int h = 0; h < kQ; ++h) acc[s][h] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int w = 0; w < nwin; ++w) {
         __syncthreads();                 // the previous window is no longer read
+        if constexpr (kForm == kNarrow) {
+            if (w + 1 == nwin) reload_narrow(pre, X, lines, n, ldx, (int64_t)w * kWin);
+        }
         stage_window<kRowLines, kWeighted, TI>(
             win, pre, wpre, (int)min((int64_t)kWin, n - (int64_t)w * kWin));
         __syncthreads();
@@ -395,9 +473,8 @@ __device__ __forceinline__ void sketch_tasks(
                 fetch(lst[r], pls[r], nls[r]);
             }
             if constexpr (s < kSpreadSlots)
-                load_window<kRowLines, TI>(
-                    pre, X, lines, ldx, l1, k1, kw1, s * kPer,
-                    (s + 1) * kPer < kPerThread ? (s + 1) * kPer : kPerThread);
+                load(pre, l1, k1, kw1, s * kPer,
+                     (s + 1) * kPer < kPerThread ? (s + 1) * kPer : kPerThread);
             constexpr int r = s % kRing;
 #pragma unroll
             for (int c = 0; c < kAhead; ++c)
@@ -406,7 +483,7 @@ __device__ __forceinline__ void sketch_tasks(
         });
         // (the next window's weights last: eight registers fewer during the
         // slots; every line group reads them, so they come from L2)
-        if constexpr (kWeighted) load_weights(wpre, wd, k1, kw1);
+        if constexpr (kWeighted) load_weights<kForm>(wpre, wd, k1, kw1);
     }
 
     // Output: FP32 (omode 0, blocks obp = bp apart), or the copy the block
@@ -525,33 +602,34 @@ __device__ __forceinline__ void sketch_tasks(
     }   // tasks
 }
 
-template <int kSlots, bool kRowLines, bool kWeighted, typename TI, int kFp8Out>
+template <int kSlots, bool kRowLines, bool kWeighted, typename TI, int kFp8Out, Form kForm>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void sketch_kernel(const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int32_t bp,
+void sketch_kernel(const TI* __restrict__ X, int64_t lines, int64_t n, int64_t ldx, int64_t ldk,
                    int32_t qn, int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
                    const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell,
                    void* __restrict__ out, int64_t ldo, int32_t npass,
                    const float* __restrict__ wd, int32_t obp, int32_t omode, int64_t ozlo) {
     __shared__ float4 win[kWin + 1];
-    sketch_tasks<kSlots, kRowLines, kWeighted, TI, kFp8Out>(
-        win, blockIdx.x, gridDim.x, X, lines, n, ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, out, ldo,
+    sketch_tasks<kSlots, kRowLines, kWeighted, TI, kFp8Out, kForm>(
+        win, blockIdx.x, gridDim.x, X, lines, n, ldx, ldk, qn, nwin, nst, bl, RC, hdr, ell, out, ldo,
         npass, wd, obp, omode, ozlo);
 }
 
-template <int S, bool R, bool W, typename TI, int Q8>
+template <int S, bool R, bool W, typename TI, int Q8, Form F = kWhole>
 hipError_t launch_one(dim3 grid, hipStream_t st, const SketchArgs& a) {
-    hipLaunchKernelGGL((sketch_kernel<S, R, W, TI, Q8>), grid, dim3(kThreads), 0, st,
-                       static_cast<const TI*>(a.X), a.lines, a.n, a.ldx, a.bp, a.qn, a.nwin, a.nst,
+    hipLaunchKernelGGL((sketch_kernel<S, R, W, TI, Q8, F>), grid, dim3(kThreads), 0, st,
+                       static_cast<const TI*>(a.X), a.lines, a.n, a.ldx, a.ldk, a.qn, a.nwin, a.nst,
                        *a.bl, a.RC, a.hdr, a.ell, a.out, a.ldo, a.npass, a.wd, a.obp, a.omode,
                        a.ozlo);
     return hipGetLastError();
 }
 
-template <bool R, bool W, typename TI, int Q8 = 0, int kMost = Q8 ? kMaxFp8Slots : kMaxSlots>
+template <bool R, bool W, typename TI, int Q8 = 0, int kMost = Q8 ? kMaxFp8Slots : kMaxSlots,
+          Form F = kWhole>
 hipError_t launch_slots(int slots, dim3 grid, hipStream_t st, const SketchArgs& a) {
 #define OSK_SLOT_CASE(S) \
     if constexpr (S <= kMost) \
-        if (slots <= S) return launch_one<S, R, W, TI, Q8>(grid, st, a);
+        if (slots <= S) return launch_one<S, R, W, TI, Q8, F>(grid, st, a);
     OSK_SLOT_CASE(1)
     OSK_SLOT_CASE(2)
     OSK_SLOT_CASE(3)

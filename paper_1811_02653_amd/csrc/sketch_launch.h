@@ -13,8 +13,8 @@ constexpr int kMaxWideSlots = 6;       // 8 BF16 column lines (8 registers per s
 // Arguments of a sketch launch (see launch_sketch).
 struct SketchArgs {
     const void* X;
-    int64_t lines, n, ldx;
-    int32_t bp, qn, nwin, nst;
+    int64_t lines, n, ldx, ldk;
+    int32_t qn, nwin, nst;
     const BlockList* bl;
     int64_t RC;
     const uint32_t* hdr;
@@ -54,11 +54,17 @@ hipError_t sketch_pair_fp8x3(int slots, hipStream_t st, const SketchArgs& a, con
 // FP32 X, rows weighted by sqrt(wd), rows of a BF16 X, columns of an FP32 X
 // and of a BF16 one (8 lines per workgroup),
 // and rows (FP32 or BF16) and columns writing the FP8 copy, plain or split.
+// sketch_narrow: fewer than 4 columns (n >= 4).  sketch_short*: value (line, k) at
+// X[line * ldx + k * ldk], loaded one at a time (n < 4).
 hipError_t sketch_rows_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_weighted(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_cols_f32(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_cols_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_narrow(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_short(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_short_weighted(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
+hipError_t sketch_short_bf16(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_rows_bf16_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);
 hipError_t sketch_cols_f32_fp8(int slots, dim3 grid, hipStream_t st, const SketchArgs& a);

@@ -16,8 +16,8 @@ namespace {
 // The first x.wgs workgroups take x's tasks, the rest y's.
 template <int kSlots, typename TI, int kFp8Out>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t bp, int32_t qn,
-                        int32_t nwin, int32_t nst, BlockList bl, int64_t RC,
+void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t qn, int32_t nwin,
+                        int32_t nst, BlockList bl, int64_t RC,
                         const uint32_t* __restrict__ hdr, const uint4* __restrict__ ell,
                         int64_t ldo, int32_t npass, int32_t obp, int32_t omode, int64_t ozlo) {
     __shared__ float4 win[kWin + 1];
@@ -28,13 +28,13 @@ void sketch_pair_kernel(SketchSide x, SketchSide y, int64_t n, int32_t bp, int32
     if constexpr (sizeof(TI) == 4) {
         if (s.rows) {
             sketch_tasks<kSlots, true, false, TI, kFp8Out>(
-                win, wg, s.wgs, X, s.lines, n, s.ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, s.out,
+                win, wg, s.wgs, X, s.lines, n, s.ldx, 0, qn, nwin, nst, bl, RC, hdr, ell, s.out,
                 ldo, npass, nullptr, obp, omode, ozlo);
             return;
         }
     }
     sketch_tasks<kSlots, false, false, TI, kFp8Out>(
-        win, wg, s.wgs, X, s.lines, n, s.ldx, bp, qn, nwin, nst, bl, RC, hdr, ell, s.out, ldo,
+        win, wg, s.wgs, X, s.lines, n, s.ldx, 0, qn, nwin, nst, bl, RC, hdr, ell, s.out, ldo,
         npass, nullptr, obp, omode, ozlo);
 }
 
@@ -46,7 +46,7 @@ hipError_t launch_pair(int slots, hipStream_t st, const SketchArgs& a, const Ske
         if (slots <= S) {                                                                         \
             hipLaunchKernelGGL((sketch_pair_kernel<S, TI, kFp8Out>),                              \
                                dim3((unsigned)(x.wgs + y.wgs)), dim3(kThreads), 0, st, x, y, a.n,  \
-                               a.bp, a.qn, a.nwin, a.nst, *a.bl, a.RC, a.hdr, a.ell, a.ldo,       \
+                               a.qn, a.nwin, a.nst, *a.bl, a.RC, a.hdr, a.ell, a.ldo,       \
                                a.npass, a.obp, a.omode, a.ozlo);                                  \
             return hipGetLastError();                                                             \
         }

@@ -914,3 +914,39 @@ def test_sketch_window_ends_and_alignment(n, lines):
     H1 = osk.GramBatch([rows], None, b=b, N=N, e=0, seeds=[9]).run()[0]
     H4 = osk.GramBatch([rows], [d], b=b, N=N, e=0, seeds=[9]).run()[0]
     assert torch.equal(H4, 4 * H1)
+
+
+def _best_ms(f, reps=5):
+    """The fastest of a few timed runs of f, after one untimed."""
+    f()
+    best = float("inf")
+    for _ in range(reps):
+        start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        start.record()
+        f()
+        stop.record()
+        stop.synchronize()
+        best = min(best, start.elapsed_time(stop))
+    return best
+
+
+@pytest.mark.parametrize("rows,n,lines,b,N", [(False, 400000, 4, 64, 2), (True, 4, 100000, 1024, 8)])
+def test_sketch_of_short_lines_keeps_pace(rows, n, lines, b, N):
+    """Three columns take no longer than four, rows of three values no longer
+    than rows of four (up to 1.5 times), and give the same sums."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn(lines if rows else n, n if rows else lines, generator=g, device="cuda")
+    sketch = osk.sketch_cols if rows else osk.sketch_rows
+    t = []
+    for Xv in (X, X[:, :3]):
+        k = Xv.shape[1] if rows else n
+        prep = osk.sketch_prepare(k, b, N, 0, seed=1)
+        out = sketch(Xv, b, N, 0, seed=1, prep=prep)
+        t.append(_best_ms(lambda: sketch(Xv, b, N, 0, seed=1, prep=prep, out=out)))
+        if rows:
+            # rows of k values as columns
+            want = osk.sketch_rows(Xv[:64].t().contiguous(), b, N, 0, seed=1, prep=prep)
+            assert torch.equal(out[:64], want)
+        elif k == n and Xv is not X:
+            assert torch.equal(out, osk.sketch_rows(X, b, N, 0, seed=1, prep=prep)[:3])
+    assert t[1] <= 1.5 * t[0], t
