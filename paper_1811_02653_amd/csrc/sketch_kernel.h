@@ -330,6 +330,8 @@ __device__ __forceinline__ void sketch_tasks(
     constexpr int kQ = kL / 4;
     static_assert(kQ == 1 || (kFp8Out == 0 && !kWeighted));
     static_assert(kForm == kWhole || !kRowLines);
+    constexpr int kAhead = kAheadOf<kSlots, kRowLines || kForm == kShort, kQ>;
+    constexpr int kTail = kTailOf<kSlots, kQ>;
     static_assert(!kWeighted || kRowLines || kForm == kShort);
     auto load = [&](Piece<kRowLines, TI> (&r)[kPerThread], int64_t l0, int64_t k0, int kw, int p0,
                     int p1) {
@@ -479,7 +481,27 @@ __device__ __forceinline__ void sketch_tasks(
 #pragma unroll
             for (int c = 0; c < kAhead; ++c)
                 if ((uint32_t)c < nls[r]) add_chunk(acc[s], win, lst[r][c]);
-            for (uint32_t c = kAhead; c < nls[r]; ++c) add_chunk(acc[s], win, chunk_at(pls[r], c));
+            if constexpr (kTail > 0) {
+                // (chunks ahead in the tail too)
+                if (nls[r] > (uint32_t)kAhead) {
+                    const uint32_t last = nls[r] - 1;
+                    uint4 next[kTail];
+#pragma unroll
+                    for (int u = 0; u < kTail; ++u)
+                        next[u] = chunk_at(pls[r], min((uint32_t)(kAhead + u), last));
+                    for (uint32_t c = kAhead; c < nls[r]; c += kTail) {
+#pragma unroll
+                        for (int u = 0; u < kTail; ++u) {
+                            const uint4 e = next[u];
+                            next[u] = chunk_at(pls[r], min(c + kTail + u, last));
+                            if (c + u < nls[r]) add_chunk(acc[s], win, e);
+                        }
+                    }
+                }
+            } else {
+                for (uint32_t c = kAhead; c < nls[r]; ++c)
+                    add_chunk(acc[s], win, chunk_at(pls[r], c));
+            }
         });
         // (the next window's weights last: eight registers fewer during the
         // slots; every line group reads them, so they come from L2)
