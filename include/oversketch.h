@@ -211,10 +211,11 @@ size_t os_sketch_rows_workspace_bytes(int64_t n, int64_t cols);
  * i.e. out = (S_{s_j}^T X)^T side by side over j.  Other arguments as in
  * os_sketch_cols; out: DEVICE cols x (nst*bp), ld ldo >= nst*bp.
  * workspace: optional DEVICE buffer (256-byte aligned, >=
- * os_sketch_rows_workspace_bytes, else OS_EWORKSPACE).  An X of fewer than 4
- * columns is transposed into it first and its rows sketched as by
- * os_sketch_cols (faster); otherwise the columns of X are sketched in place.
- * Both paths give the same sums in the same order. */
+ * os_sketch_rows_workspace_bytes, else OS_EWORKSPACE).  Where that is
+ * predicted to be faster (few columns over a long sketched dimension) X is
+ * transposed into it first and its rows sketched as by os_sketch_cols;
+ * otherwise, and without one, the columns of X are sketched in place.  Both
+ * paths give the same sums in the same order. */
 os_status os_sketch_rows(const os_sketch* sk, const void* prep, size_t prep_bytes,
                          const float* X, int64_t n, int64_t cols, int64_t ldx,
                          const uint8_t* keep_host, int kept_only, float* out, int64_t ldo,
@@ -302,7 +303,7 @@ os_status os_gemm_kept_prec(const void* At, int64_t ldat, const void* Bt, int64_
 /* Workspace bytes os_matmul needs: the prepared sketch and both sketches,
  * sized for all N+e blocks so one workspace serves any mask, plus, for a
  * row-major B (b_col_major = 0), room for B transposed (l x n; used only when
- * B cannot be read in place, see os_matmul), plus, for a product of at most
+ * B is not read in place, see os_matmul), plus, for a product of at most
  * 128 tiles of 256 x 256, the partial products of the block product's split
  * K loop (S m x l FP32 matrices, S <= 256 / tiles, at most 64 MiB).  0 on
  * invalid arguments. */
@@ -318,8 +319,8 @@ size_t os_matmul_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, int6
  * (ldc).  workspace: DEVICE, 256-byte aligned, >= os_matmul_workspace_bytes
  * for the same b_col_major.  Enqueues: prepare, sketch of A, (transpose of
  * a row-major B,) sketch of B (with A's in one launch where that is faster),
- * block product.  A row-major B of at least 4
- * columns has them sketched in place (no transpose; the same sums).  A product
+ * block product.  The columns of a row-major B are sketched in place or B is
+ * transposed first, whichever is predicted faster (the same sums).  A product
  * of at most 128 tiles of 256 x 256 may split its block product's K loop over
  * several workgroups per tile (partials in the workspace) or over the waves
  * of one, summed in a fixed order: repeatable bit for bit, summed in another
@@ -385,11 +386,11 @@ size_t os_matmul_ex_workspace_bytes(const os_sketch* sk, int64_t m, int64_t n, i
  * (a_col_major = 0, element (r, k) at A[r*lda + k]) or column-major
  * (a_col_major = 1, at A[k*lda + r], lda >= m); B n x l as in os_matmul.
  * a_dtype / b_dtype: OS_DTYPE_F32 or OS_DTYPE_BF16 (2-byte aligned, ld in
- * values), in either layout.  The columns of an FP32 column-major A or
- * row-major B (at least 4 of them) are read in place; BF16 ones are, 8 at a
- * time, where that is faster, else first transposed into the workspace.  BF16 values are converted exactly to FP32 as
- * the sketch reads them, so the result equals that of the FP32 path on the
- * converted values, bit for bit.  With A = X^T for a row-major X (n x m: A is
+ * values), in either layout.  The columns of a column-major A or a row-major
+ * B are read in place (BF16 ones 8 at a time) or first transposed into the
+ * workspace, whichever is predicted faster.  BF16 values are converted exactly
+ * to FP32 as the sketch reads them, so the result equals that of the FP32 path
+ * on the converted values, bit for bit.  With A = X^T for a row-major X (n x m: A is
  * X read as column-major) and B = dY this is the sketched weight gradient of
  * a linear layer, X^T S S^T dY, sketched over the n tokens (the product of
  * Section 4 with the tokens as the inner dimension).  Other arguments as in

@@ -385,10 +385,10 @@ def sketch_rows(X, b, N, e, seed=0, keep=None, kept_only=False, h=None, sigma=No
 
     workspace: None (sketch X's columns in place), True (allocate one) or a
     uint8 CUDA tensor of at least sketch_rows_workspace_bytes(n, cols) bytes
-    (an X of fewer than 4 columns is transposed into it first: the faster
-    path then).  X may be float32 or
-    bfloat16; a bfloat16 X always takes the transposing path (converted
-    exactly to FP32, FP32 sums)."""
+    (X is transposed into it first where that is predicted to be faster: few
+    columns over a long sketched dimension).  X may be float32 or bfloat16; a
+    bfloat16 X always takes the transposing path (converted exactly to FP32,
+    FP32 sums)."""
     torch = _torch()
     _require_cuda(X, "X")
     if X.dtype not in (torch.float32, torch.bfloat16):

@@ -206,9 +206,8 @@ os_status os_sketch_rows(const os_sketch* sk, const void* prep, size_t prep_byte
         if (!aligned(workspace, 256) || ws_bytes < osk::transpose_bytes(n, cols))
             return OS_EWORKSPACE;
     }
-    // (in place also with a workspace: faster than the transpose and the same
-    // sums, see sketch_rows_in_place_ok)
-    if (workspace && !osk::sketch_rows_in_place_ok(cols)) {
+    // (in place also with a workspace where that is as fast: the same sums)
+    if (workspace && !osk::sketch_rows_in_place_ok(n, cols, ldx, bs.nst, bp)) {
         hipStream_t s = (hipStream_t)stream;
         float* Xt = static_cast<float*>(workspace);
         const int64_t ldt = osk::round_up(n, 4);
@@ -459,10 +458,9 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
 
     // An operand's lines (rows of A, columns of B) that are rows in memory are
     // sketched as they are; columns of an FP32 matrix (a row-major B, a
-    // column-major A) are read in place, which is faster than transposing them
-    // first (sketch_rows_in_place_ok); columns of a BF16 one are read
-    // in place 8 at a time (sketch_rows_bf16_in_place_ok), else transposed as
-    // BF16.
+    // column-major A) are read in place unless transposing them first is faster
+    // (sketch_rows_in_place_ok); columns of a BF16 one are read in place 8 at a
+    // time (sketch_rows_bf16_in_place_ok), else transposed as BF16.
     // BF16 values are converted exactly to FP32 as the sketch stages them.
     // With a BF16 block product the sketch writes its BF16 copy directly
     // (rounded in the sketch's epilogue, bit for bit what the quantization
@@ -472,12 +470,16 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     const bool bf16_product = precision != OS_PREC_FP32 && !is_fp8(precision);
     const bool fp8_fused =
         is_fp8(precision) && n >= 4 && osk::sketch_fp8_fusable(sk->b, bs.nst);
+    // (the FP8 copy of fewer than 4 columns: transposed)
+    auto in_place = [&](int64_t lines, int64_t ldx) {
+        return (lines >= 4 || !fp8_fused) &&
+               osk::sketch_rows_in_place_ok(n, lines, ldx, bs.nst, bp);
+    };
     auto sketch_lines = [&](const void* X, int dtype, bool transpose, int64_t lines,
                             int64_t ldx, float* out, void* qout) -> os_status {
         const void* Xl = X;
         int64_t ldl = ldx;
-        if (transpose && dtype == OS_DTYPE_F32 &&
-            osk::sketch_rows_in_place_ok(lines)) {
+        if (transpose && dtype == OS_DTYPE_F32 && in_place(lines, ldx)) {
             const float* Xf = static_cast<const float*>(X);
             if (bf16_product)
                 return hip_status(osk::launch_sketch_rows_q(Xf, n, lines, ldx, bs.stored, bs.nst,
@@ -528,18 +530,35 @@ os_status os_matmul_ex(const os_sketch* sk, const void* A, int a_dtype, int a_co
     hipError_t e = hipSuccess;
     const bool copy = bf16_product || fp8_fused;      // the sketch writes the product's operand
     const int mode = copy ? (bf16_product ? 1 : 3) + (is_split(precision) ? 1 : 0) : 0;
+    // both sketches in one launch, where faster; a side whose columns are better
+    // transposed is so first when the tasks of both fit on the device together
+    // (1000000 x 16 columns into 4 blocks of 256: 1290 us in place, 740 transposed)
+    bool at = a_col_major != 0, bt = b_col_major == 0;
+    if (!same && a_dtype == OS_DTYPE_F32 && b_dtype == OS_DTYPE_F32 &&
+        osk::sketch_pair_fits(m, l, n, bs.nst, bp)) {
+        const bool ta = at && !in_place(m, lda), tb = bt && !in_place(l, ldb);
+        if (ta != tb) {
+            float* tx = reinterpret_cast<float*>(tx_p);
+            const int64_t ldt = osk::round_up(n, 4);
+            if ((st = hip_status(osk::launch_transpose(static_cast<const float*>(ta ? A : B), n,
+                                                       ta ? m : l, ta ? lda : ldb, tx, ldt, s))) !=
+                OS_OK)
+                return st;
+            (ta ? A : B) = tx;
+            (ta ? lda : ldb) = ldt;
+            (ta ? at : bt) = false;
+        }
+    }
     if (!same && a_dtype == b_dtype &&
-        osk::launch_sketch_pair(a_dtype == OS_DTYPE_BF16, A, a_col_major == 0, m, lda,
+        osk::launch_sketch_pair(a_dtype == OS_DTYPE_BF16, A, !at, m, lda,
                                 copy ? static_cast<void*>(aq_p) : At,
-                                B, b_col_major != 0, l, ldb,
+                                B, !bt, l, ldb,
                                 copy ? static_cast<void*>(bq_p) : Bt, n, bs.stored, bs.nst,
                                 nblocks(sk), bp, lists, copy ? wq : zs, mode, s, &e)) {
         if (e != hipSuccess) return hip_status(e);
     } else {
-        if ((st = sketch_lines(A, a_dtype, a_col_major != 0, m, lda, At, aq_p)) != OS_OK) return st;
-        if (!same &&
-            (st = sketch_lines(B, b_dtype, b_col_major == 0, l, ldb, Bt, bq_p)) != OS_OK)
-            return st;
+        if ((st = sketch_lines(A, a_dtype, at, m, lda, At, aq_p)) != OS_OK) return st;
+        if (!same && (st = sketch_lines(B, b_dtype, bt, l, ldb, Bt, bq_p)) != OS_OK) return st;
     }
     if (same) {
         Bt = At;
@@ -619,8 +638,8 @@ os_status os_matmul_cmask(const os_sketch* sk, const float* A, int64_t lda, cons
         return st;
     if (same_lines(A, OS_DTYPE_F32, false, m, lda, B, OS_DTYPE_F32, !b_col_major, l, ldb)) {
         Bt = At;
-    } else if (!b_col_major && osk::sketch_rows_in_place_ok(l)) {
-        // B's columns read in place (faster than transposed, same sums)
+    } else if (!b_col_major && osk::sketch_rows_in_place_ok(n, l, ldb, bs.nst, bp)) {
+        // B's columns read in place (no slower than transposed, same sums)
         if ((st = hip_status(osk::launch_sketch_rows(B, n, l, ldb, bs.stored, bs.nst, nblocks(sk),
                                                      bp, lists, Bt, zs, s))) != OS_OK)
             return st;

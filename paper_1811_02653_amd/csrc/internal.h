@@ -124,12 +124,18 @@ bool plan_sketch_ok(int64_t lines, int32_t nst, int32_t bp, int64_t n);
 hipError_t launch_sketch_rows(const float* X, int64_t n, int64_t cols, int64_t ldx,
                               const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                               const void* lists, float* out, int64_t ldo, hipStream_t s);
-// True when launch_sketch_rows reads X's columns with 16-byte loads (at least
-// 4 of them): then reading them in place is faster than transposing X first
-// and sketching the rows of X^T (32768 x 8192, 10 blocks of 1024: 0.72
-// against 0.39 + 0.49 ms; 20011 x 2777 at ld 2777, 5 blocks of 900: 133
-// against 115 + 92 us; the sums are the same, bit for bit).
-bool sketch_rows_in_place_ok(int64_t cols);
+// True when reading X's columns in place (launch_sketch_rows) is predicted to be
+// no slower than transposing X and sketching the rows of X^T (the sums are the
+// same, bit for bit).  A window of columns takes about 6 us longer than one of
+// rows, since each of its 16-byte requests brings its own cache line into a CU (2
+// us when all of X stays in an XCD's L2; less where a line holds several rows),
+// in each of the rounds that the line groups make of the CUs; the transpose
+// takes 8 us and 1.3 us per million values.  So whole rounds of groups are read
+// in place, few groups over many windows are not.  In place / transposed, us:
+// 32768 x 8192, 10 blocks of 1024, 720 / 880; 20011 x 2777, 5 of 900, 133 / 207;
+// 200000 x 1000, 4 of 256, 354 / 541; 200000 x 64, 4 of 256, 300 / 150; 1000000 x 33,
+// 4 of 256, 1550 / 740; 20000 x 33, 4 of 256, 21 / 25.
+bool sketch_rows_in_place_ok(int64_t n, int64_t cols, int64_t ldx, int32_t nst, int32_t bp);
 // True when the columns of a BF16 matrix are read in place, 8 per workgroup
 // (at least 8 of them, at most 6 slots per wave: a slot takes 8 registers),
 // and that is faster than transposing it first: every 16-byte request brings
@@ -157,6 +163,9 @@ bool launch_sketch_pair(bool bf16, const void* A, bool a_rows, int64_t m, int64_
                         const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,
                         const void* lists, int64_t ldo, int out_mode, hipStream_t s,
                         hipError_t* err);
+// True when the tasks of both FP32 operands' sketches fit on the device together
+// (one launch then takes the time of the longer side).
+bool sketch_pair_fits(int64_t m, int64_t l, int64_t n, int32_t nst, int32_t bp);
 // launch_sketch_rows writing the BF16 copy, as launch_sketch_cols_q.
 hipError_t launch_sketch_rows_q(const float* X, int64_t n, int64_t cols, int64_t ldx,
                                 const BlockList& bl, int32_t nst, int32_t nblk, int32_t bp,

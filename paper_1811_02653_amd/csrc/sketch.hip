@@ -858,7 +858,18 @@ hipError_t launch_sketch_rows(const float* X, int64_t n, int64_t cols, int64_t l
     return launch_sketch(false, X, false, cols, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s);
 }
 
-bool sketch_rows_in_place_ok(int64_t cols) { return cols >= 4; }
+bool sketch_rows_in_place_ok(int64_t n, int64_t cols, int64_t ldx, int32_t nst, int32_t bp) {
+    const Plan p = plan_of(n, bp);
+    const int64_t groups = (cols + kLines - 1) / kLines;
+    const int cus = device_cus();
+    if (cus < 1) return true;
+    int32_t npass, slots;
+    pass_plan(nst, p.qn, &npass, &slots, groups, cus);
+    const double rounds = (double)((groups * npass + cus - 1) / cus);
+    const double window = (double)n * (double)ldx <= (double)(1 << 20) ? 2.0 : 6.0;
+    const double extra = rounds * ((double)n / kWin) * window * std::min(1.0, (double)ldx / 24);
+    return extra <= 8 + (double)n * (double)cols * 1.3e-6;
+}
 
 bool sketch_rows_bf16_in_place_ok(int64_t n, int64_t cols, int32_t nst, int32_t bp) {
     const Plan p = plan_of(n, bp);
@@ -875,6 +886,15 @@ hipError_t launch_sketch_rows_bf16(const void* X, int64_t n, int64_t cols, int64
     if (!plan_sketch_ok(cols, nst, bp, n)) return hipErrorInvalidValue;
     return launch_sketch(false, X, true, cols, n, ldx, bl, nst, nblk, bp, lists, out, ldo, s,
                          nullptr, out_mode);
+}
+
+bool sketch_pair_fits(int64_t m, int64_t l, int64_t n, int32_t nst, int32_t bp) {
+    const Plan p = plan_of(n, bp);
+    const int cus = device_cus();
+    const int64_t groups = (m + kLines - 1) / kLines + (l + kLines - 1) / kLines;
+    int32_t npass, slots;
+    pass_plan(nst, p.qn, &npass, &slots, groups, cus);
+    return groups * npass <= cus;
 }
 
 bool launch_sketch_pair(bool bf16, const void* A, bool a_rows, int64_t m, int64_t lda, void* outA,
