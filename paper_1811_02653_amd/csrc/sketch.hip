@@ -212,6 +212,9 @@ __device__ __forceinline__ void ell_build_region_waves(F entry, int64_t n, int32
             if (u * 64 * kBW < kw) tab[u * 64 * kBW + tid] = e[u];
     }
     __syncthreads();
+    if (Z == 1) {       // (each wave its own part: no division per 64 entries)
+        for (int t = t_beg + lane; t < t_end; t += 64) atomicAdd(&mine[at(tab[t])], 1u);
+    } else
     for (int t0 = 64 * wv; t0 < kw; t0 += 64 * kBW) {
         const int p = t0 / part - z * kBW;                  // (uniform: part is a multiple of 64)
         uint32_t* to = p < 0 ? before : (p < kBW ? cur + p * bp : tot);
