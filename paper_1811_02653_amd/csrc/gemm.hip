@@ -1660,10 +1660,19 @@ Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part
     auto consider = [&](const Form& f) {
         const int64_t tiles = tiles_of(m, l, f.tile) * f.S;
         if (tiles > 0x7fffffff) return;
-        // first loads and epilogue; a split's partials written and summed
+        // what 256 tiles add for first loads and epilogue: 2 us on few CUs, and,
+        // where they fill them, 2 or 3 for rounds past the first (smaller tiles
+        // write theirs while others run); 6 with partials, which are then summed.
+        // (Fitted on 560 products of 1 to 128 steps in every form; with 6
+        // throughout, products of few steps took smaller tiles than is best: 4096 x
+        // 4096 over 4 steps, 128 / 256 tiles: BF16 23.2 / 21.0 us, split FP8 31.1 /
+        // 25.1; 3000 x 4100 over 5, FP8 26.3 / 22.6.)
         double us = (f.deep ? deep_us(kind, f.tile, tiles, chunk_bytes)
-                            : step_us(kind, f.tile, tiles)) * (double)f.chunk +
-                    (f.tile == 256 ? 6 : 0);
+                            : step_us(kind, f.tile, tiles)) * (double)f.chunk;
+        if (f.tile == 256)
+            us += f.S > 1         ? 6
+                  : tiles <= 192 ? 2
+                                 : std::min(3.0, 2.0 * (double)((tiles - 1) / kSplitSlots));
         if (f.S > 1) us += 4 + (double)f.S * (double)m * (double)l * 4 / 4e6;
         if (t == 0 || us < t) {
             t = us;
@@ -1685,7 +1694,7 @@ Form pick_form(Kind kind, int64_t m, int64_t l, int64_t total, const float* part
                             bool deep;
                             const double us =
                                 rest_us(kind, tile, rest, n, chunk_bytes, &deep) * (double)total +
-                                12;
+                                8;                     // (the second launch)
                             if (us < t) {
                                 t = us;
                                 best = Form{tile, 1, total, rest, deep};

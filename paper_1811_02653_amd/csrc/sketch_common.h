@@ -16,16 +16,16 @@ constexpr int kPerThread = kWin / kThreads;   // window positions staged per thr
 constexpr uint16_t kPad = (uint16_t)kWin;     // entry of the zero row, positive
 // List chunks of a slot fetched ahead (before the next window's loads, which
 // the chunks fetched after them wait for), and, for lists longer than that,
-// chunks fetched ahead of the one that is summed.  Kernels of few slots have
-// the registers for more, and need them: their lists are long (few buckets) and
-// no other slot's work hides their latency (2 blocks of 64, 1000000 x 1: 1288
-// us, this 776; columns, 1000000 x 16: 1880, this 1236.  Rows with 2 chunks
-// instead of 3: 100000 x 2500 into 4 blocks of 256 9 % slower.  Columns with 3
-// instead of 6, 1000000 x 16 into 4 blocks of 256: 1399 / 1291).
+// chunks fetched ahead of the one that is summed.  Kernels of one slot have the
+// registers for more, and need them: their lists are long (few buckets) and no
+// other slot's work hides their latency (2 blocks of 64, 1000000 x 1: 1288 us,
+// this 776; columns, 1000000 x 16: 1880, this 1236.  Rows with 2 chunks instead
+// of 3: 100000 x 2500 into 4 blocks of 256 9 % slower.  Columns with 3 instead of
+// 6, 1000000 x 16 into 4 blocks of 256: 1399 / 1291.  Two slots: no gain.)
 template <int kSlots, bool kRows, int kQ>
 constexpr int kAheadOf = kSlots > 1 || kQ > 1 ? 2 : (kRows ? 3 : 6);
 template <int kSlots, int kQ>
-constexpr int kTailOf = kSlots <= 2 && kQ == 1 ? 4 : 0;
+constexpr int kTailOf = kSlots == 1 && kQ == 1 ? 4 : 0;
 constexpr int kDist = 1;               // slots ahead whose lists are fetched
 
 // LDS slot of window position p (p < kWin).  Thread t stages the quads of

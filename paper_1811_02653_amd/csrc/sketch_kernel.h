@@ -490,12 +490,16 @@ __device__ __forceinline__ void sketch_tasks(
                     for (int u = 0; u < kTail; ++u)
                         next[u] = chunk_at(pls[r], min((uint32_t)(kAhead + u), last));
                     for (uint32_t c = kAhead; c < nls[r]; c += kTail) {
+                        uint4 e[kTail];
 #pragma unroll
-                        for (int u = 0; u < kTail; ++u) {
-                            const uint4 e = next[u];
-                            next[u] = chunk_at(pls[r], min(c + kTail + u, last));
-                            if (c + u < nls[r]) add_chunk(acc[s], win, e);
-                        }
+                        for (int u = 0; u < kTail; ++u) e[u] = next[u];
+                        if (c + kTail < nls[r])
+#pragma unroll
+                            for (int u = 0; u < kTail; ++u)
+                                next[u] = chunk_at(pls[r], min(c + kTail + u, last));
+#pragma unroll
+                        for (int u = 0; u < kTail; ++u)
+                            if (c + u < nls[r]) add_chunk(acc[s], win, e[u]);
                     }
                 }
             } else {

@@ -10,6 +10,8 @@ Tolerances (FP32 path against the FP64 oracle):
     (an FP32 sum of about n/b terms);
   - the product C: relative Frobenius error <= 1e-5.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -975,3 +977,49 @@ def test_sketch_of_columns_keeps_pace_with_rows(n, cols, b, N):
     assert torch.equal(*C)
     t = [_best_ms(lambda: osk.matmul(A, Y, b, N, 0, seed=1, out=C[0], workspace=wm)) for Y in (Xt.t(), X)]
     assert t[1] <= 1.5 * t[0] + 0.02, t
+
+
+class _KernelNode(ctypes.Structure):
+    """hipKernelNodeParams."""
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint32 * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def _launches(f):
+    """(workgroups, threads of each) of the kernels that f(stream) launches, from
+    a captured graph (not run)."""
+    hip, stream = osk.lib(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph, s = ctypes.c_void_p(), ctypes.c_void_p(stream.cuda_stream)
+    assert hip.hipStreamBeginCapture(s, 2) == 0                       # relaxed
+    try:
+        f(stream)
+    finally:
+        assert hip.hipStreamEndCapture(s, ctypes.byref(graph)) == 0
+    count = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)) == 0
+    out = []
+    for node in nodes:
+        p = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append((p.grid[0] * p.grid[1] * p.grid[2], p.block[0]))
+    assert hip.hipGraphDestroy(graph) == 0
+    return out
+
+
+@pytest.mark.parametrize("precision,b,nst", [("bf16", 64, 4), ("bf16x3", 64, 2), ("fp8", 128, 4),
+                                             ("fp8x3", 128, 2)])
+def test_short_product_takes_large_tiles(precision, b, nst):
+    """A product of 256 tiles of 256 x 256 and 4 K steps is run as such (smaller
+    tiles take 5 to 20 % longer), and its entries are those of a small one."""
+    m = 4096
+    g = torch.Generator(device="cuda").manual_seed(nst)
+    S = [torch.randn(m, nst * osk.block_stride(b), generator=g, device="cuda") for _ in range(2)]
+    Qa, Qb = (osk.sketch_quantize(X, b, nst, precision) for X in S)
+    C = torch.empty(m, m, device="cuda")
+    f = lambda s=None: osk.gemm_kept_prec(Qa, Qb, b, nst, precision, out=C, stream=s)  # noqa: E731
+    assert _launches(f) == [(256, 512)]
+    f()
+    assert torch.equal(C[:300, :200], osk.gemm_kept_prec(Qa[:300], Qb[:200], b, nst, precision))
