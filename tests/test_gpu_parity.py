@@ -1023,3 +1023,40 @@ def test_short_product_takes_large_tiles(precision, b, nst):
     assert _launches(f) == [(256, 512)]
     f()
     assert torch.equal(C[:300, :200], osk.gemm_kept_prec(Qa[:300], Qb[:200], b, nst, precision))
+
+
+@pytest.mark.parametrize("precision,m,l,b,nst,tile,rest", [
+    ("fp32", 4500, 4200, 1024, 1, 256, 128), ("fp32", 4500, 4200, 1056, 1, 256, 128),
+    ("fp32", 5120, 5000, 1024, 3, 256, 64), ("fp32", 16385, 1023, 1000, 2, 256, 64),
+    ("fp32", 4100, 4300, 1024, 1, 128, 64),
+    ("bf16", 4500, 4200, 1024, 4, 256, 128), ("bf16", 16385, 1023, 1024, 3, 256, 64),
+    ("bf16", 7000, 8000, 1024, 2, 256, 128),
+    ("bf16x3", 4500, 4200, 1000, 2, 256, 128), ("bf16x3", 6000, 3000, 512, 3, 256, 64),
+    ("bf16x3", 7000, 8000, 512, 2, 256, 128), ("bf16x3", 2500, 2300, 1024, 4, 128, 64),
+    ("fp8", 4500, 4200, 1024, 4, 256, 128), ("fp8", 7000, 8000, 1000, 2, 256, 128),
+    ("fp8x3", 16385, 1023, 512, 3, 256, 128), ("fp8x3", 4500, 4200, 1024, 1, 256, 128),
+    ("fp8x3", 7000, 8000, 512, 2, 256, 128)])
+def test_block_product_last_round_in_two_launches(precision, m, l, b, nst, tile, rest):
+    """Products of whole rounds of tiles and a part of one that are run as two
+    launches, the tiles of the last round as smaller ones: every entry is that of
+    products of 512 of its rows, which take one launch, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(m + l)
+    w = nst * osk.block_stride(b)
+    At, Bt = (torch.randn(r, w, generator=g, device="cuda") for r in (m, l))
+    if precision != "fp32":
+        At, Bt = (osk.sketch_quantize(S, b, nst, precision) for S in (At, Bt))
+    keep = [True, False, True] if nst == 3 else None
+    C, part = torch.empty(m, l, device="cuda"), torch.empty(512, l, device="cuda")
+
+    def product(A, out, stream=None):
+        return osk.gemm_kept_prec(A, Bt, b, nst, precision, keep=keep, out=out, stream=stream)
+
+    tiles = -(-m // tile) * -(-l // tile)
+    whole = tiles // 256 * 256
+    assert _launches(lambda s: product(At, C, s)) == [
+        (whole, 512 if tile == 256 else 256), ((tiles - whole) * (tile // rest) ** 2, 256)]
+    assert len(_launches(lambda s: product(At[:512], part, s))) == 1
+    product(At, C)
+    for r in range(0, m, 512):
+        rows = At[r:r + 512]
+        assert torch.equal(C[r:r + 512], product(rows, part[:len(rows)])), r
