@@ -531,3 +531,26 @@ def test_quantize_fp8_of_a_huge_sketch():
     assert int((Q[::4099, :b] != 0).sum()) == int((Q[0, :b] != 0).sum())     # row 0 is one of them
     del S, Q
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("b,N", [(1024, 3), (1024, 6), (1000, 8), (1024, 10), (1024, 20), (1024, 24)])
+@pytest.mark.parametrize("precision", ["bf16", "bf16x3", "fp8", "fp8x3"])
+def test_copies_written_by_the_sketch_are_the_quantized_sketches(b, N, precision):
+    """Products of more than 128 tiles of 256 x 256, which never split, with
+    sketches of 3 to 12 slots per wave, the wide ones in two passes: in every
+    layout, with a row of huge, of tiny and of no values, the product of the
+    quantized sketches, bit for bit."""
+    m, n, l = 3072, 9001, 2816
+    g = torch.Generator(device="cuda").manual_seed(b + N)
+    A = torch.randn(m, n, generator=g, device="cuda")
+    B = torch.randn(n, l, generator=g, device="cuda")
+    A[0] *= 1e30
+    A[1] *= 1e-42
+    A[2] = 0
+    S = osk.sketch_cols(A, b, N, 0, seed=3), osk.sketch_rows(B, b, N, 0, seed=3)
+    Qa, Qb = (osk.sketch_quantize(X, b, N, precision) for X in S)
+    want = osk.gemm_kept_prec(Qa, Qb, b, N, precision)
+    for Av in (A, A.t().contiguous().t()):
+        for Bv in (B, B.t().contiguous().t()):
+            got = osk.matmul_ex(Av, Bv, b, N, 0, seed=3, precision=precision)
+            assert torch.equal(got, want), (Av.stride(), Bv.stride())
