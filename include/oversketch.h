@@ -282,6 +282,9 @@ int64_t os_quantized_row(int32_t b, int32_t nst, int precision);
  *                   x * 2^-s; the row's scale bytes (s + 127, one per 64
  *                   codes, in code order) follow its codes;
  *   OS_PREC_FP8X3:  the same for S and for the residual S - dequant(code).
+ * In the FP8 forms an infinity or NaN becomes the E4M3 NaN, so that every
+ * entry of C it goes into is NaN (also of the whole path); the finite values of
+ * its 64 are then scaled for it and may round to zero.
  * Q: DEVICE, lines x os_quantized_row(b, nst, precision) (BF16 values or
  * bytes), ld ldq in the same unit, rows 16-byte aligned (Q 16-byte aligned,
  * ldq a multiple of 16 bytes). */

@@ -554,3 +554,26 @@ def test_copies_written_by_the_sketch_are_the_quantized_sketches(b, N, precision
         for Bv in (B, B.t().contiguous().t()):
             got = osk.matmul_ex(Av, Bv, b, N, 0, seed=3, precision=precision)
             assert torch.equal(got, want), (Av.stride(), Bv.stride())
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("precision", ["fp8", "fp8x3"])
+@pytest.mark.parametrize("b,N", [(128, 2), (300, 2)])
+def test_fp8_of_a_value_that_is_not_finite(value, precision, b, N):
+    """An infinity or NaN makes the entries of C that it goes into NaN, whether
+    the sketch or the quantization writes the FP8 copy, and leaves the others as
+    they are."""
+    g = torch.Generator(device="cuda").manual_seed(b)
+    A = torch.randn(70, 900, generator=g, device="cuda")
+    B = torch.randn(900, 80, generator=g, device="cuda")
+    kw = dict(seed=3, precision=precision)
+    want = osk.matmul(A, B, b, N, 0, **kw)
+    A[5, 17] = B[800, 9] = value
+    bad = torch.zeros(70, 80, dtype=torch.bool, device="cuda")
+    bad[5] = bad[:, 9] = True
+    Qa = osk.sketch_quantize(osk.sketch_cols(A, b, N, 0, seed=3), b, N, precision)
+    Qb = osk.sketch_quantize(osk.sketch_rows(B, b, N, 0, seed=3), b, N, precision)
+    assert bool(((Qa[5] & 0x7F) == 0x7F).any()) and not bool(((Qa[4, :N * b] & 0x7F) == 0x7F).any())
+    for C in (osk.matmul(A, B, b, N, 0, **kw), osk.gemm_kept_prec(Qa, Qb, b, N, precision)):
+        assert bool(C[bad].isnan().all()) and bool(C[~bad].isfinite().all())
+    assert torch.equal(osk.matmul(A, B, b, N, 0, **kw)[~bad], want[~bad])
