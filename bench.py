@@ -21,6 +21,7 @@ workload.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import sys
@@ -39,12 +40,12 @@ METRIC = "sketched AB eff. TFLOP/s (2mnl/t) at fixed rel-Frob err vs exact GEMM,
 # copy (bench.py --calibrate-copy: FETCH_SIZE 524300 KiB -> x 2.000,
 # WRITE_SIZE 1048576 KiB -> x 1.000).  Commands and raw figures:
 # profiles/gemm_kept_8192x8192_K8x1024_hbm_traffic.md.  Valid only for the
-# kernel source it was measured on (SHA-256 of that source, see
-# gemm_kept_source_sha); None otherwise.
+# source of the launch it was measured on (kernel, choice of its form, launch
+# functions: their SHA-256, see gemm_kept_source_sha); None otherwise.
 GEMM_TRAFFIC = {
-    "source_sha256": "cb24e04eb6b4f29028dcfbb6b9c15d37c31bec74bbcdc56f5d20c001e7c5a97e",
+    "source_sha256": "283c4da8d5b91c71986a1a309fe59cdfb407af71ba39d1e28db827dd773970f4",
     "workload": (8192, 32768, 8192, 1024, 8, 2),
-    "fetch_kib": 1573064.0, "fetch_scale": 2.000,
+    "fetch_kib": 1573069.0, "fetch_scale": 2.000,
     "write_kib": 262144.0, "write_scale": 1.000,
 }
 FP32_MFMA_PEAK_TFLOPS = 157.3       # MI355X dense FP32 matrix peak
@@ -99,24 +100,29 @@ def parse():
 
 
 def gemm_kept_source_sha(path):
-    """SHA-256 of the source that the FP32 gemm_kept launch compiles from:
-    gemm.hip up to the FP8 kernel (helpers and gemm_kept_kernel) plus the
-    launch_gemm_kept function; edits elsewhere in the file keep the counters
-    valid."""
+    """SHA-256 of the source that decides the FP32 gemm_kept launch: gemm.hip's
+    helpers and gemm_kept_kernel, the choice of its form (tiles, split, last
+    round) and its launch functions; edits elsewhere in the file keep the
+    counters valid."""
     import hashlib
     import re
     text = open(path).read()
-    head = text[:text.index("// FP8 (E4M3) operands")]
-    a = text.index("hipError_t launch_gemm_kept(")
-    launch = text[a:text.index("\n}\n", a) + 3]
+
+    def between(first, last):
+        a = text.index(first)
+        return text[a:text.index(last, a)]
+
+    code = (text[:text.index("// Small products: one 32 x 32 tile")] +
+            between("constexpr int64_t kSplitSlots", "// As launch_part, tb = tiles") +
+            between("hipError_t launch_gemm_kept(", "hipError_t launch_gemm_cmask("))
     # comments and blank lines do not change the kernel
-    code = re.sub(r"//[^\n]*", "", head + launch)
+    code = re.sub(r"//[^\n]*", "", code)
     code = "\n".join(line.rstrip() for line in code.splitlines() if line.strip())
     return hashlib.sha256(code.encode()).hexdigest()
 
 
 def gemm_traffic_bytes(m, n, l, b, N, e):
-    """Measured HBM bytes per gemm_kept launch, or None if the kernel source
+    """Measured HBM bytes per gemm_kept launch, or None if the launch's source
     or the workload differs from the one the counters were taken on."""
     src = os.path.join(ROOT, "paper_1811_02653_amd", "csrc", "gemm.hip")
     sha = gemm_kept_source_sha(src)
@@ -127,15 +133,23 @@ def gemm_traffic_bytes(m, n, l, b, N, e):
 
 
 def event_time_ms(torch, fn, reps, stream):
-    """Average duration of fn() over reps launches, HIP events on `stream`."""
+    """Average duration of fn() over reps launches, HIP events on `stream`.
+    Python's collector is off meanwhile: one collection of the whole heap holds
+    the launches up for about 35 ms."""
     start = torch.cuda.Event(enable_timing=True)
     stop = torch.cuda.Event(enable_timing=True)
-    with torch.cuda.stream(stream):
-        fn()
-        start.record(stream)
-        for _ in range(reps):
+    collecting = gc.isenabled()
+    gc.disable()
+    try:
+        with torch.cuda.stream(stream):
             fn()
-        stop.record(stream)
+            start.record(stream)
+            for _ in range(reps):
+                fn()
+            stop.record(stream)
+    finally:
+        if collecting:
+            gc.enable()
     stop.synchronize()
     return start.elapsed_time(stop) / reps
 
@@ -478,11 +492,10 @@ def profile_stage(torch, osk, args, A, B, C, ws, keep, stream):
     prep = osk.sketch_prepare(n, b, N, e, seed=args.seed)
     At = torch.empty((m, nst * bp), dtype=torch.float32, device=dev)
     Bt = torch.empty((l, nst * bp), dtype=torch.float32, device=dev)
-    tws = torch.empty(osk.sketch_rows_workspace_bytes(n, l), dtype=torch.uint8, device=dev)
     osk.sketch_cols(A, b, N, e, seed=args.seed, keep=keep, kept_only=args.kept_only, prep=prep,
                     out=At, stream=stream)
     osk.sketch_rows(B, b, N, e, seed=args.seed, keep=keep, kept_only=args.kept_only, prep=prep,
-                    out=Bt, workspace=tws, stream=stream)
+                    out=Bt, stream=stream)
     stored_keep = None if args.kept_only else keep
     QA = QB = None
     if args.profile_stage in ("gemm_bf16", "gemm_fp8"):
@@ -600,7 +613,6 @@ def main():
     At = torch.empty((m, nst * bp), dtype=torch.float32, device=dev)
     Bt = torch.empty((l, nst * bp), dtype=torch.float32, device=dev)
     stored_keep = None if args.kept_only else keep      # mask over the stored blocks
-    tws = torch.empty(osk.sketch_rows_workspace_bytes(n, l), dtype=torch.uint8, device=dev)
     reps = max(3, args.steps)
     t_prep = event_time_ms(torch, lambda: osk.sketch_prepare(n, b, N, e, seed=args.seed,
                                                              stream=stream), reps, stream)
@@ -616,15 +628,10 @@ def main():
                                                         kept_only=args.kept_only, prep=prep,
                                                         out=At, stream=stream),
                         reps, stream)
-    # B's columns, read in place with and without a workspace
     t_sb = event_time_ms(torch, lambda: osk.sketch_rows(B, b, N, e, seed=args.seed, keep=keep,
                                                         kept_only=args.kept_only, prep=prep,
                                                         out=Bt, workspace=None, stream=stream),
                         reps, stream)
-    t_sb_tr = event_time_ms(torch, lambda: osk.sketch_rows(B, b, N, e, seed=args.seed, keep=keep,
-                                                           kept_only=args.kept_only, prep=prep,
-                                                           out=Bt, workspace=tws, stream=stream),
-                            reps, stream)
     t_gemm = event_time_ms(torch, lambda: osk.gemm_kept(At, Bt, b, keep=stored_keep, out=C,
                                                         stream=stream), reps, stream)
     gemm_flops = 2.0 * m * l * K * bp
@@ -632,8 +639,8 @@ def main():
     sketch_entries_a = (m + 3) // 4 * float(n) * nst     # real list entries (4 lines each)
     sketch_bytes_a = 4.0 * (m * n + m * nst * bp)
     sketch_bytes_b = 4.0 * (n * l + l * nst * bp)
-    log("stages: prepare %.3f, sketch A %.3f, sketch B %.3f (with a workspace %.3f), gemm %.3f ms" %
-        (t_prep, t_sa, t_sb, t_sb_tr, t_gemm))
+    log("stages: prepare %.3f, sketch A %.3f, sketch B %.3f, gemm %.3f ms" %
+        (t_prep, t_sa, t_sb, t_gemm))
 
     # ---- accuracy against the exact FP64 product (computed on the GPU)
     step()
@@ -1046,8 +1053,7 @@ def main():
             "avg_launch_ms": t_gemm,
         },
         "cpu_baseline": cpu,
-        "stages_ms": {"prepare": t_prep, "sketch_A": t_sa, "sketch_B": t_sb, "gemm": t_gemm,
-                      "sketch_B_with_workspace": t_sb_tr},
+        "stages_ms": {"prepare": t_prep, "sketch_A": t_sa, "sketch_B": t_sb, "gemm": t_gemm},
         "sketch_roofline": {
             "bound": "hbm", "unit": "GB/s", "peak": HBM_PEAK_GBS,
             "list_entries_walked_per_real": walked / real,
