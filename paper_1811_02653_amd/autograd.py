@@ -35,8 +35,8 @@ def sketched_weight_grad(X, dY, b, N, e, seed=0, keep=None, precision="fp32", h=
     the count sketch runs over the rows (tokens) of X and dY (hashed from
     seed, or explicit tables h / sigma as in the library).  One library call
     (os_matmul_ex with A = X^T, read column-major, and B = dY): prepare,
-    transpose-and-sketch of X and of dY (dropped blocks skipped), the block
-    product in the given precision."""
+    the sketches of the columns of X and of dY (dropped blocks skipped), the
+    block product in the given precision."""
     if X.dim() != 2 or dY.dim() != 2 or X.shape[0] != dY.shape[0]:
         raise OversketchError("X and dY must be 2-D with the same number of rows")
     kept_keep = None if keep is None else np.asarray(keep, dtype=np.uint8)

@@ -39,8 +39,9 @@ int64_t quant_codes(int32_t b, int32_t nst, int prec) {
 
 // Partial products of the block product's split K loop (products with few
 // tiles), sized for all N+e blocks: K steps of 128 bytes of a row (32 FP32,
-// 64 BF16 or 128 FP8 values of each block's stride), three terms per block
-// in the split forms.
+// 64 BF16 or 128 FP8 values of each block's stride).  The split forms run twice
+// as many (a step holds both parts of half the values); room is kept for three
+// times, so that workspaces are the size they have been.
 size_t split_part_bytes(const os_sketch* sk, int64_t m, int64_t l, int prec) {
     int64_t steps;
     if (prec == OS_PREC_FP32)

@@ -37,7 +37,8 @@ namespace osk {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Prepared lists.  One wave per (window w, block i).
+// Prepared lists, built per region (window w, block i): by several waves, and
+// workgroups, for block strides up to kBWMaxBp, else by one wave.
 //   hdr[(i*nwin + w)*qn + q] = chunk base (bits 0..15) | chunk count (16..31)
 //     of group q (buckets 64q .. 64q+63) within the (i, w) region;
 //   ell region (i, w) = RC chunks of 64 lanes x 8 entries; lane L of group q

@@ -77,7 +77,8 @@ struct RawQuad<float> {
     // the quad starting d values further (its last d values are not used)
     static __device__ __forceinline__ type shift(const type& v, int d) {
         return d == 1 ? make_float4(v.y, v.z, v.w, 0.f)
-                      : (d == 2 ? make_float4(v.z, v.w, 0.f, 0.f) : make_float4(v.w, 0.f, 0.f, 0.f));
+                      : (d == 2 ? make_float4(v.z, v.w, 0.f, 0.f)
+                                : make_float4(v.w, 0.f, 0.f, 0.f));
     }
 };
 template <>
@@ -263,8 +264,8 @@ __device__ __forceinline__ void stage_window(float4* __restrict__ win,
 // the FP32 +-1.0 factor).  All four LDS reads are issued before the first
 // FMA so their latencies overlap.  kQ = 2: 8 BF16 lines per position.
 template <int kQ>
-__device__ __forceinline__ void add_half(float4 (&acc)[kQ], const float4* __restrict__ win, uint32_t w0,
-                                         uint32_t w1) {
+__device__ __forceinline__ void add_half(float4 (&acc)[kQ], const float4* __restrict__ win,
+                                         uint32_t w0, uint32_t w1) {
     const uint32_t w[2] = {w0, w1};
     float4 v[4];
     float s[4];
@@ -302,7 +303,8 @@ __device__ __forceinline__ void add_half(float4 (&acc)[kQ], const float4* __rest
 // Adds the 8 entries of one chunk, four at a time (four waves per SIMD hide
 // the LDS latency; eight reads in flight would spill).
 template <int kQ>
-__device__ __forceinline__ void add_chunk(float4 (&acc)[kQ], const float4* __restrict__ win, uint4 e) {
+__device__ __forceinline__ void add_chunk(float4 (&acc)[kQ], const float4* __restrict__ win,
+                                          uint4 e) {
     add_half(acc, win, e.x, e.y);
     __builtin_amdgcn_sched_barrier(0);
     add_half(acc, win, e.z, e.w);
@@ -530,9 +532,9 @@ __device__ __forceinline__ void sketch_tasks(
     // and stored with one instruction; lane s keeps slot s's four scales
     // until the end.  Bound: VALU issue (no other work overlaps it); with a
     // ds_bpermute butterfly, a software conversion and byte stores the sketch of
-    // a 8192 x 32768 matrix into 10 blocks of 1024 took 690 us, now 555-570
-    // (510 with FP32 output).  Split: 31.6 us for 2048 x 8192 into 5 blocks of
-    // 512, where the FP32 sketch and its quantization took 29.9 + 8.8.
+    // a 8192 x 32768 matrix into 10 blocks of 1024 took 690 us, now 492 (490
+    // with FP32 output).  Split: 31.6 us for 2048 x 8192 into 5 blocks of 512,
+    // where the FP32 sketch and its quantization took 29.9 + 8.8.
     if constexpr (kFp8Out != 0) {
         const int r4 = lane & 3;
         const uint32_t sel1 = (lane & 1) ? 0x03070105u : 0x06020400u;
@@ -559,8 +561,10 @@ __device__ __forceinline__ void sketch_tasks(
             return e4m3_pack4(y[0], y[1], y[2], y[3]);
         };
         auto store = [&](uint32_t d, int64_t col) {
-            d = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0xB1, 0xF, 0xF, true), d, sel1);
-            d = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0x4E, 0xF, 0xF, true), d, sel2);
+            uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0xB1, 0xF, 0xF, true);
+            d = __builtin_amdgcn_perm(x, d, sel1);
+            x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0x4E, 0xF, 0xF, true);
+            d = __builtin_amdgcn_perm(x, d, sel2);
             if (live) *reinterpret_cast<uint32_t*>(mine + col) = d;
         };
         auto scale_bytes = [](const int (&e)[4]) -> uint32_t {
