@@ -56,10 +56,11 @@
  * ascending block order (the "straggler-resilient sketching" remark of
  * Section 4.1: blocks dropped at sketch time count as stragglers).
  *
- * Prepared sketch: an opaque device buffer holding, for all N+e blocks, the
- * bucket/sign of every index and, per block, window of 8192 indices and group
- * of 64 buckets, the indices of each bucket (ascending), lane-interleaved and
- * padded to the group's longest bucket.  It depends only on (seed or explicit
+ * Prepared sketch: an opaque device buffer holding, per block, window of 8192
+ * indices and group of 64 buckets, the indices and signs of each bucket
+ * (ascending), lane-interleaved and padded to the group's longest bucket, the
+ * order of every block's buckets, and room for the bucket/sign of every index
+ * (written only where the preparation uses it).  It depends only on (seed or explicit
  * tables, b, N, e, n), not on a keep mask, and can be reused by every sketch
  * call with the same values.  Its size is bounded for ANY tables (a bucket
  * holding a whole window included): about (N+e) * n * 128 bytes plus
@@ -143,8 +144,8 @@ os_status os_hash_fill(const os_sketch* sk, int64_t n, int32_t* h_out, int8_t* s
 size_t os_sketch_prepare_bytes(const os_sketch* sk, int64_t n);
 
 /* Step "hash" as the sketch kernels consume it: fills the prepared sketch
- * (buckets and signs of all N+e blocks, then every block's indices grouped
- * by bucket range, ascending).  prep: DEVICE, 256-byte aligned, >=
+ * (the indices of all N+e blocks with their signs, grouped by bucket range,
+ * ascending).  prep: DEVICE, 256-byte aligned, >=
  * os_sketch_prepare_bytes(sk, n) bytes (else OS_EWORKSPACE). */
 os_status os_sketch_prepare(const os_sketch* sk, int64_t n, void* prep, size_t prep_bytes,
                             void* stream);

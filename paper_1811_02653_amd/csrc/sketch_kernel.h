@@ -641,8 +641,8 @@ void sketch_kernel(const TI* __restrict__ X, int64_t lines, int64_t n, int64_t l
                    const float* __restrict__ wd, int32_t obp, int32_t omode, int64_t ozlo) {
     __shared__ float4 win[kWin + 1];
     sketch_tasks<kSlots, kRowLines, kWeighted, TI, kFp8Out, kForm>(
-        win, blockIdx.x, gridDim.x, X, lines, n, ldx, ldk, qn, nwin, nst, bl, RC, hdr, ell, out, ldo,
-        npass, wd, obp, omode, ozlo);
+        win, blockIdx.x, gridDim.x, X, lines, n, ldx, ldk, qn, nwin, nst, bl, RC, hdr, ell, out,
+        ldo, npass, wd, obp, omode, ozlo);
 }
 
 template <int S, bool R, bool W, typename TI, int Q8, Form F = kWhole>
